@@ -294,6 +294,10 @@ int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mo
 // o_bar[u] = sum of the unit's partial sums, in chunk order (only when o_bar itself is an output).
 hipError_t launch_obar_reduce(const UnitTable& tab, const Shape& sh, const float* parts, float* o_bar,
                               hipStream_t stream);
+// The two sweeps (and the finalize kernel) for bf16 windows of more than 128 rows (kvs_score_shared.hip).
+hipError_t launch_score_shared(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
+                               const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
+                               hipStream_t stream);
 // One-pass score for bf16 windows of 65..128 rows (kvs_score_fused.hip): K is read once and kept in LDS between
 // the statistics and the alpha_bar phase; the pass over V rides along (partials in ws.fo_part).
 bool score_fused_supported(const UnitTable& tab, const Shape& sh, kvs_dtype dt);
