@@ -380,6 +380,11 @@ kvs_status for_each_group(const Plan& plan, F&& f, bool split_select = false) {
     tab.total_ochunks = ochunks;
     tab.total_fitems = fitems;
     tab.total_sparts = sparts;
+    // (all counts are functions of a unit's length and budget)
+    tab.even = 1;
+    for (const Unit& un : units) {
+      if (un.len != units[0].len || un.n_out != units[0].n_out) tab.even = 0;
+    }
     Shape sh = plan.shape;
     sh.stream = 2 * rows * sh.D * (long long)plan.elt > kStreamBytes;
     hipError_t e = hipSuccess;

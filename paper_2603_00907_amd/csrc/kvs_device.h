@@ -104,6 +104,7 @@ struct UnitTable {
   int total_ochunks;
   int total_fitems;     // work items of the one-pass score kernel
   int total_sparts;     // select workgroups
+  int even;             // 1: every unit has the same number of chunks, merge workgroups, ... (see find_unit_by)
   const Unit* host;     // HOST: the same descriptors for the launchers (meaningless on the device), else null
   Unit u[kInlineUnits]; // the descriptors of a smaller group
 
@@ -241,12 +242,22 @@ __device__ __forceinline__ void load_row_consts(const float* __restrict__ c_row,
   __syncthreads();
 }
 
+// The launch's total of a running count.
+template <int Unit::*BASE> __host__ __device__ __forceinline__ int total_of(const UnitTable& tab);
+template <> __host__ __device__ __forceinline__ int total_of<&Unit::chunk_base>(const UnitTable& tab) { return tab.total_chunks; }
+template <> __host__ __device__ __forceinline__ int total_of<&Unit::m_base>(const UnitTable& tab) { return tab.total_mblocks; }
+template <> __host__ __device__ __forceinline__ int total_of<&Unit::o_base>(const UnitTable& tab) { return tab.total_ochunks; }
+template <> __host__ __device__ __forceinline__ int total_of<&Unit::f_base>(const UnitTable& tab) { return tab.total_fitems; }
+template <> __host__ __device__ __forceinline__ int total_of<&Unit::s_base>(const UnitTable& tab) { return tab.total_sparts; }
+
 // The last unit whose running count BASE (chunks, merge workgroups, ... of the launch's earlier units) is at most x:
-// the unit that work item x of the launch belongs to.  A binary search, because the table lives in the kernel
-// arguments and every probe is a scalar load that the next one depends on (about a quarter of a microsecond when
-// it misses the scalar cache: walking the table unit by unit cost a 64-unit select launch 15 of its 37 us).
+// the unit that work item x of the launch belongs to.  A division where all units have the same count (the heads of
+// one layer); otherwise a binary search, because the table lives in the kernel arguments and every probe is a scalar
+// load that the next one depends on (about a quarter of a microsecond when it misses the scalar cache: walking the
+// table unit by unit cost a 64-unit select launch 15 of its 37 us).
 template <int Unit::*BASE>
 __device__ __forceinline__ int find_unit_by(const UnitTable& tab, int x) {
+  if (tab.even) return x / (total_of<BASE>(tab) / tab.n_units);
   int lo = 0, hi = tab.n_units - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
