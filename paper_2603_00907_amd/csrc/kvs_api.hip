@@ -237,15 +237,19 @@ PerQueryWs carve_per_query(const Plan& plan, void* base, Workspace* w) {
     return (void*)ptr;
   };
   // (the chunks of the largest group; groups of a call that has to keep them smaller need less)
-  long long max_chunks = 0;
+  long long max_chunks = 0, pieces = 0;
   for (int first = 0, end; first < plan.n_units; first = end) {
     end = group_end(plan, first, plan.group_cap);
     long long c = 0;
     for (int u = first; u < end; ++u) c += plan.units[u].n_chunks;
     max_chunks = std::max(max_chunks, c);
+    pieces = std::max(pieces, plan.dtype == KVS_F32 ? c : c << pq_split(c));
   }
+  // (where a test asks for smaller groups than these, their chunks may be cut finer: into fewer than 1024 pieces)
+  if (plan.dtype != KVS_F32 && plan.n_units > kInlineUnits)
+    pieces = std::max(pieces, std::min<long long>(8 * max_chunks, 1023));
   const size_t rd = (size_t)plan.shape.R * plan.shape.D;
-  q.o_part = (float*)take((size_t)max_chunks * (rd + plan.shape.R) * sizeof(float));
+  q.o_part = (float*)take((size_t)pieces * (rd + plan.shape.R) * sizeof(float));
   if (plan.dtype == KVS_F32) {
     q.o_f32 = (float*)take((size_t)plan.n_units * rd * sizeof(float));
   } else {
@@ -268,12 +272,19 @@ kvs_status check_per_query(const Plan& plan) {
   return KVS_OK;
 }
 
+// alpha_bar, A_t and C_t.  With bf16 inputs the kernels that form the norms recompute every row's attention anyway and
+// sum alpha_bar up on the way: the score phase is then only its first sweep (8 units of 32768 tokens, 128 query rows:
+// the second one takes 16.6 of the step's 212 us, the extra addition nothing that can be measured).
 hipError_t per_query_norms(const Plan& plan, const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
-                           const void* V, const int32_t* counts_in, const Workspace& w, const PerQueryWs& q,
-                           float* a_tok, float* c_edge, hipStream_t s) {
-  if (plan.dtype == KVS_F32)
-    return launch_per_query_norms_f32(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_f32, a_tok, c_edge, s);
-  return launch_per_query_norms(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_hi, q.o_lo, q.oo, a_tok, c_edge, s);
+                           const void* V, const int32_t* counts_in, float* alpha_bar, const Workspace& w,
+                           const PerQueryWs& q, float* a_tok, float* c_edge, hipStream_t s) {
+  const bool f32 = plan.dtype == KVS_F32;
+  const hipError_t e = launch_score(tab, sh, plan.dtype, Q, K, counts_in, f32 ? alpha_bar : nullptr, w, s);
+  if (e != hipSuccess) return e;
+  if (f32) return launch_per_query_norms_f32(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_f32, a_tok, c_edge, s);
+  Shape sh2 = sh;
+  sh2.alpha_out = alpha_bar;
+  return launch_per_query_norms(tab, sh2, Q, K, V, counts_in, w.c_row, q.o_part, q.o_hi, q.o_lo, q.oo, a_tok, c_edge, s);
 }
 
 struct Range {
@@ -765,9 +776,7 @@ kvs_status kvs_sensitivity_counts(const kvs_problem* p, const void* Q, const voi
   plan.dev_table = w.unit_tab;
   plan.stream = s;
   return for_each_group(plan, [&](const UnitTable& tab, const Shape& sh) {
-    hipError_t e = launch_score(tab, sh, plan.dtype, Q, K, counts_in, alpha_bar, w, s);
-    if (e != hipSuccess) return e;
-    return per_query_norms(plan, tab, sh, Q, K, V, counts_in, w, q, a_tok, c_edge, s);
+    return per_query_norms(plan, tab, sh, Q, K, V, counts_in, alpha_bar, w, q, a_tok, c_edge, s);
   });
 }
 
@@ -847,12 +856,10 @@ kvs_status kvs_step_per_query_counts(const kvs_problem* p, const void* Q, const 
   plan.dev_table = w.unit_tab;
   plan.stream = s;
   return for_each_group(plan, [&](const UnitTable& tab, const Shape& sh) {
-    hipError_t e = launch_score(tab, sh, plan.dtype, Q, K, counts_in, w.alpha_bar, w, s);
+    hipError_t e = per_query_norms(plan, tab, sh, Q, K, V, counts_in, w.alpha_bar, w, q, q.a_tok, q.c_edge, s);
     if (e != hipSuccess) return e;
     e = launch_select_obar(tab, sh, plan.dtype, true, w.alpha_bar, mask, slot, nullptr, nullptr, nullptr, s, nullptr,
                            nullptr, w.sel_shared);
-    if (e != hipSuccess) return e;
-    e = per_query_norms(plan, tab, sh, Q, K, V, counts_in, w, q, q.a_tok, q.c_edge, s);
     if (e != hipSuccess) return e;
     return launch_merge_norms(tab, sh, plan.dtype, K, V, counts_in, q.a_tok, q.c_edge, mask, slot, K_out, V_out,
                               counts_out, s);

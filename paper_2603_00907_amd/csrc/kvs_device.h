@@ -129,6 +129,8 @@ struct Shape {
   int stream;       // 1: the launch's K and V exceed the last-level cache, rows are read non-temporally
   int rule;         // kvs_key_rule of the merged Key
   int causal;       // 0, or the window W when query row q only sees the rows up to its own position n - W + q % W
+  float* alpha_out; // per-query aggregation (bf16): where its kernels leave alpha_bar (the sweeps then only leave the
+                    // rows' normalisers)
   int dec_chunk;    // decode attention: rows per workgroup, at least (chosen per launch, see launch_decode)
   int o_from_score; // where the partial sums of o_bar are: 0: o_part, one per chunk of the o_bar pass; 1: o_part, one
                     // per SCORE chunk (written by sweep 1); 2: fo_part, one per work item of the one-pass score kernel
@@ -278,7 +280,8 @@ hipError_t launch_unit_table(const Unit* units, int n_units, Unit* dst, hipStrea
 // Unit-wide softmax statistics from the chunks' partial ones (one small workgroup per unit).
 // (it also zeroes ws.sel_shared for the selection that follows, when there is one)
 hipError_t launch_score_finalize(const UnitTable& tab, const Shape& sh, const Workspace& ws, hipStream_t stream);
-// Both score sweeps: chunk statistics, the finalize kernel, then alpha_bar.
+// Both score sweeps: chunk statistics, the finalize kernel, then alpha_bar (null: the first sweep and the finalize
+// kernel only).
 // counts_in (here and below): cardinalities of the input rows when the cache is already a merged one, or null.
 // V non-null: the caller also needs o_bar; where the score kernel can carry the pass over V along, it does,
 // leaves the partial sums in the workspace and sets *o_layout to where they are (a value for Shape::o_from_score
@@ -325,8 +328,15 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
                               const int32_t* counts_in, const float* a_tok, const float* c_edge,
                               const uint8_t* edge_mask, const int32_t* slot, void* K_out, void* V_out, int32_t* counts,
                               hipStream_t stream);
-// Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge from Q, K, V and the rows' normalisers
-// c_row that the score sweeps leave.  o_part: [chunks of the launch][R][D] fp32; o_hi, o_lo: [n_units][R][D] bf16;
+// Workgroups per score chunk of the per-query kernels (bf16) are 2^pq_split: a launch of few chunks cuts them (a
+// workgroup of pq_out leaves one partial output, so the workspace is sized by this too).
+__host__ __device__ inline int pq_split(long long chunks) {
+  int split = 0;
+  while (split < 3 && (chunks << split) < 512) ++split;
+  return split;
+}
+// Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out) from Q, K, V
+// and the rows' normalisers c_row that the first score sweep leaves.  o_part: [chunks of the launch][R][D] fp32; o_hi, o_lo: [n_units][R][D] bf16;
 // oo: [n_units][R].
 hipError_t launch_per_query_norms(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                                   const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi,

@@ -8,7 +8,8 @@
 //   C_t = (1/R) sum_q alpha_t^{(q)} alpha_{t+1}^{(q)} ||v_t + v_{t+1} - 2 o^{(q)}||
 // The merge kernel then uses A and C in the weight form of Eq. kstar_final.
 //
-// Four kernels after the two score sweeps (which leave the normaliser c[q] of every row):
+// Four kernels after the first score sweep (which leaves the normaliser c[q] of every row; alpha_bar comes from the
+// third of them, so the second sweep is not run):
 //   pq_out_kernel         O^T[d, q] = sum_t V[t, d] P[t, q], P = alpha / R recomputed from K Q^T tile by tile.
 //                         Both products run on v_mfma_f32_32x32x16_bf16.  The contraction over tokens needs
 //                         V with the token index along the MFMA k dimension; a 32x32 block of the V tile is
@@ -29,7 +30,9 @@
 //                         ||v_t + v_{t+1} - 2o||^2 = ||v_t + v_{t+1}||^2 + 2 (X'_t + X'_{t+1}),
 //                         two square roots, and the sums over q.  Tiles overlap by one row (stride 31), so
 //                         the next token of every output row is in the same tile.  Tokens where the expansions
-//                         cancel (o^{(q)} close to v_t for some q) are marked.
+//                         cancel (o^{(q)} close to v_t for some q) are marked.  The sum of alpha^{(q)}_t over q is
+//                         alpha_bar: one addition per (t, q) here instead of a sweep of its own (16.6 us for 8 units
+//                         of 32768 tokens and 128 rows).
 //   pq_redo_kernel        the marked tokens once more, every squared norm as a sum of squared differences.
 // COUNTS: the rows are slots of an already merged cache (Sec. 3.1, streaming regime), row t standing for c_t tokens
 // whose Values add up to V[t]: every query row sees it as one token with logit e + ln c_t and value V[t] / c_t.  The
@@ -52,7 +55,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kTile = 32;                 // tokens per MFMA tile
 constexpr int kPassRows = 32 * kWaves;    // query rows per pass over the chunk
-constexpr int kRedoSpan = 4096;           // pq_redo: tokens per workgroup
+constexpr int kRedoSpan = 1024;           // pq_redo: tokens per workgroup (262144 tokens: 12.0 us, with 4096 15.2)
 constexpr float kCancel = 1.f / 16.f;     // pq_norms: a squared norm below this share of its leading term is formed again
 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -111,6 +114,17 @@ __device__ __forceinline__ void split8w(const float* f, bf16x8& hi, bf16x8& lo, 
   lo = as_bf16x8(make_uint4(l[0], l[1], l[2], l[3]));
 }
 
+// (One unit of 35154 tokens with 256 rows, 62 chunks: the step takes 132 us with its chunks cut into eight pieces for
+// these kernels, 208 with one workgroup per chunk and the second sweep.)
+// The tokens of workgroup b: piece b % 2^split of its chunk, a multiple of 32 tokens long (the last one: what is left).
+__device__ __forceinline__ void piece_range(const Unit& un, int b, int split, int& t0, int& t1) {
+  const int c0 = ((b >> split) - un.chunk_base) * un.chunk_len;
+  const int c1 = min(un.len, c0 + un.chunk_len);
+  const int per = ((un.chunk_len >> split) + kTile - 1) / kTile * kTile;
+  t0 = min(c1, c0 + (b & ((1 << split) - 1)) * per);
+  t1 = min(c1, t0 + per);
+}
+
 // A 32-row tile of K or V: global -> registers -> LDS.  Piece p of row r lands in slot p ^ (r % LPR).
 template <int D>
 struct Tile {
@@ -164,7 +178,7 @@ template <int D, bool COUNTS>
 __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
     const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
-    float* __restrict__ o_part, float* __restrict__ p_part) {
+    float* __restrict__ o_part, float* __restrict__ p_part, const int split) {
   typedef Tile<D> TL;
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;                // 32-wide blocks of the value dimension
@@ -174,12 +188,11 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
   __shared__ __attribute__((aligned(16))) float sm_cc[2][kTile];                    // COUNTS: c itself
   __shared__ uint4 sm_vt[2][DB][2][kWave];   // the V tile's blocks turned token-major: two operands per lane and block
 
-  const int ui = find_unit(tab, blockIdx.x);
+  const int ui = find_unit(tab, (int)blockIdx.x >> split);
   const Unit un = tab.unit(ui);
-  const int chunk = blockIdx.x - un.chunk_base;
-  const int t0 = chunk * un.chunk_len;
-  const int t1 = min(un.len, t0 + un.chunk_len);
-  const int ntiles = (t1 - t0 + kTile - 1) / kTile;
+  int t0, t1;
+  piece_range(un, blockIdx.x, split, t0, t1);
+  const int ntiles = (t1 - t0 + kTile - 1) / kTile;          // (a piece may be empty: it leaves zeros)
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int col = lane % 32, half = lane / 32;
   const int R = sh.R;
@@ -205,6 +218,7 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
 
   // a tile always holds 32 whole rows: the ragged last one is moved back to end at the chunk's end and the
   // rows it shares with the tile before are skipped (every unit on this path has at least 32 rows)
+  // (t1 is at least 32, also that of an empty piece)
   auto tile_base = [&](int j) { return min(t0 + j * kTile, t1 - kTile); };
 
   for (int qp = 0; qp < R; qp += kPassRows) {
@@ -314,9 +328,9 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
     }
     __syncthreads();                        // the next pass starts with buffer 0 again
     wsum += __shfl_xor(wsum, 32, kWave);    // the other half's token rows
-    if (ok && half == 0) p_part[(size_t)(un.chunk_base + chunk) * R + qrow] = wsum;
+    if (ok && half == 0) p_part[(size_t)blockIdx.x * R + qrow] = wsum;
     if (ok) {
-      float* dst = o_part + ((size_t)(un.chunk_base + chunk) * R + qrow) * D;
+      float* dst = o_part + ((size_t)blockIdx.x * R + qrow) * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
 #pragma unroll
@@ -329,41 +343,59 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
   }
 }
 
-// o^{(q)} from the chunk partials and the sums of their weights (both in chunk order), as a bf16 pair hi + lo, and
-// its squared norm.  One workgroup of D threads per (unit, query row).
+// o^{(q)} from the pieces' partials and the sums of their weights, as a bf16 pair hi + lo, and its squared norm.  One
+// workgroup per (unit, query row): thread (g, d) adds the pieces of the g-th quarter up in order, then the quarters are
+// added in order.  (Bound by the latency of the loads: with all pieces in one thread's loop, eight in flight, the
+// kernel took 13.9 us for 8 units of 64 pieces and 128 rows, and takes 8.2 with the quarters.)
+constexpr int kReduceParts = 4;
 template <int D>
-__global__ __launch_bounds__(D) void pq_out_reduce_kernel(const UnitTable tab, const Shape sh,
+__global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const UnitTable tab, const Shape sh,
                                                           const float* __restrict__ o_part,
                                                           const float* __restrict__ p_part,
                                                           uint16_t* __restrict__ o_hi, uint16_t* __restrict__ o_lo,
-                                                          float* __restrict__ oo) {
+                                                          float* __restrict__ oo, const int split) {
   __shared__ float sm_ss[D / kWave];
+  __shared__ float sm_s[kReduceParts][D], sm_w[kReduceParts];
   const int R = sh.R;
   const Unit un = tab.unit(blockIdx.x / R);
   const int q = blockIdx.x % R;
-  const int d = threadIdx.x;
+  const int d = threadIdx.x % D, g = threadIdx.x / D;
+  const int base = un.chunk_base << split, n = un.n_chunks << split;
+  const int per = (n + kReduceParts - 1) / kReduceParts;
   float s = 0.f, w = 0.f;
-#pragma unroll 8                            // (the loads of eight chunks in flight; the sums stay in chunk order)
-  for (int c = 0; c < un.n_chunks; ++c) {
-    s += o_part[((size_t)(un.chunk_base + c) * R + q) * D + d];
-    w += p_part[(size_t)(un.chunk_base + c) * R + q];
+#pragma unroll 16                           // (the loads of sixteen pieces in flight; the sums stay in order)
+  for (int c = g * per; c < min(n, g * per + per); ++c) {
+    s += o_part[((size_t)(base + c) * R + q) * D + d];
+    w += p_part[(size_t)(base + c) * R + q];
   }
-  const float m2o = -2.f * (s / w);                        // stored with the factor of ||v - o||^2 = ||v||^2 - 2 v.o + ||o||^2
-  const uint32_t hi = f32_to_bf16(m2o);
-  const uint32_t lo = f32_to_bf16(m2o - bf16_lo(hi));
-  const size_t idx = ((size_t)un.index * R + q) * D + d;
-  o_hi[idx] = (uint16_t)hi;
-  o_lo[idx] = (uint16_t)lo;
-  const float oe = -0.5f * (bf16_lo(hi) + bf16_lo(lo));    // the o the products below see
-  float ss = oe * oe;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, kWave);
-  if (d % kWave == 0) sm_ss[d / kWave] = ss;
+  sm_s[g][d] = s;
+  if (d == 0) sm_w[g] = w;
   __syncthreads();
-  if (d == 0) {
+  if (g == 0) {                             // (whole wavefronts)
+    s = sm_s[0][d];
+    w = sm_w[0];
+#pragma unroll
+    for (int i = 1; i < kReduceParts; ++i) {
+      s += sm_s[i][d];
+      w += sm_w[i];
+    }
+    const float m2o = -2.f * (s / w);                      // stored with the factor of ||v - o||^2 = ||v||^2 - 2 v.o + ||o||^2
+    const uint32_t hi = f32_to_bf16(m2o);
+    const uint32_t lo = f32_to_bf16(m2o - bf16_lo(hi));
+    const size_t idx = ((size_t)un.index * R + q) * D + d;
+    o_hi[idx] = (uint16_t)hi;
+    o_lo[idx] = (uint16_t)lo;
+    const float oe = -0.5f * (bf16_lo(hi) + bf16_lo(lo));  // the o the products below see
+    float ss = oe * oe;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, kWave);
+    if (d % kWave == 0) sm_ss[d / kWave] = ss;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
     float t = sm_ss[0];
 #pragma unroll
-    for (int w = 1; w < D / kWave; ++w) t += sm_ss[w];
+    for (int i = 1; i < D / kWave; ++i) t += sm_ss[i];
     oo[(size_t)un.index * R + q] = t;
   }
 }
@@ -381,7 +413,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
     const uint16_t* __restrict__ o_hi,
     const uint16_t* __restrict__ o_lo, const float* __restrict__ oo, float* __restrict__ a_tok,
-    float* __restrict__ c_edge) {
+    float* __restrict__ c_edge, const int split) {
   typedef Tile<D> TL;
   constexpr int KS = D / 16;
   constexpr int STRIDE = kTile - 1;         // output rows per tile: the last row only serves as "next token"
@@ -391,15 +423,16 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   __shared__ float sm_vv[2][kTile + 1];                              // ||v_r||^2 (one spare entry: the last row's "next")
   __shared__ float sm_vd[2][kTile];                                  // v_r . v_{r+1}
   __shared__ float2 sm_out[2][kWaves][kTile];                        // (sum_q A, sum_q C) of every wavefront
+  __shared__ float sm_al[2][kWaves][kTile];                          // sum_q alpha / R: the wavefront's share of alpha_bar
   __shared__ __attribute__((aligned(16))) float sm_negc[kPassRows];  // per query row of the pass: -c[q]
   __shared__ __attribute__((aligned(16))) int sm_lim[kPassRows];     // causal window: last row attended to
   __shared__ float sm_lc[2][kTile + 1], sm_ic[2][kTile + 1];         // COUNTS: log2 c and 1 / c of the tile's rows
 
-  const int ui = find_unit(tab, blockIdx.x);
+  const int ui = find_unit(tab, (int)blockIdx.x >> split);
   const Unit un = tab.unit(ui);
-  const int chunk = blockIdx.x - un.chunk_base;
-  const int t0 = chunk * un.chunk_len;
-  const int t1 = min(un.len, t0 + un.chunk_len);
+  int t0, t1;
+  piece_range(un, blockIdx.x, split, t0, t1);
+  if (t0 >= t1) return;                     // nothing left of the chunk for this piece
   const int ntiles = (t1 - t0 + STRIDE - 1) / STRIDE;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int col = lane % 32, half = lane / 32;
@@ -413,6 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   const uint16_t* Ol = o_lo + (size_t)un.index * R * D;
   float* At = a_tok + un.in_row;
   float* Ce = c_edge + un.in_row;
+  float* Al = sh.alpha_out + un.in_row;
   const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -451,7 +485,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
         const int base = tile_base(j), shift = tile_first(j) - base;
         const int r = tid, t = base + r;
         if (r >= shift && r <= shift + STRIDE - 1 && t < t1) {
-          float a = 0.f, c = 0.f;
+          float a = 0.f, c = 0.f, al = 0.f;
           uint32_t mark = 0;                               // sign bit: some wavefront, or an earlier pass, marked the token
 #pragma unroll
           for (int w = 0; w < kWaves; ++w) {
@@ -459,6 +493,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
             mark |= __float_as_uint(o.x);
             a += fabsf(o.x);
             c += o.y;
+            al += sm_al[buf][w][r];
           }
           if (r == kTile - 1) c = 0.f;                     // only the unit's last token: it has no next one
           if (qp > 0) {                                    // later passes add their query rows
@@ -466,9 +501,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
             mark |= __float_as_uint(before);
             a += fabsf(before);
             c += Ce[t];
+            al += Al[t];
           }
           At[t] = __uint_as_float(__float_as_uint(a) | (mark & 0x80000000u));
           Ce[t] = c;
+          Al[t] = al;
         }
       }
     };
@@ -539,7 +576,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
         vp = fmaf(2.f * ic * icn, sm_vd[buf][col], vv + vvn);
       }
       const int t_abs = tile_base(j) + col;
-      float sumA = 0.f, sumC = 0.f;
+      float sumA = 0.f, sumC = 0.f, sumP = 0.f;
       float leastA = INFINITY, leastC = INFINITY;   // smallest squared norms this lane forms in the tile (see below)
       // TAIL: the tile reaches into the causal window's masked rows (a uniform condition)
       auto rows = [&](auto tail_tag) {
@@ -560,6 +597,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
             const int v = 4 * g + i;
             float a = ex2(fmaf(accS[v], sl2, COUNTS ? nc[i] + lc : nc[i]));  // alpha / R
             if (TAIL && t_abs > lim[i]) a = 0.f;
+            sumP += a;
             const float x = COUNTS ? fmaf(accX[v], ic, oo_init[v]) : accX[v]; // ||o||^2 - 2 v_t . o
             // the same quantities of token t + 1: the next lane (the last column's are not used)
             const float a_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x130, 0xF, 0xF, true));
@@ -588,7 +626,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
       redo |= __shfl_xor(redo, 32, kWave);
       sumA += __shfl_xor(sumA, 32, kWave);    // the other half's 16 query rows
       sumC += __shfl_xor(sumC, 32, kWave);
-      if (half == 0) sm_out[buf][wave][col] = make_float2(redo ? -sumA : sumA, sumC * Rf);   // (sumA >= 0; -0 counts)
+      sumP += __shfl_xor(sumP, 32, kWave);
+      if (half == 0) {
+        sm_out[buf][wave][col] = make_float2(redo ? -sumA : sumA, sumC * Rf);                // (sumA >= 0; -0 counts)
+        sm_al[buf][wave][col] = sumP;
+      }
     }
     __syncthreads();
     flush(ntiles - 1);
@@ -759,17 +801,18 @@ template <int D, bool COUNTS>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi, uint16_t* o_lo,
                     float* oo, float* a_tok, float* c_edge, hipStream_t stream) {
-  const dim3 grid(tab.total_chunks), block(kThreads);
-  float* p_part = o_part + (size_t)tab.total_chunks * sh.R * D;   // the weights' sums lie behind the launch's partials
+  const int split = pq_split(tab.total_chunks);
+  const dim3 grid(tab.total_chunks << split), block(kThreads);
+  float* p_part = o_part + (size_t)grid.x * sh.R * D;       // the weights' sums lie behind the launch's partials
   hipLaunchKernelGGL((pq_out_kernel<D, COUNTS>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_part, p_part);
+                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_part, p_part, split);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((pq_out_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, o_part, p_part,
-                     o_hi, o_lo, oo);
+  hipLaunchKernelGGL((pq_out_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D * kReduceParts), 0, stream, tab, sh,
+                     o_part, p_part, o_hi, o_lo, oo, split);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge);
+                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int longest = 1;
   for (int u = 0; u < tab.n_units; ++u) longest = longest > tab.unit(u).len ? longest : tab.unit(u).len;

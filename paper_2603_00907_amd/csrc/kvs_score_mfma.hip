@@ -727,7 +727,7 @@ hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh, const void* Q, c
                      (const uint16_t*)nullptr, (float*)nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess) return e;
+  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   if (V != nullptr) {
     hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, QB>), grid, block, 0, stream, tab, sh,
                        (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
@@ -760,7 +760,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
                      (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess) return e;
+  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 1>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
                      (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
   return hipGetLastError();
@@ -1011,7 +1011,7 @@ hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh, const void* Q, co
                        (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess) return e;
+  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   for (int qp = 0; qp < sh.R; qp += 128) {
     hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
                        (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);

@@ -437,7 +437,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
                        (const uint16_t*)nullptr, (float*)nullptr, qp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess) return e;
+  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
     if (V != nullptr && qp + NW * 64 >= sh.R) {              // the last launch alone knows the finished alpha_bar
       hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, true>), grid, block, 0, stream, tab, sh,

@@ -206,7 +206,7 @@ static hipError_t launch_score_valu_t(const UnitTable& tab, const Shape& sh, con
                      counts_in, alpha_bar, ws.stats_part, ws.c_row);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess) return e;
+  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   hipLaunchKernelGGL((score_valu_kernel<T, D, 1>), grid, block, 0, stream, tab, sh, (const T*)Q, (const T*)K,
                      counts_in, alpha_bar, ws.stats_part, ws.c_row);
   return hipGetLastError();
