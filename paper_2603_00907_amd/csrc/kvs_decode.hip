@@ -6,7 +6,7 @@
 //   o = sum_S exp(e_S) V'_S / sum_S c_S exp(e_S),      e_S = scale * q . k'_S,
 // i.e. ordinary attention over the c_S copies of every slot.  With c = 1 it is plain attention.
 //
-// Split over the rows of a unit (chunks of at least 256 rows, at most 64 per unit, one workgroup
+// Split over the rows of a unit (chunks whose length is chosen per launch, at most 64 per unit, one workgroup
 // each; the grid is chunks x units): LPR adjacent lanes read one K row and one V row (16 bytes each), four query rows at a time
 // sit in registers, every lane group keeps an online softmax (running maximum, denominator,
 // D-wide numerator) for its rows, the groups of a workgroup are combined through LDS, and a second
@@ -14,7 +14,8 @@
 // timing.  The kernel is meant for decode-sized query blocks (at most KVS_MAX_DECODE_ROWS rows per
 // unit); it reads the cache once per block of four query rows.
 //
-// bf16 caches whose units have at least 32 rows take decode_mfma_kernel instead: both products on
+// From five query rows on, caches whose units have at least 32 rows take decode_mfma_kernel (bf16; fp32: its variant
+// decode_mfma_f32_kernel) instead: both products on
 // v_mfma_f32_32x32x16_bf16, 32 query rows per pass, the operands loaded from memory in the MFMA layout (a lane
 // fetches the 16-byte pieces of ITS row), so nothing is staged in LDS and the wavefronts of a workgroup, which
 // split the chunk's 32-row tiles, never wait for each other inside the loop.  The chunk partials have the same
@@ -22,6 +23,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "kvs_device.h"
 
@@ -40,10 +42,7 @@ constexpr int kUnroll = KVS_DEC_UNROLL;   // cache rows per lane group in flight
 #ifndef KVS_DEC_CHUNK
 #define KVS_DEC_CHUNK 256
 #endif
-constexpr int kDecMinChunk = KVS_DEC_CHUNK;   // rows per workgroup, at least
-
-constexpr int kDecMaxMinChunk = 1024;
-constexpr int kDecWorkgroups = 2048;          // workgroups a launch aims for (8 per CU)
+constexpr int kDecMinChunk = KVS_DEC_CHUNK;   // rows per workgroup, where the launch is large enough for it
 
 // Chunking of a unit's rows: a function of its length and of the launch's least chunk length.
 __host__ __device__ inline int dec_chunk_len(int len, int min_chunk) {
@@ -251,6 +250,33 @@ constexpr int kMfmaThreads = 256;
 constexpr int kMfmaWaves = kMfmaThreads / kWave;
 constexpr int kTile = 32;
 
+// The wavefronts' numerators, maxima and denominators (in LDS) -> the chunk's partial result for query rows qb ..
+template <int D>
+__device__ __forceinline__ void combine_waves(const float (&sm_acc)[kMfmaWaves][kTile][D + 4], int unit_index,
+                                              int chunk, int R, int qb, float* __restrict__ part) {
+  for (int o = threadIdx.x; o < kTile * D; o += kMfmaThreads) {
+    const int q = o / D, dch = o % D;
+    if (qb + q < R) {
+      float M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < kMfmaWaves; ++w) M = fmaxf(M, sm_acc[w][q][D]);
+      float num = 0.f, den = 0.f;
+#pragma unroll
+      for (int w = 0; w < kMfmaWaves; ++w) {
+        const float lw = sm_acc[w][q][D + 1];
+        if (lw > 0.f) {                                      // a wavefront that had no tile has m = -inf, l = 0
+          const float wgt = __builtin_amdgcn_exp2f(sm_acc[w][q][D] - M);
+          num = fmaf(sm_acc[w][q][dch], wgt, num);
+          den = fmaf(lw, wgt, den);
+        }
+      }
+      float* dst = part + part_index(unit_index, chunk, R, qb + q, D);
+      dst[dch] = num;
+      if (dch == 0) { dst[D] = M; dst[D + 1] = den; }
+    }
+  }
+}
+
 // Per tile of 32 cache rows and block of 32 query rows (one per lane column):
 //   S[t, q] = K_tile Q^T               8 (D = 128) products; a lane holds one query column and 16 rows
 //   online softmax per column          the running maximum is lane-private (exchanged once between the halves of
@@ -401,29 +427,187 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_kernel(
     }
     if (half == 0) { sm_acc[wave][col][D] = m_run; sm_acc[wave][col][D + 1] = l_tot; }
     __syncthreads();
-    for (int o = tid; o < kTile * D; o += kMfmaThreads) {
-      const int q = o / D, dch = o % D;
-      if (qb + q < R) {
-        float M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < kMfmaWaves; ++w) M = fmaxf(M, sm_acc[w][q][D]);
-        float num = 0.f, den = 0.f;
-#pragma unroll
-        for (int w = 0; w < kMfmaWaves; ++w) {
-          const float lw = sm_acc[w][q][D + 1];
-          if (lw > 0.f) {                                    // a wavefront that had no tile has m = -inf, l = 0
-            const float wgt = __builtin_amdgcn_exp2f(sm_acc[w][q][D] - M);
-            num = fmaf(sm_acc[w][q][dch], wgt, num);
-            den = fmaf(lw, wgt, den);
-          }
-        }
-        float* dst = part + part_index(un.index, chunk, R, qb + q, D);
-        dst[dch] = num;
-        if (dch == 0) { dst[D] = M; dst[D + 1] = den; }
-      }
-    }
+    combine_waves<D>(sm_acc, un.index, chunk, R, qb, part);
     __syncthreads();
   }
+}
+
+// fp32 caches: the same scheme with v_mfma_f32_32x32x2_f32 (fp32 products and sums).  Both operands of both products
+// come from memory as they lie: in S = K Q^T a lane holds one row of K, every second 16-byte piece of it (the
+// contraction index may be split between the halves of the wavefront in any way that both operands share); in
+// O^T += V^T P step v contracts the two rows 8 (v / 4) + 4 half + v % 4, for which the lane's accumulator element v of
+// S IS the operand, and the other one is a piece of D / 32 neighbouring channels of that row of V, channel
+// D / 32 * i + e being row i of accumulator e.  So nothing is turned and nothing staged but the Q block.
+// What bounds it: 128 products of 64 cycles per 32 rows (D = 128) and 32 KB, about the same time at 2 wavefronts per
+// SIMD; the vector-ALU kernel reads the cache once per four query rows instead (32 caches of 16384 rows, 32 query rows:
+// 127 us here, 4.2 TB/s, and 731 there).
+template <int D>
+__global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
+    const UnitTable tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
+    const float* __restrict__ V, const int32_t* __restrict__ counts, float* __restrict__ part) {
+  constexpr int NP = D / 8;                 // 16-byte pieces of a row per half of the wavefront
+  constexpr int LPR = D / 4;                // 16-byte pieces per row
+  constexpr int DB = D / 32;                // channels per lane of a V row = accumulators of O^T
+  constexpr int ACCW = D + 4;
+  typedef float vpiece __attribute__((ext_vector_type(DB)));
+  // the Q block (piece s of row r in slot s ^ r % LPR) during the tiles, the wavefronts' results afterwards
+  __shared__ __attribute__((aligned(16))) float sm_acc[kMfmaWaves][kTile][ACCW];
+  __shared__ __attribute__((aligned(16))) float sm_cnt[kMfmaWaves][kTile];
+  float4* sm_q = reinterpret_cast<float4*>(&sm_acc[0][0][0]);
+  static_assert(kTile * LPR * 16 <= sizeof(sm_acc), "the Q block fits");
+
+  const Unit un = tab.unit(blockIdx.y);
+  const int chunk = blockIdx.x;
+  if (chunk >= dec_chunks(un.len, sh.dec_chunk)) return;               // the grid is as wide as the longest unit needs
+  const int clen = dec_chunk_len(un.len, sh.dec_chunk);
+  const int t0 = chunk * clen;
+  const int t1 = min(un.len, t0 + clen);
+  const int ntiles = (t1 - t0 + kTile - 1) / kTile;
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int col = lane % 32, half = lane / 32;
+  const int R = sh.R;
+  const float sl2 = sh.scale_log2;
+  const float* Kg = K + (size_t)un.in_row * D;
+  const float* Vg = V + (size_t)un.in_row * D;
+  const float* Qu = Q + (size_t)un.index * R * D;
+  const int32_t* cnt = counts ? counts + un.in_row : nullptr;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // the ragged last tile is moved back to end at the chunk's end (every unit on this path has at least 32 rows)
+  auto tile_base = [&](int j) { return min(t0 + j * kTile, t1 - kTile); };
+  auto load_keys = [&](int j, float4 (&a)[NP]) {
+    const float4* src = reinterpret_cast<const float4*>(Kg + (size_t)(tile_base(j) + col) * D) + half;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) a[i] = src[2 * i];
+  };
+
+  for (int qb = 0; qb < R; qb += kTile) {
+    float4 a[NP];
+    asm volatile("" ::: "memory");            // (not hoisted out of the loop over the query rows: it would be spilled)
+    load_keys(min(wave, ntiles - 1), a);
+    for (int i = tid; i < kTile * LPR; i += kMfmaThreads) {
+      const int r = i / LPR, s = i % LPR;
+      const int qrow = min(qb + r, R - 1);                   // rows past R repeat the last one
+      sm_q[r * LPR + (s ^ (r % LPR))] = reinterpret_cast<const float4*>(Qu + (size_t)qrow * D)[s];
+    }
+    __syncthreads();
+    f32x16 accO[DB];
+#pragma unroll
+    for (int e = 0; e < DB; ++e) accO[e] = zero;
+    float m_run = -INFINITY, l_run = 0.f;
+
+    for (int j = wave; j < ntiles; j += kMfmaWaves) {
+      const int base_t = tile_base(j);
+      const int shift = t0 + j * kTile - base_t;             // leading rows that belong to the tile before
+      // the rows of V in two halves, and the next tile's Keys between them: all at once does not fit the registers (the
+      // marks keep the compiler from issuing them earlier)
+      vpiece vv[16];
+      auto load_values = [&](auto half_c) {
+#pragma unroll
+        for (int v = 8 * decltype(half_c)::value; v < 8 * decltype(half_c)::value + 8; ++v) {
+          const int row = 8 * (v / 4) + 4 * half + (v % 4);
+          vv[v] = reinterpret_cast<const vpiece*>(Vg + (size_t)(base_t + row) * D)[col];
+        }
+        asm volatile("" ::: "memory");
+      };
+      load_values(std::integral_constant<int, 0>{});
+      if (cnt != nullptr && half == 0) sm_cnt[wave][col] = (float)cnt[base_t + col];
+      f32x16 acc = zero;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const float4 q4 = sm_q[col * LPR + ((2 * i + half) ^ (col % LPR))];
+        const float qv[4] = {q4.x, q4.y, q4.z, q4.w};
+        const float kv[4] = {a[i].x, a[i].y, a[i].z, a[i].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e], acc, 0, 0, 0);
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      load_values(std::integral_constant<int, 1>{});
+      // accumulator element v: cache row 8 (v / 4) + 4 half + v % 4 of the tile, query column `col`
+      float p[16];
+      float tm = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = 8 * (v / 4) + 4 * half + (v % 4);
+        p[v] = (row >= shift) ? acc[v] * sl2 : -INFINITY;
+        tm = fmaxf(tm, p[v]);
+      }
+      tm = fmaxf(tm, __shfl_xor(tm, 32, kWave));             // both halves feed the same column of O^T
+      if (tm > m_run) {                                      // rare after the first tiles
+        const float corr = __builtin_amdgcn_exp2f(m_run - tm);       // the first tile meets -inf: corr = 0
+        l_run *= corr;
+#pragma unroll
+        for (int e = 0; e < DB; ++e) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) accO[e][v] *= corr;
+        }
+        m_run = tm;
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) p[v] = __builtin_amdgcn_exp2f(p[v] - m_run);
+      if (shift > 0) {                        // a row that dropped out counts for nothing whatever its Value is
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if (8 * (v / 4) + 4 * half + (v % 4) < shift) vv[v] = vpiece{};
+        }
+      }
+      // denominator: c copies of every slot
+      if (cnt != nullptr) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 c4 = *reinterpret_cast<const float4*>(&sm_cnt[wave][8 * g + 4 * half]);
+          l_run = fmaf(c4.x, p[4 * g], l_run);
+          l_run = fmaf(c4.y, p[4 * g + 1], l_run);
+          l_run = fmaf(c4.z, p[4 * g + 2], l_run);
+          l_run = fmaf(c4.w, p[4 * g + 3], l_run);
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l_run += p[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        if (v == 8) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_keys(min(j + kMfmaWaves, ntiles - 1), a);     // flies during the rest (the last tile is fetched twice)
+          asm volatile("" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int e = 0; e < DB; ++e)
+          accO[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[v][e], p[v], accO[e], 0, 0, 0);
+      }
+    }
+
+    // the wavefronts of the workgroup, in wavefront order.  O^T element v of accumulator e: channel
+    // DB (8 (v / 4) + 4 half + v % 4) + e of query column `col`
+    const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+    __syncthreads();                          // the Q block has been read
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      vpiece o;
+#pragma unroll
+      for (int e = 0; e < DB; ++e) o[e] = accO[e][v];
+      *reinterpret_cast<vpiece*>(&sm_acc[wave][col][DB * (8 * (v / 4) + 4 * half + (v % 4))]) = o;
+    }
+    if (half == 0) { sm_acc[wave][col][D] = m_run; sm_acc[wave][col][D + 1] = l_tot; }
+    __syncthreads();
+    combine_waves<D>(sm_acc, un.index, chunk, R, qb, part);
+    __syncthreads();
+  }
+}
+
+template <int D>
+hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
+                           const int32_t* counts, float* part, float* out, hipStream_t stream) {
+  int widest = 1;
+  for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
+  hipLaunchKernelGGL((decode_mfma_f32_kernel<D>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, tab, sh,
+                     (const float*)Q, (const float*)K, (const float*)V, counts, part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, part, out);
+  return hipGetLastError();
 }
 
 template <int D>
@@ -456,27 +640,43 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
 
 hipError_t launch_decode(const UnitTable& tab, const Shape& sh_in, kvs_dtype dt, const void* Q, const void* K,
                          const void* V, const int32_t* counts, float* part, float* out, hipStream_t stream) {
-  // Rows per workgroup: kDecMinChunk where the launch is small (a workgroup per 256 rows keeps every CU busy), more
-  // where that would make many more workgroups than the chip holds at once (256 caches of 4096 rows: chunks of 512
-  // rows take 0.120 ms against 0.128 with 256 and 0.149 with 128).
-  Shape sh = sh_in;
-  long long rows = 0;
-  for (int i = 0; i < tab.n_units; ++i) rows += tab.unit(i).len;
-  long long chunk = (rows / kDecWorkgroups + kWave - 1) / kWave * kWave;
-  sh.dec_chunk = (int)(chunk < kDecMinChunk ? kDecMinChunk : chunk > kDecMaxMinChunk ? kDecMaxMinChunk : chunk);
-  if (dt == KVS_F32) {
-    return sh.D == 64 ? launch_t<float, 64>(tab, sh, Q, K, V, counts, part, out, stream)
-                      : launch_t<float, 128>(tab, sh, Q, K, V, counts, part, out, stream);
-  }
-  // The vector-ALU kernel reads the cache once per four query rows: up to four rows it is as fast as the MFMA
-  // kernel (both are latency-bound on caches of a few thousand rows), above that the MFMA kernel wins (measured,
-  // 64 caches of 4096 rows: 42 against 62 us at 8 rows, 55 against 200 us at 32 rows).
+  // The vector-ALU kernels read the cache once per four query rows, the MFMA kernels once per 32.  bf16: up to four
+  // rows they are equally fast (both latency-bound on caches of a few thousand rows), above that the MFMA kernel wins
+  // (64 caches of 4096 rows: 42 against 62 us at 8 rows, 55 against 200 us at 32 rows).  fp32, 32 caches: 40.7 against
+  // 62 us at 8 rows and 4096 cache rows, 127 against 731 us at 32 rows and 16384 cache rows.
   // KVS_DEBUG_DECODE_PATH forces one of them (used by the tests to cover both).
+  Shape sh = sh_in;
   const int force = debug_switch(KVS_DEBUG_DECODE_PATH);
   bool mfma = sh.R > kQB;
   if (force == 1) mfma = false;
   if (force == 2) mfma = true;
   for (int i = 0; i < tab.n_units; ++i) mfma = mfma && tab.unit(i).len >= kTile;   // its tiles hold 32 whole rows
+  // Rows per workgroup.  Where all caches have the same length, as many as make the launch one round of resident
+  // workgroups (two per CU for the MFMA kernels, four for the vector-ALU ones), at least 256 and at most 2048 (MFMA) or
+  // 1024 rows: every workgroup has a fixed cost (the query block, the wavefronts' results combined, a partial result
+  // written).  32 caches of 22047 rows, 16 query rows: 78.2 us, with twice to four times the workgroups 85 and 97; 64
+  // of 4096, 32 query rows: 37.7 against 48.1; 256 of 4096, 4 query rows (vector ALU): 113 against 120.  Caches of
+  // different lengths leave the last workgroups of the long ones alone on the chip, and smaller pieces even that out
+  // (100 caches of 2.7 K to 21 K rows: 135 us at up to 1024 rows and 8 query rows against 153 at 2048; 148 at 2048
+  // workgroups and 4 query rows against 164 at 1024).
+  // The vector-ALU kernels go down to 64 rows in a launch that would leave compute units without a workgroup (8 caches
+  // of 4096 rows: 16.9 us with 128 against 20.9; 64 caches stay: 30.7 with 256 against 37.0); the MFMA kernels'
+  // wavefronts take 32 rows each (8 caches of 4096 rows, 32 query rows: 20.3 us with 256, 20.6 with 128, 26.7 with 64).
+  long long rows = 0;
+  for (int i = 0; i < tab.n_units; ++i) rows += tab.unit(i).len;
+  const int most = mfma && tab.even ? 2048 : 1024;
+  long long chunk = rows / (mfma ? 512 : tab.even ? 1024 : 2048);
+  if (chunk < kDecMinChunk) chunk = mfma ? kDecMinChunk : std::min<long long>(rows / 256, kDecMinChunk);
+  chunk = (chunk + kWave - 1) / kWave * kWave;
+  sh.dec_chunk = (int)(chunk < kWave ? kWave : chunk > most ? most : chunk);
+  if (dt == KVS_F32) {
+    if (mfma) {
+      return sh.D == 64 ? launch_mfma_f32<64>(tab, sh, Q, K, V, counts, part, out, stream)
+                        : launch_mfma_f32<128>(tab, sh, Q, K, V, counts, part, out, stream);
+    }
+    return sh.D == 64 ? launch_t<float, 64>(tab, sh, Q, K, V, counts, part, out, stream)
+                      : launch_t<float, 128>(tab, sh, Q, K, V, counts, part, out, stream);
+  }
   if (mfma) {
     return sh.D == 64 ? launch_mfma<64>(tab, sh, Q, K, V, counts, part, out, stream)
                       : launch_mfma<128>(tab, sh, Q, K, V, counts, part, out, stream);
