@@ -312,6 +312,9 @@ hipError_t launch_obar_reduce(const UnitTable& tab, const Shape& sh, const float
 hipError_t launch_score_shared(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
                                const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
                                hipStream_t stream);
+// The same for fp32 windows of more than 64 rows (kvs_score_split.hip).
+hipError_t launch_score_split(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
+                              const int32_t* counts_in, float* alpha_bar, const Workspace& ws, hipStream_t stream);
 // One-pass score for bf16 windows of 65..128 rows (kvs_score_fused.hip): K is read once and kept in LDS between
 // the statistics and the alpha_bar phase; the pass over V rides along (partials in ws.fo_part).
 bool score_fused_supported(const UnitTable& tab, const Shape& sh, kvs_dtype dt);

@@ -28,7 +28,8 @@
 //                           LDS copy of the Q block for every tile; in small launches also up to 256 rows, with
 //                           every block read from LDS (eight wavefronts).
 //   score_shared_kernel     (kvs_score_shared.hip) more than 128 rows.
-//   score_mfma_f32_kernel   fp32 inputs, v_mfma_f32_32x32x2_f32, 128 rows per launch.
+//   score_mfma_f32_kernel   fp32 inputs, up to 64 rows, v_mfma_f32_32x32x2_f32.
+//   score_split_kernel      (kvs_score_split.hip) fp32 inputs, more than 64 rows.
 // Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit.
 #include <cstdlib>
 #include <type_traits>
@@ -797,21 +798,19 @@ hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const 
 // index is split between the halves of the wavefront (lanes 0..31 take elements 0..D/2-1 of a row, lanes 32..63
 // the rest: any split works as long as both operands use the same one), so a lane's operands are D/2 contiguous
 // floats of one row.  The K tile (32 rows) goes straight from global memory to registers, the tile after it is
-// requested before the products of this one start; the Q block (up to 128 rows per launch, rows qp.. of every
-// unit) sits in LDS, XOR-swizzled in 16-byte pieces, and is re-read for every tile.  Accumulator layouts, the
-// running statistics of sweep 0, the transposed products of sweep 1 and the row offset qp for windows of more
-// than 128 rows are those of score_mfma_wide_kernel.  The work is bound by the fp32 matrix rate, not by memory.
+// requested before the products of this one start; the Q block (up to 64 rows) sits in LDS, XOR-swizzled in 16-byte pieces, and is re-read for every tile.  Accumulator layouts, the
+// running statistics of sweep 0 and the transposed products of sweep 1 are those of score_mfma_wide_kernel.
 template <int D, int PHASE, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
     const UnitTable tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
-    const float* __restrict__ c_row, const int qp) {
+    const float* __restrict__ c_row) {
   constexpr int ROWB = D * 4;               // bytes per row
   constexpr int LPR = ROWB / 16;            // 16-byte pieces per row
   constexpr int RPI = kWave / LPR;          // rows per load instruction of the Q block
   constexpr int HALF = D / 2;               // contraction indices per half of the wavefront
   constexpr int NQ4 = HALF / 4;             // 16-byte operand pieces per lane and row
-  constexpr int QROWS = 128;                // query rows per launch
+  constexpr int QROWS = 64;                 // query rows
   constexpr int NBLK = QROWS / 32;
 
   __shared__ __attribute__((aligned(1024))) unsigned char sm_q[QROWS * ROWB];
@@ -829,38 +828,36 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int col = lane % 32, half = lane / 32;
   const int R = sh.R;
-  const int rows_here = min(R - qp, QROWS);                 // query rows of this launch
   const float sl2 = sh.scale_log2;
   const int32_t* cnt = counts_in ? counts_in + un.in_row : nullptr;
   const float sc = cnt ? 1.f : sl2;
   const size_t part_base = (size_t)un.index * kMaxChunks;
-  const bool last_launch = qp + QROWS >= R;
 
   const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
   const uint4* Qg = reinterpret_cast<const uint4*>(Q + (size_t)un.index * R * D);
 
   if (PHASE == 1) {
     if (tid < QROWS) {
-      sm_cq[tid] = (qp + tid < R) ? c_row[(size_t)un.index * R + qp + tid] : INFINITY;
-      sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, qp + tid);
+      sm_cq[tid] = (tid < R) ? c_row[(size_t)un.index * R + tid] : INFINITY;
+      sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
     }
   }
   int lim[NBLK];
 #pragma unroll
-  for (int b = 0; b < NBLK; ++b) lim[b] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, qp + b * 32 + col);
+  for (int b = 0; b < NBLK; ++b) lim[b] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, b * 32 + col);
 
-  // the Q block, once per workgroup: every wavefront fetches 32 rows (rows past R repeat the last one); physical
+  // the Q block, once per workgroup: every wavefront fetches 16 rows (rows past R repeat the last one); physical
   // piece s of local row r holds logical piece s ^ (r % LPR)
   {
     const int st_row = lane / LPR, st_slot = lane % LPR;
-    constexpr int QLD = 32 / RPI;
+    constexpr int RPW = QROWS / kWaves, QLD = RPW / RPI;
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
-      const int lr = wave * 32 + i * RPI + st_row;
-      const int qrow = min(qp + lr, R - 1);
+      const int lr = wave * RPW + i * RPI + st_row;
+      const int qrow = min(lr, R - 1);
       const int piece = st_slot ^ (lr % LPR);
       __builtin_amdgcn_global_load_lds(KVS_GLOBAL_PTR(Qg + (size_t)qrow * LPR + piece),
-                                       KVS_LDS_PTR(sm_q + (wave * 32 + i * RPI) * ROWB), 16, 0, 0);
+                                       KVS_LDS_PTR(sm_q + (wave * RPW + i * RPI) * ROWB), 16, 0, 0);
     }
   }
   // this lane's operand pieces of Q block row `col` (+ 32 per block): logical piece half * NQ4 + i
@@ -902,7 +899,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
     float p_tok = 0.f;                              // sweep 1: this lane's token, summed over its query rows
 #pragma unroll
     for (int b = 0; b < NBLK; ++b) {
-      if (b * 32 >= rows_here) break;               // uniform: no such rows in this launch
+      if (b * 32 >= R) break;               // uniform: no such rows in this launch
       f32x16 acc[1];
       acc[0] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -965,8 +962,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
     }
     if (PHASE == 1) {
       p_tok += __shfl_xor(p_tok, 32, kWave);
-      if (qp > 0) p_tok += alpha_bar[un.in_row + base_t + col];              // the rows of the launches before
-      if (cnt && last_launch) p_tok *= (float)cnt[base_t + col];
+      if (cnt) p_tok *= (float)cnt[base_t + col];
       if (half == 0 && col >= shift) alpha_bar[un.in_row + base_t + col] = p_tok;
     }
 #pragma unroll
@@ -986,7 +982,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
       if (half == 0) sm_stats[wave][b * 32 + col] = make_float2(m_run[b], l_run[b]);
     }
     __syncthreads();
-    if (tid < rows_here) {
+    if (tid < R) {
       float M = -INFINITY;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sm_stats[w][tid].x);
@@ -996,7 +992,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
         const float2 st = sm_stats[w][tid];
         if (st.y > 0.f) Z += st.y * ex2(st.x - M);
       }
-      stats_part[(part_base + chunk) * R + qp + tid] = make_float2(M, Z);
+      stats_part[(part_base + chunk) * R + tid] = make_float2(M, Z);
     }
   }
 }
@@ -1006,23 +1002,21 @@ hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh, const void* Q, co
                         float* alpha_bar, const Workspace& ws, hipStream_t stream) {
   dim3 grid(tab.total_chunks), block(kThreads);
   hipError_t e;
-  for (int qp = 0; qp < sh.R; qp += 128) {
-    hipLaunchKernelGGL((score_mfma_f32_kernel<D, 0, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+  hipLaunchKernelGGL((score_mfma_f32_kernel<D, 0, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
+                     (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
-  for (int qp = 0; qp < sh.R; qp += 128) {
-    hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
+                     (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_f32(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const int32_t* counts_in,
                       float* alpha_bar, const Workspace& ws, hipStream_t stream) {
+  // More than 64 rows: products of three bf16 parts (8 units of 32768 tokens, 128 rows: 190 against 241 us).  Up to 64
+  // rows fp32 products keep up with memory better than the split kernel, half of whose wavefronts would have no rows.
+  if (sh.R > 64) return launch_score_split(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
   return sh.causal > 0 ? launch_f32_t<D, true>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream)
                        : launch_f32_t<D, false>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
 }

@@ -1,0 +1,85 @@
+"""The score kernels whose running sums have a fixed reference (bf16 windows of more than 128 rows, fp32 windows of more
+than 64): logits that climb far above the first stage's, blocks of query rows that are missing or partial, and numbers that
+have no split into bf16 parts."""
+
+import numpy as np
+import pytest
+
+from oracle import kvs_oracle as O
+from workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate_unit
+
+from helpers import DeviceBatch, from_device
+from test_gpu_parity import TOL_ALPHA, torch_sync, variant
+
+pytestmark = pytest.mark.gpu
+
+
+def score(units, dtype, D, G, W, causal=False):
+    batch = DeviceBatch(units, group=G, window=W, head_dim=D, dtype=dtype, n_sink=32, gap_rows=3, causal=causal)
+    batch.kvs.kvs_score_counts(batch.problem, batch.Q, batch.K, batch.V, batch.counts_in, batch.alpha_bar, batch.o_bar,
+                               batch.ws, stream=batch.stream())
+    torch_sync()
+    batch.check_guards()
+    alpha = from_device(batch.alpha_bar)
+    return [alpha[r0:r0 + u.n] for u, r0 in zip(units, batch.problem.in_rows)]
+
+
+@pytest.mark.parametrize("base,dtype,D,G,W,lens,causal", [
+    ("llama8b_8k", "bf16", 128, 5, 32, [33, 64, 65, 1500], False),    # 160 rows: five blocks on four wavefronts
+    ("llama8b_8k", "bf16", 64, 7, 32, [2000, 127], True),             # 224 rows
+    ("llama8b_8k", "bf16", 128, 9, 31, [700, 129], True),             # 279 rows: nine blocks on eight, the last of 23
+    ("stream2560", "bf16", 128, 8, 64, [1300], False),                # 512 rows, cardinalities
+    ("llama8b_8k", "bf16", 64, 13, 40, [300], False),                 # 520 rows: a second launch of eight rows
+    ("llama8b_8k", "bf16", 128, 5, 32, [45000] * 6, False),           # more workgroups than compute units: the shared tiles
+    ("tiny", "f32", 128, 5, 13, [32, 33, 1000], False),               # 65 rows: a block of one row, a wavefront without
+    ("tiny", "f32", 64, 4, 32, [511, 64], True),
+    ("tiny", "f32", 128, 3, 43, [600], False),                        # 129 rows: eight wavefronts, three without rows
+    ("stream2560", "f32", 64, 8, 33, [900, 40], True),                # 264 rows: a second launch of eight
+])
+def test_score_wide_windows(base, dtype, D, G, W, lens, causal):
+    w = variant(base, dtype=dtype, head_dim=D, group=G, window=W, n_seq=len(lens), n_kv_heads=1).scaled(fresh_tail=16)
+    lens = [max(n, W) for n in lens]
+    units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate(lens)]
+    for i, got in enumerate(score(units, dtype, D, G, W, causal)):
+        u = units[i]
+        ref, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=W if causal else 0)
+        assert np.max(np.abs(got - ref) / ref) < TOL_ALPHA, i
+
+
+@pytest.mark.parametrize("dtype,D,G,W,n", [("bf16", 128, 8, 64, 2000), ("bf16", 64, 9, 32, 1100), ("f32", 128, 4, 32, 2000),
+                                           ("f32", 64, 8, 40, 1100)])
+def test_score_logits_that_climb(dtype, D, G, W, n):
+    """Keys 25 times larger at the end than at the start: a later stage's terms exceed the first one's by far more than
+    2^64, so its sums have to be formed again with a higher reference, several times per chunk."""
+    w = variant("tiny", dtype=dtype, head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1)
+    u = generate_unit(w, 0, 0, 0, n=n)
+    K = u.K * np.linspace(0.2, 5.0, n, dtype=np.float32)[:, None] ** 2
+    u.K = bf16_bits_to_f32(f32_to_bf16_bits(K)) if dtype == "bf16" else K.astype(np.float32)
+    e = (u.Q.reshape(-1, D).astype(np.float64) @ u.K.T.astype(np.float64)) / np.sqrt(D)
+    assert e.max() > 100
+    got = score([u], dtype, D, G, W)[0]
+    ref, _ = O.score(u.Q, u.K, u.V)
+    # TOL_ALPHA is for logits up to 20: the error of a term grows with the logit.  Terms that underflow are left out.
+    seen = ref > 1e-30
+    assert seen.sum() > 100
+    assert np.max(np.abs(got - ref)[seen] / ref[seen]) < TOL_ALPHA * np.abs(e).max() / 20
+
+
+@pytest.mark.parametrize("D,G,W", [(128, 4, 32), (64, 8, 32)])
+def test_score_f32_numbers_without_a_split(D, G, W):
+    """fp32 Keys that are minus infinity, or that round to infinity as bf16, in rows of a tile's beginning, middle and end:
+    a row all of whose logits are minus infinity has no mass and changes nothing for the others."""
+    n = 700
+    w = variant("tiny", dtype="f32", head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1)
+    u = generate_unit(w, 0, 0, 0, n=n)
+    u.Q[..., 5] = np.abs(u.Q[..., 5]) + np.float32(0.1)
+    u.Q[..., 6] = np.float32(1e-38)
+    u.K[[0, 100, 255, 640, 699], 5] = -np.inf
+    u.K[[31, 333], 6] = np.float32(3.4e38)
+    got = score([u], "f32", D, G, W)[0]
+    with np.errstate(invalid="ignore"):
+        ref, _ = O.score(u.Q, u.K, u.V)
+    assert (got[[0, 100, 255, 640, 699]] == 0).all() and np.isfinite(got).all()
+    keep = ref > 0
+    assert keep.sum() == n - 5
+    assert np.max(np.abs(got - ref)[keep] / ref[keep]) < TOL_ALPHA
