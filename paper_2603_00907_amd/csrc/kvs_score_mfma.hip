@@ -43,6 +43,7 @@ using namespace mfma;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
+constexpr float kSumLimit = 1.8446744e19f;  // 2^64 (sums against a fixed reference)
 
 template <int D, int NT, int WQ, int PHASE>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
@@ -594,19 +595,38 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
           mask_causal<2>(acc, lim2, base_t, half);
         }
         if (cnt) logits_with_counts<2>(acc, cnt, base_t, half, sl2);
+        // Terms against the reference that is there: any value within 2^64 of the largest term serves (the sum is a
+        // floating-point number).  Where a lane's sum is not below that (the first tile, whose reference is minus
+        // infinity, among them) the tile's maxima join and the terms are formed again.
+        float sum[NTB];
+        bool bad = false;
 #pragma unroll
         for (int nt = 0; nt < NTB; ++nt) {
           const int b = 2 * h + nt;
-          float tm = acc[nt][0];
+          float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
-          const float m_new = fmaxf(m_run[b], tm * sc);
-          const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-          float s = 0.f;
+          for (int v = 0; v < 16; ++v) s4[v % 4] += ex2(fmaf(acc[nt][v], sc, -m_run[b]));
+          sum[nt] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+          bad = bad || !(sum[nt] < kSumLimit);
+        }
+        if (__any(bad)) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[nt][v], sc, -m_safe));
-          l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
-          m_run[b] = m_new;
+          for (int nt = 0; nt < NTB; ++nt) {
+            const int b = 2 * h + nt;
+            float tm = acc[nt][0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
+            const float m_new = fmaxf(m_run[b], tm * sc);
+            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+            float s = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[nt][v], sc, -m_safe));
+            l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
+            m_run[b] = m_new;
+          }
+        } else {
+#pragma unroll
+          for (int nt = 0; nt < NTB; ++nt) l_run[2 * h + nt] += sum[nt];
         }
       } else {
         // Sweep 1, products taken as Q K^T: accumulator element v of block nt is query row
