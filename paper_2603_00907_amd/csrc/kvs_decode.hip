@@ -60,9 +60,9 @@ __device__ __forceinline__ size_t part_index(int unit_index, int chunk, int R, i
   return (((size_t)unit_index * kMaxChunks + chunk) * R + row) * (size_t)(D + 2);
 }
 
-template <typename T, int D>
+template <typename T, int D, typename Tab>
 __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
-    const UnitTable tab, const Shape sh, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+    const Tab tab, const Shape sh, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ counts, float* __restrict__ part) {
   constexpr int EPL = Piece<T>::N;
   constexpr int LPR = D / EPL;
@@ -180,8 +180,8 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
 }
 
 // out[unit, row, :] from the unit's chunk partials, in chunk order.  One workgroup of D threads per (unit, row).
-template <int D>
-__global__ __launch_bounds__(D) void decode_reduce_kernel(const UnitTable tab, const Shape sh,
+template <int D, typename Tab>
+__global__ __launch_bounds__(D) void decode_reduce_kernel(const Tab tab, const Shape sh,
                                                           const float* __restrict__ part, float* __restrict__ out) {
   const int R = sh.R;
   const Unit un = tab.unit(blockIdx.x / R);
@@ -284,9 +284,9 @@ __device__ __forceinline__ void combine_waves(const float (&sm_acc)[kMfmaWaves][
 //   Y = V_tile[:, 32 db ..] I          the V block in the accumulator layout, which is the token-major operand
 //                                      layout the next product needs (exact: bf16 times one)
 //   O^T[d, q] += Y^T P                 P as a bf16 pair hi + lo
-template <int D>
+template <int D, typename Tab>
 __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts, float* __restrict__ part) {
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
@@ -441,9 +441,9 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_kernel(
 // What bounds it: 128 products of 64 cycles per 32 rows (D = 128) and 32 KB, about the same time at 2 wavefronts per
 // SIMD; the vector-ALU kernel reads the cache once per four query rows instead (32 caches of 16384 rows, 32 query rows:
 // 127 us here, 4.2 TB/s, and 731 there).
-template <int D>
+template <int D, typename Tab>
 __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
-    const UnitTable tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
+    const Tab tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
     const float* __restrict__ V, const int32_t* __restrict__ counts, float* __restrict__ part) {
   constexpr int NP = D / 8;                 // 16-byte pieces of a row per half of the wavefront
   constexpr int LPR = D / 4;                // 16-byte pieces per row
@@ -602,11 +602,15 @@ hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q,
                            const int32_t* counts, float* part, float* out, hipStream_t stream) {
   int widest = 1;
   for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
-  hipLaunchKernelGGL((decode_mfma_f32_kernel<D>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, tab, sh,
-                     (const float*)Q, (const float*)K, (const float*)V, counts, part);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_mfma_f32_kernel<D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, t, sh,
+                       (const float*)Q, (const float*)K, (const float*)V, counts, part);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, part, out);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
+  });
   return hipGetLastError();
 }
 
@@ -615,11 +619,15 @@ hipError_t launch_mfma(const UnitTable& tab, const Shape& sh, const void* Q, con
                        const int32_t* counts, float* part, float* out, hipStream_t stream) {
   int widest = 1;
   for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
-  hipLaunchKernelGGL((decode_mfma_kernel<D>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, tab, sh,
-                     (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, counts, part);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_mfma_kernel<D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, t, sh,
+                       (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, counts, part);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, part, out);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
+  });
   return hipGetLastError();
 }
 
@@ -628,11 +636,15 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
                     const int32_t* counts, float* part, float* out, hipStream_t stream) {
   int widest = 1;
   for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
-  hipLaunchKernelGGL((decode_partial_kernel<T, D>), dim3(widest, tab.n_units), dim3(kThreads), 0, stream, tab, sh,
-                     (const T*)Q, (const T*)K, (const T*)V, counts, part);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_partial_kernel<T, D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kThreads), 0, stream, t, sh,
+                       (const T*)Q, (const T*)K, (const T*)V, counts, part);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, part, out);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
+  });
   return hipGetLastError();
 }
 

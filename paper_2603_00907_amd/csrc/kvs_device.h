@@ -95,7 +95,8 @@ constexpr int kSelCandPart = kSelCand + kSelCandMax;
 constexpr int kSelSharedInts = kSelCandPart + kSelCandMax;
 static_assert(kSelPartLow + kSelMaxParts <= kSelHist && kSelSharedInts % 4 == 0, "layout of the exchange area");
 
-struct UnitTable {
+template <int CAP>
+struct UnitTableT {
   const Unit* ext;      // DEVICE: the descriptors of a group of more than kInlineUnits units, else null
                         // (first, beside n_units: a kernel's first scalar load then brings both)
   int n_units;
@@ -106,19 +107,49 @@ struct UnitTable {
   int total_sparts;     // select workgroups
   int even;             // 1: every unit has the same number of chunks, merge workgroups, ... (see find_unit_by)
   const Unit* host;     // HOST: the same descriptors for the launchers (meaningless on the device), else null
-  Unit u[kInlineUnits]; // the descriptors of a smaller group
+  Unit u[CAP];          // the descriptors of a smaller group
 
   // Descriptor i, on either side.  On the device the external table is read through the constant address space:
   // the index is wavefront-uniform, so these are scalar loads like those of the kernel arguments.
   __host__ __device__ __forceinline__ Unit unit(int i) const {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (ext != nullptr) return ((const __attribute__((address_space(4))) Unit*)ext)[i];
+    if (CAP == kInlineUnits && ext != nullptr) return ((const __attribute__((address_space(4))) Unit*)ext)[i];
     return u[i];
 #else
     return host != nullptr ? host[i] : u[i];
 #endif
   }
 };
+typedef UnitTableT<kInlineUnits> UnitTable;
+// The table of a launch of few units.  64 descriptors are 3.6 KB of kernel arguments, which the host copies to where
+// the GPU reads them at every launch: a launch of an empty kernel takes 4.0 to 6.7 us with them and 3.5 to 3.8 with
+// 64 bytes, and a call on one layer is five such launches.  So kernels exist for both sizes (the table's type is a
+// template argument), and launch_with_table picks the one a launch needs.
+constexpr int kFewUnits = 8;
+typedef UnitTableT<kFewUnits> FewUnitTable;
+template <typename T> struct TableTypeOf;
+template <int CAP> struct TableTypeOf<const UnitTableT<CAP>&> { typedef UnitTableT<CAP> type; };
+// f(table): f launches a kernel with the table it is handed.
+template <typename F>
+inline void launch_with_table(const UnitTable& tab, F&& f) {
+  if (tab.n_units > kFewUnits) {
+    f(tab);
+    return;
+  }
+  FewUnitTable few;
+  few.ext = nullptr;
+  few.host = nullptr;
+  few.n_units = tab.n_units;
+  few.total_chunks = tab.total_chunks;
+  few.total_mblocks = tab.total_mblocks;
+  few.total_ochunks = tab.total_ochunks;
+  few.total_fitems = tab.total_fitems;
+  few.total_sparts = tab.total_sparts;
+  few.even = tab.even;
+  for (int i = 0; i < kFewUnits; ++i) few.u[i] = tab.u[i];
+  f(few);
+}
+#define KVS_TABLE_TYPE(t) typename TableTypeOf<decltype(t)>::type
 
 struct Shape {
   int R;            // query rows per unit (G*W)
@@ -245,20 +276,22 @@ __device__ __forceinline__ void load_row_consts(const float* __restrict__ c_row,
 }
 
 // The launch's total of a running count.
-template <int Unit::*BASE> __host__ __device__ __forceinline__ int total_of(const UnitTable& tab);
-template <> __host__ __device__ __forceinline__ int total_of<&Unit::chunk_base>(const UnitTable& tab) { return tab.total_chunks; }
-template <> __host__ __device__ __forceinline__ int total_of<&Unit::m_base>(const UnitTable& tab) { return tab.total_mblocks; }
-template <> __host__ __device__ __forceinline__ int total_of<&Unit::o_base>(const UnitTable& tab) { return tab.total_ochunks; }
-template <> __host__ __device__ __forceinline__ int total_of<&Unit::f_base>(const UnitTable& tab) { return tab.total_fitems; }
-template <> __host__ __device__ __forceinline__ int total_of<&Unit::s_base>(const UnitTable& tab) { return tab.total_sparts; }
+template <int Unit::*BASE, typename Tab>
+__host__ __device__ __forceinline__ int total_of(const Tab& tab) {
+  if constexpr (BASE == &Unit::chunk_base) return tab.total_chunks;
+  else if constexpr (BASE == &Unit::m_base) return tab.total_mblocks;
+  else if constexpr (BASE == &Unit::o_base) return tab.total_ochunks;
+  else if constexpr (BASE == &Unit::f_base) return tab.total_fitems;
+  else return tab.total_sparts;
+}
 
 // The last unit whose running count BASE (chunks, merge workgroups, ... of the launch's earlier units) is at most x:
 // the unit that work item x of the launch belongs to.  A division where all units have the same count (the heads of
 // one layer); otherwise a binary search, because the table lives in the kernel arguments and every probe is a scalar
 // load that the next one depends on (about a quarter of a microsecond when it misses the scalar cache: walking the
 // table unit by unit cost a 64-unit select launch 15 of its 37 us).
-template <int Unit::*BASE>
-__device__ __forceinline__ int find_unit_by(const UnitTable& tab, int x) {
+template <int Unit::*BASE, typename Tab>
+__device__ __forceinline__ int find_unit_by(const Tab& tab, int x) {
   if (tab.even) return x / (total_of<BASE>(tab) / tab.n_units);
   int lo = 0, hi = tab.n_units - 1;
   while (lo < hi) {
@@ -269,7 +302,8 @@ __device__ __forceinline__ int find_unit_by(const UnitTable& tab, int x) {
   return lo;
 }
 // Which unit a workgroup of a chunk-indexed launch works on.
-__device__ __forceinline__ int find_unit(const UnitTable& tab, int chunk) {
+template <typename Tab>
+__device__ __forceinline__ int find_unit(const Tab& tab, int chunk) {
   return find_unit_by<&Unit::chunk_base>(tab, chunk);
 }
 

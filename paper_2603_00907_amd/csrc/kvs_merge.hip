@@ -66,9 +66,9 @@ __device__ __forceinline__ int first_slot_start(const uint8_t* __restrict__ mk, 
 }
 
 // NORMS: `alpha_bar` holds A_t and `c_edge` C_t (o_bar and o_part are not used); otherwise c_edge is not used.
-template <typename T, int D, bool STREAM, bool COUNTS, bool NORMS>
+template <typename T, int D, bool STREAM, bool COUNTS, bool NORMS, typename Tab>
 __global__ __launch_bounds__(kThreads) void merge_kernel(
-    const UnitTable tab, const Shape sh, const T* __restrict__ K, const T* __restrict__ V,
+    const Tab tab, const Shape sh, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ counts_in, const float* __restrict__ alpha_bar, const float* __restrict__ o_bar, const float* __restrict__ o_part,
     const float* __restrict__ c_edge,
     const uint8_t* __restrict__ edge_mask, const int32_t* __restrict__ slot, T* __restrict__ K_out,
@@ -456,9 +456,11 @@ static hipError_t launch_merge_k(const UnitTable& tab, const Shape& sh, const vo
                                  const float* o_part, const uint8_t* edge_mask, const int32_t* slot, void* K_out,
                                  void* V_out, int32_t* counts, hipStream_t stream, const float* c_edge = nullptr) {
   const int split = merge_split(tab.total_mblocks);
-  hipLaunchKernelGGL((merge_kernel<T, D, STREAM, COUNTS, NORMS>), dim3(tab.total_mblocks << split), dim3(kThreads), 0,
-                     stream, tab, sh, (const T*)K, (const T*)V, counts_in, alpha_bar, o_bar, o_part, c_edge, edge_mask,
-                     slot, (T*)K_out, (T*)V_out, counts, split);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((merge_kernel<T, D, STREAM, COUNTS, NORMS, KVS_TABLE_TYPE(t)>), dim3(tab.total_mblocks << split), dim3(kThreads), 0,
+                       stream, t, sh, (const T*)K, (const T*)V, counts_in, alpha_bar, o_bar, o_part, c_edge, edge_mask,
+                       slot, (T*)K_out, (T*)V_out, counts, split);
+  });
   return hipGetLastError();
 }
 

@@ -174,9 +174,9 @@ __device__ __forceinline__ bf16x8 row_operand(const uint16_t* __restrict__ m, in
 #ifndef KVS_PQ_OUT_OCC
 #define KVS_PQ_OUT_OCC 2
 #endif
-template <int D, bool COUNTS>
+template <int D, bool COUNTS, typename Tab>
 __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
     float* __restrict__ o_part, float* __restrict__ p_part, const int split) {
   typedef Tile<D> TL;
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
 // added in order.  (Bound by the latency of the loads: with all pieces in one thread's loop, eight in flight, the
 // kernel took 13.9 us for 8 units of 64 pieces and 128 rows, and takes 8.2 with the quarters.)
 constexpr int kReduceParts = 4;
-template <int D>
-__global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const UnitTable tab, const Shape sh,
+template <int D, typename Tab>
+__global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const Tab tab, const Shape sh,
                                                           const float* __restrict__ o_part,
                                                           const float* __restrict__ p_part,
                                                           uint16_t* __restrict__ o_hi, uint16_t* __restrict__ o_lo,
@@ -407,9 +407,9 @@ __global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const U
 // A lane then holds ONE token (column t = lane % 32) and 16 query rows, so the sums over q are plain
 // register additions (plus one exchange between the wavefront's halves), and token t + 1 is the next lane
 // (one DPP wavefront shift).  Per (t, q): one exp2, two square roots, eleven other instructions.
-template <int D, bool COUNTS>
+template <int D, bool COUNTS, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
     const uint16_t* __restrict__ o_hi,
     const uint16_t* __restrict__ o_lo, const float* __restrict__ oo, float* __restrict__ a_tok,
@@ -645,9 +645,9 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
 // taken in turn: D / 8 adjacent lanes share a query row, eight dimensions each (one round of coalesced loads per row), the
 // rows' terms are added per lane group in row order and the groups in a fixed butterfly order.  Every marked token leaves
 // with a non-negative A_t, so no mark outlives this kernel.
-template <int D, bool COUNTS>
+template <int D, bool COUNTS, typename Tab>
 __global__ __launch_bounds__(kThreads) void pq_redo_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
     const uint16_t* __restrict__ o_hi, const uint16_t* __restrict__ o_lo, float* __restrict__ a_tok,
     float* __restrict__ c_edge) {
@@ -804,21 +804,29 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   const int split = pq_split(tab.total_chunks);
   const dim3 grid(tab.total_chunks << split), block(kThreads);
   float* p_part = o_part + (size_t)grid.x * sh.R * D;       // the weights' sums lie behind the launch's partials
-  hipLaunchKernelGGL((pq_out_kernel<D, COUNTS>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_part, p_part, split);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_part, p_part, split);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((pq_out_reduce_kernel<D>), dim3(tab.n_units * sh.R), dim3(D * kReduceParts), 0, stream, tab, sh,
-                     o_part, p_part, o_hi, o_lo, oo, split);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_out_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D * kReduceParts), 0, stream, t, sh,
+                       o_part, p_part, o_hi, o_lo, oo, split);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int longest = 1;
   for (int u = 0; u < tab.n_units; ++u) longest = longest > tab.unit(u).len ? longest : tab.unit(u).len;
   const dim3 spans(tab.n_units, (longest + kRedoSpan - 1) / kRedoSpan);
-  hipLaunchKernelGGL((pq_redo_kernel<D, COUNTS>), spans, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, a_tok, c_edge);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_redo_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), spans, block, 0, stream, t, sh, (const uint16_t*)Q,
+                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, a_tok, c_edge);
+  });
   return hipGetLastError();
 }
 

@@ -45,9 +45,9 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr float kSumLimit = 1.8446744e19f;  // 2^64 (sums against a fixed reference)
 
-template <int D, int NT, int WQ, int PHASE>
+template <int D, int NT, int WQ, int PHASE, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row) {
   constexpr int WT = kWaves / WQ;           // wavefronts that split the tiles
@@ -376,9 +376,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
 // rows are requested when the tile starts and used when its alpha_bar values exist, one tile of arithmetic
 // later, so they cost no waiting, and they travel while the sweep's own loads are idle behind its arithmetic.
 // Every workgroup leaves the sum over its chunk in o_part[unit][chunk]; consumers add the chunks in order.
-template <int D, int PHASE, bool STREAM, bool CAUSAL, bool OBAR, int QB>
+template <int D, int PHASE, bool STREAM, bool CAUSAL, bool OBAR, int QB, typename Tab>
 __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mfma_wide_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row, const uint16_t* __restrict__ V, float* __restrict__ o_part) {
   static_assert(!OBAR || PHASE == 1, "the Value pass belongs to sweep 1");
@@ -743,20 +743,26 @@ hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh, const void* Q, c
                          const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
                          hipStream_t stream) {
   dim3 grid(tab.total_chunks), block(QB == 2 ? 256 : 512);
-  hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, QB>), grid, block, 0, stream, tab, sh,
-                     (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                     (const uint16_t*)nullptr, (float*)nullptr);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                       (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                       (const uint16_t*)nullptr, (float*)nullptr);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   if (V != nullptr) {
-    hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, QB>), grid, block, 0, stream, tab, sh,
-                       (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                       (const uint16_t*)V, ws.o_part);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                         (const uint16_t*)V, ws.o_part);
+    });
   } else {
-    hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, false, QB>), grid, block, 0, stream, tab, sh,
-                       (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                       (const uint16_t*)nullptr, (float*)nullptr);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, false, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                         (const uint16_t*)nullptr, (float*)nullptr);
+    });
   }
   return hipGetLastError();
 }
@@ -777,13 +783,17 @@ template <int D, int NT, int WQ>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
                     const int32_t* counts_in, float* alpha_bar, const Workspace& ws, hipStream_t stream) {
   dim3 grid(tab.total_chunks), block(kThreads);
-  hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 0>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 0, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                       (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
-  hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 1>), grid, block, 0, stream, tab, sh, (const uint16_t*)Q,
-                     (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                       (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   return hipGetLastError();
 }
 
@@ -820,9 +830,9 @@ hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const 
 // floats of one row.  The K tile (32 rows) goes straight from global memory to registers, the tile after it is
 // requested before the products of this one start; the Q block (up to 64 rows) sits in LDS, XOR-swizzled in 16-byte pieces, and is re-read for every tile.  Accumulator layouts, the
 // running statistics of sweep 0 and the transposed products of sweep 1 are those of score_mfma_wide_kernel.
-template <int D, int PHASE, bool CAUSAL>
+template <int D, int PHASE, bool CAUSAL, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
-    const UnitTable tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
+    const Tab tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row) {
   constexpr int ROWB = D * 4;               // bytes per row
@@ -1022,12 +1032,16 @@ hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh, const void* Q, co
                         float* alpha_bar, const Workspace& ws, hipStream_t stream) {
   dim3 grid(tab.total_chunks), block(kThreads);
   hipError_t e;
-  hipLaunchKernelGGL((score_mfma_f32_kernel<D, 0, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                     (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_mfma_f32_kernel<D, 0, CAUSAL, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const float*)Q,
+                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
-  hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                     (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const float*)Q,
+                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   return hipGetLastError();
 }
 

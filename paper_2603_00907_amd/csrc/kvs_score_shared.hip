@@ -42,9 +42,9 @@ __device__ __forceinline__ void wait_loads_and_lds() {
   asm volatile("" ::: "memory");
 }
 
-template <int D, int NW, int PHASE, bool STREAM, bool OBAR>
+template <int D, int NW, int PHASE, bool STREAM, bool OBAR, typename Tab>
 __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
-    const UnitTable tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row, const uint16_t* __restrict__ V, float* __restrict__ o_part, const int qp) {
   static_assert(!OBAR || PHASE == 1, "the Value pass belongs to sweep 1");
@@ -432,21 +432,27 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   const dim3 grid(tab.total_chunks), block(NW * kWave);
   hipError_t e;
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
-    hipLaunchKernelGGL((score_shared_kernel<D, NW, 0, STREAM, false>), grid, block, 0, stream, tab, sh,
-                       (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                       (const uint16_t*)nullptr, (float*)nullptr, qp);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_shared_kernel<D, NW, 0, STREAM, false, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                         (const uint16_t*)nullptr, (float*)nullptr, qp);
+    });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
     if (V != nullptr && qp + NW * 64 >= sh.R) {              // the last launch alone knows the finished alpha_bar
-      hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, true>), grid, block, 0, stream, tab, sh,
-                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                         (const uint16_t*)V, ws.o_part, qp);
+      launch_with_table(tab, [&](const auto& t) {
+        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, true, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                           (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                           (const uint16_t*)V, ws.o_part, qp);
+      });
     } else {
-      hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, false>), grid, block, 0, stream, tab, sh,
-                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                         (const uint16_t*)nullptr, (float*)nullptr, qp);
+      launch_with_table(tab, [&](const auto& t) {
+        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, false, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                           (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
+                           (const uint16_t*)nullptr, (float*)nullptr, qp);
+      });
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

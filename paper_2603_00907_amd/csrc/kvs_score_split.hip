@@ -48,9 +48,9 @@ __device__ __forceinline__ void split3(const float4& x, const float4& y, uint4& 
   lo = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
-template <int D, int NW, int PHASE>
+template <int D, int NW, int PHASE, typename Tab>
 __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
-    const UnitTable tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
+    const Tab tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row, const int qp) {
   constexpr int KS = D / 16;                // MFMA k-steps
@@ -320,14 +320,18 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   const dim3 grid(tab.total_chunks), block(NW * kWave);
   hipError_t e;
   for (int qp = 0; qp < sh.R; qp += NW * 32) {
-    hipLaunchKernelGGL((score_split_kernel<D, NW, 0>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_split_kernel<D, NW, 0, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const float*)Q,
+                         (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
+    });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   for (int qp = 0; qp < sh.R; qp += NW * 32) {
-    hipLaunchKernelGGL((score_split_kernel<D, NW, 1>), grid, block, 0, stream, tab, sh, (const float*)Q,
-                       (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_split_kernel<D, NW, 1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const float*)Q,
+                         (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row, qp);
+    });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;

@@ -18,9 +18,9 @@ namespace {
 constexpr int kQB = 8;          // query rows held in registers at a time
 constexpr int kThreads = 256;
 
-template <typename T, int D, int PHASE>
+template <typename T, int D, int PHASE, typename Tab>
 __global__ __launch_bounds__(kThreads) void score_valu_kernel(
-    const UnitTable tab, const Shape sh, const T* __restrict__ Q, const T* __restrict__ K,
+    const Tab tab, const Shape sh, const T* __restrict__ Q, const T* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row) {
   constexpr int EPL = Piece<T>::N;          // elements per lane
@@ -142,7 +142,8 @@ __global__ __launch_bounds__(kThreads) void score_valu_kernel(
 // and reduced by each of them cost a fifth of that sweep.  Two threads share a row and take half of
 // the chunks each, all their loads in flight at once (a loop with a run-time trip count would
 // serialise the round trips); the order of the additions is fixed.
-__global__ __launch_bounds__(kThreads) void score_finalize_kernel(const UnitTable tab, const Shape sh,
+template <typename Tab>
+__global__ __launch_bounds__(kThreads) void score_finalize_kernel(const Tab tab, const Shape sh,
                                                                   const float2* __restrict__ stats_part,
                                                                   float* __restrict__ c_row,
                                                                   unsigned int* __restrict__ sel_shared) {
@@ -192,8 +193,10 @@ __global__ __launch_bounds__(kThreads) void score_finalize_kernel(const UnitTabl
 }  // namespace
 
 hipError_t launch_score_finalize(const UnitTable& tab, const Shape& sh, const Workspace& ws, hipStream_t stream) {
-  hipLaunchKernelGGL(score_finalize_kernel, dim3(tab.n_units), dim3(kThreads), 0, stream, tab, sh, ws.stats_part,
-                     ws.c_row, ws.sel_shared);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_finalize_kernel<KVS_TABLE_TYPE(t)>), dim3(tab.n_units), dim3(kThreads), 0, stream, t, sh, ws.stats_part,
+                       ws.c_row, ws.sel_shared);
+  });
   return hipGetLastError();
 }
 
@@ -202,13 +205,17 @@ static hipError_t launch_score_valu_t(const UnitTable& tab, const Shape& sh, con
                                       const int32_t* counts_in, float* alpha_bar, const Workspace& ws,
                                       hipStream_t stream) {
   dim3 grid(tab.total_chunks), block(kThreads);
-  hipLaunchKernelGGL((score_valu_kernel<T, D, 0>), grid, block, 0, stream, tab, sh, (const T*)Q, (const T*)K,
-                     counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_valu_kernel<T, D, 0, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const T*)Q, (const T*)K,
+                       counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
-  hipLaunchKernelGGL((score_valu_kernel<T, D, 1>), grid, block, 0, stream, tab, sh, (const T*)Q, (const T*)K,
-                     counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((score_valu_kernel<T, D, 1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const T*)Q, (const T*)K,
+                       counts_in, alpha_bar, ws.stats_part, ws.c_row);
+  });
   return hipGetLastError();
 }
 

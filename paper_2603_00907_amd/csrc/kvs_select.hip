@@ -1111,9 +1111,9 @@ __device__ __forceinline__ void obar_reduce_unit(const Unit& un, const Shape& sh
 // n_reduce) add one unit's partial o_bar sums up each, the others stream one chunk of V each.
 // KEYS: edge scores a select workgroup can keep in LDS.  The small size leaves room for three workgroups per CU,
 // which matters to the workgroups of the other kinds in the same launch.
-template <typename T, int D, int KEYS>
+template <typename T, int D, int KEYS, typename Tab>
 __global__ __launch_bounds__(kSelThreads) void select_obar_kernel(
-    const UnitTable tab, const Shape sh, const int n_select, const int n_reduce, const float* __restrict__ alpha_bar,
+    const Tab tab, const Shape sh, const int n_select, const int n_reduce, const float* __restrict__ alpha_bar,
     uint8_t* __restrict__ edge_mask, int32_t* __restrict__ slot, const T* __restrict__ V,
     const int32_t* __restrict__ counts_in, float* __restrict__ o_part, const float* __restrict__ parts_in,
     float* __restrict__ o_bar_out, unsigned int* sel_shared, const unsigned timeout_ticks) {
@@ -1147,7 +1147,8 @@ __global__ __launch_bounds__(kSelThreads) void select_obar_kernel(
   }
 }
 
-__global__ void obar_reduce_kernel(const UnitTable tab, const Shape sh, const float* __restrict__ parts,
+template <typename Tab>
+__global__ void obar_reduce_kernel(const Tab tab, const Shape sh, const float* __restrict__ parts,
                                    float* __restrict__ o_bar) {
   obar_reduce_unit(tab.unit(blockIdx.x), sh, parts, o_bar);
 }
@@ -1180,13 +1181,17 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, bool with_select, con
   }
   const dim3 grid(n_select + n_reduce + n_obar), block(kSelThreads);
   if (small) {
-    hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeysSmall>), grid, block, 0, stream, tab, sh, n_select, n_reduce,
-                       alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
-                       timeout_ticks);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeysSmall, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, n_select, n_reduce,
+                         alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
+                         timeout_ticks);
+    });
   } else {
-    hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeys>), grid, block, 0, stream, tab, sh, n_select, n_reduce,
-                       alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
-                       timeout_ticks);
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeys, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, n_select, n_reduce,
+                         alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
+                         timeout_ticks);
+    });
   }
   return hipGetLastError();
 }
@@ -1211,7 +1216,9 @@ hipError_t launch_select_obar(const UnitTable& tab, const Shape& sh, kvs_dtype d
 
 hipError_t launch_obar_reduce(const UnitTable& tab, const Shape& sh, const float* parts, float* o_bar,
                               hipStream_t stream) {
-  hipLaunchKernelGGL(obar_reduce_kernel, dim3(tab.n_units), dim3(128), 0, stream, tab, sh, parts, o_bar);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((obar_reduce_kernel<KVS_TABLE_TYPE(t)>), dim3(tab.n_units), dim3(128), 0, stream, t, sh, parts, o_bar);
+  });
   return hipGetLastError();
 }
 
