@@ -279,10 +279,11 @@ hipError_t per_query_norms(const Plan& plan, const UnitTable& tab, const Shape& 
                            const void* V, const int32_t* counts_in, float* alpha_bar, const Workspace& w,
                            const PerQueryWs& q, float* a_tok, float* c_edge, hipStream_t s) {
   const bool f32 = plan.dtype == KVS_F32;
-  const hipError_t e = launch_score(tab, sh, plan.dtype, Q, K, counts_in, f32 ? alpha_bar : nullptr, w, s);
+  Shape sh2 = sh;
+  sh2.keep_rows = 1;
+  const hipError_t e = launch_score(tab, sh2, plan.dtype, Q, K, counts_in, f32 ? alpha_bar : nullptr, w, s);
   if (e != hipSuccess) return e;
   if (f32) return launch_per_query_norms_f32(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_f32, a_tok, c_edge, s);
-  Shape sh2 = sh;
   sh2.alpha_out = alpha_bar;
   return launch_per_query_norms(tab, sh2, Q, K, V, counts_in, w.c_row, q.o_part, q.o_hi, q.o_lo, q.oo, a_tok, c_edge, s);
 }

@@ -160,6 +160,9 @@ struct Shape {
   int stream;       // 1: the launch's K and V exceed the last-level cache, rows are read non-temporally
   int rule;         // kvs_key_rule of the merged Key
   int causal;       // 0, or the window W when query row q only sees the rows up to its own position n - W + q % W
+  int keep_rows;    // 1: the caller reads the rows' normalisers (c_row) after the score phase
+  int fold;         // 1: sweep 1 reduces the chunks' statistics itself (load_row_consts), no finalize kernel has run
+  unsigned int* sel_clear;  // with fold: the exchange area of the selection that follows, which sweep 1 zeroes
   float* alpha_out; // per-query aggregation (bf16): where its kernels leave alpha_bar (the sweeps then only leave the
                     // rows' normalisers)
   int dec_chunk;    // decode attention: rows per workgroup, at least (chosen per launch, see launch_decode)
@@ -269,12 +272,6 @@ __device__ __forceinline__ int last_seen_row(int causal_w, int n, int qrow) {
   return causal_w > 0 ? n - causal_w + qrow % causal_w : 0x7fffffff;
 }
 
-// The unit's normalisers c[q] (written by the finalize kernel between the two sweeps) -> LDS.
-__device__ __forceinline__ void load_row_consts(const float* __restrict__ c_row, int unit_index, int R, float* sm_c) {
-  for (int q = threadIdx.x; q < R; q += blockDim.x) sm_c[q] = c_row[(size_t)unit_index * R + q];
-  __syncthreads();
-}
-
 // The launch's total of a running count.
 template <int Unit::*BASE, typename Tab>
 __host__ __device__ __forceinline__ int total_of(const Tab& tab) {
@@ -307,6 +304,74 @@ __device__ __forceinline__ int find_unit(const Tab& tab, int chunk) {
   return find_unit_by<&Unit::chunk_base>(tab, chunk);
 }
 
+// The sweep-1 kernels for up to 128 query rows (and the 256-row form of small launches) reduce the statistics of their
+// unit themselves: a workgroup fetches them in one round trip of its prologue, which costs it less than a finalize
+// kernel between the sweeps costs the call (one fp32 unit of 1024 tokens: 27.6 against 30.1 us per step; 8 units of 8192:
+// 44.0 against 45.5; 8 of 32768, 64 chunks each: 85.0 against 86.6; 256 of 32768: 2069 against 2080).
+
+// The normalisers c[q] of the unit's query rows q0 .. q0 + n - 1 -> sm_c (infinity for rows that do not exist:
+// exp2(-inf) = 0), read from c_row or, with sh.fold, formed from the chunks' (max, sum) pairs: M_q + log2(Z_q * R), see
+// score_finalize_kernel.  Two threads share a row, the chunks of each in flight together; fixed order.  Called by all
+// THREADS threads of the workgroup; a barrier is inside, and another one has to follow before sm_c is read.
+template <int THREADS>
+__device__ __forceinline__ void load_row_consts(const Shape& sh, const Unit& un, int unit_pos, bool first_chunk,
+                                                const float* __restrict__ c_row,
+                                                const float2* __restrict__ stats_part, int q0, int n, float* sm_c) {
+  const int R = sh.R;
+  if (!sh.fold) {
+    for (int i = threadIdx.x; i < n; i += THREADS)
+      sm_c[i] = q0 + i < R ? c_row[(size_t)un.index * R + q0 + i] : INFINITY;
+    return;
+  }
+  if (first_chunk && sh.sel_clear != nullptr && unit_pos < kInlineUnits) {
+    uint4* z = reinterpret_cast<uint4*>(sh.sel_clear + (size_t)unit_pos * kSelSharedInts);
+    for (int i = threadIdx.x; i < kSelSharedInts / 4; i += THREADS) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  constexpr int HALF = THREADS / 2, PER = kMaxChunks / 2;
+  static_assert(PER % 8 == 0, "batches of eight loads");
+  __shared__ float2 sm_second[HALF];
+  const int h = (int)threadIdx.x / HALF, r = (int)threadIdx.x % HALF;
+  for (int i0 = 0; i0 < n; i0 += HALF) {
+    const int i = i0 + r, q = q0 + i;
+    const bool ok = i < n && q < R;
+    const float2* src = stats_part + (size_t)un.index * kMaxChunks * R + q;
+    float2 v[PER];
+#pragma unroll
+    for (int k0 = 0; k0 < PER; k0 += 8) {                    // (uniform: a unit of few chunks is spared the rest)
+#pragma unroll
+      for (int k = k0; k < k0 + 8; ++k) v[k] = make_float2(-INFINITY, 0.f);
+      if (2 * k0 < un.n_chunks) {
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+          if (ok && 2 * k + h < un.n_chunks) v[k] = src[(size_t)(2 * k + h) * R];
+        }
+      }
+    }
+    float M = -INFINITY, Z = 0.f;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) M = fmaxf(M, v[k].x);
+#pragma unroll
+    for (int k0 = 0; k0 < PER; k0 += 8) {
+      if (2 * k0 < un.n_chunks) {
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+          if (v[k].y > 0.f) Z += v[k].y * __builtin_amdgcn_exp2f(v[k].x - M);
+        }
+      }
+    }
+    if (h == 1) sm_second[r] = make_float2(M, Z);
+    __syncthreads();
+    if (h == 0 && i < n) {
+      const float2 b = sm_second[r];
+      const float Mq = fmaxf(M, b.x);
+      float Zq = Z * __builtin_amdgcn_exp2f(M - Mq);
+      if (b.y > 0.f) Zq += b.y * __builtin_amdgcn_exp2f(b.x - Mq);
+      sm_c[i] = ok ? Mq + log2f(Zq * (float)R) : INFINITY;
+    }
+    if (i0 + HALF < n) __syncthreads();
+  }
+}
+
 // Launchers (defined next to their kernels).  All enqueue on `stream` and return the launch status.
 // The descriptors of a group of more than kInlineUnits units (host memory) into the workspace, by kernels that
 // carry them in their arguments.
@@ -314,6 +379,15 @@ hipError_t launch_unit_table(const Unit* units, int n_units, Unit* dst, hipStrea
 // Unit-wide softmax statistics from the chunks' partial ones (one small workgroup per unit).
 // (it also zeroes ws.sel_shared for the selection that follows, when there is one)
 hipError_t launch_score_finalize(const UnitTable& tab, const Shape& sh, const Workspace& ws, hipStream_t stream);
+// Between the sweeps of a launcher whose sweep-1 kernel calls load_row_consts: nothing, sweep 1 does the finalize kernel's
+// work (sh.fold), or that kernel, for callers that read the normalisers themselves.
+inline hipError_t between_sweeps(const UnitTable& tab, Shape& sh, const Workspace& ws, const float* alpha_bar,
+                                 hipStream_t stream) {
+  if (alpha_bar == nullptr || sh.keep_rows) return launch_score_finalize(tab, sh, ws, stream);
+  sh.fold = 1;
+  sh.sel_clear = tab.total_sparts != tab.n_units ? ws.sel_shared : nullptr;
+  return hipSuccess;
+}
 // Both score sweeps: chunk statistics, the finalize kernel, then alpha_bar (null: the first sweep and the finalize
 // kernel only).
 // counts_in (here and below): cardinalities of the input rows when the cache is already a merged one, or null.

@@ -128,7 +128,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     return true;
   };
 
-  if (PHASE == 1) load_row_consts(c_row, un.index, R, sm_c);
+  if (PHASE == 1) {
+    load_row_consts<kThreads>(sh, un, ui, chunk == 0, c_row, stats_part, 0, R, sm_c);
+    __syncthreads();
+  }
 
   for (int qp = 0; qp < R; qp += PASS_ROWS) {
     const bool first_pass = (qp == 0);
@@ -454,10 +457,8 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   // normalisers (written by the finalize kernel between the sweeps) are indexed by accumulator element and come
   // from LDS.  exp2(-inf) = 0: a row that does not exist adds nothing.
   if (PHASE == 1) {
-    if (tid < QROWS) {
-      sm_cq[tid] = (tid < R) ? c_row[(size_t)un.index * R + tid] : INFINITY;
-      sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
-    }
+    if (tid < QROWS) sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
+    load_row_consts<NTHR>(sh, un, ui, chunk == 0, c_row, stats_part, 0, QROWS, sm_cq);
     __syncthreads();
   }
 
@@ -739,9 +740,10 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
 }
 
 template <int D, bool STREAM, bool CAUSAL, int QB>
-hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
+hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh_in, const void* Q, const void* K,
                          const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
                          hipStream_t stream) {
+  Shape sh = sh_in;
   dim3 grid(tab.total_chunks), block(QB == 2 ? 256 : 512);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
@@ -750,7 +752,7 @@ hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh, const void* Q, c
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
+  if ((e = between_sweeps(tab, sh, ws, alpha_bar, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   if (V != nullptr) {
     launch_with_table(tab, [&](const auto& t) {
       hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
@@ -780,8 +782,9 @@ hipError_t launch_wide(const UnitTable& tab, const Shape& sh, const void* Q, con
 }
 
 template <int D, int NT, int WQ>
-hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
+hipError_t launch_t(const UnitTable& tab, const Shape& sh_in, const void* Q, const void* K,
                     const int32_t* counts_in, float* alpha_bar, const Workspace& ws, hipStream_t stream) {
+  Shape sh = sh_in;
   dim3 grid(tab.total_chunks), block(kThreads);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 0, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
@@ -789,7 +792,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
+  if ((e = between_sweeps(tab, sh, ws, alpha_bar, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_mfma_kernel<D, NT, WQ, 1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
                        (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
@@ -867,10 +870,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
   const uint4* Qg = reinterpret_cast<const uint4*>(Q + (size_t)un.index * R * D);
 
   if (PHASE == 1) {
-    if (tid < QROWS) {
-      sm_cq[tid] = (tid < R) ? c_row[(size_t)un.index * R + tid] : INFINITY;
-      sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
-    }
+    if (tid < QROWS) sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
+    load_row_consts<kThreads>(sh, un, ui, chunk == 0, c_row, stats_part, 0, QROWS, sm_cq);
   }
   int lim[NBLK];
 #pragma unroll
@@ -1028,8 +1029,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_f32_kernel(
 }
 
 template <int D, bool CAUSAL>
-hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const int32_t* counts_in,
+hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh_in, const void* Q, const void* K, const int32_t* counts_in,
                         float* alpha_bar, const Workspace& ws, hipStream_t stream) {
+  Shape sh = sh_in;
   dim3 grid(tab.total_chunks), block(kThreads);
   hipError_t e;
   launch_with_table(tab, [&](const auto& t) {
@@ -1037,7 +1039,7 @@ hipError_t launch_f32_t(const UnitTable& tab, const Shape& sh, const void* Q, co
                        (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);
   });
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
+  if ((e = between_sweeps(tab, sh, ws, alpha_bar, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_mfma_f32_kernel<D, 1, CAUSAL, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const float*)Q,
                        (const float*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row);

@@ -44,7 +44,10 @@ __global__ __launch_bounds__(kThreads) void score_valu_kernel(
   const uint4* Kp = reinterpret_cast<const uint4*>(K + (size_t)un.in_row * D) + piece;
   const uint4* Qp = reinterpret_cast<const uint4*>(Q + (size_t)un.index * R * D) + piece;
 
-  if (PHASE == 1) load_row_consts(c_row, un.index, R, sm_c);
+  if (PHASE == 1) {
+    load_row_consts<kThreads>(sh, un, ui, chunk == 0, c_row, stats_part, 0, R, sm_c);
+    __syncthreads();
+  }
 
   for (int qb = 0; qb < R; qb += kQB) {
     float qf[kQB][EPL];
@@ -138,8 +141,8 @@ __global__ __launch_bounds__(kThreads) void score_valu_kernel(
 
 // Unit-wide softmax statistics of every query row from the chunks' (max, sum) pairs, as the one
 // constant sweep 1 needs: c[q] = M_q + log2(Z_q * R), so that alpha[q,t] / R = exp2(logit2 - c[q]).
-// One workgroup per unit: every sweep-1 workgroup needs all of c, and 64 chunks x R pairs fetched
-// and reduced by each of them cost a fifth of that sweep.  Two threads share a row and take half of
+// One workgroup per unit, for the sweeps of wide windows and for callers that read c themselves (the other sweep-1
+// kernels form c in their prologue, see load_row_consts).  Two threads share a row and take half of
 // the chunks each, all their loads in flight at once (a loop with a run-time trip count would
 // serialise the round trips); the order of the additions is fixed.
 template <typename Tab>
@@ -201,9 +204,10 @@ hipError_t launch_score_finalize(const UnitTable& tab, const Shape& sh, const Wo
 }
 
 template <typename T, int D>
-static hipError_t launch_score_valu_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
+static hipError_t launch_score_valu_t(const UnitTable& tab, const Shape& sh_in, const void* Q, const void* K,
                                       const int32_t* counts_in, float* alpha_bar, const Workspace& ws,
                                       hipStream_t stream) {
+  Shape sh = sh_in;
   dim3 grid(tab.total_chunks), block(kThreads);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_valu_kernel<T, D, 0, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const T*)Q, (const T*)K,
@@ -211,7 +215,7 @@ static hipError_t launch_score_valu_t(const UnitTable& tab, const Shape& sh, con
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = launch_score_finalize(tab, sh, ws, stream)) != hipSuccess || alpha_bar == nullptr) return e;
+  if ((e = between_sweeps(tab, sh, ws, alpha_bar, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_valu_kernel<T, D, 1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const T*)Q, (const T*)K,
                        counts_in, alpha_bar, ws.stats_part, ws.c_row);
