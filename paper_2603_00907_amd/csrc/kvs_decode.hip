@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_kernel(
 // D / 32 * i + e being row i of accumulator e.  So nothing is turned and nothing staged but the Q block.
 // What bounds it: 128 products of 64 cycles per 32 rows (D = 128) and 32 KB, about the same time at 2 wavefronts per
 // SIMD; the vector-ALU kernel reads the cache once per four query rows instead (32 caches of 16384 rows, 32 query rows:
-// 127 us here, 4.2 TB/s, and 731 there).
+// 134 us here, 4.0 TB/s, and 731 there).
 template <int D, typename Tab>
 __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
     const Tab tab, const Shape sh, const float* __restrict__ Q, const float* __restrict__ K,
@@ -509,17 +509,36 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
         }
         asm volatile("" ::: "memory");
       };
-      load_values(std::integral_constant<int, 0>{});
       if (cnt != nullptr && half == 0) sm_cnt[wave][col] = (float)cnt[base_t + col];
-      f32x16 acc = zero;
+      // Four products of each logit from zero, then added up in pairs, and eight rows of V from zero below: this
+      // instruction rounds at every product, and one chain through all of them had an error against 64 bits of 1.6 to
+      // 3.3 times the vector-ALU kernel's.  This way it is 0.97 to 1.04 times that (means over 6 inputs each of 6 shapes
+      // from 1000 to 30000 rows and 7 to 64 query rows, 0.99 over all) for 5 % of the time at 32 query rows.
+      f32x16 acc, pair[5];
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         const float4 q4 = sm_q[col * LPR + ((2 * i + half) ^ (col % LPR))];
         const float qv[4] = {q4.x, q4.y, q4.z, q4.w};
         const float kv[4] = {a[i].x, a[i].y, a[i].z, a[i].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e], acc, 0, 0, 0);
-        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        for (int g = 0; g < 2; ++g) {
+          f32x16 s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[2 * g], qv[2 * g], zero, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[2 * g + 1], qv[2 * g + 1], s, 0, 0, 0);
+          // (a binary counter of finished sums: level l holds one of 2^l groups)
+          int level = 0;
+#pragma unroll
+          for (int l = 0; l < 5; ++l) {
+            if (((2 * i + g) >> l) % 2 == 1 && level == l) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) s[v] += pair[l][v];
+              level = l + 1;
+            }
+          }
+          if (2 * i + g == 2 * NP - 1) acc = s;
+          else pair[level] = s;
+        }
+        if (i == NP / 2 - 1) load_values(std::integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_sched_barrier(0);
       load_values(std::integral_constant<int, 1>{});
@@ -565,17 +584,23 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) l_run += p[v];
       }
+      // (eight rows from zero, like the logits' four products)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (v == 8) {
+      for (int h = 0; h < 2; ++h) {
+        if (h == 1) {
           __builtin_amdgcn_sched_barrier(0);
           load_keys(min(j + kMfmaWaves, ntiles - 1), a);     // flies during the rest (the last tile is fetched twice)
           asm volatile("" ::: "memory");
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int e = 0; e < DB; ++e)
-          accO[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[v][e], p[v], accO[e], 0, 0, 0);
+        for (int e = 0; e < DB; ++e) {
+          f32x16 s = zero;
+#pragma unroll
+          for (int v = 8 * h; v < 8 * h + 8; ++v) s = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[v][e], p[v], s, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) accO[e][v] += s[v];
+        }
       }
     }
 
@@ -654,8 +679,8 @@ hipError_t launch_decode(const UnitTable& tab, const Shape& sh_in, kvs_dtype dt,
                          const void* V, const int32_t* counts, float* part, float* out, hipStream_t stream) {
   // The vector-ALU kernels read the cache once per four query rows, the MFMA kernels once per 32.  bf16: up to four
   // rows they are equally fast (both latency-bound on caches of a few thousand rows), above that the MFMA kernel wins
-  // (64 caches of 4096 rows: 42 against 62 us at 8 rows, 55 against 200 us at 32 rows).  fp32, 32 caches: 40.7 against
-  // 62 us at 8 rows and 4096 cache rows, 127 against 731 us at 32 rows and 16384 cache rows.
+  // (64 caches of 4096 rows: 42 against 62 us at 8 rows, 55 against 200 us at 32 rows).  fp32, 32 caches: 43.5 against
+  // 62 us at 8 rows and 4096 cache rows, 134 against 731 us at 32 rows and 16384 cache rows.
   // KVS_DEBUG_DECODE_PATH forces one of them (used by the tests to cover both).
   Shape sh = sh_in;
   const int force = debug_switch(KVS_DEBUG_DECODE_PATH);
