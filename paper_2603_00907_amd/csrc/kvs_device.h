@@ -388,8 +388,8 @@ inline hipError_t between_sweeps(const UnitTable& tab, Shape& sh, const Workspac
   sh.sel_clear = tab.total_sparts != tab.n_units ? ws.sel_shared : nullptr;
   return hipSuccess;
 }
-// Both score sweeps: chunk statistics, the finalize kernel, then alpha_bar (null: the first sweep and the finalize
-// kernel only).
+// Both score sweeps: chunk statistics, the finalize kernel where sweep 1 does not do its work, then alpha_bar (null: the
+// first sweep and the finalize kernel only).
 // counts_in (here and below): cardinalities of the input rows when the cache is already a merged one, or null.
 // V non-null: the caller also needs o_bar; where the score kernel can carry the pass over V along, it does,
 // leaves the partial sums in the workspace and sets *o_layout to where they are (a value for Shape::o_from_score
