@@ -15,6 +15,27 @@ constexpr int kNonTemporal = 2;           // cache-policy bit of K tile loads th
 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Sums of 2^(e - m) over a row's logits e against a reference m that stays where it is (sweep 0 of the kernels for more
+// than 64 query rows): m is kHeadroom above the largest logit seen when it was last set, and a group of terms whose own
+// sum is not below kSumLimit sets it again.  Any m would do for the sum, which is a floating-point number, but not for
+// the exponent's argument, which is rounded in proportion to its size: the largest term's stays between -7.5 and 16,
+// where that rounding is at most that of the finished normaliser.  (A row that puts its weight on one token 2^61 above
+// its first ones: 0.24e-6 to 0.40e-6 for the normaliser's error, 0.31e-6 to 0.61e-6 with a running maximum, 2.6e-6 to
+// 2.9e-6 with a limit of 2^64 and no headroom.)  Without headroom a limit this low is met in nearly every tile of a wide
+// window (8 units of 131072 tokens, 512 rows, Queries three times as large: both sweeps 478 us, 431 with headroom; at
+// their usual size 372 either way).
+constexpr float kHeadroom = 7.5f;
+constexpr float kSumLimit = 65536.f;
+
+// sum += x, where `lost` holds what the additions before have rounded away.  For a lane that meets all tiles of a chunk:
+// a sum that is nearly all one term would round every later tile's share the same way (2048 tokens: 1e-6 of the sum).
+__device__ __forceinline__ void add_compensated(float& sum, float& lost, float x) {
+  const float y = x - lost;
+  const float t = sum + y;
+  lost = (t - sum) - y;
+  sum = t;
+}
+
 // Four 16-byte LDS reads at byte addresses ad[0..3] + OFF, complete on return.  Written as inline
 // assembly on purpose: the compiler treats every LDS read as dependent on ALL outstanding
 // global->LDS loads and would wait for the tile that is still being prefetched into the other buffer;

@@ -43,7 +43,6 @@ using namespace mfma;
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr float kSumLimit = 1.8446744e19f;  // 2^64 (sums against a fixed reference)
 
 template <int D, int NT, int WQ, int PHASE, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
@@ -596,9 +595,9 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
           mask_causal<2>(acc, lim2, base_t, half);
         }
         if (cnt) logits_with_counts<2>(acc, cnt, base_t, half, sl2);
-        // Terms against the reference that is there: any value within 2^64 of the largest term serves (the sum is a
-        // floating-point number).  Where a lane's sum is not below that (the first tile, whose reference is minus
-        // infinity, among them) the tile's maxima join and the terms are formed again.
+        // Terms against the reference that is there (see kSumLimit).  Where a lane's sum is not below the limit (the
+        // first tile, whose reference is minus infinity, among them) the reference rises to the tile's maxima and the
+        // headroom, and the terms are formed again.
         float sum[NTB];
         bool bad = false;
 #pragma unroll
@@ -617,7 +616,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
             float tm = acc[nt][0];
 #pragma unroll
             for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
-            const float m_new = fmaxf(m_run[b], tm * sc);
+            const float m_new = fmaxf(m_run[b], fmaf(tm, sc, kHeadroom));
             const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
             float s = 0.f;
 #pragma unroll

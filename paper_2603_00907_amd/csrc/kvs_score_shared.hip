@@ -19,10 +19,10 @@
 // wavefronts' shares meet in LDS, and each of them finishes 16 of the stage's tokens after the next
 // barrier: alpha_bar, and with OBAR the same tokens' rows of V, requested one stage before.
 //
-// Running statistics without a running maximum: sum 2^(e - m) for a fixed reference m, which any value within 2^64 of
-// the largest term serves as (the sum is a floating-point number: it loses nothing).  The first stage of a chunk takes
-// m from its maxima; a stage after which the sum of some lane is not below 2^64 is done again with the maxima taken
-// into account, from the tiles that are still in LDS.  That leaves 3 instead of 3.75 instructions per logit.
+// Running statistics without a running maximum: sum 2^(e - m) for a reference m that stays (see kSumLimit in
+// kvs_mfma_tile.h).  The first stage of a chunk takes m from its maxima; a stage whose own sum is not below the limit in
+// some lane is done again with the maxima taken into account, from the tiles that are still in LDS.  That leaves 3
+// instead of 3.75 instructions per logit.
 #include <type_traits>
 
 #include "kvs_mfma_tile.h"
@@ -33,7 +33,6 @@ namespace {
 using namespace mfma;
 
 constexpr int kBuf = 3;                     // stages of K in LDS: one being read, two on their way
-constexpr float kSumLimit = 1.8446744e19f;  // 2^64
 
 // s_waitcnt: at most N vector-memory operations outstanding, all LDS operations done
 template <int N>
@@ -146,7 +145,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) a_ofs[kk] = col * ROWB + ((2 * kk + half) ^ (col % LPR)) * 16;
 
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+  // sums against the reference m_run, and what their additions have lost so far (see add_compensated)
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, l_lost[2] = {0.f, 0.f};
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 vr[NLD];
   float o_acc[8];
@@ -195,12 +195,15 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
       float tm = acc[nt][0];
 #pragma unroll
       for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
-      const float m_new = fmaxf(m_run[nt], tm * sc);
+      const float m_new = fmaxf(m_run[nt], fmaf(tm, sc, kHeadroom));
       const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
       float s = 0.f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[nt][v], sc, -m_safe));
-      l_run[nt] = l_run[nt] * ex2(m_run[nt] - m_safe) + s;
+      const float down = ex2(m_run[nt] - m_safe);
+      l_run[nt] *= down;
+      l_lost[nt] *= down;
+      add_compensated(l_run[nt], l_lost[nt], s);
       m_run[nt] = m_new;
     }
   };
@@ -344,9 +347,18 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
       const float l_old[2] = {l_run[0], l_run[1]};
       bool redo = true;
       if (s > 0 && plain && cnt == nullptr) {
+        l_run[0] = l_run[1] = 0.f;           // the stage's own sums
         if (two_blocks) fast(std::integral_constant<int, 2>{});
         else fast(std::integral_constant<int, 1>{});
         redo = __any(!(l_run[0] < kSumLimit) || !(l_run[1] < kSumLimit));
+        if (!redo) {
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) {
+            const float stage_sum = l_run[nt];
+            l_run[nt] = l_old[nt];
+            add_compensated(l_run[nt], l_lost[nt], stage_sum);
+          }
+        }
       }
       if (redo) {
         asm volatile("; any stage");
@@ -390,6 +402,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     // the two halves of a wavefront hold the same query column for different token rows
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
+      l_run[nt] -= l_lost[nt];
       const float m_o = __shfl_xor(m_run[nt], 32, kWave);
       const float l_o = __shfl_xor(l_run[nt], 32, kWave);
       const float m_n = fmaxf(m_run[nt], m_o);

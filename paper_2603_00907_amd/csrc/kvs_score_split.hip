@@ -26,8 +26,6 @@ namespace {
 
 using namespace mfma;
 
-constexpr float kSumLimit = 1.8446744e19f;  // 2^64 (see kvs_score_shared.hip: sums against a fixed reference)
-
 // eight floats -> three bf16 operands whose sum they are
 __device__ __forceinline__ void split3(const float4& x, const float4& y, uint4& hi, uint4& mid, uint4& lo) {
   const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
@@ -195,8 +193,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
     return a;
   };
 
-  float m_run = -INFINITY, l_run = 0.f;
-  // sweep 0, any tile: what is masked drops out, the reference rises to the maximum
+  float m_run = -INFINITY, l_run = 0.f, l_lost = 0.f;       // (see add_compensated)
+  // sweep 0, any tile: what is masked drops out, the reference rises with the maximum (see kSumLimit)
   auto add_terms_any = [&](f32x16 acc, int j) {
     const int tile_t0 = t0 + j * kTile;
     if (t1 - tile_t0 < kTile || (sh.causal > 0 && tile_t0 + kTile > un.len - sh.causal + 1)) {
@@ -219,12 +217,15 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
     float tm = acc[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[v]);
-    const float m_new = fmaxf(m_run, tm * sc);
+    const float m_new = fmaxf(m_run, fmaf(tm, sc, kHeadroom));
     const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
     float s = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[v], sc, -m_safe));
-    l_run = l_run * ex2(m_run - m_safe) + s;
+    const float down = ex2(m_run - m_safe);
+    l_run *= down;
+    l_lost *= down;
+    add_compensated(l_run, l_lost, s);
     m_run = m_new;
   };
   // sweep 1: this lane's token summed over the wavefront's query rows
@@ -271,23 +272,22 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
       continue;
     }
     if (PHASE == 0) {
-      const float l_old = l_run, m_old = m_run;
+      const float l_old = l_run, m_old = m_run, lost_old = l_lost;
       const int tile_t0 = t0 + j * kTile;
       if (j > 0 && cnt == nullptr && tile_t0 + kTile <= t1 &&
           !(sh.causal > 0 && tile_t0 + kTile > un.len - sh.causal + 1)) {
         float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v % 4] += ex2(fmaf(acc[v], sl2, -m_run));
-        l_run += (s[0] + s[1]) + (s[2] + s[3]);
-        if (__any(!(l_run < kSumLimit))) {    // the reference is too low, or the sum is not a number
-          l_run = l_old;
-          add_terms_any(acc, j);
-        }
+        const float sum = (s[0] + s[1]) + (s[2] + s[3]);
+        if (__any(!(sum < kSumLimit))) add_terms_any(acc, j);   // the reference is too low, or the sum is not a number
+        else add_compensated(l_run, l_lost, sum);
       } else {
         add_terms_any(acc, j);
       }
-      if (__any(!(l_run < kSumLimit))) {
+      if (__any(!(l_run < INFINITY))) {
         l_run = l_old;
+        l_lost = lost_old;
         m_run = m_old;
         add_terms_any(products_f32(j), j);
       }
@@ -300,6 +300,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
 
   if (PHASE == 0) {
     // the two halves of a wavefront hold the same query column for different token rows
+    l_run -= l_lost;
     const float m_o = __shfl_xor(m_run, 32, kWave);
     const float l_o = __shfl_xor(l_run, 32, kWave);
     const float m_n = fmaxf(m_run, m_o);

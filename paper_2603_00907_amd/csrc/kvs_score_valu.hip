@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void score_finalize_kernel(const Tab tab,
       const float Mq = fmaxf(a.x, b.x);
       float Zq = a.y * __builtin_amdgcn_exp2f(a.x - Mq);
       if (b.y > 0.f) Zq += b.y * __builtin_amdgcn_exp2f(b.x - Mq);
-      c_row[(size_t)un.index * R + q] = Mq + log2f(Zq * (float)R);
+      c_row[(size_t)un.index * R + q] = plus_log2(Mq, Zq * (float)R);
     }
     __syncthreads();
   }

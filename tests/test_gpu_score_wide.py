@@ -1,6 +1,6 @@
-"""The score kernels whose running sums have a fixed reference (bf16 windows of more than 128 rows, fp32 windows of more
-than 64): logits that climb far above the first stage's, blocks of query rows that are missing or partial, and numbers that
-have no split into bf16 parts."""
+"""The score kernels whose running sums have a fixed reference (windows of more than 64 rows): logits that climb far above
+the first stage's, the rounding of the terms against a low reference, blocks of query rows that are missing or partial, and
+numbers that have no split into bf16 parts."""
 
 import numpy as np
 import pytest
@@ -9,7 +9,7 @@ from oracle import kvs_oracle as O
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate_unit
 
 from helpers import DeviceBatch, from_device
-from test_gpu_parity import TOL_ALPHA, torch_sync, variant
+from test_gpu_parity import TOL_ALPHA, switches, torch_sync, variant
 
 pytestmark = pytest.mark.gpu
 
@@ -46,23 +46,68 @@ def test_score_wide_windows(base, dtype, D, G, W, lens, causal):
         assert np.max(np.abs(got - ref) / ref) < TOL_ALPHA, i
 
 
-@pytest.mark.parametrize("dtype,D,G,W,n", [("bf16", 128, 8, 64, 2000), ("bf16", 64, 9, 32, 1100), ("f32", 128, 4, 32, 2000),
-                                           ("f32", 64, 8, 40, 1100)])
-def test_score_logits_that_climb(dtype, D, G, W, n):
+@pytest.mark.parametrize("dtype,D,G,W,n,base,causal", [
+    ("bf16", 128, 8, 64, 2000, "tiny", False), ("bf16", 64, 9, 32, 1100, "tiny", False),
+    ("f32", 128, 4, 32, 2000, "tiny", False), ("f32", 64, 8, 40, 1100, "tiny", False),
+    # every wavefront with tiles and a reference of its own: two, three and four blocks of 64 rows
+    ("bf16", 128, 4, 25, 3000, "tiny", False), ("bf16", 128, 4, 32, 2000, "tiny", False),
+    ("bf16", 64, 4, 32, 1100, "stream2560", False), ("bf16", 128, 4, 32, 1500, "stream2560", True),
+    ("bf16", 128, 5, 32, 2000, "tiny", False), ("bf16", 64, 5, 32, 1500, "stream2560", True),
+    ("bf16", 128, 7, 32, 2000, "stream2560", False), ("bf16", 128, 8, 32, 1100, "tiny", True),
+    ("f32", 128, 4, 32, 1500, "stream2560", True), ("bf16", 128, 8, 64, 1500, "stream2560", True),
+])
+def test_score_logits_that_climb(dtype, D, G, W, n, base, causal):
     """Keys 25 times larger at the end than at the start: a later stage's terms exceed the first one's by far more than
-    2^64, so its sums have to be formed again with a higher reference, several times per chunk."""
-    w = variant("tiny", dtype=dtype, head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1)
+    2^64, so its sums have to be formed again with a higher reference, several times per chunk; with cardinalities
+    (stream2560) and a causal window, too."""
+    w = variant(base, dtype=dtype, head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1).scaled(fresh_tail=16)
     u = generate_unit(w, 0, 0, 0, n=n)
     K = u.K * np.linspace(0.2, 5.0, n, dtype=np.float32)[:, None] ** 2
     u.K = bf16_bits_to_f32(f32_to_bf16_bits(K)) if dtype == "bf16" else K.astype(np.float32)
     e = (u.Q.reshape(-1, D).astype(np.float64) @ u.K.T.astype(np.float64)) / np.sqrt(D)
     assert e.max() > 100
-    got = score([u], dtype, D, G, W)[0]
-    ref, _ = O.score(u.Q, u.K, u.V)
+    got = score([u], dtype, D, G, W, causal)[0]
+    ref, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=W if causal else 0)
     # TOL_ALPHA is for logits up to 20: the error of a term grows with the logit.  Terms that underflow are left out.
     seen = ref > 1e-30
     assert seen.sum() > 100
     assert np.max(np.abs(got - ref)[seen] / ref[seen]) < TOL_ALPHA * np.abs(e).max() / 20
+
+
+@pytest.mark.parametrize("dtype,G,W", [("bf16", 3, 32), ("bf16", 4, 32), ("bf16", 5, 32), ("bf16", 8, 32), ("bf16", 8, 64),
+                                       ("f32", 4, 32), ("f32", 8, 32)])
+def test_score_normaliser_of_rows_that_rise_far_above_their_first_tokens(dtype, G, W):
+    """The first 256 tokens lie 2^61 below the one token on which a row puts nearly all its weight: formed against a
+    reference from those first tokens, that term's exponent argument would be 61, rounded to 2^-19.
+
+    Rows and dominating tokens: rows of a Hadamard matrix, so that every row has one token of its own (rows 128 apart share
+    theirs) with a base-2 logit of 6 to 7.5; all others have -20.  What rounds, as base-2 exponents: the normaliser, 13 to
+    17, by up to 2^-21 (2^-20 from 16 on); sweep 0's argument, up to 16 in size, 2^-21; sweep 1's, up to 9, 2^-21.  Each is
+    uniform, so the tokens' relative errors are ln 2 sqrt(2^-40 + 2 * 2^-42) / sqrt 3 = 4.7e-7 in the root mean square,
+    with an argument of 61 ln 2 sqrt(2^-38 + ...) / sqrt 3 = 8.6e-7."""
+    D, n, R = 128, 2048, G * W
+    H = np.array([[1.0]])
+    while H.shape[0] < D:
+        H = np.block([[H, H], [H, -H]])
+    w = variant("tiny", dtype=dtype, head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1)
+    u = generate_unit(w, 0, 0, 0, n=n)
+    u.Q = H[np.arange(R) % D].reshape(G, W, D).astype(np.float32)
+    rng = np.random.default_rng(R)
+    K = np.zeros((n, D))
+    K[:, 0] = -157.0
+    K[:256, 0] = -424.0
+    tokens = 300 + rng.permutation(n - 300)[:D]
+    gain = (210.0 + rng.integers(0, 5, D)) / 128.0             # (numbers that bf16 has)
+    K[tokens] += gain[:, None] * H
+    K[tokens, 0] = np.round(rng.uniform(-158.0, -154.0, D))
+    u.K = bf16_bits_to_f32(f32_to_bf16_bits(K.astype(np.float32)))
+    with switches(score_chunk=2048):
+        got = score([u], dtype, D, G, W)[0]
+    ref, _ = O.score(u.Q, u.K, u.V)
+    mine = tokens[:min(R, D)]
+    assert (ref[mine] > 0.9 / R).all()
+    err = (got[mine] - ref[mine]) / ref[mine]
+    assert np.sqrt(np.mean(err ** 2)) < 6e-7
 
 
 @pytest.mark.parametrize("D,G,W", [(128, 4, 32), (64, 8, 32)])
