@@ -17,8 +17,9 @@ extern "C" {
 
 typedef enum {
   KVS_DEBUG_SCORE_PATH = 0,   /* KVS_SCORE_PATH=valu   1: vector-ALU score kernels also where the MFMA kernels apply   */
-  KVS_DEBUG_SCORE_WIDE = 1,   /* KVS_SCORE_WIDE=0      1: more than 128 query rows take the kernel for 64 rows per
-                                                          wavefront in several passes                                   */
+  KVS_DEBUG_SCORE_WIDE = 1,   /* KVS_SCORE_WIDE=0|shared  1: more than 128 query rows take the kernel for 64 rows per
+                                                          wavefront in several passes; 2: the kernel whose wavefronts
+                                                          share the K tiles, also in small launches (bf16)             */
   KVS_DEBUG_FUSE_OBAR = 2,    /* KVS_FUSE_OBAR=0|1     1: the pass over V never rides along in score sweep 1,
                                                        2: always (where the kernel can carry it)                        */
   KVS_DEBUG_DECODE_PATH = 3,  /* KVS_DECODE_PATH=valu|mfma   1: vector-ALU decode kernel, 2: MFMA decode kernel         */

@@ -36,7 +36,7 @@ int env_choice(const char* name, const char* one, const char* two) {
 struct SwitchInit {
   SwitchInit() {
     g_switch[KVS_DEBUG_SCORE_PATH] = env_choice("KVS_SCORE_PATH", "valu", nullptr);
-    g_switch[KVS_DEBUG_SCORE_WIDE] = env_choice("KVS_SCORE_WIDE", "0", nullptr);
+    g_switch[KVS_DEBUG_SCORE_WIDE] = env_choice("KVS_SCORE_WIDE", "0", "shared");
     g_switch[KVS_DEBUG_FUSE_OBAR] = env_choice("KVS_FUSE_OBAR", "0", "1");
     g_switch[KVS_DEBUG_DECODE_PATH] = env_choice("KVS_DECODE_PATH", "valu", "mfma");
     const char* c = std::getenv("KVS_SCORE_CHUNK");

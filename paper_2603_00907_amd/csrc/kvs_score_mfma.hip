@@ -809,18 +809,19 @@ hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const 
   const int R = sh.R;
   if (R <= 32) return launch_t<D, 1, 1>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
   if (R <= 64) return launch_t<D, 2, 1>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
-  // 65..256 rows: rows 64.. from LDS, one pass over K (KVS_DEBUG_SCORE_WIDE keeps the kernel below for more than 128)
-  const bool wide_off = debug_switch(KVS_DEBUG_SCORE_WIDE) == 1;
+  // 65..256 rows: rows 64.. from LDS, one pass over K (KVS_DEBUG_SCORE_WIDE: 1 keeps the kernels of the last two lines for
+  // more than 128, 2 the one whose wavefronts share the K tiles whatever the launch's size)
+  const int forced = debug_switch(KVS_DEBUG_SCORE_WIDE);
   if (R <= 128) return launch_wide<D, 2>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
   // More than 128 rows: the kernel whose wavefronts share the K tiles, except up to 256 rows in a launch of no more
   // workgroups than the chip has compute units, where it has one wavefront per SIMD (4 units of 32768 tokens, 224 rows:
   // the step takes 74.7 us with it and 71.8 with the eight-wavefront workgroups here; 8 units, 256 rows: 107.6
   // against 117.0 us)
-  if (R <= 256 && tab.total_chunks <= 256 && !wide_off) {
+  if (R <= 256 && tab.total_chunks <= 256 && forced == 0) {
     return R <= 192 ? launch_wide<D, 3>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream)
                     : launch_wide<D, 4>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
   }
-  if (!wide_off) return launch_score_shared(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
+  if (forced != 1) return launch_score_shared(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
   if (R <= 256) return launch_t<D, 2, 2>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);    // two passes of 128 rows
   return launch_t<D, 2, 4>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);                  // passes of 256 rows
 }

@@ -69,9 +69,15 @@ def score_path(path):
     one-pass kernel that keeps K in LDS between its phases (windows of 65..128 bf16 rows; the library never picks it
     by itself); "defer": that kernel with a wait limit of zero, so that every work item whose unit is not complete
     at once goes to its second kernel; "narrow": more than 128 query rows with the kernel that keeps 64 rows per
-    wavefront in registers (passes of 128 or 256 rows) instead of the one that reads blocks of 64 rows from LDS."""
+    wavefront in registers (passes of 128 or 256 rows) instead of the one that reads blocks of 64 rows from LDS;
+    "shared": more than 128 bf16 query rows with the kernel whose wavefronts share the K tiles (up to 256 rows the library
+    picks it for launches of more than 256 workgroups only), "shared_fuse": with the pass over V carried along."""
     if path == "narrow":
         return switches(score_wide=1)
+    if path == "shared":
+        return switches(score_wide=2)
+    if path == "shared_fuse":
+        return switches(score_wide=2, fuse_obar=2)
     if path == "fuse":
         return switches(fuse_obar=2)
     if path == "nofuse":
@@ -90,15 +96,17 @@ SCORE_CASES = [
     ("tiny", "f32", 128, 2, 3, [777], None),
     ("tiny", "f32", 64, 3, 7, [1300, 64], None),
     ("tiny", "f32", 64, 1, 1, [257], None),
-    # fp32 with four query rows or more: the fp32 matrix-core kernel (and the vector-ALU one on the same shapes)
+    # fp32 with four query rows or more: the matrix-core kernels, fp32 products up to 64 rows and products of three bf16
+    # parts beyond (and the vector-ALU one on the same shapes)
     ("tiny", "f32", 128, 4, 32, [2100, 45], None),                    # 128 rows, a ragged last tile, a short unit
     ("tiny", "f32", 128, 4, 32, [2100], "valu"),
     ("tiny", "f32", 64, 4, 16, [1000, 32], None),                     # head_dim 64, a unit of exactly one tile
-    ("tiny", "f32", 128, 5, 32, [1500], None),                        # 160 rows: two launches per sweep
-    ("tiny", "f32", 64, 7, 40, [900], None),                          # 280 rows: three launches, the last of 24 rows
+    ("tiny", "f32", 128, 5, 32, [1500], None),                        # 160 rows: eight wavefronts, three without rows
+    ("tiny", "f32", 64, 7, 40, [900], None),                          # 280 rows: two launches, the last of 24 rows
     ("tiny", "f32", 128, 1, 16, [5000], None),                        # 16 rows: half a block
     ("stream2560", "f32", 128, 4, 8, [2560, 700], None),              # with cardinalities
-    ("stream2560", "f32", 128, 5, 32, [1300], None),                  # ... and two launches
+    ("stream2560", "f32", 128, 5, 32, [1300], None),                  # ... and 160 rows
+    ("stream2560", "f32", 64, 9, 32, [700, 33], None),                # ... and 288 rows: a second launch of 32
     ("llama8b_8k", "bf16", 128, 4, 32, [2500], None),
     ("llama8b_8k", "bf16", 128, 4, 32, [2500], "valu"),
     # the one-pass kernel (K kept in LDS between the phases): ragged tiles, a last item of a few rows, a one-tile
@@ -129,10 +137,22 @@ SCORE_CASES = [
     ("llama8b_8k", "bf16", 64, 8, 32, [1900], "fuse"),                # 256 rows, head_dim 64
     ("llama8b_8k", "bf16", 128, 8, 32, [3000], "narrow"),
     ("stream2560", "bf16", 128, 7, 32, [2560, 700], "fuse"),          # 224 rows with cardinalities
-    ("stress128k", "bf16", 128, 8, 64, [3000], None),                 # 512 rows: two launches of 256 per sweep
+    ("stress128k", "bf16", 128, 8, 64, [3000], None),                 # 512 rows: one launch per sweep, eight wavefronts
     ("stress128k", "bf16", 128, 8, 64, [3000, 77], "fuse"),
     ("stress128k", "bf16", 128, 8, 64, [3000], "narrow"),             # ... passes of 256 rows, four wavefronts a tile
-    ("stress128k", "bf16", 128, 8, 100, [1200], None),                # 800 rows: four launches, the last of 32 rows
+    ("stress128k", "bf16", 128, 8, 100, [1200], None),                # 800 rows: two launches, the last of 288 rows
+    ("stress128k", "bf16", 128, 8, 68, [1300, 90], "fuse"),           # 544 rows: the last launch of 32 carries V along
+    ("stream2560", "bf16", 64, 9, 57, [900, 65], "fuse"),             # 513 rows with cardinalities: one row in the last
+    # four wavefronts share the tiles (129..256 rows): five to eight blocks of 32 rows, head dim 64, chunks shorter than a
+    # stage of 64 tokens, cardinalities, the pass over V
+    ("llama8b_8k", "bf16", 128, 5, 32, [1700, 33], "shared"),
+    ("llama8b_8k", "bf16", 128, 3, 43, [2500, 64, 65, 127], "shared_fuse"),   # 129 rows
+    ("llama8b_8k", "bf16", 64, 6, 32, [1900, 40], "shared_fuse"),
+    ("qwen7b_32k", "bf16", 128, 7, 32, [2100, 100], "shared_fuse"),
+    ("llama8b_8k", "bf16", 64, 8, 32, [3000, 129], "shared_fuse"),
+    ("stream2560", "bf16", 128, 7, 32, [2560, 700], "shared_fuse"),
+    ("stream2560", "bf16", 64, 5, 29, [1500, 33], "shared"),
+    ("stream2560", "bf16", 128, 8, 32, [1111, 63], "shared_fuse"),
     ("stress128k", "bf16", 128, 8, 100, [1200], "narrow"),
     ("llama8b_8k", "bf16", 64, 1, 4, [500], None),
     # the vector-ALU kernels as the library's own choice: windows of one to three rows; units shorter than a tile
@@ -145,7 +165,7 @@ SCORE_CASES = [
     ("stream2560", "bf16", 128, 4, 32, [900], "valu"),
     ("stream2560", "bf16", 128, 1, 20, [1500], None),
     ("stream2560", "bf16", 64, 8, 40, [1100], None),
-    ("stream2560", "bf16", 64, 8, 40, [1100, 300], "fuse"),           # 320 rows with cardinalities, two launches
+    ("stream2560", "bf16", 64, 8, 40, [1100, 300], "fuse"),           # 320 rows with cardinalities
     ("stream2560", "f32", 64, 2, 5, [600], None),
 ]
 
@@ -564,8 +584,9 @@ def test_merge_bf16_output_rounds_to_nearest_even():
 
 CAUSAL_CASES = [
     # base, dtype, D, G, W, lengths, path: every score kernel, masked rows across tile and chunk borders
-    ("tiny", "f32", 128, 4, 32, [2053, 40], None),              # fp32 matrix-core kernel, 128 rows
-    ("tiny", "f32", 64, 5, 32, [900], None),                    # ... 160 rows in two launches
+    ("tiny", "f32", 128, 4, 32, [2053, 40], None),              # fp32 as three bf16 parts, 128 rows
+    ("tiny", "f32", 64, 5, 32, [900], None),                    # ... 160 rows
+    ("tiny", "f32", 128, 9, 32, [700, 40], None),               # ... 288 rows: a second launch of 32
     ("tiny", "f32", 64, 2, 5, [777, 5], None),                  # vector-ALU kernel; a unit that is all window
     ("llama8b_8k", "bf16", 128, 1, 20, [700, 33], None),        # 20 rows in one MFMA block
     ("llama8b_8k", "bf16", 64, 2, 32, [900], None),             # 64 rows
@@ -582,6 +603,11 @@ CAUSAL_CASES = [
     ("stress128k", "bf16", 128, 8, 40, [1200], None),           # 320 rows, window 40 crosses two tiles
     ("stress128k", "bf16", 128, 8, 40, [1200, 45], "fuse"),
     ("stress128k", "bf16", 128, 8, 40, [1200], "narrow"),
+    ("stress128k", "bf16", 128, 8, 68, [1300, 90], "fuse"),     # 544 rows: a second launch of 32
+    ("llama8b_8k", "bf16", 128, 5, 32, [2053, 40], "shared"),   # four wavefronts that share the tiles: 160 to 256 rows
+    ("qwen7b_32k", "bf16", 128, 7, 32, [2500, 2053, 127], "shared_fuse"),
+    ("llama8b_8k", "bf16", 64, 8, 32, [3000, 2053, 65], "shared_fuse"),
+    ("stream2560", "bf16", 128, 7, 32, [2560, 700], "shared_fuse"),
     ("stream2560", "bf16", 128, 4, 32, [2560], None),           # with cardinalities (the tail rows are fresh tokens)
 ]
 
@@ -1017,8 +1043,8 @@ def test_step_ragged_batch_full_size_in_one_call():
 
 def test_step_stress_full_size_all_heads_in_one_call():
     """The stress configuration as it is benchmarked: 8 KV heads of 131072 tokens -> 8192 with 512 query rows
-    (two launches of 256 rows per score sweep, the selection of units four times the key cache) in one call; head 0
-    is compared with the oracle."""
+    (one launch of eight wavefronts' rows per score sweep, the selection of units four times the key cache) in one call;
+    head 0 is compared with the oracle."""
     check_whole_batch_in_one_call(WORKLOADS["stress128k"], 0, [(0, 0)])
 
 

@@ -9,7 +9,7 @@ from oracle import kvs_oracle as O
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate_unit
 
 from helpers import DeviceBatch, from_device
-from test_gpu_parity import TOL_ALPHA, switches, torch_sync, variant
+from test_gpu_parity import TOL_ALPHA, score_path, switches, torch_sync, variant
 
 pytestmark = pytest.mark.gpu
 
@@ -20,17 +20,18 @@ def score(units, dtype, D, G, W, causal=False):
                                batch.ws, stream=batch.stream())
     torch_sync()
     batch.check_guards()
-    alpha = from_device(batch.alpha_bar)
-    return [alpha[r0:r0 + u.n] for u, r0 in zip(units, batch.problem.in_rows)]
+    alpha, o_bar = from_device(batch.alpha_bar), from_device(batch.o_bar)
+    return [alpha[r0:r0 + u.n] for u, r0 in zip(units, batch.problem.in_rows)], o_bar
 
 
 @pytest.mark.parametrize("base,dtype,D,G,W,lens,causal", [
-    ("llama8b_8k", "bf16", 128, 5, 32, [33, 64, 65, 1500], False),    # 160 rows: five blocks on four wavefronts
-    ("llama8b_8k", "bf16", 64, 7, 32, [2000, 127], True),             # 224 rows
+    ("llama8b_8k", "bf16", 128, 5, 32, [33, 64, 65, 1500], False),    # 160 rows: three blocks of 64, the last half empty
+    ("llama8b_8k", "bf16", 64, 7, 32, [2000, 127], True),             # 224 rows: four
     ("llama8b_8k", "bf16", 128, 9, 31, [700, 129], True),             # 279 rows: nine blocks on eight, the last of 23
     ("stream2560", "bf16", 128, 8, 64, [1300], False),                # 512 rows, cardinalities
     ("llama8b_8k", "bf16", 64, 13, 40, [300], False),                 # 520 rows: a second launch of eight rows
     ("llama8b_8k", "bf16", 128, 5, 32, [45000] * 6, False),           # more workgroups than compute units: the shared tiles
+    ("llama8b_8k", "bf16", 128, 7, 32, [29003] * 14, True),           # ... 208 MB: K read past the caches, V carried along
     ("tiny", "f32", 128, 5, 13, [32, 33, 1000], False),               # 65 rows: a block of one row, a wavefront without
     ("tiny", "f32", 64, 4, 32, [511, 64], True),
     ("tiny", "f32", 128, 3, 43, [600], False),                        # 129 rows: eight wavefronts, three without rows
@@ -40,13 +41,15 @@ def test_score_wide_windows(base, dtype, D, G, W, lens, causal):
     w = variant(base, dtype=dtype, head_dim=D, group=G, window=W, n_seq=len(lens), n_kv_heads=1).scaled(fresh_tail=16)
     lens = [max(n, W) for n in lens]
     units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate(lens)]
-    for i, got in enumerate(score(units, dtype, D, G, W, causal)):
-        u = units[i]
-        ref, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=W if causal else 0)
+    alphas, o_bar = score(units, dtype, D, G, W, causal)
+    for i, (u, got) in enumerate(zip(units, alphas)):
+        ref, ref_o = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=W if causal else 0)
         assert np.max(np.abs(got - ref) / ref) < TOL_ALPHA, i
+        bound = TOL_ALPHA * (ref @ np.abs(O.slot_values(u.V, u.counts))) + 1e-7
+        assert (np.abs(o_bar[i] - ref_o) <= bound).all(), i
 
 
-@pytest.mark.parametrize("dtype,D,G,W,n,base,causal", [
+CLIMB_CASES = [
     ("bf16", 128, 8, 64, 2000, "tiny", False), ("bf16", 64, 9, 32, 1100, "tiny", False),
     ("f32", 128, 4, 32, 2000, "tiny", False), ("f32", 64, 8, 40, 1100, "tiny", False),
     # every wavefront with tiles and a reference of its own: two, three and four blocks of 64 rows
@@ -55,8 +58,12 @@ def test_score_wide_windows(base, dtype, D, G, W, lens, causal):
     ("bf16", 128, 5, 32, 2000, "tiny", False), ("bf16", 64, 5, 32, 1500, "stream2560", True),
     ("bf16", 128, 7, 32, 2000, "stream2560", False), ("bf16", 128, 8, 32, 1100, "tiny", True),
     ("f32", 128, 4, 32, 1500, "stream2560", True), ("bf16", 128, 8, 64, 1500, "stream2560", True),
-])
-def test_score_logits_that_climb(dtype, D, G, W, n, base, causal):
+]
+
+
+@pytest.mark.parametrize("dtype,D,G,W,n,base,causal,path", [c + (None,) for c in CLIMB_CASES] + [
+    c + ("shared",) for c in CLIMB_CASES if c[0] == "bf16" and 128 < c[2] * c[3] <= 256])   # the kernel of larger launches
+def test_score_logits_that_climb(dtype, D, G, W, n, base, causal, path):
     """Keys 25 times larger at the end than at the start: a later stage's terms exceed the first one's by far more than
     2^64, so its sums have to be formed again with a higher reference, several times per chunk; with cardinalities
     (stream2560) and a causal window, too."""
@@ -66,7 +73,8 @@ def test_score_logits_that_climb(dtype, D, G, W, n, base, causal):
     u.K = bf16_bits_to_f32(f32_to_bf16_bits(K)) if dtype == "bf16" else K.astype(np.float32)
     e = (u.Q.reshape(-1, D).astype(np.float64) @ u.K.T.astype(np.float64)) / np.sqrt(D)
     assert e.max() > 100
-    got = score([u], dtype, D, G, W, causal)[0]
+    with score_path(path):
+        got = score([u], dtype, D, G, W, causal)[0][0]
     ref, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=W if causal else 0)
     # TOL_ALPHA is for logits up to 20: the error of a term grows with the logit.  Terms that underflow are left out.
     seen = ref > 1e-30
@@ -102,7 +110,7 @@ def test_score_normaliser_of_rows_that_rise_far_above_their_first_tokens(dtype, 
     K[tokens, 0] = np.round(rng.uniform(-158.0, -154.0, D))
     u.K = bf16_bits_to_f32(f32_to_bf16_bits(K.astype(np.float32)))
     with switches(score_chunk=2048):
-        got = score([u], dtype, D, G, W)[0]
+        got = score([u], dtype, D, G, W)[0][0]
     ref, _ = O.score(u.Q, u.K, u.V)
     mine = tokens[:min(R, D)]
     assert (ref[mine] > 0.9 / R).all()
@@ -121,7 +129,7 @@ def test_score_f32_numbers_without_a_split(D, G, W):
     u.Q[..., 6] = np.float32(1e-38)
     u.K[[0, 100, 255, 640, 699], 5] = -np.inf
     u.K[[31, 333], 6] = np.float32(3.4e38)
-    got = score([u], "f32", D, G, W)[0]
+    got = score([u], "f32", D, G, W)[0][0]
     with np.errstate(invalid="ignore"):
         ref, _ = O.score(u.Q, u.K, u.V)
     assert (got[[0, 100, 255, 640, 699]] == 0).all() and np.isfinite(got).all()
