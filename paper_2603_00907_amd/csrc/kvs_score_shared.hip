@@ -23,6 +23,9 @@
 // kvs_mfma_tile.h).  The first stage of a chunk takes m from its maxima; a stage whose own sum is not below the limit in
 // some lane is done again with the maxima taken into account, from the tiles that are still in LDS.  That leaves 3
 // instead of 3.75 instructions per logit.
+// Cardinalities enter the common stage as factors of its terms, four of them per LDS read.  (With log2 c added to every logit,
+// in the stage that is kept for masked tokens, 48 units of 32768 tokens took 452 us with 160 rows and 455 with 224, now 311
+// and 339; 8 units of 32768 with 520 rows 271, now 200.)
 #include <type_traits>
 
 #include "kvs_mfma_tile.h"
@@ -61,6 +64,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   __shared__ float sm_p[2][NW][STAGE];      // sweep 1: the wavefronts' shares of alpha_bar, two stages
   __shared__ float sm_o[NW][D];             // OBAR: the wavefronts' partial o_bar
   __shared__ int sm_lim[NW * 64 + 32];           // sweep 1, causal window: the last row each query row attends to
+  __shared__ __attribute__((aligned(16))) float sm_c[2][STAGE];   // sweep 0: the cardinalities of two stages' rows
 
   const int ui = find_unit(tab, blockIdx.x);
   const Unit un = tab.unit(ui);
@@ -87,6 +91,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   const int q_first = 32 * (wave + min(wave, extra));
   const bool two_blocks = wave < extra;
 
+  // sweep 0, cardinalities of stage s: memory -> a register of the first STAGE threads (one stage later: -> LDS, as floats)
+  int32_t raw_c = 1;
+  const bool has_counts = PHASE == 0 && cnt != nullptr && wave < STAGE / kWave;
+  auto fetch_counts = [&](int s) {
+    if (has_counts) raw_c = cnt[min(t0 + s * STAGE + tid, t1 - 1)];
+  };
   // K stage s -> ring buffer `dst`; tokens past the chunk's end repeat its last one
   auto issue_stage = [&](int s, unsigned char* dst) {
     const int s0 = t0 + s * STAGE;
@@ -102,8 +112,11 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
                                        STREAM && PHASE == 0 ? kNonTemporal : 0);
     }
   };
+  fetch_counts(0);
   issue_stage(0, sm_k[0]);
   if (nstages > 1) issue_stage(1, sm_k[1]);
+  if (has_counts) sm_c[0][tid] = (float)raw_c;
+  fetch_counts(1);
   if (PHASE == 1) {                         // (read after the loop's barriers)
     sm_lim[tid] = last_seen_row(sh.causal, un.len, qp + tid);
     if (tid < 32) sm_lim[NW * 64 + tid] = 0;
@@ -168,7 +181,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     }
   };
   // sweep 0, any tile: rows past the chunk's end or the causal limit drop out, cardinalities join, the reference rises
-  auto add_terms_any = [&](f32x16 (&acc)[2], int tile_t0) {
+  auto add_terms_any = [&](f32x16 (&acc)[2], int tile_t0, const float* tile_c) {
     const int valid = t1 - tile_t0;
     if (valid < kTile) {
 #pragma unroll
@@ -184,7 +197,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     if (cnt) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float lc = log2f((float)cnt[min(tile_t0 + 8 * (v / 4) + 4 * half + (v % 4), t1 - 1)]);
+        const float lc = log2f(tile_c[8 * (v / 4) + 4 * half + (v % 4)]);
         acc[0][v] = fmaf(acc[0][v], sl2, lc);
         acc[1][v] = fmaf(acc[1][v], sl2, lc);
       }
@@ -277,7 +290,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
 
   // One stage.  `rd` and `wr` are different buffers of the ring, and saying so (__restrict__ arguments) is what keeps
   // the compiler from waiting for the loads into `wr` in front of every read of `rd`.
-  auto stage = [&](const int s, const unsigned char* __restrict__ rd, unsigned char* __restrict__ wr) {
+  auto stage = [&](const int s, const unsigned char* __restrict__ rd, unsigned char* __restrict__ wr,
+                   const float* __restrict__ rd_c) {
+    if (has_counts) {
+      sm_c[(s + 1) & 1][tid] = (float)raw_c;
+      fetch_counts(s + 2);                                   // (before stage s + 2 of K, whose loads the next wait leaves out)
+    }
     if (s + 2 < nstages) issue_stage(s + 2, wr);
     if (OBAR) load_values(s);
     const int s0 = t0 + s * STAGE;
@@ -286,8 +304,9 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     // and the order is pinned step by step: left to itself the compiler issues the products in runs and the terms in
     // runs, and the two wavefronts of a SIMD then fall into step and compete for one pipe after the other.  Operands
     // are read three steps ahead.
-    auto fast = [&](auto ntb_c) {
+    auto fast = [&](auto ntb_c, auto counts_c) {
       constexpr int NTB = decltype(ntb_c)::value;            // blocks of query rows
+      constexpr bool COUNTS = decltype(counts_c)::value;     // sweep 0: a row that stands for c tokens has c equal terms
       asm volatile("; plain stage, %0 blocks" :: "n"(NTB));
       f32x16 acc[2][2];
       bf16x8 ring[4];
@@ -298,7 +317,25 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
       for (int i = 0; i < 3; ++i) ring[i] = operand(i);
       constexpr int PER = 16 / KS;                           // terms per step and block
       float sum[2] = {0.f, 0.f};
+      // the cardinalities of the four rows that group g of a tile's terms belongs to, read one group ahead
+      float4 cc = make_float4(0.f, 0.f, 0.f, 0.f), cc_next = cc;
+      auto group_counts = [&](int g) {
+        return *reinterpret_cast<const float4*>(rd_c + (g / 4) * kTile + 8 * (g % 4) + 4 * half);
+      };
+      if constexpr (COUNTS) cc_next = group_counts(0);
       auto terms = [&](int i, int kk) {                      // share kk of tile i's terms
+        float cf[PER];
+        if constexpr (COUNTS) {
+          constexpr int STEPS = 4 / PER;                     // steps per group of four rows
+          if (kk % STEPS == 0) {
+            cc = cc_next;
+            const int g = 4 * i + kk / STEPS + 1;
+            if (g < 4 * NT) cc_next = group_counts(g);
+          }
+          const float c4[4] = {cc.x, cc.y, cc.z, cc.w};
+#pragma unroll
+          for (int j = 0; j < PER; ++j) cf[j] = c4[(kk % STEPS) * PER + j];
+        }
 #pragma unroll
         for (int nt = 0; nt < NTB; ++nt) {
           float e[PER];
@@ -308,7 +345,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
             e[j] = ex2(fmaf(acc[i & 1][nt][v], sl2, PHASE == 0 ? -m_run[nt] : -cq[nt][v]));
           }
 #pragma unroll
-          for (int j = 0; j < PER; ++j) sum[nt] += e[j];
+          for (int j = 0; j < PER; ++j) sum[nt] = COUNTS ? fmaf(cf[j], e[j], sum[nt]) : sum[nt] + e[j];
         }
         if (kk == KS - 1) {
           if (PHASE == 0) {
@@ -346,10 +383,14 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     if (PHASE == 0) {
       const float l_old[2] = {l_run[0], l_run[1]};
       bool redo = true;
-      if (s > 0 && plain && cnt == nullptr) {
+      if (s > 0 && plain) {
         l_run[0] = l_run[1] = 0.f;           // the stage's own sums
-        if (two_blocks) fast(std::integral_constant<int, 2>{});
-        else fast(std::integral_constant<int, 1>{});
+        auto run = [&](auto counts_c) {
+          if (two_blocks) fast(std::integral_constant<int, 2>{}, counts_c);
+          else fast(std::integral_constant<int, 1>{}, counts_c);
+        };
+        if (cnt != nullptr) run(std::true_type{});
+        else run(std::false_type{});
         redo = __any(!(l_run[0] < kSumLimit) || !(l_run[1] < kSumLimit));
         if (!redo) {
 #pragma unroll
@@ -369,12 +410,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
           if (s0 + i * kTile >= t1) break;
           f32x16 acc[2];
           products(rd + i * TILEB, acc);
-          add_terms_any(acc, s0 + i * kTile);
+          add_terms_any(acc, s0 + i * kTile, rd_c + i * kTile);
         }
       }
     } else if (plain) {
-      if (two_blocks) fast(std::integral_constant<int, 2>{});
-      else fast(std::integral_constant<int, 1>{});
+      if (two_blocks) fast(std::integral_constant<int, 2>{}, std::false_type{});
+      else fast(std::integral_constant<int, 1>{}, std::false_type{});
     } else {
       // (the marks keep the branches' ends and beginnings apart: merged, their accesses lose what is known about them)
       asm volatile("; any stage");
@@ -395,7 +436,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (PHASE == 1 && s > 0) finish_stage(s - 1);
-    stage(s, sm_k[s % kBuf], sm_k[(s + 2) % kBuf]);
+    stage(s, sm_k[s % kBuf], sm_k[(s + 2) % kBuf], sm_c[s & 1]);
   }
 
   if (PHASE == 0) {
