@@ -816,8 +816,14 @@ hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const 
   // More than 128 rows: the kernel whose wavefronts share the K tiles, except up to 256 rows in a launch of no more
   // workgroups than the chip has compute units, where it has one wavefront per SIMD (4 units of 32768 tokens, 224 rows:
   // the step takes 74.7 us with it and 71.8 with the eight-wavefront workgroups here; 8 units, 256 rows: 107.6
-  // against 117.0 us)
-  if (R <= 256 && tab.total_chunks <= 256 && forced == 0) {
+  // against 117.0 us).
+  // And up to 192 rows without cardinalities where the shared tiles gain too little for the one to three wavefronts of
+  // theirs that have half the others' rows: head dim 64 (8 units of 32768 tokens, 160 rows, both sweeps: 42.3 here, 47.5
+  // there), rows read past the caches (48 of 32768: 277 and 293; 48 of 16384: 153 and 175) and chunks of 256 tokens (24 of
+  // 4096: 40.5 and 44.4).  (8 of 32768: 66.6 and 64.2; with cardinalities 75.8 and 65.9, 48 of 32768 338 and 312.)
+  const bool few_rows = R <= 192 && counts_in == nullptr &&
+                        (D == 64 || sh.stream || tab.unit(0).chunk_len <= kMinChunkLen);
+  if (R <= 256 && (tab.total_chunks <= 256 || few_rows) && forced == 0) {
     return R <= 192 ? launch_wide<D, 3>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream)
                     : launch_wide<D, 4>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
   }

@@ -31,6 +31,7 @@ def score(units, dtype, D, G, W, causal=False):
     ("stream2560", "bf16", 128, 8, 64, [1300], False),                # 512 rows, cardinalities
     ("llama8b_8k", "bf16", 64, 13, 40, [300], False),                 # 520 rows: a second launch of eight rows
     ("llama8b_8k", "bf16", 128, 5, 32, [45000] * 6, False),           # more workgroups than compute units: the shared tiles
+    ("llama8b_8k", "bf16", 64, 5, 32, [20011] * 8, True),             # ... and tiles of their own, in three blocks of 64 rows
     ("llama8b_8k", "bf16", 128, 7, 32, [29003] * 14, True),           # ... 208 MB: K read past the caches, V carried along
     ("tiny", "f32", 128, 5, 13, [32, 33, 1000], False),               # 65 rows: a block of one row, a wavefront without
     ("tiny", "f32", 64, 4, 32, [511, 64], True),
