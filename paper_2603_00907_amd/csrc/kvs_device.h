@@ -304,11 +304,14 @@ __device__ __forceinline__ int find_unit(const Tab& tab, int chunk) {
   return find_unit_by<&Unit::chunk_base>(tab, chunk);
 }
 
-// A row's normaliser M + log2(s).  The logarithm is taken of s's mantissa: its instruction rounds in proportion to the
-// result, and not evenly (14 units of 20000 tokens, 224 rows: alpha_bar summed up to 1 + 3.2e-7 to 1 + 6.1e-7).
-__device__ __forceinline__ float plus_log2(float M, float s) {
-  return M + ((float)__builtin_amdgcn_frexp_expf(s) + log2f(__builtin_amdgcn_frexp_mantf(s)));
+// log2 of a positive normal number, by way of its mantissa: the instruction rounds in proportion to its result, and not
+// evenly, so that what it takes from a large logarithm doesn't cancel over the terms of a sum.
+__device__ __forceinline__ float even_log2(float x) {
+  return (float)__builtin_amdgcn_frexp_expf(x) + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(x));
 }
+// A row's normaliser M + log2(s).  (With the instruction alone, 14 units of 20000 tokens and 224 rows: alpha_bar summed up
+// to 1 + 3.2e-7 to 1 + 6.1e-7.)
+__device__ __forceinline__ float plus_log2(float M, float s) { return M + even_log2(s); }
 
 // The sweep-1 kernels for up to 128 query rows (and the 256-row form of small launches) reduce the statistics of their
 // unit themselves: a workgroup fetches them in one round trip of its prologue, which costs it less than a finalize

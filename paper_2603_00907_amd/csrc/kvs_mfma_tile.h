@@ -62,7 +62,7 @@ __device__ __forceinline__ void logits_with_counts(f32x16 (&acc)[NACC], const in
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int row = 8 * (v / 4) + 4 * half + (v % 4);
-    const float lc = log2f((float)cnt[base_t + row]);
+    const float lc = even_log2((float)cnt[base_t + row]);
 #pragma unroll
     for (int nt = 0; nt < NACC; ++nt) acc[nt][v] = fmaf(acc[nt][v], sl2, lc);
   }

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
       TL::store(sm_v[buf], rv, tid);
       if (COUNTS && tid < kTile) {
         const float c = (float)cnt[tile_base(j) + tid];
-        sm_lc[buf][tid] = __builtin_amdgcn_logf(c);          // (base 2)
+        sm_lc[buf][tid] = even_log2(c);
         sm_ic[buf][tid] = __builtin_amdgcn_rcpf(c);
         sm_cc[buf][tid] = c;
       }
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   __shared__ float sm_al[2][kWaves][kTile];                          // sum_q alpha / R: the wavefront's share of alpha_bar
   __shared__ __attribute__((aligned(16))) float sm_negc[kPassRows];  // per query row of the pass: -c[q]
   __shared__ __attribute__((aligned(16))) int sm_lim[kPassRows];     // causal window: last row attended to
-  __shared__ float sm_lc[2][kTile + 1], sm_ic[2][kTile + 1];         // COUNTS: log2 c and 1 / c of the tile's rows
+  __shared__ float sm_cc[2][kTile + 1], sm_ic[2][kTile + 1];         // COUNTS: c and 1 / c of the tile's rows
 
   const int ui = find_unit(tab, (int)blockIdx.x >> split);
   const Unit un = tab.unit(ui);
@@ -496,6 +496,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
             al += sm_al[buf][w][r];
           }
           if (r == kTile - 1) c = 0.f;                     // only the unit's last token: it has no next one
+          if (COUNTS) al *= sm_cc[buf][r];
           if (qp > 0) {                                    // later passes add their query rows
             const float before = At[t];
             mark |= __float_as_uint(before);
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
       TL::store(sm_v[buf], rv, tid);
       if (COUNTS && tid <= kTile) {           // (the spare entry stands for the last row's "next", which is never used)
         const float c = tid < kTile ? (float)cnt[tile_base(j) + tid] : 1.f;
-        sm_lc[buf][tid] = __builtin_amdgcn_logf(c);          // (base 2)
+        sm_cc[buf][tid] = c;
         sm_ic[buf][tid] = __builtin_amdgcn_rcpf(c);
       }
       __syncthreads();
@@ -566,9 +567,9 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
       // accumulator element v: query row 32 wave + 8 (v / 4) + 4 half + v % 4 of the pass, token column `col`
       float vv = sm_vv[buf][col];
       float vp = fmaf(2.f, sm_vd[buf][col], vv + sm_vv[buf][col + 1]);         // ||v_t + v_{t+1}||^2
-      float lc = 0.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
+      float cc = 1.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
       if (COUNTS) {
-        lc = sm_lc[buf][col];
+        cc = sm_cc[buf][col];
         ic = sm_ic[buf][col];
         const float icn = sm_ic[buf][col + 1];
         const float vvn = sm_vv[buf][col + 1] * icn * icn;
@@ -595,9 +596,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int v = 4 * g + i;
-            float a = ex2(fmaf(accS[v], sl2, COUNTS ? nc[i] + lc : nc[i]));  // alpha / R
+            // alpha / R (COUNTS: first of one of the c tokens; log2 c in the exponent would round with c's size)
+            float a = ex2(fmaf(accS[v], sl2, nc[i]));
             if (TAIL && t_abs > lim[i]) a = 0.f;
             sumP += a;
+            if (COUNTS) a *= cc;
             const float x = COUNTS ? fmaf(accX[v], ic, oo_init[v]) : accX[v]; // ||o||^2 - 2 v_t . o
             // the same quantities of token t + 1: the next lane (the last column's are not used)
             const float a_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x130, 0xF, 0xF, true));
@@ -700,8 +703,8 @@ __global__ __launch_bounds__(kThreads) void pq_redo_kernel(
         if (COUNTS) {
           const float c = (float)counts_in[un.in_row + t];
           const float cn = has_next ? (float)counts_in[un.in_row + t + 1] : 1.f;
-          lc = __builtin_amdgcn_logf(c);                     // (base 2)
-          lcn = __builtin_amdgcn_logf(cn);
+          lc = even_log2(c);
+          lcn = even_log2(cn);
           ic = __builtin_amdgcn_rcpf(c);
           icn = __builtin_amdgcn_rcpf(cn);
         }

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     if (cnt) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float lc = log2f(tile_c[8 * (v / 4) + 4 * half + (v % 4)]);
+        const float lc = even_log2(tile_c[8 * (v / 4) + 4 * half + (v % 4)]);
         acc[0][v] = fmaf(acc[0][v], sl2, lc);
         acc[1][v] = fmaf(acc[1][v], sl2, lc);
       }

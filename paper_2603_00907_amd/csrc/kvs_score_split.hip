@@ -109,7 +109,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
         *reinterpret_cast<uint4*>(dst + 2 * TILEB + at) = lo;
       }
     }
-    if (PHASE == 0 && cnt != nullptr && tid < kTile) sm_lc[buf][tid] = log2f(raw_c);
+    if (PHASE == 0 && cnt != nullptr && tid < kTile) sm_lc[buf][tid] = even_log2(raw_c);
   };
   fetch(0);
 

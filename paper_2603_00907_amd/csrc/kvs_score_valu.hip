@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void score_valu_kernel(
         float kf[EPL];
         Piece<T>::unpack(raw[u], kf);
         // a row that stands for c tokens with this Key: c equal softmax terms, i.e. the logit plus log c
-        const float lc = counts_in ? log2f((float)cn[u]) : 0.f;
+        const float lc = counts_in ? even_log2((float)cn[u]) : 0.f;
         float a = 0.f;
 #pragma unroll
         for (int j = 0; j < kQB; ++j) {

@@ -152,6 +152,41 @@ def check_sensitivity(w, units, lens, D, G, W, dtype, causal):
         assert (A[gap0:gap0 + 3] == -7.0).all() and (C[gap0:gap0 + 3] == -7.0).all()
 
 
+def alpha_of_both_calls(units, D, G, W):
+    """alpha_bar as kvs_sensitivity(_counts) and as kvs_score(_counts) leave it."""
+    batch = DeviceBatch(units, group=G, window=W, head_dim=D, dtype="bf16", n_sink=2, gap_rows=3)
+    a_tok, c_edge, ws = per_query_buffers(batch)
+    batch.kvs.kvs_sensitivity_counts(batch.problem, batch.Q, batch.K, batch.V, batch.counts_in, batch.alpha_bar, a_tok,
+                                     c_edge, ws, stream=batch.stream())
+    torch_sync()
+    got = from_device(batch.alpha_bar)
+    batch.alpha_bar.fill_(-7.0)
+    batch.kvs.kvs_score_counts(batch.problem, batch.Q, batch.K, batch.V, batch.counts_in, batch.alpha_bar, batch.o_bar,
+                               batch.ws, stream=batch.stream())
+    torch_sync()
+    batch.check_guards()
+    return got, from_device(batch.alpha_bar)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_alpha_of_rows_with_large_cardinalities(D):
+    """Cardinalities of 2^16 to 10^7: they multiply, so alpha_bar rounds as kvs_score's does over 64 rows.  What differs
+    between the two calls: the exponents (of one of the c tokens' share of a row, over 128 rows: about 2^-40, so numbers from
+    32 to 64) rounded once each, to steps of 2^-18: ln 2 2^-18 sqrt(2 / 12) / sqrt 128 = 0.95e-7 in the root mean square over
+    128 rows; and the order of 128 additions (2^-25 each of a sum that grows: 2^-25 sqrt(128 / 3) = 1.95e-7 at most):
+    2.9e-7 together.  log2 c, 16 to 23, as part of the exponent rounds by up to 2^-20 and in its instruction by as much
+    again, the same for all rows of a token: 8.6e-7 and 8.9e-7 here."""
+    w = variant("stream2560", dtype="bf16", head_dim=D, group=4, window=32, n_seq=2, n_kv_heads=1).scaled(fresh_tail=32, n_sink=2)
+    units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate((1500, 65))]
+    rng = np.random.default_rng(D)
+    for u in units:
+        u.counts = np.exp(rng.uniform(np.log(2.0 ** 16), np.log(1e7), u.n)).astype(np.int32)
+    got, ref = alpha_of_both_calls(units, D, 4, 32)
+    rows = np.r_[0:1500, 1503:1568]
+    rms = np.sqrt(np.mean(((got - ref)[rows] / ref[rows]) ** 2))
+    assert rms < 2.9e-7, rms
+
+
 @pytest.mark.parametrize("dtype,G,W", [("bf16", 4, 1), ("f32", 1, 2)])
 def test_sensitivity_at_the_maximum_length(dtype, G, W):
     """One unit of KVS_MAX_LEN = 2^22 rows, head dim 128 (with fp32 the longest rows there are: the last one ends one
