@@ -21,6 +21,12 @@ hipError_t launch_score_mfma(const UnitTable& tab, const Shape& sh, kvs_dtype dt
 bool score_mfma_supported(const UnitTable& tab, const Shape& sh, kvs_dtype dt);
 bool score_mfma_takes_values(const Shape& sh, kvs_dtype dt);
 
+// Which kernels score a launch: the matrix cores', or the vector ALU's (windows of one to three rows, units shorter than
+// a tile, KVS_DEBUG_SCORE_PATH, by which the tests cover both).
+static bool score_on_matrix_cores(const UnitTable& tab, const Shape& sh, kvs_dtype dt) {
+  return debug_switch(KVS_DEBUG_SCORE_PATH) != 1 && score_mfma_supported(tab, sh, dt);
+}
+
 // ---- testing switches (kvs_debug.h): process-global, initial values read from the environment once, at load
 namespace {
 std::atomic<int> g_switch[KVS_DEBUG_N_SWITCHES];
@@ -274,17 +280,21 @@ kvs_status check_per_query(const Plan& plan) {
 
 // alpha_bar, A_t and C_t.  With bf16 inputs the kernels that form the norms recompute every row's attention anyway and
 // sum alpha_bar up on the way: the score phase is then only its first sweep (8 units of 32768 tokens, 128 query rows:
-// the second one takes 16.6 of the step's 212 us, the extra addition nothing that can be measured).
+// the second one takes 16.6 of the step's 212 us, the extra addition nothing that can be measured).  Not where the score
+// phase runs on the vector ALU (one to three rows): its logits are rounded differently from the norms' products, and
+// alpha_bar formed from its normalisers and their logits had up to 1.9 times the error against 64 bits (5000 tokens,
+// one to three rows); with both of its sweeps alpha_bar is kvs_score's to the bit.
 hipError_t per_query_norms(const Plan& plan, const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
                            const void* V, const int32_t* counts_in, float* alpha_bar, const Workspace& w,
                            const PerQueryWs& q, float* a_tok, float* c_edge, hipStream_t s) {
   const bool f32 = plan.dtype == KVS_F32;
+  const bool both_sweeps = f32 || !score_on_matrix_cores(tab, sh, plan.dtype);
   Shape sh2 = sh;
   sh2.keep_rows = 1;
-  const hipError_t e = launch_score(tab, sh2, plan.dtype, Q, K, counts_in, f32 ? alpha_bar : nullptr, w, s);
+  const hipError_t e = launch_score(tab, sh2, plan.dtype, Q, K, counts_in, both_sweeps ? alpha_bar : nullptr, w, s);
   if (e != hipSuccess) return e;
   if (f32) return launch_per_query_norms_f32(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_f32, a_tok, c_edge, s);
-  sh2.alpha_out = alpha_bar;
+  sh2.alpha_out = both_sweeps ? nullptr : alpha_bar;
   return launch_per_query_norms(tab, sh2, Q, K, V, counts_in, w.c_row, q.o_part, q.o_hi, q.o_lo, q.oo, a_tok, c_edge, s);
 }
 
@@ -446,8 +456,7 @@ int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mo
 hipError_t launch_score(const UnitTable& tab, const Shape& sh, kvs_dtype dt, const void* Q, const void* K,
                         const int32_t* counts_in, float* alpha_bar, const Workspace& ws, hipStream_t stream,
                         const void* V, int* o_layout) {
-  // KVS_DEBUG_SCORE_PATH forces the vector-ALU kernels (used by the tests to cover both paths).
-  const bool force_valu = debug_switch(KVS_DEBUG_SCORE_PATH) == 1;
+  const bool matrix_cores = score_on_matrix_cores(tab, sh, dt);
   if (o_layout) *o_layout = 0;
   const bool wants_o = V != nullptr && o_layout != nullptr;
   // Windows of 65..128 bf16 rows can take the one-pass kernel, which reads K once, keeps it in LDS between the
@@ -455,7 +464,7 @@ hipError_t launch_score(const UnitTable& tab, const Shape& sh, kvs_dtype dt, con
   // alpha_bar take the two sweeps).  It is correct and saves a third of the score phase's traffic, but on this
   // chip it is slower than the two sweeps (see the measurements at the kernel), so it runs on request only:
   // KVS_DEBUG_SCORE_FUSED = 2.
-  if (!force_valu && wants_o && ws.fsync != nullptr && debug_switch(KVS_DEBUG_SCORE_FUSED) == 2 &&
+  if (matrix_cores && wants_o && ws.fsync != nullptr && debug_switch(KVS_DEBUG_SCORE_FUSED) == 2 &&
       score_fused_supported(tab, sh, dt)) {
     *o_layout = 2;
     return launch_score_fused(tab, sh, Q, K, V, counts_in, alpha_bar, ws, stream);
@@ -465,7 +474,7 @@ hipError_t launch_score(const UnitTable& tab, const Shape& sh, kvs_dtype dt, con
   // separate pass over V saves (measured at 64 units of the headline shape: 199 against 226 us for sweep 1,
   // the pass over V and the selection).  A small launch keeps the selection hidden beside the pass over V
   // (8 units: 38 against 45 us).  KVS_DEBUG_FUSE_OBAR forces one or the other.
-  if (!force_valu && score_mfma_supported(tab, sh, dt)) {
+  if (matrix_cores) {
     const int fuse = debug_switch(KVS_DEBUG_FUSE_OBAR);
     // (The selection of a unit too long for the select kernel's LDS cache of keys takes several times longer when one
     // workgroup does it, 51 us at 65536 tokens: such launches keep it hidden beside the pass over V, unless the

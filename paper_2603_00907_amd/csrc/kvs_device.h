@@ -164,7 +164,7 @@ struct Shape {
   int fold;         // 1: sweep 1 reduces the chunks' statistics itself (load_row_consts), no finalize kernel has run
   unsigned int* sel_clear;  // with fold: the exchange area of the selection that follows, which sweep 1 zeroes
   float* alpha_out; // per-query aggregation (bf16): where its kernels leave alpha_bar (the sweeps then only leave the
-                    // rows' normalisers)
+                    // rows' normalisers), or null where the score phase has left it
   int dec_chunk;    // decode attention: rows per workgroup, at least (chosen per launch, see launch_decode)
   int o_from_score; // where the partial sums of o_bar are: 0: o_part, one per chunk of the o_bar pass; 1: o_part, one
                     // per SCORE chunk (written by sweep 1); 2: fo_part, one per work item of the one-pass score kernel
@@ -455,7 +455,7 @@ __host__ __device__ inline int pq_split(long long chunks) {
   while (split < 3 && (chunks << split) < 512) ++split;
   return split;
 }
-// Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out) from Q, K, V
+// Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out, if set) from Q, K, V
 // and the rows' normalisers c_row that the first score sweep leaves.  o_part: [chunks of the launch][R][D] fp32; o_hi, o_lo: [n_units][R][D] bf16;
 // oo: [n_units][R].
 hipError_t launch_per_query_norms(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,

@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   const uint16_t* Ol = o_lo + (size_t)un.index * R * D;
   float* At = a_tok + un.in_row;
   float* Ce = c_edge + un.in_row;
-  float* Al = sh.alpha_out + un.in_row;
+  float* Al = sh.alpha_out != nullptr ? sh.alpha_out + un.in_row : nullptr;
   const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -502,11 +502,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
             mark |= __float_as_uint(before);
             a += fabsf(before);
             c += Ce[t];
-            al += Al[t];
+            if (Al != nullptr) al += Al[t];
           }
           At[t] = __uint_as_float(__float_as_uint(a) | (mark & 0x80000000u));
           Ce[t] = c;
-          Al[t] = al;
+          if (Al != nullptr) Al[t] = al;
         }
       }
     };

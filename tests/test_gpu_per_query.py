@@ -168,6 +168,19 @@ def alpha_of_both_calls(units, D, G, W):
     return got, from_device(batch.alpha_bar)
 
 
+@pytest.mark.parametrize("counts", [False, True])
+@pytest.mark.parametrize("D,R", [(128, 1), (128, 2), (64, 3)])
+def test_alpha_of_small_windows_is_kvs_scores(D, R, counts):
+    """Windows of one to three rows are scored on the vector ALU in both calls: the same kernels, the same bits."""
+    w = variant("stream2560", dtype="bf16", head_dim=D, group=1, window=R, n_seq=2, n_kv_heads=1).scaled(fresh_tail=16, n_sink=2)
+    units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate((1500, 65))]
+    if not counts:
+        for u in units:
+            u.counts = None
+    got, ref = alpha_of_both_calls(units, D, 1, R)
+    assert np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_alpha_of_rows_with_large_cardinalities(D):
     """Cardinalities of 2^16 to 10^7: they multiply, so alpha_bar rounds as kvs_score's does over 64 rows.  What differs
