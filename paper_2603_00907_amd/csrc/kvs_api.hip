@@ -246,14 +246,19 @@ PerQueryWs carve_per_query(const Plan& plan, void* base, Workspace* w) {
   long long max_chunks = 0, pieces = 0;
   for (int first = 0, end; first < plan.n_units; first = end) {
     end = group_end(plan, first, plan.group_cap);
-    long long c = 0;
-    for (int u = first; u < end; ++u) c += plan.units[u].n_chunks;
+    long long c = 0, rows = 0, longest = 0;
+    for (int u = first; u < end; ++u) {
+      const Unit& un = plan.units[u];
+      c += un.n_chunks;
+      rows += un.len;
+      longest = std::max<long long>(longest, std::min(un.len, un.chunk_len));
+    }
     max_chunks = std::max(max_chunks, c);
-    pieces = std::max(pieces, plan.dtype == KVS_F32 ? c : c << pq_split(c));
+    pieces = std::max(pieces, plan.dtype == KVS_F32 ? c : c << pq_split(c, rows, longest, plan.shape.R, plan.shape.D));
   }
-  // (where a test asks for smaller groups than these, their chunks may be cut finer: into fewer than 1024 pieces)
+  // (where a test asks for smaller groups than these, their chunks may be cut finer)
   if (plan.dtype != KVS_F32 && plan.n_units > kInlineUnits)
-    pieces = std::max(pieces, std::min<long long>(8 * max_chunks, 1023));
+    pieces = std::max(pieces, std::min<long long>(8 * max_chunks, kMaxPqPieces));
   const size_t rd = (size_t)plan.shape.R * plan.shape.D;
   q.o_part = (float*)take((size_t)pieces * (rd + plan.shape.R) * sizeof(float));
   if (plan.dtype == KVS_F32) {

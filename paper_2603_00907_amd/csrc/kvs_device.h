@@ -448,11 +448,27 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
                               const int32_t* counts_in, const float* a_tok, const float* c_edge,
                               const uint8_t* edge_mask, const int32_t* slot, void* K_out, void* V_out, int32_t* counts,
                               hipStream_t stream);
-// Workgroups per score chunk of the per-query kernels (bf16) are 2^pq_split: a launch of few chunks cuts them (a
-// workgroup of pq_out leaves one partial output, so the workspace is sized by this too).
-__host__ __device__ inline int pq_split(long long chunks) {
+// Workgroups per score chunk of the per-query kernels (bf16) are 2^pq_split (a workgroup of pq_out leaves one partial
+// output, so the workspace is sized by this too).  rows, longest: rows of the launch and of its longest chunk.
+//
+// A launch of few chunks cuts them, as long as all pieces still run at once: two workgroups on each of the 256 CUs, or
+// one where more than 64 rows of 128 channels keep a workgroup busy enough and what it does once for its piece costs
+// more (14 ragged units, 60000 rows, 256 query rows, 241 chunks: 136 us uncut, 173 in four; 8 units of 8192, 256 chunks,
+// 128 query rows, head dim 64: 69.2 in two, 71.6 uncut).  And a launch whose chunks are of different lengths, or too few,
+// because a unit has at most 64, cuts them as long as the longest piece is a larger share of the rows than that (3 ragged
+// units, 255000 rows, 128 query rows, 188 chunks: 187 us in two, 250 uncut; 14 units, where all chunks are as long: 191
+// against 175): not below 128 rows, and into at most kMaxPqPieces.
+constexpr int kMaxPqPieces = 1024;
+inline int pq_split(long long chunks, long long rows, long long longest, int R, int D) {
+  const bool light = R <= 64 || D == 64;
   int split = 0;
-  while (split < 3 && (chunks << split) < 512) ++split;
+  while (split < 3) {
+    const long long pieces = chunks << (split + 1);
+    const bool few = pieces <= (light ? 512 : 256);
+    const bool uneven = (longest >> split) * (light ? 320 : 240) > rows && (longest >> split) > 256;
+    if (!few && !(uneven && pieces <= kMaxPqPieces)) break;
+    ++split;
+  }
   return split;
 }
 // Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out, if set) from Q, K, V

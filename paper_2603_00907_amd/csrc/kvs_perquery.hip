@@ -41,6 +41,7 @@
 // A workgroup has four wavefronts; wavefront w owns query rows 32w .. 32w+31 of a pass of 128 rows and
 // keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
 // 16-byte pieces, as in the score kernels).  Results do not depend on timing: no atomics, fixed orders.
+#include <algorithm>
 #include <type_traits>
 
 #include "kvs_device.h"
@@ -114,8 +115,6 @@ __device__ __forceinline__ void split8w(const float* f, bf16x8& hi, bf16x8& lo, 
   lo = as_bf16x8(make_uint4(l[0], l[1], l[2], l[3]));
 }
 
-// (One unit of 35154 tokens with 256 rows, 62 chunks: the step takes 132 us with its chunks cut into eight pieces for
-// these kernels, 208 with one workgroup per chunk and the second sweep.)
 // The tokens of workgroup b: piece b % 2^split of its chunk, a multiple of 32 tokens long (the last one: what is left).
 __device__ __forceinline__ void piece_range(const Unit& un, int b, int split, int& t0, int& t1) {
   const int c0 = ((b >> split) - un.chunk_base) * un.chunk_len;
@@ -804,7 +803,15 @@ template <int D, bool COUNTS>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi, uint16_t* o_lo,
                     float* oo, float* a_tok, float* c_edge, hipStream_t stream) {
-  const int split = pq_split(tab.total_chunks);
+  long long rows = 0;
+  int longest = 1, longest_chunk = 1;
+  for (int u = 0; u < tab.n_units; ++u) {
+    const Unit& un = tab.unit(u);
+    rows += un.len;
+    longest = std::max(longest, un.len);
+    longest_chunk = std::max(longest_chunk, std::min(un.len, un.chunk_len));
+  }
+  const int split = pq_split(tab.total_chunks, rows, longest_chunk, sh.R, D);
   const dim3 grid(tab.total_chunks << split), block(kThreads);
   float* p_part = o_part + (size_t)grid.x * sh.R * D;       // the weights' sums lie behind the launch's partials
   launch_with_table(tab, [&](const auto& t) {
@@ -823,8 +830,6 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
                        (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
   });
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  int longest = 1;
-  for (int u = 0; u < tab.n_units; ++u) longest = longest > tab.unit(u).len ? longest : tab.unit(u).len;
   const dim3 spans(tab.n_units, (longest + kRedoSpan - 1) / kRedoSpan);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((pq_redo_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), spans, block, 0, stream, t, sh, (const uint16_t*)Q,

@@ -65,6 +65,7 @@ SENS_CASES = [
     ("stress128k", 128, 8, 40, [1200]),              # 320 rows: three passes
     ("ragged16", 128, 4, 32, [300, 5000, 9000]),     # chunks of different units in one launch
     ("llama8b_8k", 128, 1, 1, [257]),                # a single query row
+    ("ragged16", 128, 3, 22, [34001, 17003, 16999]), # 168 chunks of two lengths, cut in four: the last pieces are empty
 ]
 
 
