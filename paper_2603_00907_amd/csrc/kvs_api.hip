@@ -154,7 +154,8 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
   if (const int forced = debug_switch(KVS_DEBUG_GROUP_UNITS)) plan->group_cap = std::min(forced, kMaxGroupUnits);
   {
     long long total = 0;
-    for (int u = 0; u < group_end(*plan, 0, plan->group_cap); ++u) total += p->len[u];
+    const int first_group = group_end(*plan, 0, plan->group_cap);
+    for (int u = 0; u < first_group; ++u) total += p->len[u];
     // (a launch of up to a million tokens gets half as many workgroups, one round of two per CU: the streaming
     // workload's 256 caches of 2560 rows take 0.265 ms per step that way against 0.273)
     long long want = total / (total <= (1ll << 20) ? kScoreWorkgroups / 2 : kScoreWorkgroups);

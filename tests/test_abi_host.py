@@ -266,6 +266,24 @@ def test_causal_flag_is_validated_on_the_host():
     assert status_of(kvs.kvs_workspace_size, problem(lens=[1024, 3], budgets=[512, 3])) == kvs.KVS_OK
 
 
+def test_a_calls_plan_takes_time_linear_in_its_units():
+    """The work before a call's first launch: eight times the units take about eight times as long (64 if every unit
+    looked at all units of its launch), the shortest of thirty calls each."""
+    import time
+    took = {}
+    for n in (128, 1024):
+        p = problem(lens=[600] * n, budgets=[512] * n)
+        kvs.kvs_workspace_size(p)
+        took[n] = min(_timed(lambda: kvs.kvs_workspace_size(p), time.perf_counter) for _ in range(30))
+    assert took[1024] < 24 * took[128], took
+
+
+def _timed(call, clock):
+    start = clock()
+    call()
+    return clock() - start
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU; any other --gpus value ends with a message and a non-zero status before
     anything touches a device."""
