@@ -55,6 +55,17 @@ __host__ __device__ inline int dec_chunks(int len, int min_chunk) {
   return (len + cl - 1) / cl;
 }
 
+// Chunks of the unit that has most of them.
+int most_chunks(const UnitTable& tab, int min_chunk) {
+  int most = 1;
+  for (int i = 0, before = 0; i < tab.n_units; ++i) {
+    const int len = tab.unit(i).len;
+    if (len != before) most = std::max(most, dec_chunks(len, min_chunk));
+    before = len;
+  }
+  return most;
+}
+
 // partial result of one (unit, chunk, query row): numerator[D], running maximum, denominator
 __device__ __forceinline__ size_t part_index(int unit_index, int chunk, int R, int row, int D) {
   return (((size_t)unit_index * kMaxChunks + chunk) * R + row) * (size_t)(D + 2);
@@ -625,8 +636,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
 template <int D>
 hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                            const int32_t* counts, float* part, float* out, hipStream_t stream) {
-  int widest = 1;
-  for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
+  const int widest = most_chunks(tab, sh.dec_chunk);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((decode_mfma_f32_kernel<D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, t, sh,
                        (const float*)Q, (const float*)K, (const float*)V, counts, part);
@@ -642,8 +652,7 @@ hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q,
 template <int D>
 hipError_t launch_mfma(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                        const int32_t* counts, float* part, float* out, hipStream_t stream) {
-  int widest = 1;
-  for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
+  const int widest = most_chunks(tab, sh.dec_chunk);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((decode_mfma_kernel<D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kMfmaThreads), 0, stream, t, sh,
                        (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, counts, part);
@@ -659,8 +668,7 @@ hipError_t launch_mfma(const UnitTable& tab, const Shape& sh, const void* Q, con
 template <typename T, int D>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts, float* part, float* out, hipStream_t stream) {
-  int widest = 1;
-  for (int i = 0; i < tab.n_units; ++i) widest = std::max(widest, dec_chunks(tab.unit(i).len, sh.dec_chunk));
+  const int widest = most_chunks(tab, sh.dec_chunk);
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((decode_partial_kernel<T, D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kThreads), 0, stream, t, sh,
                        (const T*)Q, (const T*)K, (const T*)V, counts, part);
@@ -671,6 +679,45 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
     hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
   });
   return hipGetLastError();
+}
+
+// Rows per workgroup of a launch (n_units units, `rows` rows, `first` of them in the first unit), from the lengths alone:
+// a call's results don't depend on its budgets.  Every workgroup has a fixed cost (the query block, the wavefronts'
+// results combined, a partial result written), and the launch takes as long as its rounds of resident workgroups do, two
+// per CU for the MFMA kernels and four for the vector-ALU ones.
+// Equal lengths: the fewest rounds whose workgroups take up to 2048 rows (MFMA, up to 32 query rows) or 1024, at least 256,
+// and for them the shortest pieces that fit.  32 caches of 22047 rows, 16 query rows: 78.2 us in one round, with twice to
+// four times the workgroups 85 and 97; 64 of 4096, 32 query rows: 37.7 against 48.1; 64 of 17187, where one round would
+// take more rows than that: 64 query rows 222 us with two rounds of 1088, 272 with 1024 rows, which don't fit two; 4 query
+// rows (vector ALU) 115 with two rounds, 137 with 1024 rows.
+// Different lengths leave the last workgroups of the long caches alone on the chip, and smaller pieces even that out:
+// about 2048 workgroups on the vector ALU (100 caches of 2.7 K to 21 K rows, 4 query rows: 148 us against 164 at 1024),
+// 768 for the MFMA kernels (64 caches, 500000 rows, 8 query rows: 56.4 us, 65.2 at 512), and from 786432 rows on, where
+// 768 would be cut off at 1024 rows each, rounds of up to 1024 rows, two at least (256 caches, 1100000 rows, 64 query
+// rows: 275 us, 320 with 1024 rows).
+// The vector-ALU kernels go down to 64 rows in a launch that would leave compute units without a workgroup (8 caches
+// of 4096 rows: 16.9 us with 128 against 20.9; 64 caches stay: 30.7 with 256 against 37.0); the MFMA kernels'
+// wavefronts take 32 rows each (8 caches of 4096 rows, 32 query rows: 20.3 us with 256, 20.6 with 128, 26.7 with 64).
+int rows_per_workgroup(int n_units, int first, bool even, long long rows, bool mfma, int R) {
+  auto round_up = [](long long x) { return (x + kWave - 1) / kWave * kWave; };
+  if (!mfma && rows < 256 * kDecMinChunk) return (int)std::max<long long>(kWave, round_up(rows / 256));
+  const long long slots = mfma ? 512 : 1024;
+  if (even) {
+    const long long most = mfma && R <= kTile ? 2048 : 1024;
+    for (long long rounds = std::max<long long>(1, rows / (slots * most));; ++rounds) {
+      long long chunk = std::max<long long>(kDecMinChunk, round_up(rows / (slots * rounds)));
+      while (chunk <= most && (long long)n_units * dec_chunks(first, (int)chunk) > slots * rounds) chunk += kWave;
+      if (chunk <= most) return (int)chunk;
+    }
+  }
+  if (!mfma || rows < 3 * 256 * 1024) {
+    const long long chunk = round_up(rows / (mfma ? 768 : 2048));
+    return (int)std::min<long long>(std::max<long long>(kDecMinChunk, chunk), 1024);
+  }
+  for (long long rounds = 2;; ++rounds) {
+    const long long chunk = round_up(rows / (slots * rounds));
+    if (chunk <= 1024) return (int)chunk;
+  }
 }
 
 }  // namespace
@@ -687,25 +734,18 @@ hipError_t launch_decode(const UnitTable& tab, const Shape& sh_in, kvs_dtype dt,
   bool mfma = sh.R > kQB;
   if (force == 1) mfma = false;
   if (force == 2) mfma = true;
-  for (int i = 0; i < tab.n_units; ++i) mfma = mfma && tab.unit(i).len >= kTile;   // its tiles hold 32 whole rows
-  // Rows per workgroup.  Where all caches have the same length, as many as make the launch one round of resident
-  // workgroups (two per CU for the MFMA kernels, four for the vector-ALU ones), at least 256 and at most 2048 (MFMA) or
-  // 1024 rows: every workgroup has a fixed cost (the query block, the wavefronts' results combined, a partial result
-  // written).  32 caches of 22047 rows, 16 query rows: 78.2 us, with twice to four times the workgroups 85 and 97; 64
-  // of 4096, 32 query rows: 37.7 against 48.1; 256 of 4096, 4 query rows (vector ALU): 113 against 120.  Caches of
-  // different lengths leave the last workgroups of the long ones alone on the chip, and smaller pieces even that out
-  // (100 caches of 2.7 K to 21 K rows: 135 us at up to 1024 rows and 8 query rows against 153 at 2048; 148 at 2048
-  // workgroups and 4 query rows against 164 at 1024).
-  // The vector-ALU kernels go down to 64 rows in a launch that would leave compute units without a workgroup (8 caches
-  // of 4096 rows: 16.9 us with 128 against 20.9; 64 caches stay: 30.7 with 256 against 37.0); the MFMA kernels'
-  // wavefronts take 32 rows each (8 caches of 4096 rows, 32 query rows: 20.3 us with 256, 20.6 with 128, 26.7 with 64).
+  const int first = tab.unit(0).len;
+  int shortest = first;
   long long rows = 0;
-  for (int i = 0; i < tab.n_units; ++i) rows += tab.unit(i).len;
-  const int most = mfma && tab.even ? 2048 : 1024;
-  long long chunk = rows / (mfma ? 512 : tab.even ? 1024 : 2048);
-  if (chunk < kDecMinChunk) chunk = mfma ? kDecMinChunk : std::min<long long>(rows / 256, kDecMinChunk);
-  chunk = (chunk + kWave - 1) / kWave * kWave;
-  sh.dec_chunk = (int)(chunk < kWave ? kWave : chunk > most ? most : chunk);
+  bool even = true;                                        // (the budgets don't matter here: tab.even is not it)
+  for (int i = 0; i < tab.n_units; ++i) {
+    const int len = tab.unit(i).len;
+    rows += len;
+    shortest = std::min(shortest, len);
+    even = even && len == first;
+  }
+  if (shortest < kTile) mfma = false;                      // its tiles hold 32 whole rows
+  sh.dec_chunk = rows_per_workgroup(tab.n_units, first, even, rows, mfma, sh.R);
   if (dt == KVS_F32) {
     if (mfma) {
       return sh.D == 64 ? launch_mfma_f32<64>(tab, sh, Q, K, V, counts, part, out, stream)

@@ -1261,6 +1261,27 @@ def check_decode(units, dtype, D, G, W, path):
         assert (np.abs(got[i] - want) <= bound).all(), (i, np.max(np.abs(got[i] - want) / bound))
 
 
+@pytest.mark.parametrize("dtype,D,G,path", [("bf16", 64, 1, "valu"), ("bf16", 128, 8, "mfma"), ("f32", 64, 8, "mfma")])
+def test_decode_attention_does_not_depend_on_budgets(dtype, D, G, path):
+    """40 caches of 8192 rows, one of them with a smaller budget: the same bits (the rows per workgroup, and with them the
+    order of the sums, follow from the lengths)."""
+    import torch
+    import paper_2603_00907_amd as kvs
+    g = torch.Generator(device="cuda").manual_seed(3)
+    lens = [8192] * 40
+    draw = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    Q, K, V = draw(40, G, D), draw(sum(lens), D), draw(sum(lens), D)
+    out = []
+    for budgets in (lens, lens[:7] + [500] + lens[8:]):
+        p = kvs.Problem(lens=lens, budgets=budgets, group=G, window=1, head_dim=D, dtype=dtype, n_sink=0)
+        out.append(torch.empty((40, G, D), dtype=torch.float32, device="cuda"))
+        ws = torch.full((kvs.kvs_decode_workspace_size(p),), 0xFF, dtype=torch.uint8, device="cuda")
+        with switch_override("decode_path", {"valu": 1, "mfma": 2}[path]):
+            kvs.kvs_decode_attention(p, Q, K, V, None, out[-1], ws, stream=torch.cuda.current_stream().cuda_stream)
+            torch_sync()
+    assert torch.equal(out[0], out[1])
+
+
 def test_decode_attention_over_the_output_of_a_step():
     """End to end: merge a cache, then attend over (K', V', counts) with fresh queries; the GPU result equals
     the oracle's attention over the oracle's merged cache (both within their tolerances)."""
