@@ -222,14 +222,17 @@ __global__ __launch_bounds__(D) void decode_reduce_kernel(const Tab tab, const S
       m[i] = src[D];
       l[i] = src[D + 1];
     }
+    float n8 = 0.f, d8 = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (c0 + i < nc && l[i] > 0.f) {
         const float w = __builtin_amdgcn_exp2f(m[i] - M);
-        num = fmaf(x[i], w, num);
-        den = fmaf(l[i], w, den);
+        n8 = fmaf(x[i], w, n8);
+        d8 = fmaf(l[i], w, d8);
       }
     }
+    num += n8;                              // (eight chunks' sum first: 64 chunks round eight times at the whole's size)
+    den += d8;
   }
   out[((size_t)un.index * R + row) * D + d] = num / den;
 }
@@ -392,20 +395,23 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_kernel(
       float p[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) p[v] = __builtin_amdgcn_exp2f(sv[v] - m_run);
-      // denominator: c copies of every slot
+      // denominator: c copies of every slot (the tile's sum first: a chain over all tiles rounds sixteen times as often
+      // at the size of the whole)
+      float sum = 0.f;
       if (cnt != nullptr) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 c4 = *reinterpret_cast<const float4*>(&sm_cnt[wave][8 * g + 4 * half]);
-          l_run = fmaf(c4.x, p[4 * g], l_run);
-          l_run = fmaf(c4.y, p[4 * g + 1], l_run);
-          l_run = fmaf(c4.z, p[4 * g + 2], l_run);
-          l_run = fmaf(c4.w, p[4 * g + 3], l_run);
+          sum = fmaf(c4.x, p[4 * g], sum);
+          sum = fmaf(c4.y, p[4 * g + 1], sum);
+          sum = fmaf(c4.z, p[4 * g + 2], sum);
+          sum = fmaf(c4.w, p[4 * g + 3], sum);
         }
       } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) l_run += p[v];
+        for (int v = 0; v < 16; ++v) sum += p[v];
       }
+      l_run += sum;
       // as the operand of the next product, element i of k-step s is accumulator element 8 s + i
       bf16x8 ph[2], pl[2];
       split8(p, ph[0], pl[0]);
@@ -582,19 +588,21 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
         }
       }
       // denominator: c copies of every slot
+      float sum = 0.f;                        // (the tile's first, as above)
       if (cnt != nullptr) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 c4 = *reinterpret_cast<const float4*>(&sm_cnt[wave][8 * g + 4 * half]);
-          l_run = fmaf(c4.x, p[4 * g], l_run);
-          l_run = fmaf(c4.y, p[4 * g + 1], l_run);
-          l_run = fmaf(c4.z, p[4 * g + 2], l_run);
-          l_run = fmaf(c4.w, p[4 * g + 3], l_run);
+          sum = fmaf(c4.x, p[4 * g], sum);
+          sum = fmaf(c4.y, p[4 * g + 1], sum);
+          sum = fmaf(c4.z, p[4 * g + 2], sum);
+          sum = fmaf(c4.w, p[4 * g + 3], sum);
         }
       } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) l_run += p[v];
+        for (int v = 0; v < 16; ++v) sum += p[v];
       }
+      l_run += sum;
       // (eight rows from zero, like the logits' four products)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
