@@ -2,7 +2,8 @@
 // taken as the sum of three bf16 numbers, so that the products run at the bf16 matrix rate (16 times the fp32 one).
 //
 // x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid), each rounded to nearest: 24 bits and
-// signs, so nothing is lost but what lies below 2^-27 of x.  Of the nine products six are formed (hi hi, hi mid, mid hi,
+// signs, so nothing is lost but what lies below 2^-27 of x, or below 2^-126, where bf16 has no normal numbers (see
+// products_f32 for the rows where that counts).  Of the nine products six are formed (hi hi, hi mid, mid hi,
 // mid mid, hi lo, lo hi; the others are below 2^-26 of the largest), each exact in the fp32 accumulator, in two chains
 // from small to large.  48 MFMAs of 32 cycles per 32 x 32 logits (D = 128) against 64 of 64 cycles: the step over 8
 // units of 32768 tokens with 128 rows takes 190 us against 241 with fp32 products, 64 units of 16384 683 against 875.
@@ -18,13 +19,17 @@
 // the wavefronts in sweep 1 are those of kvs_score_shared.hip.
 //
 // Infinities and NaN (and numbers that round to infinity as bf16) have no such split: a tile whose sums come out not
-// finite is done again with fp32 MFMAs, straight from memory, so that what it contributes is what it always did.
+// finite is done again with fp32 MFMAs, straight from memory, so that what it contributes is what it always did.  Nor have
+// numbers below 2^-100, whose parts fall below 2^-126: a wavefront with such a query element, or with one so large that
+// what a Key of that kind loses could count, takes fp32 MFMAs for all its tiles.
 #include "kvs_mfma_tile.h"
 
 namespace kvs {
 namespace {
 
 using namespace mfma;
+
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 // eight floats -> three bf16 operands whose sum they are
 __device__ __forceinline__ void split3(const float4& x, const float4& y, uint4& hi, uint4& mid, uint4& lo) {
@@ -113,8 +118,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
   };
   fetch(0);
 
-  // this wavefront's query rows, split (rows past R repeat the last one)
+  // this wavefront's query rows, split (rows past R repeat the last one).  plain: the split would lose what counts.  Below
+  // 2^-100 an element's third part is no normal number, and a Key of up to 2^127 may meet what is lost (2^-127 or less of
+  // the element); a Key's own loss, and a product of parts that is no normal number, count where they meet 2^90 or a scale
+  // of 2^60.  Elsewhere either is below 2^-36 of the base-2 logit.
   bf16x8 bq[3][KS];
+  u16x2 most = {0, 0}, least = {0xFFFF, 0xFFFF};             // of the elements' magnitudes, as bits of bf16 numbers
   {
     const float* qr = Qu + (size_t)min(qp + q_first + col, R - 1) * D + 8 * half;
 #pragma unroll
@@ -122,10 +131,23 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
       const float4* src = reinterpret_cast<const float4*>(qr + 16 * kk);
       uint4 hi, mid, lo;
       split3(src[0], src[1], hi, mid, lo);
+      for (const uint32_t w : {hi.x, hi.y, hi.z, hi.w}) {
+        const u16x2 a = __builtin_bit_cast(u16x2, w & 0x7FFF7FFFu);
+        most = __builtin_elementwise_max(most, a);
+        least = __builtin_elementwise_min(least, a);
+      }
       bq[0][kk] = __builtin_bit_cast(bf16x8, hi);
       bq[1][kk] = __builtin_bit_cast(bf16x8, mid);
       bq[2][kk] = __builtin_bit_cast(bf16x8, lo);
     }
+  }
+  bool plain = __any(sl2 >= 0x1p60f || __uint_as_float((uint32_t)max(most.x, most.y) << 16) * sl2 >= 0x1p90f);
+  if (__any(min(least.x, least.y) < (__float_as_uint(0x1p-100f) >> 16))) {    // such an element, or a zero
+    const float* qr = Qu + (size_t)min(qp + q_first + col, R - 1) * D + half * (D / 2);
+    bool small = false;
+#pragma unroll 1
+    for (int i = 0; i < D / 2; ++i) small |= (qr[i] != 0.f) & (fabsf(qr[i]) < 0x1p-100f);
+    plain |= __any(small);
   }
   // sweep 1: the normalisers of the lane's 16 accumulator rows (exp2(-inf) = 0: no such row)
   float cq[16];
@@ -176,7 +198,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
     for (int v = 0; v < 16; ++v) a[v] += b[v];
     return a;
   };
-  // the same with fp32 products, from memory (tiles with numbers that have no split)
+  // the same with fp32 products, from memory (numbers that have no split)
   auto products_f32 = [&](int j) {
     f32x16 a = zero;
     const float4* kr = reinterpret_cast<const float4*>(Kg + (size_t)min(t0 + j * kTile + col, t1 - 1) * D) + half * (D / 8);
@@ -285,7 +307,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
       } else {
         add_terms_any(acc, j);
       }
-      if (__any(!(l_run < INFINITY))) {
+      if (plain || __any(!(l_run < INFINITY))) {
         l_run = l_old;
         l_lost = lost_old;
         m_run = m_old;
@@ -293,7 +315,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
       }
     } else {
       float p = share(acc, j);
-      if (__any(!(p < INFINITY))) p = share(products_f32(j), j);
+      if (plain || __any(!(p < INFINITY))) p = share(products_f32(j), j);
       if (half == 0) sm_p[j & 1][wave][col] = p;
     }
   }

@@ -119,6 +119,25 @@ def test_score_normaliser_of_rows_that_rise_far_above_their_first_tokens(dtype, 
     assert np.sqrt(np.mean(err ** 2)) < 6e-7
 
 
+@pytest.mark.parametrize("exponent", [-122, 100])
+@pytest.mark.parametrize("D,G,W", [(128, 4, 32), (64, 8, 32)])
+def test_score_f32_numbers_whose_parts_are_too_small(D, G, W, exponent):
+    """One channel of the queries of about 2^exponent in a third of the rows, and of the keys of about 2^-exponent: the
+    products are ordinary numbers, but the second and third bf16 parts of the small factors are not normal numbers."""
+    w = variant("tiny", dtype="f32", head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1)
+    u = generate_unit(w, 0, 0, 0, n=700)
+    rng = np.random.default_rng(exponent + 200)
+    Q = u.Q.reshape(G * W, D).copy()
+    Q[:, 5] = 0.0
+    Q[::3, 5] = np.float32(2.0 ** exponent) * (1 + rng.random(len(Q[::3]), dtype=np.float32))
+    u.Q = Q.reshape(u.Q.shape)
+    u.K = u.K.copy()
+    u.K[:, 5] = np.float32(2.0 ** -exponent) * (1 + rng.random(u.n, dtype=np.float32)) * np.sqrt(D)
+    got = score([u], "f32", D, G, W)[0][0]
+    ref, _ = O.score(u.Q, u.K, u.V)
+    assert np.max(np.abs(got - ref) / ref) < TOL_ALPHA
+
+
 @pytest.mark.parametrize("D,G,W", [(128, 4, 32), (64, 8, 32)])
 def test_score_f32_numbers_without_a_split(D, G, W):
     """fp32 Keys that are minus infinity, or that round to infinity as bf16, in rows of a tile's beginning, middle and end:
