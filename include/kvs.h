@@ -217,14 +217,16 @@ kvs_status kvs_decode_attention(const kvs_problem* p, const void* Q, const void*
  *   C_t = mean_q alpha^{(q)}_t alpha^{(q)}_{t+1} ||v_t + v_{t+1} - 2 o^{(q)}||      (edge t, t+1)
  * kvs_merge_compact_norms is kvs_merge_compact with these A and C in u_t = A_t - C_{t-1} - C_t (Eq.
  * kstar_final); Values, cardinalities, key_rule and the fallback are as there.  The partition still comes from
- * kvs_select on alpha_bar.  With one query row the results are those of the calls above.
+ * kvs_select on alpha_bar.  With one query row the results are those of the calls above, to rounding.
  * Restrictions: with io_dtype KVS_BF16 every unit has at least 32 rows (KVS_ERR_INVALID_ARG; the matrix-core
  * kernels work on whole tiles), with KVS_F32 any length is taken (vector-ALU kernels, written for the small
  * configurations, not for speed).  kvs_merge_compact_norms takes both dtypes and any length.
  * The *_counts forms take the input rows' cardinalities (streaming regime, as kvs_step_counts; NULL = the plain
  * call): every query row then sees row t as one token with logit e + ln counts_in[t] and value
  * V[t] / counts_in[t], and the merge adds the cardinalities up.
- *   alpha_bar DEVICE out [rows] fp32, as from kvs_score
+ *   alpha_bar DEVICE out [rows] fp32: kvs_score's, bit for bit for windows of one to three rows; else (bf16) from other
+ *             products and another order of their sums, so that edges whose scores are as close as fp32 rounding may be
+ *             chosen differently than by kvs_step
  *   a_tok     DEVICE out / in [rows] fp32: A_t
  *   c_edge    DEVICE out / in [rows] fp32: C_t; the entry of a unit's last row is 0 and never read
  *   ws        DEVICE workspace of kvs_per_query_workspace_size(p) bytes, 256-byte aligned (kvs_sensitivity,

@@ -472,8 +472,8 @@ inline int pq_split(long long chunks, long long rows, long long longest, int R, 
   return split;
 }
 // Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out, if set) from Q, K, V
-// and the rows' normalisers c_row that the first score sweep leaves.  o_part: [chunks of the launch][R][D] fp32; o_hi, o_lo: [n_units][R][D] bf16;
-// oo: [n_units][R].
+// and the rows' normalisers c_row that the first score sweep leaves.  o_part: [pieces of the launch's chunks][R][D] fp32,
+// then their weights' sums [pieces][R]; o_hi, o_lo: [n_units][R][D] bf16; oo: [n_units][R].
 hipError_t launch_per_query_norms(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                                   const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi,
                                   uint16_t* o_lo, float* oo, float* a_tok, float* c_edge, hipStream_t stream);

@@ -7,9 +7,10 @@
 // mid mid, hi lo, lo hi; the others are below 2^-26 of the largest), each exact in the fp32 accumulator, in two chains
 // from small to large.  48 MFMAs of 32 cycles per 32 x 32 logits (D = 128) against 64 of 64 cycles: the step over 8
 // units of 32768 tokens with 128 rows takes 190 us against 241 with fp32 products, 64 units of 16384 683 against 875.
-// The error of alpha_bar against 64 bits is smaller than with fp32 products, whose sums take eight times as many rounding
-// steps: over the shapes from 1024 to 100000 tokens, 112 to 512 rows, largest relative error 0.9e-6 to 2.4e-5 against
-// 1.8e-6 to 4.2e-5, 2-norm of the error 0.6 to 0.95 times.
+// The error of alpha_bar against 64 bits is smaller than with fp32 products and a running maximum (the products' sums take
+// eight times as many rounding steps there): 23000 tokens, 96 to 320 rows, Queries of half, once and twice the usual size,
+// 2-norm of the error 0.9e-7 to 1.2e-6 against 3.7e-7 to 2.0e-6, largest relative error 0.5e-6 to 0.7e-5 against 1.3e-6 to
+// 1.5e-5.
 //
 // A workgroup's wavefronts own 32 query rows each (operands of all three parts in registers: 96 for D = 128) and walk
 // the same tiles of 32 tokens: a tile is fetched, split once and left in LDS as three bf16 tiles (XOR-swizzled 16-byte
