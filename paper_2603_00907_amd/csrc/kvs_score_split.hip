@@ -295,19 +295,20 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_split_kernel(
       continue;
     }
     if (PHASE == 0) {
-      const float l_old = l_run, m_old = m_run, lost_old = l_lost;
       const int tile_t0 = t0 + j * kTile;
-      if (j > 0 && cnt == nullptr && tile_t0 + kTile <= t1 &&
+      if (!plain && j > 0 && cnt == nullptr && tile_t0 + kTile <= t1 &&
           !(sh.causal > 0 && tile_t0 + kTile > un.len - sh.causal + 1)) {
         float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v % 4] += ex2(fmaf(acc[v], sl2, -m_run));
         const float sum = (s[0] + s[1]) + (s[2] + s[3]);
-        if (__any(!(sum < kSumLimit))) add_terms_any(acc, j);   // the reference is too low, or the sum is not a number
-        else add_compensated(l_run, l_lost, sum);
-      } else {
-        add_terms_any(acc, j);
+        if (!__any(!(sum < kSumLimit))) {      // (else the reference is too low, or the sum is not a number)
+          add_compensated(l_run, l_lost, sum);
+          continue;
+        }
       }
+      const float l_old = l_run, m_old = m_run, lost_old = l_lost;
+      add_terms_any(acc, j);
       if (plain || __any(!(l_run < INFINITY))) {
         l_run = l_old;
         l_lost = lost_old;
