@@ -9,7 +9,7 @@
 // The merge kernel then uses A and C in the weight form of Eq. kstar_final.
 //
 // Four kernels after the first score sweep (which leaves the normaliser c[q] of every row; alpha_bar comes from the
-// third of them, so the second sweep is not run):
+// third of them, so the second sweep is not run, except for windows of one to three rows):
 //   pq_out_kernel         O^T[d, q] = sum_t V[t, d] P[t, q], P = alpha / R recomputed from K Q^T tile by tile.
 //                         Both products run on v_mfma_f32_32x32x16_bf16.  The contraction over tokens needs
 //                         V with the token index along the MFMA k dimension; a 32x32 block of the V tile is
@@ -36,8 +36,9 @@
 //   pq_redo_kernel        the marked tokens once more, every squared norm as a sum of squared differences.
 // COUNTS: the rows are slots of an already merged cache (Sec. 3.1, streaming regime), row t standing for c_t tokens
 // whose Values add up to V[t]: every query row sees it as one token with logit e + ln c_t and value V[t] / c_t.  The
-// products still run on the stored rows; log2 c_t joins the logit, and 1 / c_t scales the attention weight of the
-// Value sum (o), the product V_t . o and the squared norms afterwards.
+// products still run on the stored rows; log2 c_t joins the logit (pq_norms_kernel: c_t multiplies the term, so that
+// alpha_bar doesn't carry the rounding of a larger exponent), and 1 / c_t scales the attention weight of the Value sum (o),
+// the product V_t . o and the squared norms afterwards.
 // A workgroup has four wavefronts; wavefront w owns query rows 32w .. 32w+31 of a pass of 128 rows and
 // keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
 // 16-byte pieces, as in the score kernels).  Results do not depend on timing: no atomics, fixed orders.

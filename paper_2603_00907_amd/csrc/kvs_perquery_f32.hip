@@ -55,7 +55,7 @@ __device__ __forceinline__ void load_counts(float* sm_lc, float* sm_ic, const in
                                             int nrows, long long limit, int tid) {
   if (tid < nrows) {
     const float c = (cnt != nullptr && row0 + tid < limit) ? (float)cnt[row0 + tid] : 1.f;
-    sm_lc[tid] = __builtin_amdgcn_logf(c);         // (the hardware's base-2 logarithm)
+    sm_lc[tid] = even_log2(c);                     // (as in the sweep that formed the normalisers)
     sm_ic[tid] = __builtin_amdgcn_rcpf(c);
   }
 }

@@ -30,7 +30,8 @@
 //   score_shared_kernel     (kvs_score_shared.hip) more than 128 rows.
 //   score_mfma_f32_kernel   fp32 inputs, up to 64 rows, v_mfma_f32_32x32x2_f32.
 //   score_split_kernel      (kvs_score_split.hip) fp32 inputs, more than 64 rows.
-// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit.
+// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit; over 64 rows sweep 1
+// multiplies the sum over the rows by c instead.
 #include <cstdlib>
 #include <type_traits>
 
