@@ -27,6 +27,12 @@ static bool score_on_matrix_cores(const UnitTable& tab, const Shape& sh, kvs_dty
   return debug_switch(KVS_DEBUG_SCORE_PATH) != 1 && score_mfma_supported(tab, sh, dt);
 }
 
+// Whether sweep 1 carries the pass over V along (KVS_DEBUG_FUSE_OBAR forces one or the other).
+static bool values_ride(const Shape& sh, kvs_dtype dt) {
+  const int fuse = debug_switch(KVS_DEBUG_FUSE_OBAR);
+  return fuse != 1 && score_mfma_takes_values(sh, dt) && (fuse == 2 || sh.ride != 0);
+}
+
 // ---- testing switches (kvs_debug.h): process-global, initial values read from the environment once, at load
 namespace {
 std::atomic<int> g_switch[KVS_DEBUG_N_SWITCHES];
@@ -368,13 +374,15 @@ int compute_units() {
 }
 
 // Calls f(table, shape) for every launch group (see group_end).
-// split_select: the caller hands the launchers an exchange area, so a unit's selection may take several workgroups.
+// select: whether the call selects edges with an exchange area at hand, so that a unit's selection may take several
+// workgroups, and whether it also needs o_bar.
+enum class Select { kOneWorkgroup, kAlone, kWithValues };
 template <typename F>
-kvs_status for_each_group(const Plan& plan, F&& f, bool split_select = false) {
+kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneWorkgroup) {
   // An error that the calling thread's earlier HIP calls left pending is not this call's: it is dropped here,
   // so that what the launchers read after their launches is theirs.
   (void)hipGetLastError();
-  const int split_mode = split_select ? debug_switch(KVS_DEBUG_SELECT_SPLIT) : 1;
+  const int split_mode = select != Select::kOneWorkgroup ? debug_switch(KVS_DEBUG_SELECT_SPLIT) : 1;
   const int n_cus = split_mode == 1 ? 0 : compute_units();
   // A group of more than kInlineUnits units needs memory for its descriptors.  Where a test asks for every unit's
   // selection to be spread over workgroups, the exchange area's kInlineUnits entries bound the group as well (left
@@ -391,8 +399,7 @@ kvs_status for_each_group(const Plan& plan, F&& f, bool split_select = false) {
     int chunks = 0, mblocks = 0, ochunks = 0, fitems = 0, sparts = 0;
     long long rows = 0;
     for (Unit& un : units) {
-      un.s_base = sparts;
-      sparts += select_parts(un, plan.shape, tab.n_units, n_cus, split_mode);
+      un.s_base = sparts++;
       un.chunk_base = chunks;
       un.m_base = mblocks;
       un.o_base = ochunks;
@@ -415,9 +422,34 @@ kvs_status for_each_group(const Plan& plan, F&& f, bool split_select = false) {
     }
     Shape sh = plan.shape;
     sh.stream = 2 * rows * sh.D * (long long)plan.elt > kStreamBytes;
+    // Parts that go over all keys of their unit by themselves, or parts that meet and go over their share: the meetings
+    // cost about what the keys of 32768 tokens do (steps of 8 bf16 units, 128 query rows: 8192 tokens 37.8 us against 42.3
+    // with parts that meet, 16384 52.2 and 57.3, 24576 68.5 and 71.5, 32768 83.9 and 84.0; one unit of 65000: 68 against
+    // 64).  Launches of many units have no parts that meet (see select_parts).
+    const bool few_units = tab.n_units * 8 <= n_cus;
+    sh.sel_slices = split_mode >= 2 ? 0 : few_units ? kSelRegSlices : kSelMaxSlices;
+    // The pass over V rides along in sweep 1 when the launch is a large one (the streaming policy's threshold):
+    // the edge selection then runs as a short launch of its own, which costs less than the separate pass over V saves
+    // (measured at 64 units of the headline shape: 199 against 226 us for sweep 1, the pass over V and the selection).
+    // A small launch keeps the selection hidden beside the pass over V (8 units of 32768 tokens: 37 against 44 us), and
+    // so does one with a unit of more than 32768 tokens whose selection is not shared out by meeting parts (128 ragged
+    // units of 4 K to 64 K tokens: 1055 against 1076 us per step).
+    sh.ride = sh.stream;
+    for (const Unit& un : units) {
+      if (un.len > kSelRegSlices * 4 * kSelThreads && !(few_units && select_exchanges(un, sh))) sh.ride = 0;
+    }
     hipError_t e = hipSuccess;
     if (tab.n_units <= kInlineUnits) {
       std::copy(units.begin(), units.end(), tab.u);
+      const bool beside = select == Select::kWithValues && !(score_on_matrix_cores(tab, sh, plan.dtype) &&
+                                                             values_ride(sh, plan.dtype));
+      for (int i = sparts = 0; i < tab.n_units; ++i) {
+        const int parts = select_parts(units[i], sh, tab.n_units, n_cus, split_mode, beside);
+        tab.u[i].s_base = sparts;
+        sparts += parts;
+        if (parts > 1 && select_exchanges(units[i], sh)) sh.sel_exchange = 1;
+      }
+      tab.total_sparts = sparts;
     } else {
       tab.host = units.data();
       tab.ext = plan.dev_table;
@@ -437,10 +469,18 @@ kvs_status for_each_group(const Plan& plan, F&& f, bool split_select = false) {
 
 }  // namespace
 
-int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mode) {
+int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mode, bool beside_values) {
   const int r = un.len - un.n_out;
   const int E = (un.len - 2 - sh.n_recent) - sh.n_sink + 1;      // eligible edges
   if (mode == 1 || r <= 0 || E < 64) return 1;
+  // Parts that go over all keys of their unit by themselves: as many as it has slices, or as the chip's compute units give
+  // each unit.  Beside the pass over V in a launch of many units one workgroup per unit is hidden, and what several do
+  // twice is taken from that pass.
+  const int slices = select_slices(E);
+  if (mode == 0 && slices <= sh.sel_slices) {
+    if (beside_values && n_units * 8 > n_cus) return 1;
+    return std::max(1, std::min(slices, n_cus / n_units));
+  }
   const int groups = (E + 6) / 4 + 1;                            // upper bound of the kernel's group count
   const int fit = (groups + kSelPartKeys / 4 - 1) / (kSelPartKeys / 4);   // fewest parts whose keys fit their LDS
   // one select workgroup per CU, so that the parts of a launch run together (a test may ask for more)
@@ -475,25 +515,8 @@ hipError_t launch_score(const UnitTable& tab, const Shape& sh, kvs_dtype dt, con
     *o_layout = 2;
     return launch_score_fused(tab, sh, Q, K, V, counts_in, alpha_bar, ws, stream);
   }
-  // The pass over V rides along in sweep 1 when the launch is a large one (the streaming policy's threshold):
-  // the edge selection then runs as a short launch of its own, one CU per unit, which costs less than the
-  // separate pass over V saves (measured at 64 units of the headline shape: 199 against 226 us for sweep 1,
-  // the pass over V and the selection).  A small launch keeps the selection hidden beside the pass over V
-  // (8 units: 38 against 45 us).  KVS_DEBUG_FUSE_OBAR forces one or the other.
   if (matrix_cores) {
-    const int fuse = debug_switch(KVS_DEBUG_FUSE_OBAR);
-    // (The selection of a unit too long for the select kernel's LDS cache of keys takes several times longer when one
-    // workgroup does it, 51 us at 65536 tokens: such launches keep it hidden beside the pass over V, unless the
-    // unit's selection is spread over several workgroups.)
-    int longest = 0;
-    for (int i = 0; i < tab.n_units; ++i) {
-      const int parts = (i + 1 < tab.n_units ? tab.unit(i + 1).s_base : tab.total_sparts) - tab.unit(i).s_base;
-      if (parts <= 1) longest = std::max(longest, tab.unit(i).len);
-    }
-    bool want = sh.stream != 0 && longest <= kSelUnitKeys;
-    if (fuse == 1) want = false;
-    if (fuse == 2) want = true;
-    const bool with_v = wants_o && score_mfma_takes_values(sh, dt) && want;
+    const bool with_v = wants_o && values_ride(sh, dt);
     if (with_v) *o_layout = 1;
     return launch_score_mfma(tab, sh, dt, Q, K, counts_in, alpha_bar, ws, with_v ? V : nullptr, stream);
   }
@@ -576,13 +599,13 @@ kvs_status kvs_select(const kvs_problem* p, const float* alpha_bar, uint8_t* edg
   if (with_ws) plan.dev_table = w.unit_tab;
   plan.stream = s;
   return for_each_group(plan, [&](const UnitTable& tab, const Shape& sh) {
-    if (tab.total_sparts != tab.n_units) {      // (the score kernels clear the area when they run before the selection)
+    if (sh.sel_exchange) {      // (the score kernels clear the area when they run before the selection)
       const hipError_t e = launch_select_clear(tab, w.sel_shared, s);
       if (e != hipSuccess) return e;
     }
     return launch_select_obar(tab, sh, plan.dtype, true, alpha_bar, edge_mask, slot_of_token, nullptr,
                               nullptr, nullptr, s, nullptr, nullptr, w.sel_shared);
-  }, /*split_select=*/with_ws);
+  }, with_ws ? Select::kAlone : Select::kOneWorkgroup);
 }
 
 kvs_status kvs_merge_compact(const kvs_problem* p, const void* K, const void* V, const float* alpha_bar,
@@ -688,7 +711,7 @@ static kvs_status step_with_workspace(Plan& plan, const void* Q, const void* K, 
     if (e != hipSuccess) return e;
     return launch_merge(tab, sh2, plan.dtype, K, V, counts_in, w.alpha_bar, nullptr, w.o_part, mask, slot, K_out,
                         V_out, counts_out, s);
-  }, /*split_select=*/true);
+  }, Select::kWithValues);
 }
 
 kvs_status kvs_step_counts(const kvs_problem* p, const void* Q, const void* K, const void* V, const int32_t* counts_in,
@@ -879,7 +902,7 @@ kvs_status kvs_step_per_query_counts(const kvs_problem* p, const void* Q, const 
     if (e != hipSuccess) return e;
     return launch_merge_norms(tab, sh, plan.dtype, K, V, counts_in, q.a_tok, q.c_edge, mask, slot, K_out, V_out,
                               counts_out, s);
-  }, /*split_select=*/true);
+  }, Select::kAlone);
 }
 
 kvs_status kvs_decode_workspace_size(const kvs_problem* p, size_t* bytes) {

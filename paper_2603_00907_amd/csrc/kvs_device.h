@@ -76,13 +76,15 @@ __host__ __device__ inline int obar_chunks(int len) {
 
 // Selection over several workgroups ("parts") per unit.  A part keeps at most kSelPartKeys edge scores in LDS; what
 // the parts of a unit exchange goes through kSelSharedInts unsigned ints of device memory per unit of the launch,
-// which must be zero when the select kernel starts (the score finalize kernel of the same call clears them):
+// which must be zero when the select kernel starts (the score kernels of the same call clear them, sh.sel_exchange):
 //   [kSelNotMin] ~(smallest key), [kSelMax] largest key, [kSelNCand] candidates listed so far,
 //   [kSelArrive + phase] parts that finished a phase (bit kSelGaveUp: a part ran out of time there),
 //   [kSelPartLow + part] keys of a part in the bins below the threshold's,
 //   [kSelHist + bin] histogram of the first digit, [kSelCand + i] keys of the threshold's bin and
 //   [kSelCandPart + i] the parts they came from.
-constexpr int kSelUnitKeys = 32768;       // keys that ONE workgroup can keep in LDS (the full-size select kernel)
+constexpr int kSelThreads = 1024;         // threads of a select workgroup
+constexpr int kSelRegSlices = 8;          // slices of 4096 keys that a select workgroup keeps in registers when two of them
+constexpr int kSelMaxSlices = 16;         // share a CU, and at most
 constexpr int kSelMaxParts = 32;
 constexpr int kSelPartKeys = 8192;
 constexpr int kSelMinPartKeys = 2048;     // parts are not made smaller than this unless a test asks for it
@@ -158,7 +160,10 @@ struct Shape {
   int n_recent;
   float scale_log2; // logit scale * log2(e): logits are kept in the base-2 domain
   int stream;       // 1: the launch's K and V exceed the last-level cache, rows are read non-temporally
+  int ride;         // 1: the pass over V rides along in score sweep 1 where the kernel can carry it
   int rule;         // kvs_key_rule of the merged Key
+  int sel_slices;   // the parts of units of more slices than this meet through the exchange area, see select_parts
+  int sel_exchange; // 1: the launch has such a unit: the area must be zero when the select kernel starts
   int causal;       // 0, or the window W when query row q only sees the rows up to its own position n - W + q % W
   int keep_rows;    // 1: the caller reads the rows' normalisers (c_row) after the score phase
   int fold;         // 1: sweep 1 reduces the chunks' statistics itself (load_row_consts), no finalize kernel has run
@@ -169,6 +174,13 @@ struct Shape {
   int o_from_score; // where the partial sums of o_bar are: 0: o_part, one per chunk of the o_bar pass; 1: o_part, one
                     // per SCORE chunk (written by sweep 1); 2: fo_part, one per work item of the one-pass score kernel
 };
+
+// Slices of 4 * kSelThreads keys of a unit with E eligible edges (with the padding to aligned groups of four).
+__host__ __device__ inline int select_slices(int E) { return ((E + 6) / 4 + kSelThreads - 1) / kSelThreads; }
+// Whether the parts of a unit's selection meet through the exchange area (or each goes over all its keys by itself).
+__host__ __device__ inline bool select_exchanges(const Unit& un, const Shape& sh) {
+  return select_slices((un.len - 2 - sh.n_recent) - sh.n_sink + 1) > sh.sel_slices;
+}
 
 // How many partials of o_bar a unit has, and where its partial c starts (index of its first float).
 __host__ __device__ inline int obar_partials(const Shape& sh, const Unit& un) {
@@ -394,7 +406,7 @@ inline hipError_t between_sweeps(const UnitTable& tab, Shape& sh, const Workspac
                                  hipStream_t stream) {
   if (alpha_bar == nullptr || sh.keep_rows) return launch_score_finalize(tab, sh, ws, stream);
   sh.fold = 1;
-  sh.sel_clear = tab.total_sparts != tab.n_units ? ws.sel_shared : nullptr;
+  sh.sel_clear = sh.sel_exchange ? ws.sel_shared : nullptr;
   return hipSuccess;
 }
 // Both score sweeps: chunk statistics, the finalize kernel where sweep 1 does not do its work, then alpha_bar (null: the
@@ -420,8 +432,8 @@ hipError_t launch_select_obar(const UnitTable& tab, const Shape& sh, kvs_dtype d
 // Zeroes the exchange area of the launch's units (callers that did not run the score kernels before the selection).
 hipError_t launch_select_clear(const UnitTable& tab, unsigned int* sel_shared, hipStream_t stream);
 // How many select workgroups a unit gets in a launch of n_units units on a chip of n_cus compute units
-// (mode: the KVS_DEBUG_SELECT_SPLIT switch).  1: the single-workgroup selection.
-int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mode);
+// (mode: the KVS_DEBUG_SELECT_SPLIT switch; sh.sel_slices is set; beside_values: beside a pass over V).
+int select_parts(const Unit& un, const Shape& sh, int n_units, int n_cus, int mode, bool beside_values);
 // o_bar[u] = sum of the unit's partial sums, in chunk order (only when o_bar itself is an output).
 hipError_t launch_obar_reduce(const UnitTable& tab, const Shape& sh, const float* parts, float* o_bar,
                               hipStream_t stream);

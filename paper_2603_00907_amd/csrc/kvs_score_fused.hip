@@ -624,7 +624,7 @@ hipError_t launch_fused_t(const UnitTable& tab, const Shape& sh, const void* Q, 
                           const int32_t* counts_in, float* alpha_bar, const Workspace& ws, hipStream_t stream,
                           int grid_first, int grid_second, unsigned timeout_ticks, unsigned stagger_ticks) {
   hipLaunchKernelGGL(score_fused_init_kernel, dim3(tab.n_units), dim3(kQRows), 0, stream, tab, sh.R, ws.c_row, ws.fsync,
-                     ws.sel_shared);
+                     sh.sel_exchange ? ws.sel_shared : nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((score_fused_kernel<D, STREAM, CAUSAL, false>), dim3(grid_first), dim3(kThreads), 0, stream, tab,

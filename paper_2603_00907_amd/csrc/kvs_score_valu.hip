@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void score_finalize_kernel(const Tab tab,
 hipError_t launch_score_finalize(const UnitTable& tab, const Shape& sh, const Workspace& ws, hipStream_t stream) {
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((score_finalize_kernel<KVS_TABLE_TYPE(t)>), dim3(tab.n_units), dim3(kThreads), 0, stream, t, sh, ws.stats_part,
-                       ws.c_row, ws.sel_shared);
+                       ws.c_row, sh.sel_exchange ? ws.sel_shared : nullptr);
   });
   return hipGetLastError();
 }

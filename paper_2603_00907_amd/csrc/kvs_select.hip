@@ -7,33 +7,37 @@
 // n_sink <= m <= len-2-n_recent (App. C, paragraph (i): pairs with small accumulated attention
 // mass; Sec. 5: the first tokens are always preserved); the r = len - budget smallest scores are
 // selected in one parallel step (Sec. 3.1), ties going to the lower index; consecutive selected
-// edges chain into one output slot.  One workgroup of 1024 threads per unit.  Scores are
+// edges chain into one output slot.  Workgroups of 1024 threads.  Scores are
 // non-negative floats, so their bit patterns order like unsigned integers: an MSB-first radix
-// select (11 + 11 + 10 bits, LDS histograms; the keys stretched to their full span first, the
-// digits after the first settled on a short list) finds the r-th smallest key T and how many
+// select (LDS histograms; the keys stretched to their full span first, the digits after the first
+// settled on a short list) finds the r-th smallest key T and how many
 // keys equal to T are still wanted; a final pass in index order takes every key below T and the
 // first `want` keys equal to T, and turns the selection into the slot map with DPP prefix scans
-// and a scan over the 16 wavefronts.  Keys of units up to kLdsKeys edges are kept in LDS between
-// the passes; longer units recompute them from alpha_bar (L2-resident) in every pass with the
-// same stretched ranking.  In a launch of few units a long unit is selected by several workgroups
-// ("parts") instead, which meet through an exchange area in device memory (see select_unit_split);
-// the kernel exists in two LDS sizes (kLdsKeys and kLdsKeysSmall keys per workgroup).
+// and a scan over the 16 wavefronts.  Keys of units up to 16 slices of 4096 edges are kept in
+// registers between the passes, and several workgroups may share such a unit without exchanging
+// anything (select_unit_slices); longer units recompute them from alpha_bar (L2-resident) in every pass
+// with the same stretched ranking, or, in a launch of few units, are selected by several workgroups
+// that meet through an exchange area in device memory (select_unit_split).
+// Selection alone, one launch in a trace: 8 units of 8192 tokens with a small pass over V 13.3 -> 7.9 us, 8 of 32768
+// 15.9 -> 13.3, 64 of 32768 21.5 -> 18.2 (before: keys in LDS, parts that met or one workgroup per unit).
 //
 // o_bar pass, per chunk of a unit: rows of V are read by LPR adjacent lanes (16 bytes each), scaled
 // by alpha_bar[t] and summed per lane, then over the workgroup; the chunk's sum goes to the
 // workspace; whoever needs o_bar (every merge workgroup, or a tiny reduce kernel when o_bar itself
 // is an output) adds the chunks up in chunk order, so the result does not depend on timing and no
 // device-wide fence is needed (one costs a whole L2 write-back on this chip).
+#include <algorithm>
+#include <type_traits>
+
 #include "kvs_device.h"
 
 namespace kvs {
 namespace {
 
-constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
-constexpr int kLdsKeys = kSelUnitKeys;    // keys a workgroup can keep in LDS: the full-size kernel ...
-constexpr int kLdsKeysSmall = kSelPartKeys;   // ... and the one for launches whose units are short or split into parts
-constexpr int kBins = 2048;
+constexpr int kSliceKeys = 4 * kSelThreads;   // keys of one slice of a unit: four per thread
+constexpr int kBins = 2048;               // bins of a digit of 11 bits, and
+constexpr int kSelFineShift = 20, kSelFineBins = 4096;   // of the first 12 bits
 
 __device__ __forceinline__ uint32_t edge_key(const float* __restrict__ a, int m) {
   return __float_as_uint(a[m] + a[m + 1]);
@@ -43,20 +47,21 @@ __device__ __forceinline__ int lanes_below(uint64_t ballot, int lane) {
   return __popcll(ballot & ((1ull << lane) - 1ull));
 }
 
+constexpr int kFewCand = 20;              // candidates that every wavefront ranks by itself
 constexpr int kCand = 2048;               // keys of the first-pass bin that are refined in LDS
 
+// KEYS: edge scores kept in LDS (the parts that meet through the exchange area keep theirs there).
 template <int KEYS>
 struct SelectSmemT {
-  static constexpr int kKeys = KEYS;
   uint32_t keys[KEYS];
   uint32_t cand[kCand];
-  int hist[kBins];
-  int wave[kSelWaves];
+  int hist[kSelFineBins];
+  int wave[kSelWaves], wave_eq[kSelWaves];
   int pick[3];           // digit, keys below it, keys in it
-  int lt[kSelWaves], eq[kSelWaves];
+  int lt[kSelMaxSlices * kSelWaves], eq[kSelMaxSlices * kSelWaves];
   uint32_t wmin[kSelWaves], wmax[kSelWaves];
   int ncand;
-  int plt[kSelMaxParts], peq[kSelMaxParts];     // split selection: the parts' counts of selected keys
+  int plt[kSelMaxParts], peq[kSelMaxParts];     // exchanging parts: the parts' counts of selected keys
   uint8_t cpart[kCand];                         // ... and the part every listed key came from
 };
 
@@ -86,20 +91,26 @@ __device__ __forceinline__ int waves_before(const int* x, int wave, int lane) {
   return idx ? __builtin_amdgcn_readlane(v, idx - 1) : 0;
 }
 
-// Exclusive scan of the histogram (two bins per thread); finds the bin that holds rank `want`
+// Exclusive scan of the histogram (BPT bins per thread); finds the bin that holds rank `want`
 // (1-based), extends (prefix, pmask, want) by that digit and returns the number of keys in the bin.
-template <typename SM>
+template <int BPT = 2, typename SM>
 __device__ __forceinline__ int pick_bin(SM& sm, int shift, int bins, uint32_t& prefix, uint32_t& pmask,
                                         int& want) {
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int h0 = sm.hist[2 * tid], h1 = sm.hist[2 * tid + 1];
-  const int incl = wave_incl_scan(h0 + h1);
+  int h[BPT], sum = 0;
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) { h[i] = sm.hist[BPT * tid + i]; sum += h[i]; }
+  const int incl = wave_incl_scan(sum);
   if (lane == kWave - 1) sm.wave[wave] = incl;
   __syncthreads();
-  const int base = waves_before(sm.wave, wave, lane);
-  const int excl = base + incl - (h0 + h1);
-  if (want > excl && want <= excl + h0) { sm.pick[0] = 2 * tid; sm.pick[1] = excl; sm.pick[2] = h0; }
-  else if (want > excl + h0 && want <= excl + h0 + h1) { sm.pick[0] = 2 * tid + 1; sm.pick[1] = excl + h0; sm.pick[2] = h1; }
+  int excl = waves_before(sm.wave, wave, lane) + incl - sum;
+  if (want > excl && want <= excl + sum) {
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      if (want > excl && want <= excl + h[i]) { sm.pick[0] = BPT * tid + i; sm.pick[1] = excl; sm.pick[2] = h[i]; }
+      excl += h[i];
+    }
+  }
   __syncthreads();
   prefix |= (uint32_t)sm.pick[0] << shift;
   pmask |= (uint32_t)(bins - 1) << shift;
@@ -131,16 +142,32 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
 }
 
 // The first digit of the threshold is known (prefix, pmask) and `want` is its rank among the keys that share
-// it: settles the remaining 21 bits.  sm.cand[0 .. ncand) lists those keys when ncand <= kCand; otherwise the
-// passes run over sm.keys[0 .. nkeys).  Returns the number of keys equal to the threshold; prefix is then the
-// threshold and `want` the number of keys equal to it that are still wanted.
-template <typename SM>
-__device__ __forceinline__ int refine_threshold(SM& sm, const int ncand, const int nkeys, uint32_t& prefix,
+// it: settles the remaining SHIFT bits.  sm.cand[0 .. ncand) lists those keys when ncand <= kCand; otherwise
+// all_keys(f) calls f for every key of the thread.  Returns the number of keys equal to the threshold; prefix is then
+// the threshold and `want` the number of keys equal to it that are still wanted.
+template <int SHIFT, typename SM, typename F>
+__device__ __forceinline__ int refine_threshold(SM& sm, const int ncand, F&& all_keys, uint32_t& prefix,
                                                 uint32_t& pmask, int& want) {
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   constexpr uint32_t kNone = 0xffffffffu;
   int n_equal;                         // keys equal to the threshold
-  if (ncand <= kWave) {
+  if (ncand <= kFewCand) {
+    // Every wavefront for itself, without a barrier: lane i holds candidate i and is compared with all of them.  (About
+    // 5 instructions a candidate: 0.3 us for 14 of them, the form below 0.8.)
+    const uint32_t c = lane < ncand ? sm.cand[lane] : kNone;
+    int b = 0, e = 0, f = 0;
+    for (int j = 0; j < ncand; ++j) {
+      const uint32_t cj = (uint32_t)__builtin_amdgcn_readlane((int)c, j);
+      b += cj < c;
+      e += cj == c;
+      f += (cj == c) & (j < lane);
+    }
+    const uint64_t at = __ballot(lane < ncand && b + f == want - 1);
+    const int i = __builtin_amdgcn_readfirstlane(__ffsll((long long)at) - 1);
+    prefix = (uint32_t)__builtin_amdgcn_readlane((int)c, i);
+    want -= __builtin_amdgcn_readlane(b, i);
+    n_equal = __builtin_amdgcn_readlane(e, i);
+  } else if (ncand <= kWave) {
     // A handful of candidates: all against all.  Lane i of every wavefront holds candidate i, wavefront
     // w compares with candidates 4w..4w+3 (one LDS address per read: a broadcast), and the partial
     // counts meet in LDS.  Ties go by list position: equal keys are interchangeable here, only the
@@ -178,7 +205,7 @@ __device__ __forceinline__ int refine_threshold(SM& sm, const int ncand, const i
   } else {
     const bool listed = (ncand <= kCand);
     const int shifts[2] = {10, 0};
-    const int widths[2] = {11, 10};
+    const int widths[2] = {SHIFT - 10, 10};
     n_equal = 0;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -192,10 +219,9 @@ __device__ __forceinline__ int refine_threshold(SM& sm, const int ncand, const i
           if ((k & pmask) == prefix) atomicAdd(&sm.hist[(k >> shift) & (bins - 1)], 1);
         }
       } else {                            // a bin too crowded for the list: full passes over the keys
-        for (int i = tid; i < nkeys; i += kSelThreads) {
-          const uint32_t k = sm.keys[i];
-          if ((k & pmask) == prefix) atomicAdd(&sm.hist[(k >> shift) & (bins - 1)], 1);
-        }
+        all_keys([&](uint32_t k) {
+          if (k != kNone && (k & pmask) == prefix) atomicAdd(&sm.hist[(k >> shift) & (bins - 1)], 1);
+        });
       }
       __syncthreads();
       n_equal = pick_bin(sm, shift, bins, prefix, pmask, want);
@@ -204,195 +230,236 @@ __device__ __forceinline__ int refine_threshold(SM& sm, const int ncand, const i
   return n_equal;
 }
 
-// Select for a unit whose keys fit the LDS.  Key i' belongs to the edge after token lo_al + i', where
-// lo_al <= lo is the first token whose alpha_bar element sits on a 16-byte boundary: groups of four
-// keys then coincide with aligned groups of four elements of alpha_bar, edge_mask and slot.  Keys
-// of tokens outside [lo, hi] are 0xffffffff: no threshold reaches them.  One CU does all of this,
-// so the instruction count per key is what matters: groups that lie wholly inside [lo, hi] (all but
-// the first and the last) take paths without per-key checks.
-template <typename SM>
-__device__ __forceinline__ void select_unit_cached(const Unit& un, const float* __restrict__ a,
+// Select for a unit of at most NG slices of kSliceKeys keys: thread t holds the t-th group of four keys of every slice in
+// registers.  Key i' belongs to the edge after token lo_al + i', where lo_al <= lo is the first token whose alpha_bar
+// element sits on a 16-byte boundary: groups of four keys then coincide with aligned groups of four elements of
+// alpha_bar, edge_mask and slot.  Keys of tokens outside [lo, hi] are 0xffffffff: no threshold reaches them.
+// P workgroups share a unit: each of them goes over ALL the unit's keys up to the threshold, which needs nothing from the
+// others, and writes the mask and the slots of its own slices only.  What they do twice costs less than meeting: a
+// meeting of workgroups through device memory is 1.6 to 2.1 us and three were needed.  One CU issues one vector
+// instruction of a wavefront per SIMD and four cycles, so an instruction per key is 0.25 us for 32768 keys and the
+// count per key is what matters: wavefronts whose 64 groups of a slice all lie inside [lo, hi] (uniform; all but the
+// first and the last) take paths without per-key checks.
+template <int NG, typename SM>
+__device__ __forceinline__ void select_unit_slices(const Unit& un, const float* __restrict__ a,
                                                    uint8_t* __restrict__ mk, int32_t* __restrict__ sl, SM& sm,
-                                                   int lo, int hi, int r) {
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+                                                   const int lo, const int hi, const int r, const int part,
+                                                   const int P) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int n = un.len;
   const int pad0 = (int)((un.in_row + lo) & 3);
   const int lo_al = lo - pad0;
-  const int G = (hi - lo_al + 4) / 4;              // groups of four keys, at most SM::kKeys / 4
-  constexpr int GPT = SM::kKeys / 4 / kSelThreads; // groups per thread
+  const int G = (hi - lo_al + 4) / 4;              // groups of four keys, at most NG * kSelThreads
+  const int S = (G + kSelThreads - 1) / kSelThreads;
+  const int s0 = part * S / P, s1 = (part + 1) * S / P;      // this workgroup's slices
   constexpr uint32_t kNone = 0xffffffffu;
-  uint4* k4 = reinterpret_cast<uint4*>(sm.keys);
 
-  // ---- keys and the histogram of their first digit: all of a thread's loads are in flight together
-  for (int b = tid; b < kBins; b += kSelThreads) sm.hist[b] = 0;
-  if (tid == 0) sm.ncand = 0;
-  __syncthreads();
-  {
-    float4 v[GPT];
-    float nx[GPT];
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int g = u * kSelThreads + tid;
-      const int m0 = lo_al + 4 * g;                // may lie up to 3 tokens before the unit: still alpha_bar
-      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      nx[u] = 0.f;
-      if (m0 >= lo && m0 + 3 <= hi) {              // hi <= n - 2: element m0 + 4 exists
-        v[u] = *reinterpret_cast<const float4*>(a + m0);
-        nx[u] = a[m0 + 4];
-      } else if (g < G) {                          // first or last group: nothing is read past the unit's end
-        v[u].x = a[min(m0, n - 1)];
-        v[u].y = a[min(m0 + 1, n - 1)];
-        v[u].z = a[min(m0 + 2, n - 1)];
-        v[u].w = a[min(m0 + 3, n - 1)];
-        nx[u] = a[min(m0 + 4, n - 1)];
+  if (hi - lo < 3) {                               // fewer than four edges: r rounds of one thread
+    if (part != 0) return;
+    if (tid == 0) {
+      unsigned taken = 0;
+      for (int i = 0; i < r; ++i) {
+        uint32_t best = kNone;
+        int at = 0;
+        for (int m = lo; m <= hi; ++m) {
+          const uint32_t key = edge_key(a, m);
+          if (!(taken >> (m - lo) & 1) && key < best) { best = key; at = m - lo; }
+        }
+        taken |= 1u << at;
       }
+      sm.pick[0] = (int)taken;
     }
-    // raw keys, their minimum and maximum
-    uint32_t k[GPT][4];
-    uint32_t kmin = kNone, kmax = 0;
+    __syncthreads();
+    const unsigned taken = (unsigned)sm.pick[0];
+    for (int m = tid; m < n; m += kSelThreads) {
+      const int e = min(max(m - lo, 0), 4);        // edges of [lo, hi] before token m
+      mk[m] = m >= lo && m <= hi ? (taken >> e) & 1 : 0;
+      sl[m] = m - __popc(taken & ((1u << e) - 1u));
+    }
+    return;
+  }
+
+  // groups that lie wholly inside [lo, hi]: full0 <= g < full1
+  const int full0 = pad0 ? 1 : 0, full1 = (hi - lo_al + 1) / 4;
+  auto plain = [&](int u) {
+    const int g = u * kSelThreads + wave * kWave;
+    return g >= full0 && g + kWave <= full1;
+  };
+  const char* ab = reinterpret_cast<const char*>(a + lo_al);         // (up to 3 tokens before the unit: still alpha_bar)
+  // ---- raw keys, their minimum and maximum: all of a thread's loads are in flight together.  Groups past the last full
+  //      one are moved back to end at hi (hi <= n - 2: the element after a group exists); `gone`: keys of a group that
+  //      are not its own
+  for (int b = tid; b < kSelFineBins; b += kSelThreads) sm.hist[b] = 0;
+  if (tid == 0) sm.ncand = 0;
+  auto offset = [&](int u) { return (uint32_t)min(4 * (u * kSelThreads + tid), hi - 3 - lo_al) * 4u; };
+  typedef float f4_t __attribute__((ext_vector_type(4), aligned(4)));
+  f4_t v[NG];
+  float nx[NG];                                    // the element after the group, where the next lane does not hold it
+  // plain wavefronts: lane 63's, fetched for all slices at once, slice u's by lane u
+  const float border = *reinterpret_cast<const float*>(
+      ab + (uint32_t)min(4 * (lane * kSelThreads + wave * kWave + kWave), hi + 1 - lo_al) * 4u);
+  static_assert(NG <= kWave, "one lane per slice");
 #pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int g = u * kSelThreads + tid;
-      const int m0 = lo_al + 4 * g;
+  for (int u = 0; u < NG; ++u) {
+    if (u < S) {
+      v[u] = *reinterpret_cast<const f4_t*>(ab + offset(u));
+      if (!plain(u)) nx[u] = *reinterpret_cast<const float*>(ab + offset(u) + 16u);
+    }
+  }
+  uint32_t k[NG][4];
+  uint32_t kmin = kNone, kmax = 0;
+#pragma unroll
+  for (int u = 0; u < NG; ++u) {
+    if (u < S) {
+      float next;
+      if (plain(u)) {
+        const int last = __builtin_amdgcn_readlane(__builtin_bit_cast(int, border), u);
+        next = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(last, __builtin_bit_cast(int, v[u].x), 0x130, 0xF,
+                                                                     0xF, false));          // wave_shl:1
+      } else {
+        next = nx[u];
+      }
       k[u][0] = __float_as_uint(v[u].x + v[u].y);
       k[u][1] = __float_as_uint(v[u].y + v[u].z);
       k[u][2] = __float_as_uint(v[u].z + v[u].w);
-      k[u][3] = __float_as_uint(v[u].w + nx[u]);
-      if (m0 >= lo && m0 + 3 <= hi) {
-        kmin = min(kmin, min(min(k[u][0], k[u][1]), min(k[u][2], k[u][3])));
-        kmax = max(kmax, max(max(k[u][0], k[u][1]), max(k[u][2], k[u][3])));
+      k[u][3] = __float_as_uint(v[u].w + next);
+      if (plain(u)) {
+        kmin = min(min(kmin, k[u][0]), min(min(k[u][1], k[u][2]), k[u][3]));
+        kmax = max(max(kmax, k[u][0]), max(max(k[u][1], k[u][2]), k[u][3]));
+      } else {
+        const int g4 = 4 * (u * kSelThreads + tid), gone = max(g4, pad0) - min(g4, hi - 3 - lo_al);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          kmax = max(kmax, j < gone ? 0u : k[u][j]);
+          k[u][j] = j < gone ? kNone : k[u][j];
+          kmin = min(kmin, k[u][j]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) k[u][j] = kNone;
+    }
+  }
+  kmin = wave_min_u32(kmin);
+  kmax = wave_max_u32(kmax);
+  if (lane == 0) { sm.wmin[wave] = kmin; sm.wmax[wave] = kmax; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) { kmin = min(kmin, sm.wmin[w]); kmax = max(kmax, sm.wmax[w]); }
+  // Keys are counted from kmin on.  The first digit is that of (key - kmin) << lshift, the span stretched to 32 bits:
+  // monotone, and it separates neighbouring tokens' keys, which mostly share their top IEEE bits (equal digits in one
+  // wavefront instruction serialise in the LDS atomics).  The list of the threshold's bin takes the stretched keys.
+  const uint32_t span = kmax - kmin;               // < 2^31: the keys are bit patterns of non-negative floats
+  const int lshift = min(span ? __clz(span) : 32, kSelFineShift);
+#pragma unroll
+  for (int u = 0; u < NG; ++u) {
+    if (u < S) {
+      if (plain(u)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          k[u][j] -= kmin;
+          atomicAdd(&sm.hist[k[u][j] >> (kSelFineShift - lshift)], 1);
+        }
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const bool ok = (g < G) && (m0 + j >= lo) && (m0 + j <= hi);
-          k[u][j] = ok ? k[u][j] : kNone;
-          kmin = min(kmin, k[u][j]);
-          kmax = max(kmax, ok ? k[u][j] : 0u);
-        }
-      }
-    }
-    kmin = wave_min_u32(kmin);
-    kmax = wave_max_u32(kmax);
-    if (lane == 0) { sm.wmin[wave] = kmin; sm.wmax[wave] = kmax; }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) { kmin = min(kmin, sm.wmin[w]); kmax = max(kmax, sm.wmax[w]); }
-    // Keys are ranked as (key - kmin) << lshift, the span stretched to 31 bits: monotone, and the
-    // first digit then separates neighbouring tokens' keys, which mostly share their top IEEE bits
-    // (equal digits in one wavefront instruction serialise in the LDS atomics).  Bit 31 stays clear,
-    // so the out-of-range marker shares no digit with a real key.
-    const uint32_t span = kmax - kmin;             // < 2^31: the keys are bit patterns of non-negative floats
-    const int lshift = span ? __clz(span) - 1 : 0;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int g = u * kSelThreads + tid;
-      const int m0 = lo_al + 4 * g;
-      if (m0 >= lo && m0 + 3 <= hi) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          k[u][j] = (k[u][j] - kmin) << lshift;
-          atomicAdd(&sm.hist[k[u][j] >> 21], 1);
-        }
-        k4[g] = make_uint4(k[u][0], k[u][1], k[u][2], k[u][3]);
-      } else if (g < G) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
           if (k[u][j] != kNone) {
-            k[u][j] = (k[u][j] - kmin) << lshift;
-            atomicAdd(&sm.hist[k[u][j] >> 21], 1);
+            k[u][j] -= kmin;
+            atomicAdd(&sm.hist[k[u][j] >> (kSelFineShift - lshift)], 1);
           }
         }
-        k4[g] = make_uint4(k[u][0], k[u][1], k[u][2], k[u][3]);
       }
     }
   }
   __syncthreads();
   uint32_t prefix = 0, pmask = 0;
   int want = r;                        // rank (1-based) among the keys that share `prefix`
-  pick_bin(sm, 21, 2048, prefix, pmask, want);
+  pick_bin<kSelFineBins / kSelThreads>(sm, kSelFineShift, kSelFineBins, prefix, pmask, want);
 
-  // ---- the keys of that bin go to a short list (one LDS atomic per wavefront: every lane counts its
-  //      matches, a scan gives it its place); the remaining 21 bits are settled on the list
-  {
-    uint4 q[GPT];
-    int c = 0;
+  // ---- the keys of that bin (a few dozen, nearly always) go to a short list; the remaining bits are settled on the list
+  const uint32_t bin0 = prefix >> lshift, width = 1u << (kSelFineShift - lshift);      // the bin in unstretched keys
 #pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int g = u * kSelThreads + tid;
-      q[u] = make_uint4(kNone, kNone, kNone, kNone);
-      if (g < G) q[u] = k4[g];
-      c += (((q[u].x ^ prefix) >> 21) == 0) + (((q[u].y ^ prefix) >> 21) == 0) + (((q[u].z ^ prefix) >> 21) == 0) +
-           (((q[u].w ^ prefix) >> 21) == 0);
-    }
-    const int incl = wave_incl_scan(c);
-    const int tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-    if (tot > 0) {                                 // wavefront-uniform
-      int base = 0;
-      if (lane == 0) base = atomicAdd(&sm.ncand, tot);
-      int pos = __builtin_amdgcn_readfirstlane(base) + incl - c;
-      if (c > 0) {
+  for (int u = 0; u < NG; ++u) {
+    if (u < S) {
+      uint32_t d[4];
 #pragma unroll
-        for (int u = 0; u < GPT; ++u) {
-          const uint32_t kk[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+      for (int j = 0; j < 4; ++j) d[j] = k[u][j] - bin0;     // (0xffffffff: at least 2^31 above any bin)
+      if (min(min(d[0], d[1]), min(d[2], d[3])) < width) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (((kk[j] ^ prefix) >> 21) == 0) {
-              if (pos < kCand) sm.cand[pos] = kk[j];
-              ++pos;
-            }
+        for (int j = 0; j < 4; ++j) {
+          if (d[j] < width) {
+            const int pos = atomicAdd(&sm.ncand, 1);
+            if (pos < kCand) sm.cand[pos] = k[u][j] << lshift;
           }
         }
       }
     }
   }
   __syncthreads();
-  const int n_equal = refine_threshold(sm, sm.ncand, 4 * G, prefix, pmask, want);   // keys equal to the threshold
-  const uint32_t T = prefix;           // `want` keys equal to T are taken, the lowest indices first
+  const int n_equal = refine_threshold<kSelFineShift>(sm, sm.ncand, [&](auto&& f) {      // keys equal to the threshold
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f(k[u][j] == kNone ? kNone : k[u][j] << lshift);
+    }
+  }, prefix, pmask, want);
+  const uint32_t T = prefix >> lshift; // `want` keys equal to T are taken, the lowest indices first
   // When every key equal to T is taken (nearly always: T is then the only one), "selected" is simply
   // "below T + 1" and nothing has to be ranked.
   const bool simple = (n_equal == want);
   const uint32_t Tc = simple ? T + 1 : T;
 
-  // ---- ordered pass: wavefront w owns the groups [g0, g1), lane l the groups g0 + it * 64 + l
-  constexpr int ITS = SM::kKeys / 4 / kSelWaves / kWave;     // rounds per wavefront
-  const int per_g = ((G + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave * kWave;
-  const int g0 = min(G, wave * per_g), g1 = min(G, g0 + per_g);
-  uint4 q[ITS];
-  int n_lt = 0, n_eq = 0;               // wavefront totals: keys below Tc, keys equal to T (if they matter)
+  // ---- selected edges before this thread's group of a slice: every wavefront's count over the slices before this
+  //      workgroup's and its counts of each of those, scanned in index order (slice by slice, wavefront by wavefront)
+  {
+    int lt0 = 0, eq0 = 0;
 #pragma unroll
-  for (int it = 0; it < ITS; ++it) {
-    const int g = g0 + it * kWave + lane;
-    q[it] = make_uint4(kNone, kNone, kNone, kNone);
-    if (g < g1) q[it] = k4[g];
-    n_lt += __popcll(__ballot(q[it].x < Tc)) + __popcll(__ballot(q[it].y < Tc)) + __popcll(__ballot(q[it].z < Tc)) +
-            __popcll(__ballot(q[it].w < Tc));
-  }
-  if (!simple) {
+    for (int u = 0; u < NG; ++u) {
+      if (u < s1) {
+        int lt = 0, eq = 0;
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      n_eq += __popcll(__ballot(q[it].x == T)) + __popcll(__ballot(q[it].y == T)) + __popcll(__ballot(q[it].z == T)) +
-              __popcll(__ballot(q[it].w == T));
+        for (int j = 0; j < 4; ++j) lt += __popcll(__ballot(k[u][j] < Tc));
+        if (!simple) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) eq += __popcll(__ballot(k[u][j] == T));
+        }
+        if (u < s0) {
+          lt0 += lt;
+          eq0 += eq;
+        } else if (lane == 0) {
+          sm.lt[u * kSelWaves + wave] = lt;
+          sm.eq[u * kSelWaves + wave] = eq;
+        }
+      }
     }
+    if (lane == 0) { sm.wave[wave] = lt0; sm.wave_eq[wave] = eq0; }
   }
-  if (lane == 0) { sm.lt[wave] = n_lt; sm.eq[wave] = n_eq; }
   __syncthreads();
-  int eq_before = 0, sel_before = waves_before(sm.lt, wave, lane);
-  if (!simple) {
-    for (int w = 0; w < wave; ++w) {
-      const int e = sm.eq[w];
-      sel_before += min(max(want - eq_before, 0), e);
-      eq_before += e;
+  constexpr int EPL = NG * kSelWaves > kWave ? NG * kSelWaves / kWave : 1;   // entries per lane
+  static_assert(kSelWaves % EPL == 0, "a lane's entries belong to one slice");
+  // sum over the entries before (slice u, this wavefront), for every own u: lane (16 u + wave) / EPL holds it
+  auto entries_before = [&](const int* x, const int* before) {
+    int sum = 0, mine = 0;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int idx = lane * EPL + i;
+      const int e = idx >= s0 * kSelWaves && idx < s1 * kSelWaves ? x[idx] : 0;
+      if (i < wave % EPL) mine += e;
+      sum += e;
     }
-  }
+    const int own = wave_incl_scan(sum) - sum + mine;
+    return s0 > 0 ? own + waves_before(before, kSelWaves, lane) : own;
+  };
+  const int lt_scan = entries_before(sm.lt, sm.wave);
+  const int eq_scan = simple ? 0 : entries_before(sm.eq, sm.wave_eq);
 
   // Four tokens' mask bytes and slots; whole groups inside [lo, hi] go out as one 4-byte and one
   // 16-byte store.  `below`: selected edges before the group's first token.
-  auto write_group = [&](int g, const bool* sel, int below) {
-    const int m0 = lo_al + 4 * g;
+  auto write_group = [&](int m0, const bool* sel, int below, bool full) {
     int s4[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) { s4[j] = m0 + j - below; below += sel[j]; }
-    if (m0 >= lo && m0 + 3 <= hi) {
+    if (full) {
       *reinterpret_cast<uint32_t*>(mk + m0) =
           (uint32_t)sel[0] | ((uint32_t)sel[1] << 8) | ((uint32_t)sel[2] << 16) | ((uint32_t)sel[3] << 24);
       *reinterpret_cast<int4*>(sl + m0) = make_int4(s4[0], s4[1], s4[2], s4[3]);
@@ -403,57 +470,62 @@ __device__ __forceinline__ void select_unit_cached(const Unit& un, const float* 
       }
     }
   };
-
-  if (n_eq == 0) {
-    // nothing to rank in this wavefront (the usual case): all rounds' scans at once
-    int cnt[ITS], incl[ITS];
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      cnt[it] = (q[it].x < Tc) + (q[it].y < Tc) + (q[it].z < Tc) + (q[it].w < Tc);
-      incl[it] = wave_incl_scan(cnt[it]);
-    }
+  for (int u = 0; u < NG; ++u) {
+    if (u >= s0 && u < s1) {
+      const int src = (u * kSelWaves + wave) / EPL;
+      const int g4 = 4 * (u * kSelThreads + tid);
+      int below = __builtin_amdgcn_readlane(lt_scan, src);
+      // a moved group's own keys are its last ones: they go back to their tokens' places
+      const int gone = max(g4 - (hi - 3 - lo_al), 0);
+      uint32_t q[4];
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      const int g = g0 + it * kWave + lane;
-      const bool sel[4] = {q[it].x < Tc, q[it].y < Tc, q[it].z < Tc, q[it].w < Tc};
-      if (g < g1) write_group(g, sel, sel_before + incl[it] - cnt[it]);
-      sel_before += __builtin_amdgcn_readlane(incl[it], kWave - 1);
-    }
-  } else {
-    // ties with the threshold: ranked in index order, round by round
+      for (int j = 0; j < 4; ++j) q[j] = k[u][j];
+      if (!plain(u)) {
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) {
-      const int g = g0 + it * kWave + lane;
-      const uint32_t kk[4] = {q[it].x, q[it].y, q[it].z, q[it].w};
-      bool sel[4], eq[4];
-      int lane_eq = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        sel[j] = kk[j] < T;
-        eq[j] = kk[j] == T;
-        lane_eq += eq[j];
+        for (int s = 0; s < 3; ++s) {
+          if (s < gone) { q[0] = q[1]; q[1] = q[2]; q[2] = q[3]; q[3] = kNone; }
+        }
       }
-      const int incl_eq = wave_incl_scan(lane_eq);
-      int rank = eq_before + incl_eq - lane_eq;
+      bool sel[4];
+      if (simple) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (eq[j]) { sel[j] = rank < want; ++rank; }
+        for (int j = 0; j < 4; ++j) sel[j] = q[j] < Tc;
+        const int cnt = sel[0] + sel[1] + sel[2] + sel[3];
+        below += wave_incl_scan(cnt) - cnt;
+      } else {                                     // ties with the threshold: ranked in index order
+        const int eq_before = __builtin_amdgcn_readlane(eq_scan, src);
+        bool eq[4];
+        int lane_lt = 0, lane_eq = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          sel[j] = q[j] < T;
+          eq[j] = q[j] == T;
+          lane_lt += sel[j];
+          lane_eq += eq[j];
+        }
+        int rank = eq_before + wave_incl_scan(lane_eq) - lane_eq;
+        below += wave_incl_scan(lane_lt) - lane_lt + min(rank, want);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (eq[j]) { sel[j] = rank < want; ++rank; }
+        }
       }
-      eq_before += __builtin_amdgcn_readlane(incl_eq, kWave - 1);
-      const int lane_cnt = sel[0] + sel[1] + sel[2] + sel[3];
-      const int incl = wave_incl_scan(lane_cnt);
-      if (g < g1) write_group(g, sel, sel_before + incl - lane_cnt);
-      sel_before += __builtin_amdgcn_readlane(incl, kWave - 1);
+      write_group(lo_al + g4, sel, below, plain(u));
     }
   }
   // tokens outside the eligible edge range
-  for (int t = tid; t < lo && t < n; t += kSelThreads) { mk[t] = 0; sl[t] = t; }
-  for (int t = hi + 1 + tid; t < n; t += kSelThreads) { mk[t] = 0; sl[t] = t - r; }
+  if (part == 0) {
+    for (int t = tid; t < lo && t < n; t += kSelThreads) { mk[t] = 0; sl[t] = t; }
+  }
+  if (part == P - 1) {
+    for (int t = hi + 1 + tid; t < n; t += kSelThreads) { mk[t] = 0; sl[t] = t - r; }
+  }
 }
 
-// Select for a unit whose keys do not fit the LDS: the passes of the radix select and the ordered pass read
-// alpha_bar again each time.  Same key layout as select_unit_cached (groups of four edges on 16-byte boundaries
-// of alpha_bar, 0xffffffff outside [lo, hi]), same ranking (stretched keys), same tie rule (lowest index first).
+// Select for a unit whose keys do not fit the registers: the passes of the radix select and the ordered pass read
+// alpha_bar again each time.  Groups of four edges on 16-byte boundaries of alpha_bar, 0xffffffff
+// outside [lo, hi]; same ranking (stretched keys), same tie rule (lowest index first).
 template <typename SM>
 __device__ __forceinline__ void select_unit_long(const Unit& un, const float* __restrict__ a, uint8_t* __restrict__ mk,
                                                  int32_t* __restrict__ sl, SM& sm, int lo, int hi, int r) {
@@ -887,7 +959,7 @@ __device__ __forceinline__ bool select_unit_split(const Unit& un, const float* _
     sm.peq[tid] = 0;
   }
   __syncthreads();
-  const int n_equal = refine_threshold(sm, nb, 0, prefix, pmask, want);
+  const int n_equal = refine_threshold<21>(sm, nb, [](auto&&) {}, prefix, pmask, want);   // (nb <= kCand: all listed)
   const uint32_t T = prefix;           // `want` keys equal to T are taken, the lowest indices first
   const bool simple = (n_equal == want);
   const uint32_t Tc = simple ? T + 1 : T;
@@ -996,10 +1068,12 @@ __device__ __forceinline__ bool select_unit_split(const Unit& un, const float* _
   return true;
 }
 
-template <typename SM>
+// One of the P workgroups that select a unit (without an exchange area; P > 1 only where the keys fit the registers).
+template <int NG, typename SM>
 __device__ __forceinline__ void select_unit(const Unit& un, const Shape& sh, const float* __restrict__ alpha_bar,
-                            uint8_t* __restrict__ edge_mask, int32_t* __restrict__ slot, SM& sm) {
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+                            uint8_t* __restrict__ edge_mask, int32_t* __restrict__ slot, SM& sm, const int part,
+                            const int P) {
+  const int tid = threadIdx.x;
   const int n = un.len;
   const int r = n - un.n_out;
   const float* a = alpha_bar + un.in_row;
@@ -1013,16 +1087,17 @@ __device__ __forceinline__ void select_unit(const Unit& un, const Shape& sh, con
     for (int t = tid; t < n; t += kSelThreads) { mk[t] = 0; sl[t] = t; }
     return;
   }
-  if (E + 6 <= SM::kKeys) {            // with the padding to aligned groups of four at both ends
-    select_unit_cached(un, a, mk, sl, sm, lo, hi, r);
-    return;
+  if constexpr (NG <= kSelRegSlices) {             // (the host has picked NG by the launch's longest unit)
+    select_unit_slices<NG>(un, a, mk, sl, sm, lo, hi, r, part, P);
+  } else if (select_slices(E) <= NG) {
+    select_unit_slices<NG>(un, a, mk, sl, sm, lo, hi, r, part, P);
+  } else {
+    // longer units: every pass recomputes the keys from alpha_bar (L2-resident).  One CU walks the whole unit several
+    // times, so the instruction count per key is what counts: a lane takes four consecutive edges from one aligned
+    // 16-byte load plus one element, whole groups inside [lo, hi] skip the per-key checks, keys are ranked stretched,
+    // and the ordered pass writes four tokens per lane.
+    select_unit_long(un, a, mk, sl, sm, lo, hi, r);
   }
-
-  // ---- longer units: every pass recomputes the keys from alpha_bar (L2-resident).  One CU walks the whole unit
-  //      several times, so the instruction count per key is what counts: as in the cached path a lane takes four
-  //      consecutive edges from one aligned 16-byte load plus one element, whole groups inside [lo, hi] skip the
-  //      per-key checks, keys are ranked stretched, and the ordered pass writes four tokens per lane.
-  select_unit_long(un, a, mk, sl, sm, lo, hi, r);
 }
 
 template <typename T, int D, bool STREAM>
@@ -1107,36 +1182,43 @@ __device__ __forceinline__ void obar_reduce_unit(const Unit& un, const Shape& sh
   }
 }
 
-// Three kinds of workgroups: blocks [0, n_select) select one unit's edges each, blocks [n_select, n_select +
-// n_reduce) add one unit's partial o_bar sums up each, the others stream one chunk of V each.
-// KEYS: edge scores a select workgroup can keep in LDS.  The small size leaves room for three workgroups per CU,
-// which matters to the workgroups of the other kinds in the same launch.
-template <typename T, int D, int KEYS, typename Tab>
-__global__ __launch_bounds__(kSelThreads) void select_obar_kernel(
+// Three kinds of workgroups: blocks [0, n_select) select one unit's edges each (or a part of them), blocks [n_select,
+// n_select + n_reduce) add one unit's partial o_bar sums up each, the others stream one chunk of V each.
+// NG: slices of a unit that a select workgroup can keep in registers, as many as the launch's longest such unit has (2, 8
+// or 16); with 16 the kernel also has the selection of longer units: by parts that meet through the exchange area, or by
+// one workgroup, pass by pass.  The small forms have the registers for two workgroups per CU, which matters to the
+// workgroups of the other kinds in the same launch.
+template <typename T, int D, int NG, typename Tab>
+__global__ __launch_bounds__(kSelThreads, NG <= kSelRegSlices ? 8 : 4) void select_obar_kernel(
     const Tab tab, const Shape sh, const int n_select, const int n_reduce, const float* __restrict__ alpha_bar,
     uint8_t* __restrict__ edge_mask, int32_t* __restrict__ slot, const T* __restrict__ V,
     const int32_t* __restrict__ counts_in, float* __restrict__ o_part, const float* __restrict__ parts_in,
     float* __restrict__ o_bar_out, unsigned int* sel_shared, const unsigned timeout_ticks) {
-  __shared__ SelectSmemT<KEYS> sm;
+  constexpr bool LONG = NG > kSelRegSlices;
+  __shared__ SelectSmemT<LONG ? kSelPartKeys : 4> sm;
   __shared__ float sm_o[kSelWaves][128];
   const int b = blockIdx.x;
   if (b < n_select) {
     const int ui = n_select == tab.n_units ? b : find_unit_by<&Unit::s_base>(tab, b);     // (one workgroup per unit: no search)
     const Unit un = tab.unit(ui);
     const int P = (ui + 1 < tab.n_units ? tab.unit(ui + 1).s_base : tab.total_sparts) - un.s_base;
-    if (P <= 1) {
-      select_unit(un, sh, alpha_bar, edge_mask, slot, sm);
-    } else {
-      // (the host gives a unit several parts only when it has edges to select: r > 0, lo <= hi)
-      const int part = b - un.s_base;
-      const bool done = select_unit_split(un, alpha_bar + un.in_row, edge_mask + un.in_row, slot + un.in_row, sm,
-                                          sel_shared + (size_t)ui * kSelSharedInts, part, P, sh.n_sink,
-                                          un.len - 2 - sh.n_recent, un.len - un.n_out, timeout_ticks);
-      if (!done && part == 0) {
-        __syncthreads();
-        select_unit(un, sh, alpha_bar, edge_mask, slot, sm);
+    const int part = b - un.s_base;
+    bool done = false;
+    if constexpr (LONG) {
+      if (P > 1 && select_exchanges(un, sh)) {
+        // (the host gives a unit several parts only when it has edges to select: r > 0, lo <= hi)
+        done = select_unit_split(un, alpha_bar + un.in_row, edge_mask + un.in_row, slot + un.in_row, sm,
+                                 sel_shared + (size_t)ui * kSelSharedInts, part, P, sh.n_sink,
+                                 un.len - 2 - sh.n_recent, un.len - un.n_out, timeout_ticks);
+        if (!done) {
+          done = part != 0;
+          __syncthreads();
+          if (!done) select_unit<NG>(un, sh, alpha_bar, edge_mask, slot, sm, 0, 1);
+          done = true;
+        }
       }
     }
+    if (!done) select_unit<NG>(un, sh, alpha_bar, edge_mask, slot, sm, part, P);
   } else if (b < n_select + n_reduce) {
     obar_reduce_unit(tab.unit(b - n_select), sh, parts_in, o_bar_out);
   } else {
@@ -1166,33 +1248,28 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, bool with_select, con
   const int n_reduce = o_bar_out ? tab.n_units : 0;
   const int n_obar = V ? tab.total_ochunks : 0;
   if (n_select + n_reduce + n_obar == 0) return hipSuccess;
-  if (with_select && tab.total_sparts != tab.n_units && sel_shared == nullptr) return hipErrorInvalidValue;
   // a part waits at most 200 us for the others (the clock of wall_clock64() runs at 100 MHz); KVS_DEBUG_SELECT_SPLIT = 3
   // makes that zero, so that the parts give up at their first wait and part 0 does the unit alone (a test of that way out)
   const unsigned timeout_ticks = debug_switch(KVS_DEBUG_SELECT_SPLIT) == 3 ? 0u : 20000u;
-  // the small-LDS kernel when no unit needs more keys in one workgroup's LDS than it holds (a unit split into parts
-  // does not; if its parts give up, its first part selects it from alpha_bar, pass by pass)
-  bool small = true;
+  int slices = 1;                      // of the longest unit; more than kSelRegSlices: the kernel with all paths
   for (int i = 0; with_select && i < tab.n_units; ++i) {
     const Unit un = tab.unit(i);
+    if (un.len <= un.n_out) continue;
     const int parts = (i + 1 < tab.n_units ? tab.unit(i + 1).s_base : tab.total_sparts) - un.s_base;
-    const int E = (un.len - 2 - sh.n_recent) - sh.n_sink + 1;
-    if (parts == 1 && un.len > un.n_out && E + 6 > kLdsKeysSmall) small = false;
+    const int need = select_slices((un.len - 2 - sh.n_recent) - sh.n_sink + 1);
+    slices = std::max(slices, parts > 1 && select_exchanges(un, sh) ? kSelMaxSlices : need);
   }
   const dim3 grid(n_select + n_reduce + n_obar), block(kSelThreads);
-  if (small) {
+  auto launch = [&](auto ng) {
     launch_with_table(tab, [&](const auto& t) {
-      hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeysSmall, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, n_select, n_reduce,
-                         alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
-                         timeout_ticks);
+      hipLaunchKernelGGL((select_obar_kernel<T, D, decltype(ng)::value, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+                         n_select, n_reduce, alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in,
+                         o_bar_out, sel_shared, timeout_ticks);
     });
-  } else {
-    launch_with_table(tab, [&](const auto& t) {
-      hipLaunchKernelGGL((select_obar_kernel<T, D, kLdsKeys, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, n_select, n_reduce,
-                         alpha_bar, edge_mask, slot, (const T*)V, counts_in, o_part, parts_in, o_bar_out, sel_shared,
-                         timeout_ticks);
-    });
-  }
+  };
+  if (slices <= 2) launch(std::integral_constant<int, 2>{});
+  else if (slices <= kSelRegSlices) launch(std::integral_constant<int, kSelRegSlices>{});
+  else launch(std::integral_constant<int, kSelMaxSlices>{});
   return hipGetLastError();
 }
 
