@@ -321,9 +321,15 @@ __device__ __forceinline__ int find_unit(const Tab& tab, int chunk) {
 __device__ __forceinline__ float even_log2(float x) {
   return (float)__builtin_amdgcn_frexp_expf(x) + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(x));
 }
-// A row's normaliser M + log2(s).  (With the instruction alone, 14 units of 20000 tokens and 224 rows: alpha_bar summed up
-// to 1 + 3.2e-7 to 1 + 6.1e-7.)
-__device__ __forceinline__ float plus_log2(float M, float s) { return M + even_log2(s); }
+// A row's normaliser M + log2(s), rounded once: what the sum of M and the exponent loses joins the logarithm of the
+// mantissa.  (With the instruction alone, 14 units of 20000 tokens and 224 rows: alpha_bar summed up to 1 + 3.2e-7 to
+// 1 + 6.1e-7.)
+__device__ __forceinline__ float plus_log2(float M, float s) {
+  const float e = (float)__builtin_amdgcn_frexp_expf(s);
+  const float hi = M + e, part = hi - M;
+  const float lost = (M - (hi - part)) + (e - part);
+  return hi + (lost + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(s)));
+}
 
 // The sweep-1 kernels for up to 128 query rows (and the 256-row form of small launches) reduce the statistics of their
 // unit themselves: a workgroup fetches them in one round trip of its prologue, which costs it less than a finalize
