@@ -53,6 +53,23 @@ __device__ __forceinline__ void lds_read_4x16(bf16x8& a0, bf16x8& a1, bf16x8& a2
       : "memory");
 }
 
+// 2^-k, k the exponent of the largest cardinality that the wavefront's lanes hold: a power of two, so that multiplying and
+// dividing by it is exact.
+__device__ __forceinline__ float unit_of_counts(float c) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) c = fmaxf(c, __shfl_xor(c, m, kWave));
+  return __uint_as_float((254u << 23) - (__float_as_uint(c) & 0x7f800000u));       // (c is at least 1 and below 2^32)
+}
+
+// Four floats of LDS at byte address ad, complete on return (inline assembly for the same reason).
+__device__ __forceinline__ void lds_read_four(float (&r)[4], uint32_t ad) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4 x;
+  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x) : "v"(ad) : "memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = x[i];
+}
+
 // Rows that stand for c tokens with one Key (an already merged cache) enter the softmax as c equal
 // terms, i.e. with log2(c) added to the base-2 logit.  Turns the raw dot products of this lane's 16
 // accumulator rows (tile at token base_t of the unit whose cardinalities start at cnt) into logits.

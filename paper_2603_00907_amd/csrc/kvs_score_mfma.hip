@@ -30,8 +30,9 @@
 //   score_shared_kernel     (kvs_score_shared.hip) more than 128 rows.
 //   score_mfma_f32_kernel   fp32 inputs, up to 64 rows, v_mfma_f32_32x32x2_f32.
 //   score_split_kernel      (kvs_score_split.hip) fp32 inputs, more than 64 rows.
-// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit; over 64 rows sweep 1
-// multiplies the sum over the rows by c instead.
+// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit; over 64 rows c multiplies
+// the terms (256 caches of 2560 rows, 128 query rows: sweep 0 56 -> 41 us, sweep 1 63 -> 60 with the cardinalities in the
+// tile's loads).
 #include <cstdlib>
 #include <type_traits>
 
@@ -400,6 +401,8 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   __shared__ __attribute__((aligned(1024))) unsigned char sm_k[NW][TILEB];
   __shared__ __attribute__((aligned(1024))) unsigned char sm_q[QROWS * ROWB];
   __shared__ float2 sm_stats[NW][QROWS];
+  __shared__ int sm_ci[NW][kWave];                               // the tile's cardinalities (32 rows, twice), as they come,
+  __shared__ __attribute__((aligned(16))) float sm_cf[NW][kTile];   // and of the tile at hand as numbers
   __shared__ __attribute__((aligned(16))) float sm_cq[QROWS];     // sweep 1: the rows' normalisers ...
   __shared__ __attribute__((aligned(16))) int sm_lim[QROWS];      // ... and the last row each attends to
 
@@ -415,7 +418,6 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   const int R = sh.R;
   const float sl2 = sh.scale_log2;
   const int32_t* cnt = counts_in ? counts_in + un.in_row : nullptr;
-  const float sc = cnt ? 1.f : sl2;        // the accumulators hold finished logits when cardinalities were added
   const size_t part_base = (size_t)un.index * kMaxChunks;
 
   const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
@@ -437,6 +439,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
     a_addr[kk] = (uint32_t)(size_t)KVS_LDS_PTR(my_k) + off;
     q_addr[kk] = (uint32_t)(size_t)KVS_LDS_PTR(sm_q) + off;
   }
+  const uint32_t cf_addr = (uint32_t)(size_t)KVS_LDS_PTR(sm_cf[wave]) + 16 * half;
   // the ragged last tile is moved back to end at the chunk's end, see score_mfma_kernel
   auto issue_tile = [&](int j) {
     const int tile_t0 = t0 + j * kTile;
@@ -450,6 +453,8 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
       __builtin_amdgcn_global_load_lds(KVS_GLOBAL_PTR(base + ld_off[i]), KVS_LDS_PTR(my_k + i * 1024), 16, 0,
                                        (STREAM && PHASE == 0) ? kNonTemporal : 0);
     }
+    // (with the tile: a load of their own at the tile's end waits for the tile behind it)
+    if (cnt) __builtin_amdgcn_global_load_lds(KVS_GLOBAL_PTR(cnt + base_t + col), KVS_LDS_PTR(sm_ci[wave]), 4, 0, 0);
     return true;
   };
 
@@ -502,6 +507,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   float m_run[2 * QB], l_run[2 * QB];
 #pragma unroll
   for (int b = 0; b < 2 * QB; ++b) { m_run[b] = -INFINITY; l_run[b] = 0.f; }
+  float c_unit = 1.f;                       // sweep 0: what the cardinalities are multiplied with in l_run
   // OBAR: this lane's 16-byte piece of sum_t w_t V[t] over the wavefront's tiles (w = alpha_bar, or alpha_bar / c)
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   float o_acc[8];
@@ -522,6 +528,17 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
 #pragma unroll
     for (int g = 0; g < KS / 4; ++g)
       lds_read_4x16<0>(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3], a_addr + 4 * g);
+    float cf = 1.f;                             // the cardinality of tile row `col`
+    if (cnt) {
+      cf = (float)sm_ci[wave][lane];
+      if (PHASE == 0) {
+        // (in units of a power of two near the first tile's largest, so that a reference stays near the logits
+        // themselves: an exponent's argument rounds in proportion to its size)
+        if (it == 0) c_unit = unit_of_counts(cf);
+        sm_cf[wave][col] = cf * c_unit;         // (both halves of the wavefront write the same)
+      }
+      asm volatile("" : "+v"(cf) : : "memory"); // (here, before the next tile's loads into the same place)
+    }
     issue_tile(j + NW);                         // the buffer is free again
     // OBAR: the tile's Value rows, RPI whole rows per load; they are used at the end of the tile
     u32x4 vr[NLD];
@@ -598,40 +615,74 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
           const int lim2[2] = {lim[2 * h], lim[2 * h + 1]};
           mask_causal<2>(acc, lim2, base_t, half);
         }
-        if (cnt) logits_with_counts<2>(acc, cnt, base_t, half, sl2);
         // Terms against the reference that is there (see kSumLimit).  Where a lane's sum is not below the limit (the
         // first tile, whose reference is minus infinity, among them) the reference rises to the tile's maxima and the
-        // headroom, and the terms are formed again.
-        float sum[NTB];
-        bool bad = false;
+        // headroom, and the terms are formed again.  A row that stands for c tokens has c equal terms: c multiplies the
+        // term, at no cost (a fused addition), and joins the logit as log2(c) only where a reference is set.
+        auto sums = [&](auto counts_c) {
+          constexpr bool COUNTS = decltype(counts_c)::value;
+          float sum[NTB];
+          bool bad = false;
+          if (COUNTS) {
+            float s4[NTB][4];
 #pragma unroll
-        for (int nt = 0; nt < NTB; ++nt) {
-          const int b = 2 * h + nt;
-          float s4[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int nt = 0; nt < NTB; ++nt) s4[nt][0] = s4[nt][1] = s4[nt][2] = s4[nt][3] = 0.f;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) s4[v % 4] += ex2(fmaf(acc[nt][v], sc, -m_run[b]));
-          sum[nt] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-          bad = bad || !(sum[nt] < kSumLimit);
-        }
-        if (__any(bad)) {
+            for (int g = 0; g < 4; ++g) {           // (four rows' cardinalities at a time: registers)
+              float cr[4];
+              lds_read_four(cr, cf_addr + 32 * g);
 #pragma unroll
-          for (int nt = 0; nt < NTB; ++nt) {
-            const int b = 2 * h + nt;
-            float tm = acc[nt][0];
+              for (int nt = 0; nt < NTB; ++nt) {
 #pragma unroll
-            for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
-            const float m_new = fmaxf(m_run[b], fmaf(tm, sc, kHeadroom));
-            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            float s = 0.f;
+                for (int i = 0; i < 4; ++i)
+                  s4[nt][i] = fmaf(cr[i], ex2(fmaf(acc[nt][4 * g + i], sl2, -m_run[2 * h + nt])), s4[nt][i]);
+              }
+            }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[nt][v], sc, -m_safe));
-            l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
-            m_run[b] = m_new;
+            for (int nt = 0; nt < NTB; ++nt) sum[nt] = (s4[nt][0] + s4[nt][1]) + (s4[nt][2] + s4[nt][3]);
+          } else {
+#pragma unroll
+            for (int nt = 0; nt < NTB; ++nt) {
+              float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int v = 0; v < 16; ++v) s4[v % 4] += ex2(fmaf(acc[nt][v], sl2, -m_run[2 * h + nt]));
+              sum[nt] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+            }
           }
-        } else {
 #pragma unroll
-          for (int nt = 0; nt < NTB; ++nt) l_run[2 * h + nt] += sum[nt];
-        }
+          for (int nt = 0; nt < NTB; ++nt) bad = bad || !(sum[nt] < kSumLimit);
+          if (__any(bad)) {
+#pragma unroll
+            for (int nt = 0; nt < NTB; ++nt) {
+              const int b = 2 * h + nt;
+              float tm = -INFINITY, s = 0.f;
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                float cr[4];
+                if (COUNTS) lds_read_four(cr, cf_addr + 32 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                  tm = fmaxf(tm, fmaf(acc[nt][4 * g + i], sl2, COUNTS ? __builtin_amdgcn_logf(cr[i]) : 0.f));
+              }
+              const float m_new = fmaxf(m_run[b], tm + kHeadroom);
+              const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                float cr[4] = {1.f, 1.f, 1.f, 1.f};
+                if (COUNTS) lds_read_four(cr, cf_addr + 32 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s = fmaf(cr[i], ex2(fmaf(acc[nt][4 * g + i], sl2, -m_safe)), s);
+              }
+              l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
+              m_run[b] = m_new;
+            }
+          } else {
+#pragma unroll
+            for (int nt = 0; nt < NTB; ++nt) l_run[2 * h + nt] += sum[nt];
+          }
+        };
+        if (cnt) sums(std::true_type{});
+        else sums(std::false_type{});
       } else {
         // Sweep 1, products taken as Q K^T: accumulator element v of block nt is query row
         // 32 (2 h + nt) + 8 (v / 4) + 4 half + v % 4, and the lane's column is ONE token, so the sum over the
@@ -688,7 +739,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
           for (int e = 0; e < 8; ++e) o_acc[e] = fmaf(w, vf[e], o_acc[e]);
         }
       }
-      if (cnt) p_tok *= (float)cnt[base_t + col];
+      p_tok *= cf;                                          // (1 without cardinalities)
       if (half == 0 && col >= shift) alpha_bar[un.in_row + base_t + col] = p_tok;
     }
   }
@@ -724,7 +775,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
       const float m_s = (m_n == -INFINITY) ? 0.f : m_n;
       l_run[b] = l_run[b] * ex2(m_run[b] - m_s) + l_o * ex2(m_o - m_s);
       m_run[b] = m_n;
-      if (half == 0) sm_stats[wave][b * 32 + col] = make_float2(m_run[b], l_run[b]);
+      if (half == 0) sm_stats[wave][b * 32 + col] = make_float2(m_run[b], l_run[b] / c_unit);
     }
     __syncthreads();
     if (tid < QROWS && tid < R) {
