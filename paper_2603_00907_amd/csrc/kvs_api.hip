@@ -230,7 +230,8 @@ Workspace carve(const Plan& plan, void* base) {
 
 // Extra workspace of the per-query aggregation, laid out behind the ordinary one.
 struct PerQueryWs {
-  float* o_part;     // [a launch's chunks][R][D] partial outputs, then [a launch's chunks][R] sums of their weights
+  float* o_part;     // [a launch's pieces][R][D] partial outputs, then [a launch's pieces][R] references and sums of terms
+                     // (float2), then [a launch's pieces][R] sums of the weights
   uint16_t* o_hi;    // [n_units][R][D]  bf16 inputs: -2 o as a bf16 pair hi + lo
   uint16_t* o_lo;
   float* o_f32;      // [n_units][R][D]  fp32 inputs: o itself
@@ -267,7 +268,7 @@ PerQueryWs carve_per_query(const Plan& plan, void* base, Workspace* w) {
   if (plan.dtype != KVS_F32 && plan.n_units > kInlineUnits)
     pieces = std::max(pieces, std::min<long long>(8 * max_chunks, kMaxPqPieces));
   const size_t rd = (size_t)plan.shape.R * plan.shape.D;
-  q.o_part = (float*)take((size_t)pieces * (rd + plan.shape.R) * sizeof(float));
+  q.o_part = (float*)take((size_t)pieces * (rd + 3 * plan.shape.R) * sizeof(float));
   if (plan.dtype == KVS_F32) {
     q.o_f32 = (float*)take((size_t)plan.n_units * rd * sizeof(float));
   } else {
@@ -290,9 +291,9 @@ kvs_status check_per_query(const Plan& plan) {
   return KVS_OK;
 }
 
-// alpha_bar, A_t and C_t.  With bf16 inputs the kernels that form the norms recompute every row's attention anyway and
-// sum alpha_bar up on the way: the score phase is then only its first sweep (8 units of 32768 tokens, 128 query rows:
-// the second one takes 16.6 of the step's 212 us, the extra addition nothing that can be measured).  Not where the score
+// alpha_bar, A_t and C_t.  With bf16 inputs the kernels that form the norms sum alpha_bar up on the way, and without
+// cardinalities those before them leave the rows' normalisers, so that no score sweep runs (8 units of 32768 tokens, 128
+// query rows, with the marked tokens done by the norms' kernel: 186 -> 160 us per step).  Not where the score
 // phase runs on the vector ALU (one to three rows): its logits are rounded differently from the norms' products, and
 // alpha_bar formed from its normalisers and their logits had up to 1.9 times the error against 64 bits (5000 tokens,
 // one to three rows); with both of its sweeps alpha_bar is kvs_score's to the bit.
@@ -302,9 +303,14 @@ hipError_t per_query_norms(const Plan& plan, const UnitTable& tab, const Shape& 
   const bool f32 = plan.dtype == KVS_F32;
   const bool both_sweeps = f32 || !score_on_matrix_cores(tab, sh, plan.dtype);
   Shape sh2 = sh;
-  sh2.keep_rows = 1;
-  const hipError_t e = launch_score(tab, sh2, plan.dtype, Q, K, counts_in, both_sweeps ? alpha_bar : nullptr, w, s);
-  if (e != hipSuccess) return e;
+  if (both_sweeps || counts_in != nullptr) {
+    sh2.keep_rows = 1;
+    const hipError_t e = launch_score(tab, sh2, plan.dtype, Q, K, counts_in, both_sweeps ? alpha_bar : nullptr, w, s);
+    if (e != hipSuccess) return e;
+  } else {
+    sh2.c_row_out = w.c_row;
+    sh2.sel_clear = sh.sel_exchange ? w.sel_shared : nullptr;
+  }
   if (f32) return launch_per_query_norms_f32(tab, sh, Q, K, V, counts_in, w.c_row, q.o_part, q.o_f32, a_tok, c_edge, s);
   sh2.alpha_out = both_sweeps ? nullptr : alpha_bar;
   return launch_per_query_norms(tab, sh2, Q, K, V, counts_in, w.c_row, q.o_part, q.o_hi, q.o_lo, q.oo, a_tok, c_edge, s);

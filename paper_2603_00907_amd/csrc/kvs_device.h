@@ -167,9 +167,11 @@ struct Shape {
   int causal;       // 0, or the window W when query row q only sees the rows up to its own position n - W + q % W
   int keep_rows;    // 1: the caller reads the rows' normalisers (c_row) after the score phase
   int fold;         // 1: sweep 1 reduces the chunks' statistics itself (load_row_consts), no finalize kernel has run
-  unsigned int* sel_clear;  // with fold: the exchange area of the selection that follows, which sweep 1 zeroes
-  float* alpha_out; // per-query aggregation (bf16): where its kernels leave alpha_bar (the sweeps then only leave the
-                    // rows' normalisers), or null where the score phase has left it
+  unsigned int* sel_clear;  // with fold: the exchange area of the selection that follows, which sweep 1 zeroes (per-query
+                            // aggregation, with c_row_out: its kernels do)
+  float* alpha_out; // per-query aggregation (bf16): where its kernels leave alpha_bar, or null where the score phase has left it
+  float* c_row_out; // per-query aggregation (bf16): where its kernels leave the rows' normalisers, or null where the
+                    // score phase has left them
   int dec_chunk;    // decode attention: rows per workgroup, at least (chosen per launch, see launch_decode)
   int o_from_score; // where the partial sums of o_bar are: 0: o_part, one per chunk of the o_bar pass; 1: o_part, one
                     // per SCORE chunk (written by sweep 1); 2: fo_part, one per work item of the one-pass score kernel
@@ -477,10 +479,11 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
 // units, 255000 rows, 128 query rows, 188 chunks: 187 us in two, 250 uncut; 14 units, where all chunks are as long: 191
 // against 175): not below 128 rows, and into at most kMaxPqPieces.
 constexpr int kMaxPqPieces = 1024;
+constexpr int kMaxPqSplit = 3;
 inline int pq_split(long long chunks, long long rows, long long longest, int R, int D) {
   const bool light = R <= 64 || D == 64;
   int split = 0;
-  while (split < 3) {
+  while (split < kMaxPqSplit) {
     const long long pieces = chunks << (split + 1);
     const bool few = pieces <= (light ? 512 : 256);
     const bool uneven = (longest >> split) * (light ? 320 : 240) > rows && (longest >> split) > 256;
@@ -490,8 +493,8 @@ inline int pq_split(long long chunks, long long rows, long long longest, int R, 
   return split;
 }
 // Per-query aggregation (bf16, every unit at least 32 rows): a_tok, c_edge and alpha_bar (sh.alpha_out, if set) from Q, K, V
-// and the rows' normalisers c_row that the first score sweep leaves.  o_part: [pieces of the launch's chunks][R][D] fp32,
-// then their weights' sums [pieces][R]; o_hi, o_lo: [n_units][R][D] bf16; oo: [n_units][R].
+// and, unless they leave them in sh.c_row_out (the same array) themselves, the rows' normalisers c_row.  o_part: [pieces of
+// the launch's chunks][R][D] fp32, then references and sums [pieces][R] float2, then weights' sums [pieces][R]; o_hi, o_lo: [n_units][R][D] bf16; oo: [n_units][R].
 hipError_t launch_per_query_norms(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                                   const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi,
                                   uint16_t* o_lo, float* oo, float* a_tok, float* c_edge, hipStream_t stream);

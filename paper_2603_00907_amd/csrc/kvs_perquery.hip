@@ -8,9 +8,12 @@
 //   C_t = (1/R) sum_q alpha_t^{(q)} alpha_{t+1}^{(q)} ||v_t + v_{t+1} - 2 o^{(q)}||
 // The merge kernel then uses A and C in the weight form of Eq. kstar_final.
 //
-// Four kernels after the first score sweep (which leaves the normaliser c[q] of every row; alpha_bar comes from the
-// third of them, so the second sweep is not run, except for windows of one to three rows):
-//   pq_out_kernel         O^T[d, q] = sum_t V[t, d] P[t, q], P = alpha / R recomputed from K Q^T tile by tile.
+// Three kernels, without a score sweep before them.  (With cardinalities the first sweep runs and leaves the rows' normalisers:
+// those are then numbers from 20 to 40, whose rounding is most of the error of alpha_bar, and the kernels' own would
+// round differently from kvs_score's: 3.4e-7 in the root mean square for cardinalities up to 1e7.  Windows of one to three
+// rows run both sweeps and have alpha_bar from them.)
+//   pq_out_kernel         O^T[d, q] = sum_t V[t, d] P[t, q], P = 2^(logit - reference) from K Q^T tile by tile, every piece
+//                         of a chunk with a reference of its own for every row (see kSumLimit), which rises now and then.
 //                         Both products run on v_mfma_f32_32x32x16_bf16.  The contraction over tokens needs
 //                         V with the token index along the MFMA k dimension; a 32x32 block of the V tile is
 //                         turned by one more MFMA against an identity operand (exact in bf16), which leaves it
@@ -18,8 +21,9 @@
 //                         (one block per wavefront, shared through LDS).
 //                         P enters as a bf16 pair hi + lo, so that the rounding of P to bf16 does not limit
 //                         the accuracy of o; the sum of the weights, as the pairs carry them, is kept beside it.
-//                         Chunk partials go to memory and are added in chunk order.
-//   pq_out_reduce_kernel  o^{(q)} = (sum of the chunk partials) / (sum of their weights): a convex combination of the
+//                         The pieces' partials go to memory, with the references and the sums of the terms.
+//   pq_out_reduce_kernel  the rows' normalisers, and o^{(q)} = (sum of the partials) / (sum of their weights), each
+//                         brought to a common reference and added in the order of the chunks: a convex combination of the
 //                         Values with the weights as they were rounded, so that where a row puts nearly all its
 //                         weight on one token, o - v_t is as accurate as the small weights of the others (dividing
 //                         by the nominal sum 1 / R would leave the weights' rounding times ||v_t||).
@@ -30,14 +34,14 @@
 //                         ||v_t + v_{t+1} - 2o||^2 = ||v_t + v_{t+1}||^2 + 2 (X'_t + X'_{t+1}),
 //                         two square roots, and the sums over q.  Tiles overlap by one row (stride 31), so
 //                         the next token of every output row is in the same tile.  Tokens where the expansions
-//                         cancel (o^{(q)} close to v_t for some q) are marked.  The sum of alpha^{(q)}_t over q is
+//                         cancel (o^{(q)} close to v_t for some q) are marked, and done once more at the end, every
+//                         squared norm as a sum of squared differences (redo_marked).  The sum of alpha^{(q)}_t over q is
 //                         alpha_bar: one addition per (t, q) here instead of a sweep of its own (16.6 us for 8 units
 //                         of 32768 tokens and 128 rows).
-//   pq_redo_kernel        the marked tokens once more, every squared norm as a sum of squared differences.
 // COUNTS: the rows are slots of an already merged cache (Sec. 3.1, streaming regime), row t standing for c_t tokens
 // whose Values add up to V[t]: every query row sees it as one token with logit e + ln c_t and value V[t] / c_t.  The
-// products still run on the stored rows; log2 c_t joins the logit (pq_norms_kernel: c_t multiplies the term, so that
-// alpha_bar doesn't carry the rounding of a larger exponent), and 1 / c_t scales the attention weight of the Value sum (o),
+// products still run on the stored rows; c_t multiplies the term in the sums over a row (a logarithm in the exponent would
+// round with its size), the weight of the Value SUM is the term of ONE token, and 1 / c_t scales
 // the product V_t . o and the squared norms afterwards.
 // A workgroup has four wavefronts; wavefront w owns query rows 32w .. 32w+31 of a pass of 128 rows and
 // keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
@@ -45,22 +49,18 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "kvs_device.h"
+#include "kvs_mfma_tile.h"
 
 namespace kvs {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+using namespace mfma;                     // bf16x8, f32x16, kTile, ex2, kHeadroom, kSumLimit, add_compensated
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kTile = 32;                 // tokens per MFMA tile
 constexpr int kPassRows = 32 * kWaves;    // query rows per pass over the chunk
-constexpr int kRedoSpan = 1024;           // pq_redo: tokens per workgroup (262144 tokens: 12.0 us, with 4096 15.2)
+constexpr int kRedoSpan = 1024;           // redo_marked: tokens of a call
 constexpr float kCancel = 1.f / 16.f;     // pq_norms: a squared norm below this share of its leading term is formed again
-
-__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // (one instruction; written out because the compiler forms it from nested fminf only now and then)
 __device__ __forceinline__ float min3(float a, float b, float c) {
@@ -178,14 +178,13 @@ template <int D, bool COUNTS, typename Tab>
 __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
-    float* __restrict__ o_part, float* __restrict__ p_part, const int split) {
+    float* __restrict__ o_part, float* __restrict__ p_part, float2* __restrict__ stat_part, const int split) {
   typedef Tile<D> TL;
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;                // 32-wide blocks of the value dimension
   __shared__ __attribute__((aligned(16))) unsigned char sm_k[2][TL::BYTES];
   __shared__ __attribute__((aligned(16))) unsigned char sm_v[2][TL::BYTES];
-  __shared__ __attribute__((aligned(16))) float sm_lc[2][kTile], sm_ic[2][kTile];   // COUNTS: log2 c and 1 / c of the tile's rows
-  __shared__ __attribute__((aligned(16))) float sm_cc[2][kTile];                    // COUNTS: c itself
+  __shared__ __attribute__((aligned(16))) float sm_cc[2][kTile];                    // COUNTS: the rows' cardinalities
   __shared__ uint4 sm_vt[2][DB][2][kWave];   // the V tile's blocks turned token-major: two operands per lane and block
 
   const int ui = find_unit(tab, (int)blockIdx.x >> split);
@@ -227,12 +226,15 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
     bf16x8 bq[KS];
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) bq[kk] = row_operand<D>(Qu, qrow, ok, kk, half);
-    const float cq = ok ? c_row[(size_t)un.index * R + qrow] : INFINITY;   // exp2(-inf) = 0: no such row
+    // reference of the row's exponents: its normaliser (always with cardinalities), or one of this piece's own
+    // (exp2(-inf) = 0: no such row)
+    float m_run = !ok ? INFINITY : c_row != nullptr ? c_row[(size_t)un.index * R + qrow] : -INFINITY;
+    float z = 0.f, z_lost = 0.f;            // sum of the row's terms (only against a reference of its own)
     const int lim = last_seen_row(sh.causal, un.len, qrow);               // causal window: last row attended to
     f32x16 accO[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) accO[db] = zero;
-    float wsum = 0.f;                       // sum of alpha / R over this lane's token rows, as the pairs hi + lo carry it
+    float wsum = 0.f;                       // the same sum over this lane's token rows, as the pairs hi + lo carry it
 
     typename TL::Regs rk = TL::load(Kg + (size_t)tile_base(0) * TL::ROWB, tid);
     typename TL::Regs rv = TL::load(Vg + (size_t)tile_base(0) * TL::ROWB, tid);
@@ -241,10 +243,7 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
       TL::store(sm_k[buf], rk, tid);
       TL::store(sm_v[buf], rv, tid);
       if (COUNTS && tid < kTile) {
-        const float c = (float)cnt[tile_base(j) + tid];
-        sm_lc[buf][tid] = even_log2(c);
-        sm_ic[buf][tid] = __builtin_amdgcn_rcpf(c);
-        sm_cc[buf][tid] = c;
+        sm_cc[buf][tid] = (float)cnt[tile_base(j) + tid];
       }
       __syncthreads();
       const int shift = t0 + j * kTile - tile_base(j);       // leading rows that belong to the tile before
@@ -272,38 +271,55 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::operand(sm_k[buf], col, kk, half), bq[kk], acc, 0, 0, 0);
-      // accumulator element v: token row 8 (v / 4) + 4 half + v % 4, query column `col`
+      // accumulator element v: token row 8 (v / 4) + 4 half + v % 4, query column `col`.  The weight of a row's Values is
+      // 2^(logit - reference), also where they are the sum over c tokens (c equal terms, each of V / c).
       float p[16];
-      if (COUNTS) {
-        // (alpha / R) / c: the weight of the Value SUM of the row
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 lc = *reinterpret_cast<const float4*>(&sm_lc[buf][8 * g + 4 * half]);
-          const float4 ic = *reinterpret_cast<const float4*>(&sm_ic[buf][8 * g + 4 * half]);
-          p[4 * g] = ex2(fmaf(acc[4 * g], sl2, lc.x - cq)) * ic.x;
-          p[4 * g + 1] = ex2(fmaf(acc[4 * g + 1], sl2, lc.y - cq)) * ic.y;
-          p[4 * g + 2] = ex2(fmaf(acc[4 * g + 2], sl2, lc.z - cq)) * ic.z;
-          p[4 * g + 3] = ex2(fmaf(acc[4 * g + 3], sl2, lc.w - cq)) * ic.w;
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) p[v] = ex2(fmaf(acc[v], sl2, -cq));
-      }
       // rows of the tile before (a moved-back last tile) and rows behind the causal window's limit drop out;
       // both are rare and uniform per tile, so the common tile carries no per-element test
-      if (shift > 0 || (sh.causal > 0 && tile_base(j) + kTile > un.len - sh.causal + 1)) {
+      const bool masked = shift > 0 || (sh.causal > 0 && tile_base(j) + kTile > un.len - sh.causal + 1);
+      auto seen = [&](int v) {
+        const int row = 8 * (v / 4) + 4 * half + (v % 4);
+        return row >= shift && tile_base(j) + row <= lim;
+      };
+      auto terms = [&](float m) {           // the tile's terms against reference m; returns their sum
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = 8 * (v / 4) + 4 * half + (v % 4);
-          p[v] = (row >= shift && tile_base(j) + row <= lim) ? p[v] : 0.f;
+        for (int v = 0; v < 16; ++v) p[v] = ex2(fmaf(acc[v], sl2, -m));
+        if (masked) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) p[v] = seen(v) ? p[v] : 0.f;
         }
+        float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s4[v % 4] += p[v];
+        return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      };
+      float ts = terms(m_run);
+      // A sum that is not below the limit (the first tile's, whose reference is minus infinity, among them): the
+      // reference rises to the tile's largest logit and the headroom, in both halves of the wavefront alike, and what
+      // has been added up is brought to it (see kSumLimit).  Never against a finished normaliser.
+      if (!COUNTS && c_row == nullptr && __any(!(ts < kSumLimit))) {
+        float tm = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) tm = fmaxf(tm, !masked || seen(v) ? acc[v] : -INFINITY);
+        tm = fmaxf(tm, __shfl_xor(tm, 32, kWave));
+        const float m_new = fmaxf(m_run, fmaf(tm, sl2, kHeadroom));
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float down = m_run == m_new ? 1.f : ex2(m_run - m_safe);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) accO[db] *= down;
+        wsum *= down;
+        z *= down;
+        z_lost *= down;
+        m_run = m_new;
+        ts = terms(m_safe);
       }
+      add_compensated(z, z_lost, ts);
       // as the operand of the next product, element i of k-step s is accumulator element 8 s + i
       bf16x8 ph[2], pl[2];
       float pw[16];
       split8w(p, ph[0], pl[0], pw);
       split8w(p + 8, ph[1], pl[1], pw + 8);
-      if (COUNTS) {                         // (the pair carries (alpha / R) / c)
+      if (COUNTS) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 cc = *reinterpret_cast<const float4*>(&sm_cc[buf][8 * g + 4 * half]);
@@ -328,7 +344,12 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
     }
     __syncthreads();                        // the next pass starts with buffer 0 again
     wsum += __shfl_xor(wsum, 32, kWave);    // the other half's token rows
-    if (ok && half == 0) p_part[(size_t)blockIdx.x * R + qrow] = wsum;
+    z -= z_lost;
+    z += __shfl_xor(z, 32, kWave);
+    if (ok && half == 0) {
+      p_part[(size_t)blockIdx.x * R + qrow] = wsum;
+      if (c_row == nullptr) stat_part[(size_t)blockIdx.x * R + qrow] = make_float2(m_run, z);
+    }
     if (ok) {
       float* dst = o_part + ((size_t)blockIdx.x * R + qrow) * D;
 #pragma unroll
@@ -343,42 +364,105 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
   }
 }
 
-// o^{(q)} from the pieces' partials and the sums of their weights, as a bf16 pair hi + lo, and its squared norm.  One
-// workgroup per (unit, query row): thread (g, d) adds the pieces of the g-th quarter up in order, then the quarters are
-// added in order.  (Bound by the latency of the loads: with all pieces in one thread's loop, eight in flight, the
-// kernel took 13.9 us for 8 units of 64 pieces and 128 rows, and takes 8.2 with the quarters.)
+// o^{(q)} from the pieces' partials and the sums of their weights, as a bf16 pair hi + lo, and its squared norm; and, where
+// the pieces had references of their own (stat_part: reference and sum of the terms), the row's normaliser
+// M + log2(Z * R) from them.  One workgroup per (unit, query row): the pieces' factors 2^(reference - M) first, a
+// thread per piece, while the partials travel; then thread (g, d) adds the pieces of the g-th quarter up in order and the
+// quarters are added in order.  (Bound by the latency of the loads: with all pieces in one thread's loop, eight in flight,
+// the kernel took 13.9 us for 8 units of 64 pieces and 128 rows, and takes 8.2 with the quarters.)
 constexpr int kReduceParts = 4;
 template <int D, typename Tab>
 __global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const Tab tab, const Shape sh,
                                                           const float* __restrict__ o_part,
                                                           const float* __restrict__ p_part,
+                                                          const float2* __restrict__ stat_part,
                                                           uint16_t* __restrict__ o_hi, uint16_t* __restrict__ o_lo,
                                                           float* __restrict__ oo, const int split) {
+  constexpr int NT = D * kReduceParts, NW = NT / kWave;
+  constexpr int MAXP = kMaxChunks << kMaxPqSplit, PPT = MAXP / NT;      // most pieces of a unit, per thread
+  constexpr int UN = 16;                    // partials in flight per thread
   __shared__ float sm_ss[D / kWave];
-  __shared__ float sm_s[kReduceParts][D], sm_w[kReduceParts];
+  __shared__ float sm_s[kReduceParts][D];
+  __shared__ float sm_f[MAXP];              // the pieces' factors
+  __shared__ float sm_m[NW], sm_w[NW], sm_z[NW];
   const int R = sh.R;
-  const Unit un = tab.unit(blockIdx.x / R);
+  const int ui = blockIdx.x / R;
+  const Unit un = tab.unit(ui);
   const int q = blockIdx.x % R;
-  const int d = threadIdx.x % D, g = threadIdx.x / D;
+  const int tid = threadIdx.x, d = tid % D, g = tid / D;
   const int base = un.chunk_base << split, n = un.n_chunks << split;
+  if (q == 0 && sh.sel_clear != nullptr && ui < kInlineUnits) {          // the exchange area of the selection that follows
+    uint4* zero = reinterpret_cast<uint4*>(sh.sel_clear + (size_t)ui * kSelSharedInts);
+    for (int i = tid; i < kSelSharedInts / 4; i += NT) zero[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   const int per = (n + kReduceParts - 1) / kReduceParts;
-  float s = 0.f, w = 0.f;
-#pragma unroll 16                           // (the loads of sixteen pieces in flight; the sums stay in order)
-  for (int c = g * per; c < min(n, g * per + per); ++c) {
-    s += o_part[((size_t)(base + c) * R + q) * D + d];
-    w += p_part[(size_t)(base + c) * R + q];
+  const int c0 = g * per, c1 = min(n, c0 + per);
+  float v[UN];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) v[u] = c + u < c1 ? o_part[((size_t)(base + c + u) * R + q) * D + d] : 0.f;
+  };
+  load(c0);
+  float2 st[PPT];
+  float pw[PPT];
+  float M = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < PPT; ++i) {
+    const int c = tid + i * NT;
+    st[i] = make_float2(-INFINITY, 0.f);
+    pw[i] = 0.f;
+    if (c < n) {
+      pw[i] = p_part[(size_t)(base + c) * R + q];
+      if (stat_part != nullptr) st[i] = stat_part[(size_t)(base + c) * R + q];
+    }
+    M = fmaxf(M, st[i].x);
+  }
+  if (stat_part != nullptr) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m, kWave));
+    if (tid % kWave == 0) sm_m[tid / kWave] = M;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NW; ++i) M = fmaxf(M, sm_m[i]);
+  }
+  float w = 0.f, z = 0.f;
+#pragma unroll
+  for (int i = 0; i < PPT; ++i) {
+    const float f = stat_part == nullptr ? 1.f : st[i].x == -INFINITY ? 0.f : ex2(st[i].x - M);
+    sm_f[tid + i * NT] = f;
+    w = fmaf(pw[i], f, w);
+    z = fmaf(st[i].y, f, z);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    w += __shfl_xor(w, m, kWave);
+    z += __shfl_xor(z, m, kWave);
+  }
+  if (tid % kWave == 0) {
+    sm_w[tid / kWave] = w;
+    sm_z[tid / kWave] = z;
+  }
+  __syncthreads();
+  float s = 0.f;
+  for (int c = c0; c < c1; c += UN) {
+    if (c != c0) load(c);
+#pragma unroll
+    for (int u = 0; u < UN; ++u) s = fmaf(v[u], sm_f[min(c + u, MAXP - 1)], s);
   }
   sm_s[g][d] = s;
-  if (d == 0) sm_w[g] = w;
   __syncthreads();
   if (g == 0) {                             // (whole wavefronts)
     s = sm_s[0][d];
     w = sm_w[0];
+    z = sm_z[0];
 #pragma unroll
-    for (int i = 1; i < kReduceParts; ++i) {
-      s += sm_s[i][d];
+    for (int i = 1; i < kReduceParts; ++i) s += sm_s[i][d];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) {
       w += sm_w[i];
+      z += sm_z[i];
     }
+    if (tid == 0 && stat_part != nullptr) sh.c_row_out[(size_t)un.index * R + q] = plus_log2(M, z * (float)R);
     const float m2o = -2.f * (s / w);                      // stored with the factor of ||v - o||^2 = ||v||^2 - 2 v.o + ||o||^2
     const uint32_t hi = f32_to_bf16(m2o);
     const uint32_t lo = f32_to_bf16(m2o - bf16_lo(hi));
@@ -401,275 +485,37 @@ __global__ __launch_bounds__(D * kReduceParts) void pq_out_reduce_kernel(const T
 }
 
 // ------------------------------------------------------------------------------------------------
-// A_t and C_t of every token of the chunk.
-//
-// Both products are taken with the query rows as the accumulator ROWS: S'[q, t] = Q K^T, X'[q, t] = (-2 O) V^T.
-// A lane then holds ONE token (column t = lane % 32) and 16 query rows, so the sums over q are plain
-// register additions (plus one exchange between the wavefront's halves), and token t + 1 is the next lane
-// (one DPP wavefront shift).  Per (t, q): one exp2, two square roots, eleven other instructions.
-template <int D, bool COUNTS, typename Tab>
-__global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
-    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-    const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
-    const uint16_t* __restrict__ o_hi,
-    const uint16_t* __restrict__ o_lo, const float* __restrict__ oo, float* __restrict__ a_tok,
-    float* __restrict__ c_edge, const int split) {
-  typedef Tile<D> TL;
-  constexpr int KS = D / 16;
-  constexpr int STRIDE = kTile - 1;         // output rows per tile: the last row only serves as "next token"
-  constexpr int PPT = TL::LPR / 8;          // pieces per thread when 8 threads share a row
-  __shared__ __attribute__((aligned(16))) unsigned char sm_k[2][TL::BYTES];
-  __shared__ __attribute__((aligned(16))) unsigned char sm_v[2][TL::BYTES];
-  __shared__ float sm_vv[2][kTile + 1];                              // ||v_r||^2 (one spare entry: the last row's "next")
-  __shared__ float sm_vd[2][kTile];                                  // v_r . v_{r+1}
-  __shared__ float2 sm_out[2][kWaves][kTile];                        // (sum_q A, sum_q C) of every wavefront
-  __shared__ float sm_al[2][kWaves][kTile];                          // sum_q alpha / R: the wavefront's share of alpha_bar
-  __shared__ __attribute__((aligned(16))) float sm_negc[kPassRows];  // per query row of the pass: -c[q]
-  __shared__ __attribute__((aligned(16))) int sm_lim[kPassRows];     // causal window: last row attended to
-  __shared__ float sm_cc[2][kTile + 1], sm_ic[2][kTile + 1];         // COUNTS: c and 1 / c of the tile's rows
-
-  const int ui = find_unit(tab, (int)blockIdx.x >> split);
-  const Unit un = tab.unit(ui);
-  int t0, t1;
-  piece_range(un, blockIdx.x, split, t0, t1);
-  if (t0 >= t1) return;                     // nothing left of the chunk for this piece
-  const int ntiles = (t1 - t0 + STRIDE - 1) / STRIDE;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int col = lane % 32, half = lane / 32;
-  const int R = sh.R;
-  const float Rf = (float)R;
-  const float sl2 = sh.scale_log2;
-  const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
-  const unsigned char* Vg = reinterpret_cast<const unsigned char*>(V + (size_t)un.in_row * D);
-  const uint16_t* Qu = Q + (size_t)un.index * R * D;
-  const uint16_t* Oh = o_hi + (size_t)un.index * R * D;
-  const uint16_t* Ol = o_lo + (size_t)un.index * R * D;
-  float* At = a_tok + un.in_row;
-  float* Ce = c_edge + un.in_row;
-  float* Al = sh.alpha_out != nullptr ? sh.alpha_out + un.in_row : nullptr;
-  const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  // Tile j puts out tokens t0 + 31 j .. + 30 and reads one row more.  Near the unit's end it is moved back
-  // to hold 32 existing rows; the `shift` leading rows then belong to earlier tiles.
-  auto tile_first = [&](int j) { return t0 + j * STRIDE; };
-  auto tile_base = [&](int j) { return min(tile_first(j), un.len - kTile); };
-
-  for (int qp = 0; qp < R; qp += kPassRows) {
-    const int qrow = qp + 32 * wave + col;
-    const bool ok = qrow < R;
-    bf16x8 bq[KS], boh[KS], bol[KS];        // this wavefront's 32 query rows: Q, and -2 o as hi + lo
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      bq[kk] = row_operand<D>(Qu, qrow, ok, kk, half);
-      boh[kk] = row_operand<D>(Oh, qrow, ok, kk, half);
-      bol[kk] = row_operand<D>(Ol, qrow, ok, kk, half);
-    }
-    if (tid < kPassRows) {                  // (read after the first tile's barriers)
-      const int q = qp + tid;
-      sm_negc[tid] = (q < R) ? -c_row[(size_t)un.index * R + q] : -INFINITY;   // exp2(-inf) = 0: no such row
-      sm_lim[tid] = last_seen_row(sh.causal, un.len, q);
-    }
-    // ||o^{(q)}||^2 of this lane's 16 accumulator rows: the value the X' accumulator starts from
-    f32x16 oo_init;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int q = qp + 32 * wave + 8 * (v / 4) + 4 * half + (v % 4);
-      oo_init[v] = (q < R) ? oo[(size_t)un.index * R + q] : 0.f;
-    }
-
-    // sums of the tile before -> memory (threads 0..31, one row each; the wavefronts in a fixed order)
-    auto flush = [&](int j) {
-      if (tid < kTile) {
-        const int buf = j & 1;
-        const int base = tile_base(j), shift = tile_first(j) - base;
-        const int r = tid, t = base + r;
-        if (r >= shift && r <= shift + STRIDE - 1 && t < t1) {
-          float a = 0.f, c = 0.f, al = 0.f;
-          uint32_t mark = 0;                               // sign bit: some wavefront, or an earlier pass, marked the token
-#pragma unroll
-          for (int w = 0; w < kWaves; ++w) {
-            const float2 o = sm_out[buf][w][r];
-            mark |= __float_as_uint(o.x);
-            a += fabsf(o.x);
-            c += o.y;
-            al += sm_al[buf][w][r];
-          }
-          if (r == kTile - 1) c = 0.f;                     // only the unit's last token: it has no next one
-          if (COUNTS) al *= sm_cc[buf][r];
-          if (qp > 0) {                                    // later passes add their query rows
-            const float before = At[t];
-            mark |= __float_as_uint(before);
-            a += fabsf(before);
-            c += Ce[t];
-            if (Al != nullptr) al += Al[t];
-          }
-          At[t] = __uint_as_float(__float_as_uint(a) | (mark & 0x80000000u));
-          Ce[t] = c;
-          if (Al != nullptr) Al[t] = al;
-        }
-      }
-    };
-
-    typename TL::Regs rk = TL::load(Kg + (size_t)tile_base(0) * TL::ROWB, tid);
-    typename TL::Regs rv = TL::load(Vg + (size_t)tile_base(0) * TL::ROWB, tid);
-    for (int j = 0; j < ntiles; ++j) {
-      const int buf = j & 1;
-      TL::store(sm_k[buf], rk, tid);
-      TL::store(sm_v[buf], rv, tid);
-      if (COUNTS && tid <= kTile) {           // (the spare entry stands for the last row's "next", which is never used)
-        const float c = tid < kTile ? (float)cnt[tile_base(j) + tid] : 1.f;
-        sm_cc[buf][tid] = c;
-        sm_ic[buf][tid] = __builtin_amdgcn_rcpf(c);
-      }
-      __syncthreads();
-      {                                     // the next tile flies during this one (the last one is fetched twice)
-        const int jn = min(j + 1, ntiles - 1);
-        rk = TL::load(Kg + (size_t)tile_base(jn) * TL::ROWB, tid);
-        rv = TL::load(Vg + (size_t)tile_base(jn) * TL::ROWB, tid);
-        asm volatile("" ::: "memory");        // issue them here: sunk below the products they would be waited for at once
-      }
-      if (j > 0) flush(j - 1);
-      // squared norms of the rows and of the sums of adjacent rows: eight threads per row
-      {
-        const int r = tid / 8, part = tid % 8;
-        const int rn = min(r + 1, kTile - 1);
-        float s_rr = 0.f, s_rn = 0.f;
-#pragma unroll
-        for (int x = 0; x < PPT; ++x) {           // (two bf16 products per instruction, added in fp32)
-          const uint4 a = TL::piece_at(sm_v[buf], r, part * PPT + x);
-          const uint4 b = TL::piece_at(sm_v[buf], rn, part * PPT + x);
-          s_rr = dot2(a.x, a.x, s_rr); s_rn = dot2(a.x, b.x, s_rn);
-          s_rr = dot2(a.y, a.y, s_rr); s_rn = dot2(a.y, b.y, s_rn);
-          s_rr = dot2(a.z, a.z, s_rr); s_rn = dot2(a.z, b.z, s_rn);
-          s_rr = dot2(a.w, a.w, s_rr); s_rn = dot2(a.w, b.w, s_rn);
-        }
-        s_rr = row_group_sum<8>(s_rr);
-        s_rn = row_group_sum<8>(s_rn);
-        if (part == 0) {
-          sm_vv[buf][r] = s_rr;
-          sm_vd[buf][r] = s_rn;
-          if (r == kTile - 1) sm_vv[buf][kTile] = 0.f;       // read by the last column, whose edge is never used
-        }
-      }
-      // S' = Q K^T and X' = (-2 O) V^T for this wavefront's 32 query rows
-      f32x16 accS = zero, accX = COUNTS ? zero : oo_init;     // X'' = ||o||^2 - 2 v.o (COUNTS: -2 V.o, scaled below)
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-        accS = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[kk], TL::operand(sm_k[buf], col, kk, half), accS, 0, 0, 0);
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const bf16x8 bv = TL::operand(sm_v[buf], col, kk, half);
-        accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(boh[kk], bv, accX, 0, 0, 0);
-        accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bol[kk], bv, accX, 0, 0, 0);
-      }
-      __syncthreads();                      // sm_vv / sm_vp of this tile are complete
-      // accumulator element v: query row 32 wave + 8 (v / 4) + 4 half + v % 4 of the pass, token column `col`
-      float vv = sm_vv[buf][col];
-      float vp = fmaf(2.f, sm_vd[buf][col], vv + sm_vv[buf][col + 1]);         // ||v_t + v_{t+1}||^2
-      float cc = 1.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
-      if (COUNTS) {
-        cc = sm_cc[buf][col];
-        ic = sm_ic[buf][col];
-        const float icn = sm_ic[buf][col + 1];
-        const float vvn = sm_vv[buf][col + 1] * icn * icn;
-        vv = vv * ic * ic;
-        vp = fmaf(2.f * ic * icn, sm_vd[buf][col], vv + vvn);
-      }
-      const int t_abs = tile_base(j) + col;
-      float sumA = 0.f, sumC = 0.f, sumP = 0.f;
-      float leastA = INFINITY, leastC = INFINITY;   // smallest squared norms this lane forms in the tile (see below)
-      // TAIL: the tile reaches into the causal window's masked rows (a uniform condition)
-      auto rows = [&](auto tail_tag) {
-        constexpr bool TAIL = decltype(tail_tag)::value;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int q0 = 32 * wave + 8 * g + 4 * half;
-          const float4 nc4 = *reinterpret_cast<const float4*>(&sm_negc[q0]);
-          const float nc[4] = {nc4.x, nc4.y, nc4.z, nc4.w};
-          int lim[4] = {0, 0, 0, 0};
-          if (TAIL) {
-            const int4 l4 = *reinterpret_cast<const int4*>(&sm_lim[q0]);
-            lim[0] = l4.x; lim[1] = l4.y; lim[2] = l4.z; lim[3] = l4.w;
-          }
-          float d2s[4], p2s[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int v = 4 * g + i;
-            // alpha / R (COUNTS: first of one of the c tokens; log2 c in the exponent would round with c's size)
-            float a = ex2(fmaf(accS[v], sl2, nc[i]));
-            if (TAIL && t_abs > lim[i]) a = 0.f;
-            sumP += a;
-            if (COUNTS) a *= cc;
-            const float x = COUNTS ? fmaf(accX[v], ic, oo_init[v]) : accX[v]; // ||o||^2 - 2 v_t . o
-            // the same quantities of token t + 1: the next lane (the last column's are not used)
-            const float a_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x130, 0xF, 0xF, true));
-            const float x_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xF, 0xF, true));
-            const float d2 = vv + x;                                       // ||v_t - o||^2
-            const float p2 = fmaf(2.f, x + x_n, vp);                       // ||v_t + v_{t+1} - 2o||^2
-            // (a rounding-size negative value stands for zero: the square roots take the magnitude)
-            sumA = fmaf(a * fabsf(fmaf(-2.f * Rf, a, 1.f)), __builtin_amdgcn_sqrtf(fabsf(d2)), sumA);
-            sumC = fmaf(a * a_n, __builtin_amdgcn_sqrtf(fabsf(p2)), sumC);
-            d2s[i] = d2;
-            p2s[i] = p2;
-          }
-          leastA = min3(min3(leastA, d2s[0], d2s[1]), d2s[2], d2s[3]);
-          leastC = min3(min3(leastC, p2s[0], p2s[1]), p2s[2], p2s[3]);
-          __builtin_amdgcn_sched_barrier(0);  // four rows at a time: interleaving all sixteen runs out of registers
-        }
-      };
-      if (sh.causal > 0 && tile_base(j) + kTile > un.len - sh.causal + 1) rows(std::true_type{});
-      else rows(std::false_type{});
-      // Cancellation.  Where o^{(q)} comes close to v_t (a query row that puts nearly all its weight on one token) the
-      // expansion above loses what is left of ||v_t - o||^2 to the rounding of its terms of size ||v_t||^2.  A token
-      // one of whose squared norms falls below kCancel of its leading term is marked (the sign bit of its A_t, which
-      // is never negative) and formed again by pq_redo_kernel, from differences.  The test costs one three-way
-      // minimum per (t, q).
-      int redo = (leastA < kCancel * vv || leastC < kCancel * vp) ? 1 : 0;
-      redo |= __shfl_xor(redo, 32, kWave);
-      sumA += __shfl_xor(sumA, 32, kWave);    // the other half's 16 query rows
-      sumC += __shfl_xor(sumC, 32, kWave);
-      sumP += __shfl_xor(sumP, 32, kWave);
-      if (half == 0) {
-        sm_out[buf][wave][col] = make_float2(redo ? -sumA : sumA, sumC * Rf);                // (sumA >= 0; -0 counts)
-        sm_al[buf][wave][col] = sumP;
-      }
-    }
-    __syncthreads();
-    flush(ntiles - 1);
-    __syncthreads();                        // the next pass reuses the buffers
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Tokens that pq_norms_kernel marked (sign bit of A_t): A_t and C_t over all query rows once more, every squared norm
-// as a sum of squared differences: ||v_t - o||^2 from v_t and the stored pair -2 o = hi + lo, likewise
-// ||v_t + v_{t+1} - 2 o||^2.  One workgroup per span of kRedoSpan tokens; the span's marked tokens are listed and
+// Tokens of [t0, t1) (at most kRedoSpan) that pq_norms_kernel has marked (sign bit of A_t): A_t and C_t over all query rows
+// once more, every squared norm as a sum of squared differences: ||v_t - o||^2 from v_t and the stored pair -2 o = hi + lo,
+// likewise ||v_t + v_{t+1} - 2 o||^2.  The marked tokens are listed and
 // taken in turn: D / 8 adjacent lanes share a query row, eight dimensions each (one round of coalesced loads per row), the
 // rows' terms are added per lane group in row order and the groups in a fixed butterfly order.  Every marked token leaves
-// with a non-negative A_t, so no mark outlives this kernel.
-template <int D, bool COUNTS, typename Tab>
-__global__ __launch_bounds__(kThreads) void pq_redo_kernel(
-    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-    const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
-    const uint16_t* __restrict__ o_hi, const uint16_t* __restrict__ o_lo, float* __restrict__ a_tok,
-    float* __restrict__ c_edge) {
+// with a non-negative A_t, so no mark outlives pq_norms_kernel.
+template <int D>
+struct RedoSmem {
+  int list[kRedoSpan];
+  int n;
+  float row[4][D];                          // k_t, k_{t+1}, v_t, v_{t+1} (the Values divided by their cardinalities)
+  float sum[2][kWaves];
+};
+template <int D, bool COUNTS>
+__device__ __forceinline__ void redo_marked(
+    const Shape& sh, const Unit& un, const int t0, const int t1, const uint16_t* __restrict__ Q,
+    const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in,
+    const float* __restrict__ c_row, const uint16_t* __restrict__ o_hi, const uint16_t* __restrict__ o_lo, float* a_tok,
+    float* c_edge, RedoSmem<D>& sm) {
   constexpr int LPR = D / 8;                // lanes per query row
   constexpr int RPP = kThreads / LPR;       // query rows per pass of the workgroup
-  __shared__ int sm_list[kRedoSpan];
-  __shared__ int sm_n;
-  __shared__ float sm_row[4][D];            // k_t, k_{t+1}, v_t, v_{t+1} (the Values divided by their cardinalities)
-  __shared__ float sm_sum[2][kWaves];
+  int (&sm_list)[kRedoSpan] = sm.list;
+  int& sm_n = sm.n;
+  float (&sm_row)[4][D] = sm.row;
+  float (&sm_sum)[2][kWaves] = sm.sum;
   static_assert(kRedoSpan / kThreads <= 32, "one bit per token and thread");
 
-  const Unit un = tab.unit(blockIdx.x);
-  const int t0 = blockIdx.y * kRedoSpan;
-  const int t1 = min(un.len, t0 + kRedoSpan);
-  if (t0 >= t1) return;                     // (the grid is sized for the launch's longest unit)
   const int tid = threadIdx.x, part = tid % LPR;
   float* At = a_tok + un.in_row;
   float* Ce = c_edge + un.in_row;
-  // nearly always no token of the span is marked: one look at all of them (bit k: token t0 + tid + 256 k)
+  // the span's marks: bit k is token t0 + tid + 256 k
   uint32_t marks = 0;
 #pragma unroll
   for (int k = 0; k < kRedoSpan / kThreads; ++k) {
@@ -800,41 +646,292 @@ __global__ __launch_bounds__(kThreads) void pq_redo_kernel(
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// A_t and C_t of every token of the chunk.
+//
+// Both products are taken with the query rows as the accumulator ROWS: S'[q, t] = Q K^T, X'[q, t] = (-2 O) V^T.
+// A lane then holds ONE token (column t = lane % 32) and 16 query rows, so the sums over q are plain
+// register additions (plus one exchange between the wavefront's halves), and token t + 1 is the next lane
+// (one DPP wavefront shift).  Per (t, q): one exp2, two square roots, eleven other instructions.
+template <int D, bool COUNTS, typename Tab>
+__global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
+    const uint16_t* __restrict__ o_hi,
+    const uint16_t* __restrict__ o_lo, const float* __restrict__ oo, float* a_tok, float* c_edge, const int split) {
+  typedef Tile<D> TL;
+  constexpr int KS = D / 16;
+  constexpr int STRIDE = kTile - 1;         // output rows per tile: the last row only serves as "next token"
+  constexpr int PPT = TL::LPR / 8;          // pieces per thread when 8 threads share a row
+  __shared__ __attribute__((aligned(16))) unsigned char sm_k[2][TL::BYTES];
+  __shared__ __attribute__((aligned(16))) unsigned char sm_v[2][TL::BYTES];
+  __shared__ int sm_marked;                                          // a token of the piece has been marked
+  __shared__ float sm_vv[2][kTile + 1];                              // ||v_r||^2 (one spare entry: the last row's "next")
+  __shared__ float sm_vd[2][kTile];                                  // v_r . v_{r+1}
+  __shared__ float2 sm_out[2][kWaves][kTile];                        // (sum_q A, sum_q C) of every wavefront
+  __shared__ float sm_al[2][kWaves][kTile];                          // sum_q alpha / R: the wavefront's share of alpha_bar
+  __shared__ __attribute__((aligned(16))) float sm_negc[kPassRows];  // per query row of the pass: -c[q]
+  __shared__ __attribute__((aligned(16))) int sm_lim[kPassRows];     // causal window: last row attended to
+  __shared__ float sm_cc[2][kTile + 1], sm_ic[2][kTile + 1];         // COUNTS: c and 1 / c of the tile's rows
+
+  const int ui = find_unit(tab, (int)blockIdx.x >> split);
+  const Unit un = tab.unit(ui);
+  int t0, t1;
+  piece_range(un, blockIdx.x, split, t0, t1);
+  if (t0 >= t1) return;                     // nothing left of the chunk for this piece
+  const int ntiles = (t1 - t0 + STRIDE - 1) / STRIDE;
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  if (tid == 0) sm_marked = 0;              // (the first tile's barriers come before the first mark)
+  const int col = lane % 32, half = lane / 32;
+  const int R = sh.R;
+  const float Rf = (float)R;
+  const float sl2 = sh.scale_log2;
+  const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
+  const unsigned char* Vg = reinterpret_cast<const unsigned char*>(V + (size_t)un.in_row * D);
+  const uint16_t* Qu = Q + (size_t)un.index * R * D;
+  const uint16_t* Oh = o_hi + (size_t)un.index * R * D;
+  const uint16_t* Ol = o_lo + (size_t)un.index * R * D;
+  float* At = a_tok + un.in_row;
+  float* Ce = c_edge + un.in_row;
+  float* Al = sh.alpha_out != nullptr ? sh.alpha_out + un.in_row : nullptr;
+  const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // Tile j puts out tokens t0 + 31 j .. + 30 and reads one row more.  Near the unit's end it is moved back
+  // to hold 32 existing rows; the `shift` leading rows then belong to earlier tiles.
+  auto tile_first = [&](int j) { return t0 + j * STRIDE; };
+  auto tile_base = [&](int j) { return min(tile_first(j), un.len - kTile); };
+
+  for (int qp = 0; qp < R; qp += kPassRows) {
+    const int qrow = qp + 32 * wave + col;
+    const bool ok = qrow < R;
+    bf16x8 bq[KS], boh[KS], bol[KS];        // this wavefront's 32 query rows: Q, and -2 o as hi + lo
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      bq[kk] = row_operand<D>(Qu, qrow, ok, kk, half);
+      boh[kk] = row_operand<D>(Oh, qrow, ok, kk, half);
+      bol[kk] = row_operand<D>(Ol, qrow, ok, kk, half);
+    }
+    if (tid < kPassRows) {                  // (read after the first tile's barriers)
+      const int q = qp + tid;
+      sm_negc[tid] = (q < R) ? -c_row[(size_t)un.index * R + q] : -INFINITY;   // exp2(-inf) = 0: no such row
+      sm_lim[tid] = last_seen_row(sh.causal, un.len, q);
+    }
+    // ||o^{(q)}||^2 of this lane's 16 accumulator rows: the value the X' accumulator starts from
+    f32x16 oo_init;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int q = qp + 32 * wave + 8 * (v / 4) + 4 * half + (v % 4);
+      oo_init[v] = (q < R) ? oo[(size_t)un.index * R + q] : 0.f;
+    }
+
+    // sums of the tile before -> memory (threads 0..31, one row each; the wavefronts in a fixed order)
+    auto flush = [&](int j) {
+      if (tid < kTile) {
+        const int buf = j & 1;
+        const int base = tile_base(j), shift = tile_first(j) - base;
+        const int r = tid, t = base + r;
+        if (r >= shift && r <= shift + STRIDE - 1 && t < t1) {
+          float a = 0.f, c = 0.f, al = 0.f;
+          uint32_t mark = 0;                               // sign bit: some wavefront, or an earlier pass, marked the token
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) {
+            const float2 o = sm_out[buf][w][r];
+            mark |= __float_as_uint(o.x);
+            a += fabsf(o.x);
+            c += o.y;
+            al += sm_al[buf][w][r];
+          }
+          if (r == kTile - 1) c = 0.f;                     // only the unit's last token: it has no next one
+          if (COUNTS) al *= sm_cc[buf][r];
+          if (qp > 0) {                                    // later passes add their query rows
+            const float before = At[t];
+            mark |= __float_as_uint(before);
+            a += fabsf(before);
+            c += Ce[t];
+            if (Al != nullptr) al += Al[t];
+          }
+          if (mark & 0x80000000u) sm_marked = 1;
+          At[t] = __uint_as_float(__float_as_uint(a) | (mark & 0x80000000u));
+          Ce[t] = c;
+          if (Al != nullptr) Al[t] = al;
+        }
+      }
+    };
+
+    typename TL::Regs rk = TL::load(Kg + (size_t)tile_base(0) * TL::ROWB, tid);
+    typename TL::Regs rv = TL::load(Vg + (size_t)tile_base(0) * TL::ROWB, tid);
+    for (int j = 0; j < ntiles; ++j) {
+      const int buf = j & 1;
+      TL::store(sm_k[buf], rk, tid);
+      TL::store(sm_v[buf], rv, tid);
+      if (COUNTS && tid <= kTile) {           // (the spare entry stands for the last row's "next", which is never used)
+        const float c = tid < kTile ? (float)cnt[tile_base(j) + tid] : 1.f;
+        sm_cc[buf][tid] = c;
+        sm_ic[buf][tid] = __builtin_amdgcn_rcpf(c);
+      }
+      __syncthreads();
+      {                                     // the next tile flies during this one (the last one is fetched twice)
+        const int jn = min(j + 1, ntiles - 1);
+        rk = TL::load(Kg + (size_t)tile_base(jn) * TL::ROWB, tid);
+        rv = TL::load(Vg + (size_t)tile_base(jn) * TL::ROWB, tid);
+        asm volatile("" ::: "memory");        // issue them here: sunk below the products they would be waited for at once
+      }
+      if (j > 0) flush(j - 1);
+      // squared norms of the rows and of the sums of adjacent rows: eight threads per row
+      {
+        const int r = tid / 8, part = tid % 8;
+        const int rn = min(r + 1, kTile - 1);
+        float s_rr = 0.f, s_rn = 0.f;
+#pragma unroll
+        for (int x = 0; x < PPT; ++x) {           // (two bf16 products per instruction, added in fp32)
+          const uint4 a = TL::piece_at(sm_v[buf], r, part * PPT + x);
+          const uint4 b = TL::piece_at(sm_v[buf], rn, part * PPT + x);
+          s_rr = dot2(a.x, a.x, s_rr); s_rn = dot2(a.x, b.x, s_rn);
+          s_rr = dot2(a.y, a.y, s_rr); s_rn = dot2(a.y, b.y, s_rn);
+          s_rr = dot2(a.z, a.z, s_rr); s_rn = dot2(a.z, b.z, s_rn);
+          s_rr = dot2(a.w, a.w, s_rr); s_rn = dot2(a.w, b.w, s_rn);
+        }
+        s_rr = row_group_sum<8>(s_rr);
+        s_rn = row_group_sum<8>(s_rn);
+        if (part == 0) {
+          sm_vv[buf][r] = s_rr;
+          sm_vd[buf][r] = s_rn;
+          if (r == kTile - 1) sm_vv[buf][kTile] = 0.f;       // read by the last column, whose edge is never used
+        }
+      }
+      // S' = Q K^T and X' = (-2 O) V^T for this wavefront's 32 query rows
+      f32x16 accS = zero, accX = COUNTS ? zero : oo_init;     // X'' = ||o||^2 - 2 v.o (COUNTS: -2 V.o, scaled below)
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        accS = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[kk], TL::operand(sm_k[buf], col, kk, half), accS, 0, 0, 0);
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {
+        const bf16x8 bv = TL::operand(sm_v[buf], col, kk, half);
+        accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(boh[kk], bv, accX, 0, 0, 0);
+        accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bol[kk], bv, accX, 0, 0, 0);
+      }
+      __syncthreads();                      // sm_vv / sm_vp of this tile are complete
+      // accumulator element v: query row 32 wave + 8 (v / 4) + 4 half + v % 4 of the pass, token column `col`
+      float vv = sm_vv[buf][col];
+      float vp = fmaf(2.f, sm_vd[buf][col], vv + sm_vv[buf][col + 1]);         // ||v_t + v_{t+1}||^2
+      float cc = 1.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
+      if (COUNTS) {
+        cc = sm_cc[buf][col];
+        ic = sm_ic[buf][col];
+        const float icn = sm_ic[buf][col + 1];
+        const float vvn = sm_vv[buf][col + 1] * icn * icn;
+        vv = vv * ic * ic;
+        vp = fmaf(2.f * ic * icn, sm_vd[buf][col], vv + vvn);
+      }
+      const int t_abs = tile_base(j) + col;
+      float sumA = 0.f, sumC = 0.f, sumP = 0.f;
+      float leastA = INFINITY, leastC = INFINITY;   // smallest squared norms this lane forms in the tile (see below)
+      // TAIL: the tile reaches into the causal window's masked rows (a uniform condition)
+      auto rows = [&](auto tail_tag) {
+        constexpr bool TAIL = decltype(tail_tag)::value;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int q0 = 32 * wave + 8 * g + 4 * half;
+          const float4 nc4 = *reinterpret_cast<const float4*>(&sm_negc[q0]);
+          const float nc[4] = {nc4.x, nc4.y, nc4.z, nc4.w};
+          int lim[4] = {0, 0, 0, 0};
+          if (TAIL) {
+            const int4 l4 = *reinterpret_cast<const int4*>(&sm_lim[q0]);
+            lim[0] = l4.x; lim[1] = l4.y; lim[2] = l4.z; lim[3] = l4.w;
+          }
+          float d2s[4], p2s[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int v = 4 * g + i;
+            // alpha / R (COUNTS: first of one of the c tokens; log2 c in the exponent would round with c's size)
+            float a = ex2(fmaf(accS[v], sl2, nc[i]));
+            if (TAIL && t_abs > lim[i]) a = 0.f;
+            sumP += a;
+            if (COUNTS) a *= cc;
+            const float x = COUNTS ? fmaf(accX[v], ic, oo_init[v]) : accX[v]; // ||o||^2 - 2 v_t . o
+            // the same quantities of token t + 1: the next lane (the last column's are not used)
+            const float a_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), 0x130, 0xF, 0xF, true));
+            const float x_n = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xF, 0xF, true));
+            const float d2 = vv + x;                                       // ||v_t - o||^2
+            const float p2 = fmaf(2.f, x + x_n, vp);                       // ||v_t + v_{t+1} - 2o||^2
+            // (a rounding-size negative value stands for zero: the square roots take the magnitude)
+            sumA = fmaf(a * fabsf(fmaf(-2.f * Rf, a, 1.f)), __builtin_amdgcn_sqrtf(fabsf(d2)), sumA);
+            sumC = fmaf(a * a_n, __builtin_amdgcn_sqrtf(fabsf(p2)), sumC);
+            d2s[i] = d2;
+            p2s[i] = p2;
+          }
+          leastA = min3(min3(leastA, d2s[0], d2s[1]), d2s[2], d2s[3]);
+          leastC = min3(min3(leastC, p2s[0], p2s[1]), p2s[2], p2s[3]);
+          __builtin_amdgcn_sched_barrier(0);  // four rows at a time: interleaving all sixteen runs out of registers
+        }
+      };
+      if (sh.causal > 0 && tile_base(j) + kTile > un.len - sh.causal + 1) rows(std::true_type{});
+      else rows(std::false_type{});
+      // Cancellation.  Where o^{(q)} comes close to v_t (a query row that puts nearly all its weight on one token) the
+      // expansion above loses what is left of ||v_t - o||^2 to the rounding of its terms of size ||v_t||^2.  A token
+      // one of whose squared norms falls below kCancel of its leading term is marked (the sign bit of its A_t, which
+      // is never negative) and formed again by redo_marked, from differences.  The test costs one three-way
+      // minimum per (t, q).
+      int redo = (leastA < kCancel * vv || leastC < kCancel * vp) ? 1 : 0;
+      redo |= __shfl_xor(redo, 32, kWave);
+      sumA += __shfl_xor(sumA, 32, kWave);    // the other half's 16 query rows
+      sumC += __shfl_xor(sumC, 32, kWave);
+      sumP += __shfl_xor(sumP, 32, kWave);
+      if (half == 0) {
+        sm_out[buf][wave][col] = make_float2(redo ? -sumA : sumA, sumC * Rf);                // (sumA >= 0; -0 counts)
+        sm_al[buf][wave][col] = sumP;
+      }
+    }
+    __syncthreads();
+    flush(ntiles - 1);
+    __syncthreads();                        // the next pass reuses the buffers
+  }
+  // The marked tokens, nearly always none (one in 30000 on the generated inputs), by the workgroup that has marked them:
+  // a launch of its own for them was 12 us behind the 55 of this kernel (8 units of 32768 tokens, 128 rows).
+  if (sm_marked) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this workgroup's A_t and C_t are out
+    __syncthreads();
+    static_assert(sizeof(RedoSmem<D>) <= sizeof(sm_k), "the K tiles' buffers are free now");
+    RedoSmem<D>& sm = *reinterpret_cast<RedoSmem<D>*>(&sm_k[0][0]);
+    for (int t = t0; t < t1; t += kRedoSpan) {
+      redo_marked<D, COUNTS>(sh, un, t, min(t1, t + kRedoSpan), Q, K, V, counts_in, c_row, o_hi, o_lo, a_tok, c_edge, sm);
+      __syncthreads();
+    }
+  }
+}
+
 template <int D, bool COUNTS>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi, uint16_t* o_lo,
                     float* oo, float* a_tok, float* c_edge, hipStream_t stream) {
   long long rows = 0;
-  int longest = 1, longest_chunk = 1;
+  int longest_chunk = 1;
   for (int u = 0; u < tab.n_units; ++u) {
     const Unit& un = tab.unit(u);
     rows += un.len;
-    longest = std::max(longest, un.len);
     longest_chunk = std::max(longest_chunk, std::min(un.len, un.chunk_len));
   }
   const int split = pq_split(tab.total_chunks, rows, longest_chunk, sh.R, D);
   const dim3 grid(tab.total_chunks << split), block(kThreads);
-  float* p_part = o_part + (size_t)grid.x * sh.R * D;       // the weights' sums lie behind the launch's partials
+  float2* stat_part = reinterpret_cast<float2*>(o_part + (size_t)grid.x * sh.R * D);   // behind the launch's partials
+  float* p_part = reinterpret_cast<float*>(stat_part + (size_t)grid.x * sh.R);
+  const bool own_rows = sh.c_row_out != nullptr;            // the normalisers come from here
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_part, p_part, split);
+                       (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
+                       stat_part, split);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((pq_out_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D * kReduceParts), 0, stream, t, sh,
-                       o_part, p_part, o_hi, o_lo, oo, split);
+                       o_part, p_part, own_rows ? stat_part : nullptr, o_hi, o_lo, oo, split);
   });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   launch_with_table(tab, [&](const auto& t) {
     hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
                        (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
-  });
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const dim3 spans(tab.n_units, (longest + kRedoSpan - 1) / kRedoSpan);
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((pq_redo_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), spans, block, 0, stream, t, sh, (const uint16_t*)Q,
-                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, a_tok, c_edge);
   });
   return hipGetLastError();
 }
