@@ -35,10 +35,7 @@ namespace {
 #endif
 constexpr int kThreads = KVS_DEC_THREADS;
 constexpr int kQB = 4;                    // query rows per block
-#ifndef KVS_DEC_UNROLL
-#define KVS_DEC_UNROLL 2
-#endif
-constexpr int kUnroll = KVS_DEC_UNROLL;   // cache rows per lane group in flight
+constexpr int kFewRows = 2, kMoreRows = 4;   // cache rows per lane group in flight, see launch_t
 #ifndef KVS_DEC_CHUNK
 #define KVS_DEC_CHUNK 256
 #endif
@@ -71,7 +68,7 @@ __device__ __forceinline__ size_t part_index(int unit_index, int chunk, int R, i
   return (((size_t)unit_index * kMaxChunks + chunk) * R + row) * (size_t)(D + 2);
 }
 
-template <typename T, int D, typename Tab>
+template <typename T, int D, int kUnroll, typename Tab>
 __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
     const Tab tab, const Shape sh, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ counts, float* __restrict__ part) {
@@ -190,51 +187,67 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
   }
 }
 
-// out[unit, row, :] from the unit's chunk partials, in chunk order.  One workgroup of D threads per (unit, row).
-template <int D, typename Tab>
-__global__ __launch_bounds__(D) void decode_reduce_kernel(const Tab tab, const Shape sh,
+// out[unit, row, :] from the unit's chunk partials, in chunk order.  One workgroup per (unit, row), PARTS * D threads:
+// thread (g, d) adds up the g-th part of the chunks in order, eight at a time, and the parts are added in order.
+// Bound by latency: everything a thread needs is requested at once, so that the partials cost one round trip (a workgroup of
+// D threads that went over the chunks eight at a time, for the maximum and again for the sums, made eight of them: 5.7 us
+// for 8 units of 32 chunks, 3.0 now).  Four parts, or one where no unit has more than eight chunks (256 units of four:
+// 4.4 us, 5.1 with four parts).
+template <int D, int PARTS, typename Tab>
+__global__ __launch_bounds__(PARTS * D) void decode_reduce_kernel(const Tab tab, const Shape sh,
                                                           const float* __restrict__ part, float* __restrict__ out) {
+  constexpr int PER = PARTS == 1 ? 8 : kMaxChunks / PARTS;   // most chunks of a part
+  static_assert(kMaxChunks <= kWave && PER % 8 == 0, "a lane per chunk, eight chunks' sums at a time");
+  __shared__ float sm_num[PARTS][D];
   const int R = sh.R;
   const Unit un = tab.unit(blockIdx.x / R);
   const int row = blockIdx.x % R;
   const int nc = dec_chunks(un.len, sh.dec_chunk);
-  const int d = threadIdx.x;
-  // the maximum over the chunks first (all loads in flight at once), then the weighted sums in chunk order,
-  // eight chunks' loads in flight at a time: the partials come from memory and a loop that waits for every
-  // load costs a round trip per chunk
-  float M = -INFINITY;
-  {
-    float mv[kMaxChunks / 8];
-    for (int c0 = 0; c0 < nc; c0 += kMaxChunks / 8) {
+  const int tid = threadIdx.x, d = tid % D, g = __builtin_amdgcn_readfirstlane(tid / D), lane = tid % kWave;
+  // (of parts that have more than eight chunks, the rest in a second batch)
+  const int per = (nc + PARTS - 1) / PARTS;
+  const int c0 = g * per, c1 = min(nc, c0 + per);
+  const float* src = part + part_index(un.index, 0, R, row, D);
+  const uint32_t stride = (uint32_t)R * (D + 2);
+  float x[PER];
 #pragma unroll
-      for (int i = 0; i < kMaxChunks / 8; ++i) mv[i] = part[part_index(un.index, min(c0 + i, nc - 1), R, row, D) + D];
+  for (int i = 0; i < PER; ++i) x[i] = 0.f;
 #pragma unroll
-      for (int i = 0; i < kMaxChunks / 8; ++i) M = fmaxf(M, mv[i]);
+  for (int i0 = 0; i0 < PER; i0 += 8) {
+    if (c0 + i0 < c1) {
+#pragma unroll
+      for (int i = i0; i < i0 + 8; ++i) x[i] = src[min(c0 + i, nc - 1) * stride + d];
     }
   }
-  float num = 0.f, den = 0.f;
-  for (int c0 = 0; c0 < nc; c0 += 8) {
-    float x[8], m[8], l[8];
+  const float m = src[min(lane, nc - 1) * stride + D];
+  const float l = lane < nc ? src[min(lane, nc - 1) * stride + D + 1] : 0.f;
+  float M = lane < nc ? m : -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float* src = part + part_index(un.index, min(c0 + i, nc - 1), R, row, D);
-      x[i] = src[d];
-      m[i] = src[D];
-      l[i] = src[D + 1];
-    }
-    float n8 = 0.f, d8 = 0.f;
+  for (int k = 32; k >= 1; k >>= 1) M = fmaxf(M, __shfl_xor(M, k, kWave));
+  const uint64_t used = __ballot(l > 0.f);       // (a chunk without a term is left out, whatever its partial holds)
+  const float w = __builtin_amdgcn_exp2f(m - M);
+  float den = l > 0.f ? l * w : 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (c0 + i < nc && l[i] > 0.f) {
-        const float w = __builtin_amdgcn_exp2f(m[i] - M);
-        n8 = fmaf(x[i], w, n8);
-        d8 = fmaf(l[i], w, d8);
-      }
+  for (int k = 1; k < kWave; k <<= 1) den += __shfl_xor(den, k, kWave);
+  float num = 0.f;
+#pragma unroll
+  for (int i0 = 0; i0 < PER; i0 += 8) {
+    float n8 = 0.f;
+#pragma unroll
+    for (int i = i0; i < i0 + 8; ++i) {
+      const float wc = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), min(c0 + i, kWave - 1)));
+      n8 = c0 + i < c1 && ((used >> (c0 + i)) & 1) ? fmaf(x[i], wc, n8) : n8;
     }
-    num += n8;                              // (eight chunks' sum first: 64 chunks round eight times at the whole's size)
-    den += d8;
+    num += n8;
   }
-  out[((size_t)un.index * R + row) * D + d] = num / den;
+  sm_num[g][d] = num;
+  __syncthreads();
+  if (g == 0) {
+    num = sm_num[0][d];
+#pragma unroll
+    for (int i = 1; i < PARTS; ++i) num += sm_num[i][d];
+    out[((size_t)un.index * R + row) * D + d] = num / den;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -641,6 +654,19 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void decode_mfma_f32_kernel(
   }
 }
 
+// most: chunks of the unit that has most of them
+template <int D>
+hipError_t launch_reduce(const UnitTable& tab, const Shape& sh, int most, const float* part, float* out, hipStream_t stream) {
+  const dim3 grid(tab.n_units * sh.R);
+  launch_with_table(tab, [&](const auto& t) {
+    if (most <= 8)
+      hipLaunchKernelGGL((decode_reduce_kernel<D, 1, KVS_TABLE_TYPE(t)>), grid, dim3(D), 0, stream, t, sh, part, out);
+    else
+      hipLaunchKernelGGL((decode_reduce_kernel<D, 4, KVS_TABLE_TYPE(t)>), grid, dim3(4 * D), 0, stream, t, sh, part, out);
+  });
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                            const int32_t* counts, float* part, float* out, hipStream_t stream) {
@@ -651,10 +677,7 @@ hipError_t launch_mfma_f32(const UnitTable& tab, const Shape& sh, const void* Q,
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
-  });
-  return hipGetLastError();
+  return launch_reduce<D>(tab, sh, widest, part, out, stream);
 }
 
 template <int D>
@@ -667,26 +690,27 @@ hipError_t launch_mfma(const UnitTable& tab, const Shape& sh, const void* Q, con
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
-  });
-  return hipGetLastError();
+  return launch_reduce<D>(tab, sh, widest, part, out, stream);
 }
 
 template <typename T, int D>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts, float* part, float* out, hipStream_t stream) {
   const int widest = most_chunks(tab, sh.dec_chunk);
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units), dim3(kThreads), 0, stream, t, sh,
-                       (const T*)Q, (const T*)K, (const T*)V, counts, part);
-  });
+  auto launch = [&](auto unroll) {
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((decode_partial_kernel<T, D, decltype(unroll)::value, KVS_TABLE_TYPE(t)>), dim3(widest, tab.n_units),
+                         dim3(kThreads), 0, stream, t, sh, (const T*)Q, (const T*)K, (const T*)V, counts, part);
+    });
+  };
+  // A launch with no more than a workgroup per compute unit is a chain of round trips, and four rows in flight per lane
+  // group make fewer of them (one cache of 32768 rows 25.3 -> 23.6 us, 16 of 4096 18.8 -> 17.8); more workgroups have the
+  // rows in flight between them (64 of 4096: 29.5 with two, 34.3 with four; 256: 112 and 126).
+  if (widest * tab.n_units <= 256) launch(std::integral_constant<int, kMoreRows>{});
+  else launch(std::integral_constant<int, kFewRows>{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((decode_reduce_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh, part, out);
-  });
-  return hipGetLastError();
+  return launch_reduce<D>(tab, sh, widest, part, out, stream);
 }
 
 // Rows per workgroup of a launch (n_units units, `rows` rows, `first` of them in the first unit), from the lengths alone:
