@@ -457,6 +457,8 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
       }
       tab.total_sparts = sparts;
     } else {
+      tab.regular = units_regular(units.data(), tab.n_units);
+      std::copy(units.begin(), units.begin() + 2, tab.u);
       tab.host = units.data();
       tab.ext = plan.dev_table;
       e = launch_unit_table(units.data(), tab.n_units, plan.dev_table, plan.stream);

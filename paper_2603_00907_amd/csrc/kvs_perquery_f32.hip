@@ -73,8 +73,8 @@ __device__ __forceinline__ float dot_rows(const float* a, const float* b) {
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kThreads) void pq_out_f32_kernel(const UnitTable tab, const Shape sh,
+template <int D, typename Tab>
+__global__ __launch_bounds__(kThreads) void pq_out_f32_kernel(const Tab tab, const Shape sh,
                                                               const float* __restrict__ Q, const float* __restrict__ K,
                                                               const float* __restrict__ V,
                                                               const int32_t* __restrict__ counts_in,
@@ -141,8 +141,8 @@ __global__ __launch_bounds__(kThreads) void pq_out_f32_kernel(const UnitTable ta
 
 // o[unit, q, :] = (sum of the chunk partials) / (sum of their weights), both in chunk order.  One workgroup of D
 // threads per (unit, row).
-template <int D>
-__global__ __launch_bounds__(D) void pq_reduce_f32_kernel(const UnitTable tab, const Shape sh,
+template <int D, typename Tab>
+__global__ __launch_bounds__(D) void pq_reduce_f32_kernel(const Tab tab, const Shape sh,
                                                           const float* __restrict__ o_part,
                                                           const float* __restrict__ p_part, float* __restrict__ o) {
   const int R = sh.R;
@@ -158,8 +158,8 @@ __global__ __launch_bounds__(D) void pq_reduce_f32_kernel(const UnitTable tab, c
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kThreads) void pq_norms_f32_kernel(const UnitTable tab, const Shape sh,
+template <int D, typename Tab>
+__global__ __launch_bounds__(kThreads) void pq_norms_f32_kernel(const Tab tab, const Shape sh,
                                                                 const float* __restrict__ Q,
                                                                 const float* __restrict__ K,
                                                                 const float* __restrict__ V,
@@ -258,15 +258,21 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const float* Q, const
                     hipStream_t stream) {
   const dim3 grid(tab.total_chunks), block(kThreads);
   float* p_part = o_part + (size_t)tab.total_chunks * sh.R * D;   // the weights' sums lie behind the launch's partials
-  hipLaunchKernelGGL((pq_out_f32_kernel<D>), grid, block, 0, stream, tab, sh, Q, K, V, counts_in, c_row, o_part,
-                     p_part);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_out_f32_kernel<D, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, Q, K, V, counts_in, c_row,
+                       o_part, p_part);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((pq_reduce_f32_kernel<D>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, tab, sh, o_part, p_part,
-                     o);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_reduce_f32_kernel<D, KVS_TABLE_TYPE(t)>), dim3(tab.n_units * sh.R), dim3(D), 0, stream, t, sh,
+                       o_part, p_part, o);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((pq_norms_f32_kernel<D>), grid, block, 0, stream, tab, sh, Q, K, V, counts_in, c_row, o, a_tok,
-                     c_edge);
+  launch_with_table(tab, [&](const auto& t) {
+    hipLaunchKernelGGL((pq_norms_f32_kernel<D, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, Q, K, V, counts_in, c_row,
+                       o, a_tok, c_edge);
+  });
   return hipGetLastError();
 }
 
