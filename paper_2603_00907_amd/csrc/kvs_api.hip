@@ -431,9 +431,11 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     // Parts that go over all keys of their unit by themselves, or parts that meet and go over their share: the meetings
     // cost about what the keys of 32768 tokens do (steps of 8 bf16 units, 128 query rows: 8192 tokens 37.8 us against 42.3
     // with parts that meet, 16384 52.2 and 57.3, 24576 68.5 and 71.5, 32768 83.9 and 84.0; one unit of 65000: 68 against
-    // 64).  Launches of many units have no parts that meet (see select_parts).
+    // 64), and more of them beside a pass over V (8 units of 32768: that launch 18.7 us against 17.2; without the pass
+    // 13.3 against 15.9).  Launches of many units have no parts that meet (see select_parts).
     const bool few_units = tab.n_units * 8 <= n_cus;
-    sh.sel_slices = split_mode >= 2 ? 0 : few_units ? kSelRegSlices : kSelMaxSlices;
+    const int alone_slices = select == Select::kWithValues && !sh.stream ? kSelRegSlices - 2 : kSelRegSlices;
+    sh.sel_slices = split_mode >= 2 ? 0 : few_units ? alone_slices : kSelMaxSlices;
     // The pass over V rides along in sweep 1 when the launch is a large one (the streaming policy's threshold):
     // the edge selection then runs as a short launch of its own, which costs less than the separate pass over V saves
     // (measured at 64 units of the headline shape: 199 against 226 us for sweep 1, the pass over V and the selection).

@@ -380,7 +380,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
 // rows are requested when the tile starts and used when its alpha_bar values exist, one tile of arithmetic
 // later, so they cost no waiting, and they travel while the sweep's own loads are idle behind its arithmetic.
 // Every workgroup leaves the sum over its chunk in o_part[unit][chunk]; consumers add the chunks in order.
-template <int D, int PHASE, bool STREAM, bool CAUSAL, bool OBAR, int QB, typename Tab>
+// COUNTS: the launch has cardinalities (sweep 0; both ways in one kernel cost the one without them 0.6 us of 7.7 in a
+// small launch and 1 % in a large one.  Sweep 1 has one multiplication for them and no form of its own).
+template <int D, int PHASE, bool STREAM, bool CAUSAL, bool OBAR, bool COUNTS, int QB, typename Tab>
 __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mfma_wide_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   const int col = lane % 32, half = lane / 32;
   const int R = sh.R;
   const float sl2 = sh.scale_log2;
-  const int32_t* cnt = counts_in ? counts_in + un.in_row : nullptr;
+  const int32_t* cnt = COUNTS && counts_in ? counts_in + un.in_row : nullptr;
   const size_t part_base = (size_t)un.index * kMaxChunks;
 
   const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
@@ -619,70 +621,75 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
         // first tile, whose reference is minus infinity, among them) the reference rises to the tile's maxima and the
         // headroom, and the terms are formed again.  A row that stands for c tokens has c equal terms: c multiplies the
         // term, at no cost (a fused addition), and joins the logit as log2(c) only where a reference is set.
-        auto sums = [&](auto counts_c) {
-          constexpr bool COUNTS = decltype(counts_c)::value;
-          float sum[NTB];
-          bool bad = false;
-          if (COUNTS) {
-            float s4[NTB][4];
+        float sum[NTB];
+        bool bad = false;
+        if (COUNTS) {
+          float s4[NTB][4];
 #pragma unroll
-            for (int nt = 0; nt < NTB; ++nt) s4[nt][0] = s4[nt][1] = s4[nt][2] = s4[nt][3] = 0.f;
+          for (int nt = 0; nt < NTB; ++nt) s4[nt][0] = s4[nt][1] = s4[nt][2] = s4[nt][3] = 0.f;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {           // (four rows' cardinalities at a time: registers)
-              float cr[4];
-              lds_read_four(cr, cf_addr + 32 * g);
-#pragma unroll
-              for (int nt = 0; nt < NTB; ++nt) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                  s4[nt][i] = fmaf(cr[i], ex2(fmaf(acc[nt][4 * g + i], sl2, -m_run[2 * h + nt])), s4[nt][i]);
-              }
-            }
-#pragma unroll
-            for (int nt = 0; nt < NTB; ++nt) sum[nt] = (s4[nt][0] + s4[nt][1]) + (s4[nt][2] + s4[nt][3]);
-          } else {
+          for (int g = 0; g < 4; ++g) {           // (four rows' cardinalities at a time: registers)
+            float cr[4];
+            lds_read_four(cr, cf_addr + 32 * g);
 #pragma unroll
             for (int nt = 0; nt < NTB; ++nt) {
-              float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-              for (int v = 0; v < 16; ++v) s4[v % 4] += ex2(fmaf(acc[nt][v], sl2, -m_run[2 * h + nt]));
-              sum[nt] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+              for (int i = 0; i < 4; ++i)
+                s4[nt][i] = fmaf(cr[i], ex2(fmaf(acc[nt][4 * g + i], sl2, -m_run[2 * h + nt])), s4[nt][i]);
             }
           }
 #pragma unroll
-          for (int nt = 0; nt < NTB; ++nt) bad = bad || !(sum[nt] < kSumLimit);
-          if (__any(bad)) {
+          for (int nt = 0; nt < NTB; ++nt) sum[nt] = (s4[nt][0] + s4[nt][1]) + (s4[nt][2] + s4[nt][3]);
+        } else {
 #pragma unroll
-            for (int nt = 0; nt < NTB; ++nt) {
-              const int b = 2 * h + nt;
-              float tm = -INFINITY, s = 0.f;
+          for (int nt = 0; nt < NTB; ++nt) {
+            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s4[v % 4] += ex2(fmaf(acc[nt][v], sl2, -m_run[2 * h + nt]));
+            sum[nt] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+          }
+        }
+#pragma unroll
+        for (int nt = 0; nt < NTB; ++nt) bad = bad || !(sum[nt] < kSumLimit);
+        if (__any(bad)) {
+#pragma unroll
+          for (int nt = 0; nt < NTB; ++nt) {
+            const int b = 2 * h + nt;
+            float tm = COUNTS ? -INFINITY : acc[nt][0];
+            if (COUNTS) {
 #pragma unroll
               for (int g = 0; g < 4; ++g) {
                 float cr[4];
-                if (COUNTS) lds_read_four(cr, cf_addr + 32 * g);
+                lds_read_four(cr, cf_addr + 32 * g);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                  tm = fmaxf(tm, fmaf(acc[nt][4 * g + i], sl2, COUNTS ? __builtin_amdgcn_logf(cr[i]) : 0.f));
+                for (int i = 0; i < 4; ++i) tm = fmaxf(tm, fmaf(acc[nt][4 * g + i], sl2, __builtin_amdgcn_logf(cr[i])));
               }
-              const float m_new = fmaxf(m_run[b], tm + kHeadroom);
-              const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+            } else {
+#pragma unroll
+              for (int v = 1; v < 16; ++v) tm = fmaxf(tm, acc[nt][v]);
+            }
+            const float m_new = fmaxf(m_run[b], COUNTS ? tm + kHeadroom : fmaf(tm, sl2, kHeadroom));
+            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+            float s = 0.f;
+            if (COUNTS) {
 #pragma unroll
               for (int g = 0; g < 4; ++g) {
-                float cr[4] = {1.f, 1.f, 1.f, 1.f};
-                if (COUNTS) lds_read_four(cr, cf_addr + 32 * g);
+                float cr[4];
+                lds_read_four(cr, cf_addr + 32 * g);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s = fmaf(cr[i], ex2(fmaf(acc[nt][4 * g + i], sl2, -m_safe)), s);
               }
-              l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
-              m_run[b] = m_new;
-            }
-          } else {
+            } else {
 #pragma unroll
-            for (int nt = 0; nt < NTB; ++nt) l_run[2 * h + nt] += sum[nt];
+              for (int v = 0; v < 16; ++v) s += ex2(fmaf(acc[nt][v], sl2, -m_safe));
+            }
+            l_run[b] = l_run[b] * ex2(m_run[b] - m_safe) + s;
+            m_run[b] = m_new;
           }
-        };
-        if (cnt) sums(std::true_type{});
-        else sums(std::false_type{});
+        } else {
+#pragma unroll
+          for (int nt = 0; nt < NTB; ++nt) l_run[2 * h + nt] += sum[nt];
+        }
       } else {
         // Sweep 1, products taken as Q K^T: accumulator element v of block nt is query row
         // 32 (2 h + nt) + 8 (v / 4) + 4 half + v % 4, and the lane's column is ONE token, so the sum over the
@@ -799,23 +806,27 @@ hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh_in, const void* Q
                          hipStream_t stream) {
   Shape sh = sh_in;
   dim3 grid(tab.total_chunks), block(QB == 2 ? 256 : 512);
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
-                       (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                       (const uint16_t*)nullptr, (float*)nullptr);
-  });
+  auto sweep0 = [&](auto counts_c) {
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, decltype(counts_c)::value, QB, KVS_TABLE_TYPE(t)>), grid,
+                         block, 0, stream, t, sh, (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar,
+                         ws.stats_part, ws.c_row, (const uint16_t*)nullptr, (float*)nullptr);
+    });
+  };
+  if (counts_in != nullptr) sweep0(std::true_type{});
+  else sweep0(std::false_type{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = between_sweeps(tab, sh, ws, alpha_bar, stream)) != hipSuccess || alpha_bar == nullptr) return e;
   if (V != nullptr) {
     launch_with_table(tab, [&](const auto& t) {
-      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, true, true, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
                          (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
                          (const uint16_t*)V, ws.o_part);
     });
   } else {
     launch_with_table(tab, [&](const auto& t) {
-      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, false, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+      hipLaunchKernelGGL((score_mfma_wide_kernel<D, 1, STREAM, CAUSAL, false, true, QB, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
                          (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
                          (const uint16_t*)nullptr, (float*)nullptr);
     });
