@@ -109,11 +109,20 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   if (!NORMS && o_bar == nullptr) {
     const int nc = obar_partials(sh, un);
     const int d = tid % D, h = tid / D;
+    // (uniform: a unit of few chunks is spared the rest of the loads: 8 units of 8192 tokens, 8 chunks each, 39.2 -> 38.1 us
+    // per step)
     float v[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = h * PER + i;
-      v[i] = (c < nc) ? o_part[((size_t)un.index * kMaxChunks + c) * D + d] : 0.f;
+    for (int i0 = 0; i0 < PER; i0 += 4) {
+#pragma unroll
+      for (int i = i0; i < i0 + 4; ++i) v[i] = 0.f;
+      if (i0 * PARTS < nc) {
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) {
+          const int c = i * PARTS + h;
+          if (c < nc) v[i] = o_part[((size_t)un.index * kMaxChunks + c) * D + d];
+        }
+      }
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) part_sum += v[i];
