@@ -53,12 +53,13 @@ __device__ __forceinline__ void lds_read_4x16(bf16x8& a0, bf16x8& a1, bf16x8& a2
       : "memory");
 }
 
-// 2^-k, k the exponent of the largest cardinality that the wavefront's lanes hold: a power of two, so that multiplying and
-// dividing by it is exact.
+// 2^-k, k the exponent of the largest cardinality that the wavefront's lanes hold (0 where none is above 1): a power of two,
+// so that multiplying and dividing by it is exact.
 __device__ __forceinline__ float unit_of_counts(float c) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) c = fmaxf(c, __shfl_xor(c, m, kWave));
-  return __uint_as_float((254u << 23) - (__float_as_uint(c) & 0x7f800000u));       // (c is at least 1 and below 2^32)
+  c = fmaxf(c, 1.f);
+  return __uint_as_float((254u << 23) - (__float_as_uint(c) & 0x7f800000u));
 }
 
 // Four floats of LDS at byte address ad, complete on return (inline assembly for the same reason).
