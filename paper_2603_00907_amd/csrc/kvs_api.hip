@@ -167,11 +167,40 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
     long long want = total / (total <= (1ll << 20) ? kScoreWorkgroups / 2 : kScoreWorkgroups);
     if (const int forced = debug_switch(KVS_DEBUG_SCORE_CHUNK)) want = forced;   // tuning aid
     want = std::min<long long>(std::max<long long>(want, kMinChunkLen), kMaxChunkLen);
-    for (int u = 0; u < p->n_units; ++u) {
-      Unit& un = plan->units[u];
-      const long long per = std::max<long long>(want, (un.len + kMaxChunks - 1) / kMaxChunks);
-      un.chunk_len = (int)((per + kWave - 1) / kWave * kWave);
-      un.n_chunks = (un.len + un.chunk_len - 1) / un.chunk_len;
+    auto chunk_len = [&](int len, long long w) {
+      const long long per = std::max<long long>(w, (len + kMaxChunks - 1) / kMaxChunks);
+      return (int)((per + kWave - 1) / kWave * kWave);
+    };
+    // Units of different lengths end in chunks of their own, so that a launch has a few more workgroups than meant: a last
+    // round that is nearly empty (two workgroups of the kernel for 65 to 128 bf16 rows run on a CU at a time).  Slightly longer
+    // chunks in that launch group do without it: 64 ragged units of 4 K to 64 K tokens, 1076 workgroups, sweeps 121 + 136 us;
+    // at most 1024, 109 + 122 (the step of two such groups 1064 -> 1043 us).  Per group, since the chunks that suit one
+    // group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of 97 + 105.
+    const bool wide = plan->dtype == KVS_BF16 && plan->shape.R > 64 && plan->shape.R <= 128 &&
+                      debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
+    for (int first = 0, end; first < p->n_units; first = end) {
+      end = group_end(*plan, first, plan->group_cap);
+      auto workgroups = [&](long long w) {
+        long long n = 0;
+        for (int u = first; u < end; ++u) {
+          const int cl = chunk_len(plan->units[u].len, w);
+          n += (plan->units[u].len + cl - 1) / cl;
+        }
+        return n;
+      };
+      constexpr long long kRound = kScoreWorkgroups / 2;
+      const long long n = wide ? workgroups(want) : 0, full = n / kRound * kRound;
+      long long longer = want;
+      if (full >= kScoreWorkgroups && n > full && n - full <= kRound / 4) {
+        for (long long w = want + kWave; w <= want + want / 4; w += kWave) {
+          if (workgroups(w) <= full) { longer = w; break; }
+        }
+      }
+      for (int u = first; u < end; ++u) {
+        Unit& un = plan->units[u];
+        un.chunk_len = chunk_len(un.len, longer);
+        un.n_chunks = (un.len + un.chunk_len - 1) / un.chunk_len;
+      }
     }
   }
   // the one-pass score kernel (bf16, 65..128 query rows, every unit at least a tile long) keeps per-item tables
