@@ -450,10 +450,11 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     tab.total_ochunks = ochunks;
     tab.total_fitems = fitems;
     tab.total_sparts = sparts;
-    // (all counts are functions of a unit's length and budget)
+    // (the other counts are functions of a unit's length and budget; score chunks have the length that suits the unit's
+    // group in make_plan, and where a test has the groups cut elsewhere, one of them may hold units of two of those)
     tab.even = 1;
     for (const Unit& un : units) {
-      if (un.len != units[0].len || un.n_out != units[0].n_out) tab.even = 0;
+      if (un.len != units[0].len || un.n_out != units[0].n_out || un.chunk_len != units[0].chunk_len) tab.even = 0;
     }
     Shape sh = plan.shape;
     sh.stream = 2 * rows * sh.D * (long long)plan.elt > kStreamBytes;

@@ -56,16 +56,16 @@ struct Unit {
   int s_base;           // select workgroups of the launch's earlier units (a unit has one, or several parts)
 };
 
-// Whether the descriptors of a group follow from the first two by equal steps: units of one length and budget whose rows
-// lie at equal distances (the heads of all layers of a model).  A group of more than kInlineUnits such units needs no
+// Whether the descriptors of a group follow from the first two by equal steps: units of one length, budget and chunk length
+// whose rows lie at equal distances (the heads of all layers of a model).  A group of more than kInlineUnits such units needs no
 // launches that write descriptors: 256 caches of 2560 rows 224 -> 221 us per step, a decode step over 256 caches of 4096
 // rows 112 -> 105.  (Smaller groups keep a table: forming the descriptors is code to fetch and costs a per-layer step 2 us.)
 inline bool units_regular(const Unit* u, int n) {
   if (n < 2) return false;
   const long long di = u[1].in_row - u[0].in_row, dout = u[1].out_row - u[0].out_row;
   for (int i = 1; i < n; ++i) {
-    if (u[i].len != u[0].len || u[i].n_out != u[0].n_out || u[i].in_row - u[i - 1].in_row != di ||
-        u[i].out_row - u[i - 1].out_row != dout) {
+    if (u[i].len != u[0].len || u[i].n_out != u[0].n_out || u[i].chunk_len != u[0].chunk_len ||
+        u[i].in_row - u[i - 1].in_row != di || u[i].out_row - u[i - 1].out_row != dout) {
       return false;
     }
   }

@@ -112,6 +112,25 @@ static void whole_calls(std::mt19937& rng, kvs_dtype dt, int group, int window, 
   }
 }
 
+// Equal units in several launch groups, some with chunks of another length than the others (65 to 128 bf16 rows), and
+// launches that cut the groups elsewhere: every table has to stand for itself.
+static void equal_units(int nu, int len, int window) {
+  Problem pr(std::vector<int32_t>(nu, len), std::vector<int32_t>(nu, len / 4), 4, window, 128, KVS_BF16);
+  size_t ws_bytes = 0, pq_bytes = 0;
+  EXPECT(kvs_workspace_size(&pr.p, &ws_bytes) == KVS_OK);
+  EXPECT(kvs_per_query_workspace_size(&pr.p, &pq_bytes) == KVS_OK);
+  Arena a;
+  void* Q = a.take((size_t)nu * 4 * window * 128 * 2);
+  void* K = a.take((size_t)pr.rows_in * 128 * 2);
+  void* V = a.take((size_t)pr.rows_in * 128 * 2);
+  void* Ko = a.take((size_t)pr.rows_out * 128 * 2);
+  void* Vo = a.take((size_t)pr.rows_out * 128 * 2);
+  int32_t* cnt = (int32_t*)a.take((size_t)pr.rows_out * 4);
+  void* ws = a.take(pq_bytes);
+  EXPECT(kvs_step(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr) == KVS_OK);
+  EXPECT(kvs_step_per_query(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, pq_bytes, nullptr) == KVS_OK);
+}
+
 int main() {
   std::mt19937 rng(12345);
   size_t bytes = 0;
@@ -149,6 +168,14 @@ int main() {
   kvs_debug_set(KVS_DEBUG_SCORE_FUSED, 0);
   kvs_debug_set(KVS_DEBUG_SELECT_SPLIT, 2);     // as many select workgroups per unit as the units can have
   whole_calls(rng, KVS_BF16, 4, 32, 128);
+  for (int mode : {0, 2, 3}) {                  // (2 and 3: launches of at most 64 units)
+    kvs_debug_set(KVS_DEBUG_SELECT_SPLIT, mode);
+    for (int window : {17, 32}) {
+      equal_units(164, 21000, window);
+      equal_units(256, 20000, window);
+      equal_units(300, 2560, window);
+    }
+  }
   kvs_debug_set(KVS_DEBUG_SELECT_SPLIT, 1);     // never more than one
   whole_calls(rng, KVS_F32, 1, 8, 64);
   kvs_debug_set(KVS_DEBUG_SELECT_SPLIT, 0);

@@ -37,6 +37,23 @@ static void check_table(const UnitTable& tab) {
     ochunks += obar_chunks(u.len);
   }
   if (tab.total_chunks != chunks || tab.total_mblocks != mblocks || tab.total_ochunks != ochunks) __builtin_trap();
+  // what the kernels find by a division (`even`) and form from the first two descriptors (`regular`)
+  for (int i = 0; i < tab.n_units; ++i) {
+    const Unit u = tab.unit(i);
+    if (tab.even && (u.chunk_base != i * (chunks / tab.n_units) || u.m_base != i * (mblocks / tab.n_units) ||
+                     u.o_base != i * (ochunks / tab.n_units) || u.f_base != i * (tab.total_fitems / tab.n_units) ||
+                     u.s_base != i * (tab.total_sparts / tab.n_units))) {
+      __builtin_trap();
+    }
+    if (tab.regular) {
+      const Unit &a = tab.u[0], &b = tab.u[1];
+      if (!tab.even || u.len != a.len || u.n_out != a.n_out || u.chunk_len != a.chunk_len || u.n_chunks != a.n_chunks ||
+          u.index != a.index + i || u.in_row != a.in_row + i * (b.in_row - a.in_row) ||
+          u.out_row != a.out_row + i * (b.out_row - a.out_row)) {
+        __builtin_trap();
+      }
+    }
+  }
   for (int i = 0; i < tab.n_units; ++i) {          // select workgroups: one or several per unit, in unit order
     const int next = i + 1 < tab.n_units ? tab.unit(i + 1).s_base : tab.total_sparts;
     const int parts = next - tab.unit(i).s_base;
