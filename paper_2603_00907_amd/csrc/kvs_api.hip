@@ -470,11 +470,15 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     // the edge selection then runs as a short launch of its own, which costs less than the separate pass over V saves
     // (measured at 64 units of the headline shape: 199 against 226 us for sweep 1, the pass over V and the selection).
     // A small launch keeps the selection hidden beside the pass over V (8 units of 32768 tokens: 37 against 44 us), and
-    // so does one with a unit of more than 32768 tokens whose selection is not shared out by meeting parts (128 ragged
-    // units of 4 K to 64 K tokens: 1055 against 1076 us per step).
+    // so does one with a unit of more than 32768 tokens whose selection is not shared out by meeting parts: a launch of
+    // many units (128 ragged ones of 4 K to 64 K tokens: 1055 against 1076 us per step), or a unit too long for the parts
+    // that it may have (32 of 131072: 1052 against 1122; 24 of 100000: 632 and 698; 8 of 524288: 1306 and 1388).
     sh.ride = sh.stream;
     for (const Unit& un : units) {
-      if (un.len > kSelRegSlices * 4 * kSelThreads && !(few_units && select_exchanges(un, sh))) sh.ride = 0;
+      if (un.len <= kSelRegSlices * 4 * kSelThreads) continue;
+      const bool meet = few_units && select_exchanges(un, sh) &&
+                        select_parts(un, sh, tab.n_units, n_cus, split_mode, /*beside_values=*/false) > 1;
+      if (!meet) sh.ride = 0;
     }
     hipError_t e = hipSuccess;
     if (tab.n_units <= kInlineUnits) {

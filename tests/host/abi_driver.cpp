@@ -12,7 +12,7 @@
 #include "kvs.h"
 #include "kvs_debug.h"
 
-namespace kvs { int stub_launches(); }
+namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); }
 
 static int g_failed = 0;
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); ++g_failed; } } while (0)
@@ -131,6 +131,30 @@ static void equal_units(int nu, int len, int window) {
   EXPECT(kvs_step_per_query(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, pq_bytes, nullptr) == KVS_OK);
 }
 
+// One step over nu equal units (one launch, more than the caches hold): whether sweep 1 carries the pass over V, and the
+// select workgroups per unit.  A unit of more than 32768 tokens whose selection is not shared out by parts that meet keeps V
+// apart: that selection is then hidden beside the pass.
+static void values_ride(int nu, int len, int budget, bool rode, int parts) {
+  Problem pr(std::vector<int32_t>(nu, len), std::vector<int32_t>(nu, budget), 4, 32, 128, KVS_BF16);
+  pr.p.n_sink = 32;
+  size_t ws_bytes = 0;
+  EXPECT(kvs_workspace_size(&pr.p, &ws_bytes) == KVS_OK);
+  Arena a;
+  void* Q = a.take((size_t)nu * 128 * 128 * 2);
+  void* K = a.take((size_t)pr.rows_in * 128 * 2);
+  void* V = a.take((size_t)pr.rows_in * 128 * 2);
+  void* Ko = a.take((size_t)pr.rows_out * 128 * 2);
+  void* Vo = a.take((size_t)pr.rows_out * 128 * 2);
+  int32_t* cnt = (int32_t*)a.take((size_t)pr.rows_out * 4);
+  void* ws = a.take(ws_bytes);
+  EXPECT(kvs_step(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr) == KVS_OK);
+  if (kvs::stub_values_rode() != rode || kvs::stub_most_parts() != parts) {
+    std::printf("%d x %d: V %s, %d select workgroups per unit\n", nu, len, kvs::stub_values_rode() ? "rode" : "apart",
+                kvs::stub_most_parts());
+    EXPECT(!"the rule above");
+  }
+}
+
 int main() {
   std::mt19937 rng(12345);
   size_t bytes = 0;
@@ -184,6 +208,18 @@ int main() {
     whole_calls(rng, KVS_BF16, 4, 32, 128);
   }
   kvs_debug_set(KVS_DEBUG_GROUP_UNITS, 0);
+  values_ride(64, 32768, 8192, true, 4);        // (256 compute units, also where there is no GPU)
+  values_ride(16, 32790, 8192, false, 8);       // eight slices, by as many workgroups that do not meet
+  values_ride(8, 131072, 8192, true, 32);       // by parts that meet
+  values_ride(8, 262000, 8192, true, 32);       // the longest that 32 parts can hold
+  values_ride(32, 65500, 8192, true, 8);
+  values_ride(33, 65500, 8192, false, 1);       // a launch of many units
+  values_ride(32, 131072, 8192, false, 1);      // too long for the parts that the unit may have
+  values_ride(20, 131072, 8192, false, 1);
+  values_ride(24, 100000, 8192, false, 1);
+  values_ride(8, 300000, 8192, false, 1);
+  values_ride(8, 524288, 8192, false, 1);
+  values_ride(8, 131072, 131072, false, 1);     // nothing to select: as before the selection was shared out
   EXPECT(kvs_debug_set(99, 1) == -1);
   std::printf(g_failed ? "host layer: %d checks failed\n" : "host layer: all checks passed (%d stub launches)\n",
               g_failed ? g_failed : kvs::stub_launches());

@@ -7,6 +7,10 @@ namespace kvs {
 
 static int g_launches = 0;
 int stub_launches() { return g_launches; }
+static bool g_values_rode = false;      // the last score launch carried the pass over V
+static int g_most_parts = 0;            // select workgroups of the unit that had most of them in the last selection
+bool stub_values_rode() { return g_values_rode; }
+int stub_most_parts() { return g_most_parts; }
 
 static hipError_t ok() { ++g_launches; return hipSuccess; }
 
@@ -74,7 +78,11 @@ hipError_t launch_score_finalize(const UnitTable& tab, const Shape&, const Works
 hipError_t launch_score_valu(const UnitTable& tab, const Shape&, kvs_dtype, const void*, const void*, const int32_t*,
                              float*, const Workspace&, hipStream_t) { check_table(tab); return ok(); }
 hipError_t launch_score_mfma(const UnitTable& tab, const Shape&, kvs_dtype, const void*, const void*, const int32_t*,
-                             float*, const Workspace&, const void*, hipStream_t) { check_table(tab); return ok(); }
+                             float*, const Workspace&, const void* V, hipStream_t) {
+  check_table(tab);
+  g_values_rode = V != nullptr;
+  return ok();
+}
 bool score_mfma_supported(const UnitTable& tab, const Shape& sh, kvs_dtype) {
   if (sh.R < 4) return false;
   for (int i = 0; i < tab.n_units; ++i) if (tab.unit(i).len < 32) return false;
@@ -92,6 +100,11 @@ hipError_t launch_select_obar(const UnitTable& tab, const Shape&, kvs_dtype, boo
                               const void*, const int32_t*, float*, hipStream_t, const float*, float*, unsigned int* sel_shared) {
   check_table(tab);
   if (tab.total_sparts != tab.n_units && sel_shared == nullptr) __builtin_trap();
+  g_most_parts = 0;
+  for (int i = 0; i < tab.n_units; ++i) {
+    const int parts = (i + 1 < tab.n_units ? tab.unit(i + 1).s_base : tab.total_sparts) - tab.unit(i).s_base;
+    if (parts > g_most_parts) g_most_parts = parts;
+  }
   return ok();
 }
 hipError_t launch_select_clear(const UnitTable& tab, unsigned int* sel_shared, hipStream_t) {
