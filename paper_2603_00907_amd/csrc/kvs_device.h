@@ -59,7 +59,8 @@ struct Unit {
 // Whether the descriptors of a group follow from the first two by equal steps: units of one length, budget and chunk length
 // whose rows lie at equal distances (the heads of all layers of a model).  A group of more than kInlineUnits such units needs no
 // launches that write descriptors: 256 caches of 2560 rows 224 -> 221 us per step, a decode step over 256 caches of 4096
-// rows 112 -> 105.  (Smaller groups keep a table: forming the descriptors is code to fetch and costs a per-layer step 2 us.)
+// rows 112 -> 105.  (Smaller groups keep a table, see RegularTable: forming the descriptors is code to fetch and costs a
+// per-layer step 2 us.)
 inline bool units_regular(const Unit* u, int n) {
   if (n < 2) return false;
   const long long di = u[1].in_row - u[0].in_row, dout = u[1].out_row - u[0].out_row;
@@ -124,7 +125,7 @@ struct UnitTableT {
   int total_fitems;     // work items of the one-pass score kernel
   int total_sparts;     // select workgroups
   int even;             // 1: every unit has the same number of chunks, merge workgroups, ... (see find_unit_by)
-  int regular;          // 1: more than kInlineUnits units, and regular ones (units_regular): u[0] and u[1] stand for all
+  int regular;          // HOST: more than kInlineUnits units, and regular ones (units_regular): kernels get a RegularTable
   const Unit* host;     // HOST: the same descriptors for the launchers (meaningless on the device), else null
   Unit u[CAP];          // the descriptors of a smaller group
 
@@ -132,8 +133,30 @@ struct UnitTableT {
   // the index is wavefront-uniform, so these are scalar loads like those of the kernel arguments.
   __host__ __device__ __forceinline__ Unit unit(int i) const {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (CAP != kInlineUnits || (ext == nullptr && !regular)) return u[i];
-    if (!regular) return ((const __attribute__((address_space(4))) Unit*)ext)[i];
+    if (CAP == kInlineUnits && ext != nullptr) return ((const __attribute__((address_space(4))) Unit*)ext)[i];
+    return u[i];
+#else
+    return host != nullptr ? host[i] : u[i];
+#endif
+  }
+};
+typedef UnitTableT<kInlineUnits> UnitTable;
+// The table of a launch of few units.  64 descriptors are 3.6 KB of kernel arguments, which the host copies to where
+// the GPU reads them at every launch: a launch of an empty kernel takes 4.0 to 6.7 us with them and 3.5 to 3.8 with
+// 64 bytes, and a call on one layer is five such launches.  So kernels exist for the tables below (the table's type is
+// a template argument), and launch_with_table picks the one a launch needs.
+constexpr int kFewUnits = 8;
+typedef UnitTableT<kFewUnits> FewUnitTable;
+// The table of a group of more than kInlineUnits regular units: the first two descriptors stand for all.  A type of its own,
+// since the arithmetic in the kernels for up to 64 units was code to fetch there (steps on 36 ragged units of 1000 to 2300
+// tokens, 128 query rows 39.3 us with it and 37.7 without; 36 of 1500, 32 rows, head dim 64 28.0 and 27.2; 64 of 2000, 32
+// rows 44.2 and 43.1) and the other 62 descriptors are arguments to copy here (per-query step on 100 units of 1100 130.3
+// and 126.2).
+struct RegularTable {
+  static constexpr int even = 1;
+  int n_units, total_chunks, total_mblocks, total_ochunks, total_fitems, total_sparts;
+  Unit u[2];
+  __device__ __forceinline__ Unit unit(int i) const {
     i = __builtin_amdgcn_readfirstlane(i);          // (uniform, but it may come from a vector register: scalar arithmetic)
     Unit x = u[0];
     x.in_row += i * (u[1].in_row - u[0].in_row);
@@ -145,23 +168,19 @@ struct UnitTableT {
     x.f_base += i * (u[1].f_base - u[0].f_base);
     x.s_base += i * (u[1].s_base - u[0].s_base);
     return x;
-#else
-    return host != nullptr ? host[i] : u[i];
-#endif
   }
 };
-typedef UnitTableT<kInlineUnits> UnitTable;
-// The table of a launch of few units.  64 descriptors are 3.6 KB of kernel arguments, which the host copies to where
-// the GPU reads them at every launch: a launch of an empty kernel takes 4.0 to 6.7 us with them and 3.5 to 3.8 with
-// 64 bytes, and a call on one layer is five such launches.  So kernels exist for both sizes (the table's type is a
-// template argument), and launch_with_table picks the one a launch needs.
-constexpr int kFewUnits = 8;
-typedef UnitTableT<kFewUnits> FewUnitTable;
 template <typename T> struct TableTypeOf;
-template <int CAP> struct TableTypeOf<const UnitTableT<CAP>&> { typedef UnitTableT<CAP> type; };
+template <typename T> struct TableTypeOf<const T&> { typedef T type; };
 // f(table): f launches a kernel with the table it is handed.
 template <typename F>
 inline void launch_with_table(const UnitTable& tab, F&& f) {
+  if (tab.regular) {
+    const RegularTable r = {tab.n_units, tab.total_chunks, tab.total_mblocks, tab.total_ochunks, tab.total_fitems,
+                            tab.total_sparts, {tab.u[0], tab.u[1]}};
+    f(r);
+    return;
+  }
   if (tab.n_units > kFewUnits) {
     f(tab);
     return;
