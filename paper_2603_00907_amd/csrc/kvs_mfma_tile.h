@@ -2,6 +2,8 @@
 // and the per-tile adjustments of the logits (cardinalities, causal window).
 #pragma once
 
+#include <type_traits>
+
 #include "kvs_device.h"
 
 namespace kvs {
@@ -26,6 +28,7 @@ __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x)
 // their usual size 372 either way).
 constexpr float kHeadroom = 7.5f;
 constexpr float kSumLimit = 65536.f;
+constexpr float kLeastUnit = 1.f / 4096.f;
 
 // sum += x, where `lost` holds what the additions before have rounded away.  For a lane that meets all tiles of a chunk:
 // a sum that is nearly all one term would round every later tile's share the same way (2048 tokens: 1e-6 of the sum).
@@ -53,13 +56,33 @@ __device__ __forceinline__ void lds_read_4x16(bf16x8& a0, bf16x8& a1, bf16x8& a2
       : "memory");
 }
 
+// A float that all lanes hold, as a scalar.
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+
 // 2^-k, k the exponent of the largest cardinality that the wavefront's lanes hold (0 where none is above 1): a power of two,
 // so that multiplying and dividing by it is exact.
 __device__ __forceinline__ float unit_of_counts(float c) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) c = fmaxf(c, __shfl_xor(c, m, kWave));
   c = fmaxf(c, 1.f);
-  return __uint_as_float((254u << 23) - (__float_as_uint(c) & 0x7f800000u));
+  return uniform(__uint_as_float((254u << 23) - (__float_as_uint(c) & 0x7f800000u)));
+}
+
+// The least of c over the wavefront's lower 32 lanes, in every lane (DPP moves: shifts inside a row of 16 lanes, then the last
+// lane of row 0 into row 1).
+__device__ __forceinline__ float least_of_tile(float c) {
+  auto step = [&](auto ctrl) {
+    const int x = __builtin_bit_cast(int, c);
+    c = fminf(c, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, decltype(ctrl)::value, 0xF, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{});     // row_shr:1
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  step(std::integral_constant<int, 0x142>{});     // row_bcast:15
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), 31));
 }
 
 // Four floats of LDS at byte address ad, complete on return (inline assembly for the same reason).

@@ -509,7 +509,8 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   float m_run[2 * QB], l_run[2 * QB];
 #pragma unroll
   for (int b = 0; b < 2 * QB; ++b) { m_run[b] = -INFINITY; l_run[b] = 0.f; }
-  float c_unit = 1.f;                       // sweep 0: what the cardinalities are multiplied with in l_run
+  float c_unit = 1.f;                       // sweep 0: what the cardinalities are multiplied with in l_run, and the limit of
+  float limit = kSumLimit;                  // a tile's sums
   // OBAR: this lane's 16-byte piece of sum_t w_t V[t] over the wavefront's tiles (w = alpha_bar, or alpha_bar / c)
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   float o_acc[8];
@@ -536,8 +537,14 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
       if (PHASE == 0) {
         // (in units of a power of two near the first tile's largest, so that a reference stays near the logits
         // themselves: an exponent's argument rounds in proportion to its size)
-        if (it == 0) c_unit = unit_of_counts(cf);
-        sm_cf[wave][col] = cf * c_unit;         // (both halves of the wavefront write the same)
+        if (it == 0) {
+          c_unit = unit_of_counts(cf);
+          limit = uniform(kSumLimit * c_unit);  // (no cardinality is below one)
+        }
+        const float c = cf * c_unit;
+        sm_cf[wave][col] = c;                   // (both halves of the wavefront write the same)
+        // (a unit so large that ordinary sums would meet that limit: the tile's own least cardinality)
+        if (c_unit < kLeastUnit) limit = uniform(kSumLimit * fminf(1.f, least_of_tile(c)));
       }
       asm volatile("" : "+v"(cf) : : "memory"); // (here, before the next tile's loads into the same place)
     }
@@ -650,7 +657,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
           }
         }
 #pragma unroll
-        for (int nt = 0; nt < NTB; ++nt) bad = bad || !(sum[nt] < kSumLimit);
+        for (int nt = 0; nt < NTB; ++nt) bad = bad || !(sum[nt] < limit);
         if (__any(bad)) {
 #pragma unroll
           for (int nt = 0; nt < NTB; ++nt) {

@@ -119,6 +119,40 @@ def test_score_normaliser_of_rows_that_rise_far_above_their_first_tokens(dtype, 
     assert np.sqrt(np.mean(err ** 2)) < 6e-7
 
 
+@pytest.mark.parametrize("G,W", [(3, 32), (4, 32), (5, 32), (8, 32), (8, 64)])
+@pytest.mark.parametrize("count,first", [(1 << 22, -292.0), (1 << 10, -196.0)])
+def test_score_normaliser_of_rows_that_small_cardinalities_dominate(count, first, G, W):
+    """As above, with first tokens that stand for 2^22 (2^10) tokens each and lie 2^44 (2^32) below: in a sum in units of
+    their cardinality the one token on which a row puts its weight has a term that many times smaller than its exponential,
+    whose argument would be 37 (25), rounded to 2^-19 (2^-20), before the sum meets a limit of 2^16.  The same rounding
+    as above, the same bound."""
+    D, n, R = 128, 2048, G * W
+    H = np.array([[1.0]])
+    while H.shape[0] < D:
+        H = np.block([[H, H], [H, -H]])
+    w = variant("stream2560", dtype="bf16", head_dim=D, group=G, window=W, n_seq=1, n_kv_heads=1).scaled(fresh_tail=16)
+    u = generate_unit(w, 0, 0, 0, n=n)
+    u.Q = H[np.arange(R) % D].reshape(G, W, D).astype(np.float32)
+    rng = np.random.default_rng(R)
+    u.counts = np.ones(n, dtype=np.int32)
+    u.counts[:256] = count
+    K = np.zeros((n, D))
+    K[:, 0] = -157.0
+    K[:256, 0] = first
+    tokens = 300 + rng.permutation(n - 300)[:D]
+    gain = (210.0 + rng.integers(0, 5, D)) / 128.0             # (numbers that bf16 has)
+    K[tokens] += gain[:, None] * H
+    K[tokens, 0] = np.round(rng.uniform(-158.0, -154.0, D))
+    u.K = bf16_bits_to_f32(f32_to_bf16_bits(K.astype(np.float32)))
+    with switches(score_chunk=2048):
+        got = score([u], "bf16", D, G, W)[0][0]
+    ref, _ = O.score(u.Q, u.K, u.V, counts=u.counts)
+    mine = tokens[:min(R, D)]
+    assert (ref[mine] > 0.9 / R).all()
+    err = (got[mine] - ref[mine]) / ref[mine]
+    assert np.sqrt(np.mean(err ** 2)) < 6e-7
+
+
 @pytest.mark.parametrize("exponent", [-122, 100])
 @pytest.mark.parametrize("D,G,W", [(128, 4, 32), (64, 8, 32)])
 def test_score_f32_numbers_whose_parts_are_too_small(D, G, W, exponent):
