@@ -171,10 +171,12 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
       const long long per = std::max<long long>(w, (len + kMaxChunks - 1) / kMaxChunks);
       return (int)((per + kWave - 1) / kWave * kWave);
     };
-    // Units of different lengths end in chunks of their own, so that a launch has a few more workgroups than meant: a last
-    // round that is nearly empty (two workgroups of the kernel for 65 to 128 bf16 rows run on a CU at a time).  Slightly longer
-    // chunks in that launch group do without it: 64 ragged units of 4 K to 64 K tokens, 1076 workgroups, sweeps 121 + 136 us;
-    // at most 1024, 109 + 122 (the step of two such groups 1064 -> 1043 us).  Per group, since the chunks that suit one
+    // Units end in chunks of their own, so that a launch has a few more workgroups than meant: a last round that is nearly
+    // empty (two workgroups of the kernel for 65 to 128 bf16 rows run on a CU at a time).  Slightly longer chunks in that
+    // launch group do without it: 64 ragged units of 4 K to 64 K tokens, 1076 workgroups, sweeps 121 + 136 us; at most 1024,
+    // 109 + 122 (the step of two such groups 1066 -> 1032 us, with per-query norms, whose workgroups are the same chunks,
+    // 1915 -> 1821).  Equal units too: 100 of 21000 tokens, 1100 workgroups 566 us, 1000 539; with per-query norms 997 and
+    // 948, with cardinalities 584 and 554; 100 of 11000 296 and 289.  Per group, since the chunks that suit one
     // group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of 97 + 105.
     const bool wide = plan->dtype == KVS_BF16 && plan->shape.R > 64 && plan->shape.R <= 128 &&
                       debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
@@ -192,7 +194,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
       const long long n = wide ? workgroups(want) : 0, full = n / kRound * kRound;
       long long longer = want;
       if (full >= kScoreWorkgroups && n > full && n - full <= kRound / 4) {
-        for (long long w = want + kWave; w <= want + want / 4; w += kWave) {
+        for (long long w = want + kWave; w <= want + want / 4; w += kWave) {     // (beyond kMaxChunkLen where that is the aim)
           if (workgroups(w) <= full) { longer = w; break; }
         }
       }

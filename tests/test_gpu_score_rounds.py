@@ -1,12 +1,13 @@
-"""Launches of ragged units whose score chunks are lengthened so that the last round of workgroups is not nearly empty (65 to
-128 bf16 rows): every token is scored once, in one launch group and in two with chunk lengths of their own."""
+"""Launches whose score chunks are lengthened so that the last round of workgroups is not nearly empty (65 to 128 bf16 rows):
+every token is scored once, in one launch group and in two with chunk lengths of their own, ragged units and equal ones, with
+cardinalities and in the per-query kernels."""
 
 import numpy as np
 import pytest
 
 from oracle import kvs_oracle as O
 
-from test_gpu_parity import TOL_ALPHA
+from test_gpu_parity import TOL_ALPHA, switches
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +50,50 @@ def test_score_with_longer_chunks(n, longest, D, G, W, seed):
         ref, ref_o = O.score(Q[i].float().cpu().numpy().reshape(G, W, D), k, v)
         assert np.max(np.abs(got[rows[i]:rows[i] + lens[i]] - ref) / ref) < TOL_ALPHA, i
         assert (np.abs(got_o[i] - ref_o) <= TOL_ALPHA * (ref @ np.abs(v)) + 1e-7).all(), i
+
+
+@pytest.mark.parametrize("counts", [False, True])
+@pytest.mark.parametrize("D,G,W", [(64, 3, 22), (128, 4, 32)])
+def test_equal_units_with_longer_chunks(D, G, W, counts):
+    """100 units of 11000 tokens: 1100 chunks of 1088 tokens become 1000 of 1152, also for the per-query kernels."""
+    import torch
+    import paper_2603_00907_amd as kvs
+    n, length = 100, 11000
+    want = n * length // 1024
+    assert n * length > 1 << 20 and workgroups([length] * n, want) == 1100
+    p = kvs.Problem(lens=[length] * n, budgets=[2048] * n, group=G, window=W, head_dim=D, dtype="bf16", n_sink=4)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    K, V = (torch.randn((n * length, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    Q = torch.randn((n, G * W, D), generator=gen, device="cuda").to(torch.bfloat16)
+    c = torch.randint(1, 20, (n * length,), generator=gen, device="cuda", dtype=torch.int32) if counts else None
+    s = torch.cuda.current_stream().cuda_stream
+
+    def calls():
+        ws = torch.full((kvs.kvs_per_query_workspace_size(p),), 0xFF, dtype=torch.uint8, device="cuda")
+        out = [torch.full((n * length,), -7.0, device="cuda") for _ in range(4)] + [torch.full((n, D), -7.0, device="cuda")]
+        if counts:
+            kvs.kvs_score_counts(p, Q, K, V, c, out[0], out[4], ws, stream=s)
+            kvs.kvs_sensitivity_counts(p, Q, K, V, c, out[1], out[2], out[3], ws, stream=s)
+        else:
+            kvs.kvs_score(p, Q, K, V, out[0], out[4], ws, stream=s)
+            kvs.kvs_sensitivity(p, Q, K, V, out[1], out[2], out[3], ws, stream=s)
+        torch.cuda.synchronize()
+        return [x.cpu().numpy() for x in out]
+
+    alpha, alpha_pq, a_tok, c_edge, o_bar = calls()
+    for i in (0, 63, 64, n - 1):
+        rows = slice(i * length, (i + 1) * length)
+        ref, ref_o = O.score(Q[i].float().cpu().numpy().reshape(G, W, D), K[rows].float().cpu().numpy(),
+                             V[rows].float().cpu().numpy(), counts=c[rows].cpu().numpy() if counts else None)
+        assert np.max(np.abs(alpha[rows] - ref) / ref) < TOL_ALPHA, i
+        assert np.max(np.abs(alpha_pq[rows] - ref) / ref) < TOL_ALPHA, i
+        values = O.slot_values(V[rows].float().cpu().numpy(), c[rows].cpu().numpy() if counts else None)
+        assert (np.abs(o_bar[i] - ref_o) <= TOL_ALPHA * (ref @ np.abs(values)) + 1e-7).all(), i
+    with switches(score_chunk=want):                                    # the same calls without the rule
+        plain = calls()
+    # (each within its own bar, TOL_ALPHA or test_gpu_per_query's TOL_NORMS: no row concentrates on these inputs)
+    for got, other, tol in ((alpha, plain[0], TOL_ALPHA), (alpha_pq, plain[1], TOL_ALPHA), (a_tok, plain[2], 5e-5)):
+        assert np.max(np.abs(got - other) / other) < 2 * tol
+    inner = np.arange(n * length) % length != length - 1                # (a unit's last token has no edge)
+    assert (c_edge[~inner] == 0).all()
+    assert np.max(np.abs(c_edge - plain[3])[inner] / plain[3][inner]) < 2 * 5e-5
