@@ -555,9 +555,10 @@ hipError_t launch_score(const UnitTable& tab, const Shape& sh, kvs_dtype dt, con
   // statistics and the alpha_bar phase and carries the pass over V along (it needs V: callers that only want
   // alpha_bar take the two sweeps).  It is correct and saves a third of the score phase's traffic, but on this
   // chip it is slower than the two sweeps (see the measurements at the kernel), so it runs on request only:
-  // KVS_DEBUG_SCORE_FUSED = 2.
+  // KVS_DEBUG_SCORE_FUSED = 2.  (Its counters and its table are for kInlineUnits units: make_plan keeps to them, unless the
+  // switch was set since.)
   if (matrix_cores && wants_o && ws.fsync != nullptr && debug_switch(KVS_DEBUG_SCORE_FUSED) == 2 &&
-      score_fused_supported(tab, sh, dt)) {
+      tab.n_units <= kInlineUnits && score_fused_supported(tab, sh, dt)) {
     *o_layout = 2;
     return launch_score_fused(tab, sh, Q, K, V, counts_in, alpha_bar, ws, stream);
   }

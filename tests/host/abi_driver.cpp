@@ -12,7 +12,7 @@
 #include "kvs.h"
 #include "kvs_debug.h"
 
-namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); }
+namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); extern bool stub_asks_for_fused; }
 
 static int g_failed = 0;
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); ++g_failed; } } while (0)
@@ -220,6 +220,10 @@ int main() {
   values_ride(8, 300000, 8192, false, 1);
   values_ride(8, 524288, 8192, false, 1);
   values_ride(8, 131072, 131072, false, 1);     // nothing to select: as before the selection was shared out
+  kvs::stub_asks_for_fused = true;              // the switch for the one-pass kernel changes inside a call on a large group
+  equal_units(100, 2560, 32);
+  kvs::stub_asks_for_fused = false;
+  kvs_debug_set(KVS_DEBUG_SCORE_FUSED, 0);
   EXPECT(kvs_debug_set(99, 1) == -1);
   std::printf(g_failed ? "host layer: %d checks failed\n" : "host layer: all checks passed (%d stub launches)\n",
               g_failed ? g_failed : kvs::stub_launches());

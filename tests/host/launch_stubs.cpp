@@ -9,6 +9,7 @@ static int g_launches = 0;
 int stub_launches() { return g_launches; }
 static bool g_values_rode = false;      // the last score launch carried the pass over V
 static int g_most_parts = 0;            // select workgroups of the unit that had most of them in the last selection
+bool stub_asks_for_fused = false;       // launch_unit_table sets KVS_DEBUG_SCORE_FUSED, as another thread may at any time
 bool stub_values_rode() { return g_values_rode; }
 int stub_most_parts() { return g_most_parts; }
 
@@ -72,6 +73,7 @@ hipError_t launch_unit_table(const Unit* units, int n_units, Unit* dst, hipStrea
   for (int i = 0; i < n_units; ++i) touch = touch + units[i].len;   // (readable to its end, for the sanitizer)
   g_written = dst;
   g_written_n = n_units;
+  if (stub_asks_for_fused) kvs_debug_set(KVS_DEBUG_SCORE_FUSED, 2);
   return ok();
 }
 hipError_t launch_score_finalize(const UnitTable& tab, const Shape&, const Workspace&, hipStream_t) { check_table(tab); return ok(); }
@@ -94,6 +96,7 @@ hipError_t launch_score_fused(const UnitTable& tab, const Shape&, const void*, c
                               float*, const Workspace& ws, hipStream_t) {
   check_table(tab);
   if (ws.fstats == nullptr || ws.fo_part == nullptr || ws.fsync == nullptr) __builtin_trap();
+  if (tab.n_units > kInlineUnits) __builtin_trap();          // its counters are for that many, and its table
   return ok();
 }
 hipError_t launch_select_obar(const UnitTable& tab, const Shape&, kvs_dtype, bool, const float*, uint8_t*, int32_t*,
