@@ -133,7 +133,7 @@ kvs_status kvs_select(const kvs_problem* p, const float* alpha_bar,
  *   K_out, V_out DEVICE out [out rows, D] io_dtype;  counts_out DEVICE out [out rows] i32          */
 /*   ws           optional (also for the _counts and _norms forms).  The kernel needs none; with a workspace (256-byte
  *                aligned, at least kvs_workspace_size(p) bytes) a call with more than 64 short units puts up to 1024 of
- *                them into one launch, whose unit descriptors then live there.  Same results either way.
+ *                them into one launch, whose unit descriptors may then live there.  Same results either way.
  *   edge_mask and slot_of_token are taken as kvs_select writes them: slot_of_token[t] = number of zero mask bytes
  *   before t.  The mask byte of a unit's last token is read as 0 whatever it holds; a slot index outside the
  *   unit's output rows is never written.  Nothing else about a mask from outside the library is checked.   */

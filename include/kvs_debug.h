@@ -40,7 +40,7 @@ typedef enum {
                                                        n tenths of a microsecond apart                                 */
   KVS_DEBUG_GROUP_UNITS = 10, /* KVS_GROUP_UNITS=<n>   most units of one launch (the library puts up to 1024 short units, or 2 M
                                                        tokens, into one; groups of more than 64 keep their descriptors in
-                                                       the workspace)                                                   */
+                                                       the workspace, unless all follow from the first two)             */
   KVS_DEBUG_N_SWITCHES = 11
 } kvs_debug_switch;
 

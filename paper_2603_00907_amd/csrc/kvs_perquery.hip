@@ -28,8 +28,8 @@
 //                         weight on one token, o - v_t is as accurate as the small weights of the others (dividing
 //                         by the nominal sum 1 / R would leave the weights' rounding times ||v_t||).
 //                         -2 o^{(q)} stored as a bf16 pair hi + lo, and ||o^{(q)}||^2.
-//   pq_norms_kernel       per tile of 32 tokens: S' = Q K^T (logits), X' = (-2 O) V^T (hi and lo), then per (t, q)
-//                         (accumulated on top of ||o||^2), then per (t, q)
+//   pq_norms_kernel       per tile of 32 tokens: S' = Q K^T (logits), X' = (-2 O) V^T (hi and lo, accumulated on top of
+//                         ||o||^2), then per (t, q)
 //                         ||v_t - o||^2 = ||v_t||^2 + X',
 //                         ||v_t + v_{t+1} - 2o||^2 = ||v_t + v_{t+1}||^2 + 2 (X'_t + X'_{t+1}),
 //                         two square roots, and the sums over q.  Tiles overlap by one row (stride 31), so
@@ -168,7 +168,9 @@ __device__ __forceinline__ bf16x8 row_operand(const uint16_t* __restrict__ m, in
 }
 
 // ------------------------------------------------------------------------------------------------
-// o_part[(chunk of the launch), q, :] = sum over the chunk's tokens of (alpha^{(q)}_t / R) V[t]
+// o_part[(piece of the launch), q, :] = sum over the piece's tokens of 2^(logit - reference) V[t], p_part the sum of those
+// weights.  The reference: the row's normaliser where c_row is given (the weights are then alpha^{(q)}_t / R, with
+// cardinalities that of one of the c tokens); else the piece's own, which goes to stat_part with the sum of the terms.
 // Two workgroups per CU: the 64 accumulator registers of O^T and the 32 of the Q operands leave no room for a
 // third wavefront per SIMD (at 168 registers the compiler spills inside the tile loop).
 #ifndef KVS_PQ_OUT_OCC
@@ -811,7 +813,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
         accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(boh[kk], bv, accX, 0, 0, 0);
         accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bol[kk], bv, accX, 0, 0, 0);
       }
-      __syncthreads();                      // sm_vv / sm_vp of this tile are complete
+      __syncthreads();                      // sm_vv / sm_vd of this tile are complete
       // accumulator element v: query row 32 wave + 8 (v / 4) + 4 half + v % 4 of the pass, token column `col`
       float vv = sm_vv[buf][col];
       float vp = fmaf(2.f, sm_vd[buf][col], vv + sm_vv[buf][col + 1]);         // ||v_t + v_{t+1}||^2

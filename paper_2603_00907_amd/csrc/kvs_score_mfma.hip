@@ -483,7 +483,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   // Sweep 1 takes the products the other way round (query rows as accumulator rows, see below), so the
   // normalisers are indexed by accumulator element and come from LDS; the chunks' statistics that they are formed from are
   // fetched in the same round trip as the Q block and the tile (before those: 8 units of 8192 tokens 39.4 instead of 38.8
-  // us per step, 256 of 32768 2077 instead of 2062).  exp2(-inf) = 0: a row that does not exist adds nothing.
+  // us per step; a whole model's step is the same within its noise).  exp2(-inf) = 0: a row that does not exist adds nothing.
   if (PHASE == 1) {
     if (tid < QROWS) sm_lim[tid] = last_seen_row(CAUSAL ? sh.causal : 0, un.len, tid);
     load_row_consts<NTHR>(sh, un, ui, chunk == 0, c_row, stats_part, 0, QROWS, sm_cq);

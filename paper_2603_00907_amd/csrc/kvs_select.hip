@@ -23,8 +23,9 @@
 //
 // o_bar pass, per chunk of a unit: rows of V are read by LPR adjacent lanes (16 bytes each), scaled
 // by alpha_bar[t] and summed per lane, then over the workgroup; the chunk's sum goes to the
-// workspace; whoever needs o_bar (every merge workgroup, or a tiny reduce kernel when o_bar itself
-// is an output) adds the chunks up in chunk order, so the result does not depend on timing and no
+// workspace; whoever needs o_bar adds the chunks up in a fixed order (every merge workgroup several
+// strided subsets side by side and then those, a tiny reduce kernel, where o_bar itself is an output,
+// chunk by chunk: the two may differ in the last bits), so the result does not depend on timing and no
 // device-wide fence is needed (one costs a whole L2 write-back on this chip).
 #include <algorithm>
 #include <type_traits>
