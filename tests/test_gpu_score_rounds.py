@@ -97,3 +97,34 @@ def test_equal_units_with_longer_chunks(D, G, W, counts):
     inner = np.arange(n * length) % length != length - 1                # (a unit's last token has no edge)
     assert (c_edge[~inner] == 0).all()
     assert np.max(np.abs(c_edge - plain[3])[inner] / plain[3][inner]) < 2 * 5e-5
+
+
+def test_launches_that_hold_units_of_two_groups():
+    """164 units of 21000 tokens are planned as groups of 100, with chunks of 2112 tokens, and 64, with chunks of 2048; with the
+    selection spread on request, launches take 64 units each, and one of them has units of both: the same edges, the same
+    sums of Values."""
+    import torch
+    import paper_2603_00907_amd as kvs
+    n, length, D = 164, 21000, 64
+    assert workgroups([length] * 100, 2048) == 1100 and workgroups([length] * 100, 2112) == 1000
+    p = kvs.Problem(lens=[length] * n, budgets=[5000] * n, group=3, window=22, head_dim=D, dtype="bf16", n_sink=4)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    K, V = (torch.randn((n * length, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    Q = torch.randn((n, 66, D), generator=gen, device="cuda").to(torch.bfloat16)
+
+    def step():
+        ws = torch.full((kvs.kvs_workspace_size(p),), 0xFF, dtype=torch.uint8, device="cuda")
+        Ko, Vo = (torch.full((p.rows_out, D), -7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        co = torch.full((p.rows_out,), -7, dtype=torch.int32, device="cuda")
+        slot = torch.full((n * length,), -7, dtype=torch.int32, device="cuda")
+        kvs.kvs_step(p, Q, K, V, Ko, Vo, co, ws, slot_of_token_out=slot, stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        return slot, co, Vo, Ko
+
+    ref = step()
+    assert (ref[1].view(n, -1).sum(dim=1) == length).all()
+    with switches(select_split=2):
+        got = step()
+    assert all(torch.equal(a, b) for a, b in zip(got[:3], ref[:3]))
+    off = (got[3].float() - ref[3].float()).norm(dim=1) / ref[3].float().norm(dim=1)     # (o_bar's partials are others)
+    assert off.max() < 1e-2
