@@ -12,8 +12,14 @@
 // rows 1140 and 1064.  NW = 4 wavefronts cover up to 256 rows (two workgroups per CU), NW = 8 up to 512 (one per CU);
 // beyond that there is one launch per 512 rows.
 //
-// K streams into a ring of kBuf stages (NW * 16 tokens each) by global_load_lds, two stages ahead, 16-byte pieces
-// XOR-swizzled by the row number; one barrier per stage.  Sweep 0 takes S^T = K Q^T (a lane holds one query column
+// K streams into a ring of stages by global_load_lds, 16-byte pieces XOR-swizzled by the row number; one barrier per stage.
+// A stage is NW * 32 tokens, the next one on its way, or with the pass over V, whose rows take registers, NW * 16 tokens, two
+// on their way (with the rows of V of NW * 32 tokens in registers, or half of them at a time, the kernel spilled, and sweep 1
+// of 64 units of 32768 tokens took 236 to 310 us instead of 210).  A long stage matters because the pipeline of products and
+// terms fills and drains once per stage, and so does the size of its steps: one block of 32 rows at a time leaves registers
+// for a whole tile's operands (64 rows at a time and stages of NW * 16 tokens: sweep 0 of 8 units of 131072 tokens, 512 rows,
+// 178 us, now 167; 64 of 32768, 224 rows, 183 and 164, with V in sweep 1 210 and 212).
+//  Sweep 0 takes S^T = K Q^T (a lane holds one query column
 // and 16 token rows: running statistics are lane-private and no wavefront needs another's).  Sweep 1 takes S = Q K^T
 // (a lane holds one token and 16 query rows: the sum over the wavefront's rows is a sum over registers); the
 // wavefronts' shares meet in LDS, and each of them finishes 16 of the stage's tokens after the next
@@ -35,8 +41,6 @@ namespace {
 
 using namespace mfma;
 
-constexpr int kBuf = 3;                     // stages of K in LDS: one being read, two on their way
-
 // s_waitcnt: at most N vector-memory operations outstanding, all LDS operations done
 template <int N>
 __device__ __forceinline__ void wait_loads_and_lds() {
@@ -55,9 +59,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   constexpr int RPI = kWave / LPR;          // rows per load instruction
   constexpr int ROWB = D * 2;
   constexpr int TILEB = kTile * ROWB;
-  constexpr int STAGE = 16 * NW;            // tokens per stage: 16 rows fetched by every wavefront
+  constexpr int RW = OBAR ? 16 : 32;        // rows of a stage that every wavefront fetches
+  constexpr int AHEAD = OBAR ? 2 : 1;       // stages of K on their way while one is read
+  constexpr int kBuf = AHEAD + 1;
+  constexpr int STAGE = RW * NW;            // tokens per stage
   constexpr int NT = STAGE / kTile;         // tiles per stage
-  constexpr int NLD = 16 / RPI;             // load instructions per wavefront and stage
+  constexpr int NLD = RW / RPI;             // load instructions per wavefront and stage
   constexpr int STAGEB = STAGE * ROWB;
 
   __shared__ __attribute__((aligned(1024))) unsigned char sm_k[kBuf][STAGEB];
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   };
   fetch_counts(0);
   issue_stage(0, sm_k[0]);
-  if (nstages > 1) issue_stage(1, sm_k[1]);
+  if (AHEAD == 2 && nstages > 1) issue_stage(1, sm_k[1]);
   if (has_counts) sm_c[0][tid] = (float)raw_c;
   fetch_counts(1);
   if (PHASE == 1) {                         // (read after the loop's barriers)
@@ -247,8 +254,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   // n < NLD, r < RPI, token (n, r) in lane n * RPI + r (the rows of V that its load n brings, too)
   auto finish_stage = [&](int s) {
     const int s0 = t0 + s * STAGE;
-    const int l16 = lane % 16;
-    const int row = ((l16 / RPI) * NW + wave) * RPI + l16 % RPI;
+    const int lt = lane % RW;
+    const int row = ((lt / RPI) * NW + wave) * RPI + lt % RPI;
     float p = 0.f;
     {
       const float* src = &sm_p[s & 1][0][row];
@@ -274,7 +281,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
                                 "+v"(o_acc[5]), "+v"(o_acc[6]), "+v"(o_acc[7]) :: "memory");
     // a row that stands for c tokens has c equal terms in every softmax sum (2^(e + log2 c) = c 2^e)
     if (cnt && last_launch && ok) p *= (float)cnt[t];
-    if (lane < 16 && ok) alpha_bar[un.in_row + t] = p;
+    if (lane < RW && ok) alpha_bar[un.in_row + t] = p;
   };
   auto load_values = [&](int s) {
     const int s0 = t0 + s * STAGE;
@@ -296,88 +303,83 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
       sm_c[(s + 1) & 1][tid] = (float)raw_c;
       fetch_counts(s + 2);                                   // (before stage s + 2 of K, whose loads the next wait leaves out)
     }
-    if (s + 2 < nstages) issue_stage(s + 2, wr);
+    if (s + AHEAD < nstages) issue_stage(s + AHEAD, wr);
     if (OBAR) load_values(s);
     const int s0 = t0 + s * STAGE;
     const bool plain = s0 + STAGE <= min(t1, causal_from - 1);   // no token of the stage is masked for anybody
-    // The common stage: step (tile i, k-step kk) issues two products of tile i and forms a share of tile i - 1's terms,
-    // and the order is pinned step by step: left to itself the compiler issues the products in runs and the terms in
-    // runs, and the two wavefronts of a SIMD then fall into step and compete for one pipe after the other.  Operands
-    // are read three steps ahead.
+    // The common stage, block after block (a tile against 32 of the wavefront's rows): k-step kk of block m issues one product
+    // and forms a share of block m - 1's terms, and the order is pinned step by step: left to itself the compiler issues the
+    // products in runs and the terms in runs, and the two wavefronts of a SIMD then fall into step and compete for one pipe
+    // after the other.  A tile's operands stay in registers for its blocks; each is replaced by the next tile's when the last
+    // block has used it.
     auto fast = [&](auto ntb_c, auto counts_c) {
       constexpr int NTB = decltype(ntb_c)::value;            // blocks of query rows
       constexpr bool COUNTS = decltype(counts_c)::value;     // sweep 0: a row that stands for c tokens has c equal terms
       asm volatile("; plain stage, %0 blocks" :: "n"(NTB));
-      f32x16 acc[2][2];
-      bf16x8 ring[4];
-      auto operand = [&](int step) {
-        return *reinterpret_cast<const bf16x8*>(rd + (step / KS) * TILEB + a_ofs[step % KS]);
-      };
+      f32x16 acc[2];
+      bf16x8 a[KS];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) ring[i] = operand(i);
-      constexpr int PER = 16 / KS;                           // terms per step and block
-      float sum[2] = {0.f, 0.f};
-      // the cardinalities of the four rows that group g of a tile's terms belongs to, read one group ahead
+      for (int kk = 0; kk < KS; ++kk) a[kk] = *reinterpret_cast<const bf16x8*>(rd + a_ofs[kk]);
+      constexpr int M = NT * NTB;                            // blocks of the stage
+      constexpr int PER = 16 / KS;                           // terms per step
+      float sum = 0.f, share = 0.f;
+      // the cardinalities of the four rows that group g of a block's terms belongs to, read one group ahead
       float4 cc = make_float4(0.f, 0.f, 0.f, 0.f), cc_next = cc;
-      auto group_counts = [&](int g) {
-        return *reinterpret_cast<const float4*>(rd_c + (g / 4) * kTile + 8 * (g % 4) + 4 * half);
+      auto group_counts = [&](int m, int g) {
+        return *reinterpret_cast<const float4*>(rd_c + (m / NTB) * kTile + 8 * g + 4 * half);
       };
-      if constexpr (COUNTS) cc_next = group_counts(0);
-      auto terms = [&](int i, int kk) {                      // share kk of tile i's terms
+      if constexpr (COUNTS) cc_next = group_counts(0, 0);
+      auto terms = [&](int m, int kk) {                      // share kk of block m's terms
+        const int nt = m % NTB;
         float cf[PER];
         if constexpr (COUNTS) {
           constexpr int STEPS = 4 / PER;                     // steps per group of four rows
           if (kk % STEPS == 0) {
             cc = cc_next;
-            const int g = 4 * i + kk / STEPS + 1;
-            if (g < 4 * NT) cc_next = group_counts(g);
+            const int g = 4 * m + kk / STEPS + 1;
+            if (g < 4 * M) cc_next = group_counts(g / 4, g % 4);
           }
           const float c4[4] = {cc.x, cc.y, cc.z, cc.w};
 #pragma unroll
           for (int j = 0; j < PER; ++j) cf[j] = c4[(kk % STEPS) * PER + j];
         }
+        float e[PER];
 #pragma unroll
-        for (int nt = 0; nt < NTB; ++nt) {
-          float e[PER];
-#pragma unroll
-          for (int j = 0; j < PER; ++j) {
-            const int v = kk * PER + j;
-            e[j] = ex2(fmaf(acc[i & 1][nt][v], sl2, PHASE == 0 ? -m_run[nt] : -cq[nt][v]));
-          }
-#pragma unroll
-          for (int j = 0; j < PER; ++j) sum[nt] = COUNTS ? fmaf(cf[j], e[j], sum[nt]) : sum[nt] + e[j];
+        for (int j = 0; j < PER; ++j) {
+          const int v = kk * PER + j;
+          e[j] = ex2(fmaf(acc[m & 1][v], sl2, PHASE == 0 ? -m_run[nt] : -cq[nt][v]));
         }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) sum = COUNTS ? fmaf(cf[j], e[j], sum) : sum + e[j];
         if (kk == KS - 1) {
           if (PHASE == 0) {
-#pragma unroll
-            for (int nt = 0; nt < NTB; ++nt) l_run[nt] += sum[nt];
-          } else {
-            float p = NTB == 2 ? sum[0] + sum[1] : sum[0];
+            l_run[nt] += sum;
+          } else if (nt == NTB - 1) {
+            float p = NTB == 2 ? share + sum : sum;
             p += __shfl_xor(p, 32, kWave);
-            if (half == 0) sm_p[s & 1][wave][i * kTile + col] = p;
+            if (half == 0) sm_p[s & 1][wave][(m / NTB) * kTile + col] = p;
+          } else {
+            share = sum;
           }
-          sum[0] = sum[1] = 0.f;
+          sum = 0.f;
         }
       };
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
+      for (int m = 0; m < M; ++m) {
+        const int i = m / NTB, nt = m % NTB;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-          const int step = i * KS + kk;
-          if (step + 3 < NT * KS) ring[(step + 3) & 3] = operand(step + 3);
-#pragma unroll
-          for (int nt = 0; nt < NTB; ++nt) {
-            const bf16x8 x = ring[step & 3];
-            const f32x16 c = kk == 0 ? zero : acc[i & 1][nt];
-            acc[i & 1][nt] = (PHASE == 0) ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, bq[nt][kk], c, 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[nt][kk], x, c, 0, 0, 0);
-          }
-          if (i > 0) terms(i - 1, kk);
+          const f32x16 c = kk == 0 ? zero : acc[m & 1];
+          acc[m & 1] = (PHASE == 0) ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], bq[nt][kk], c, 0, 0, 0)
+                                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[nt][kk], a[kk], c, 0, 0, 0);
+          if (nt == NTB - 1 && i + 1 < NT)
+            a[kk] = *reinterpret_cast<const bf16x8*>(rd + (i + 1) * TILEB + a_ofs[kk]);
+          if (m > 0) terms(m - 1, kk);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) terms(NT - 1, kk);
+      for (int kk = 0; kk < KS; ++kk) terms(M - 1, kk);
       asm volatile("; plain stage ends, %0 blocks" :: "n"(NTB));
     };
     if (PHASE == 0) {
@@ -431,12 +433,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   for (int s = 0; s < nstages; ++s) {
     // stage s has landed (of the loads after it, at most those of stage s + 1 may be outstanding) in every wavefront,
     // and nobody reads the buffer of stage s - 1 any more
-    if (s + 1 < nstages) wait_loads_and_lds<NLD>();
+    if (AHEAD == 2 && s + 1 < nstages) wait_loads_and_lds<NLD>();
     else wait_loads_and_lds<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (PHASE == 1 && s > 0) finish_stage(s - 1);
-    stage(s, sm_k[s % kBuf], sm_k[(s + 2) % kBuf], sm_c[s & 1]);
+    stage(s, sm_k[s % kBuf], sm_k[(s + AHEAD) % kBuf], sm_c[s & 1]);
   }
 
   if (PHASE == 0) {
