@@ -98,7 +98,8 @@ int group_end(const Plan& plan, int first, int cap) {
   return i;
 }
 
-kvs_status make_plan(const kvs_problem* p, Plan* plan) {
+// per_query: the chunks are the pieces of the per-query kernels as well.
+kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
   if (p == nullptr) return KVS_ERR_INVALID_ARG;
   if (p->n_units < 1 || p->group < 1 || p->window < 1) return KVS_ERR_INVALID_ARG;
   if ((long long)p->group * p->window > KVS_MAX_Q_ROWS) return KVS_ERR_INVALID_ARG;
@@ -180,6 +181,18 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
     // group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of 97 + 105.
     const bool wide = plan->dtype == KVS_BF16 && plan->shape.R > 64 && plan->shape.R <= 128 &&
                       debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
+    // Whole rounds of as few workgroups as run at once: a workgroup of the kernels for more than 128 rows spends 6 to 12 us
+    // on what it does once for its chunk (the time of 160 to 310 tokens), a launch whose last round is half full half a
+    // round.  Of one to four rounds with the shortest chunks that fit them, the one whose rounds take the least time, counted
+    // in tokens.  Sweeps of 8 units of 131072 tokens, 512 rows, 256 workgroups at a time: two rounds 167 + 200 us, one
+    // 159 + 194; 48 of 32768 with 224 rows, 512 at a time: 768 workgroups 132 + 166, 480 126 + 162.  Steps: 48 of 16384, 224
+    // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
+    // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
+    // better in more rounds (128 ragged units 1029 -> 1081).  fp32 above 64 rows: no difference.
+    const int rows = plan->shape.R;
+    const bool rounds = !per_query && (plan->dtype == KVS_BF16 || rows <= 64) && debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
+    const long long at_once = rows > 256 ? 256 : 512, once = rows > 128 ? 256 : 128;
+    const int grain = rows > 256 ? 256 : 128;        // tokens of a stage of those kernels
     for (int first = 0, end; first < p->n_units; first = end) {
       end = group_end(*plan, first, plan->group_cap);
       auto workgroups = [&](long long w) {
@@ -196,6 +209,30 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan) {
       if (full >= kScoreWorkgroups && n > full && n - full <= kRound / 4) {
         for (long long w = want + kWave; w <= want + want / 4; w += kWave) {     // (beyond kMaxChunkLen where that is the aim)
           if (workgroups(w) <= full) { longer = w; break; }
+        }
+      }
+      bool equal = true;
+      long long tokens = 0;
+      for (int u = first; u < end; ++u) {
+        tokens += plan->units[u].len;
+        equal = equal && plan->units[u].len == plan->units[first].len;
+      }
+      if (rounds && (equal || rows > 128) && tokens >= at_once * want) {
+        long long best = 0;
+        for (long long k = 1; k <= 4; ++k) {
+          long long w = (tokens + k * at_once - 1) / (k * at_once);
+          if (equal) {
+            const long long per_unit = k * at_once / (end - first);
+            if (per_unit == 0) continue;
+            w = (plan->units[first].len + per_unit - 1) / per_unit;
+          }
+          w = (w + grain - 1) / grain * grain;
+          while (w <= kMaxRoundChunkLen && workgroups(w) > k * at_once) w += grain;
+          if (w > kMaxRoundChunkLen || w < kMinChunkLen) continue;
+          if (best == 0 || k * (w + once) < best) {
+            best = k * (w + once);
+            longer = w;
+          }
         }
       }
       for (int u = first; u < end; ++u) {
@@ -823,7 +860,7 @@ kvs_status kvs_step_static(const kvs_problem* p, const void* Q, const void* K, c
 kvs_status kvs_per_query_workspace_size(const kvs_problem* p, size_t* bytes) {
   if (bytes == nullptr) return KVS_ERR_INVALID_ARG;
   Plan plan;
-  kvs_status st = make_plan(p, &plan);
+  kvs_status st = make_plan(p, &plan, /*per_query=*/true);
   if (st != KVS_OK) return st;
   if ((st = check_per_query(plan)) != KVS_OK) return st;
   Workspace w;
@@ -840,7 +877,7 @@ kvs_status kvs_sensitivity_counts(const kvs_problem* p, const void* Q, const voi
                                   const int32_t* counts_in, float* alpha_bar, float* a_tok, float* c_edge, void* ws,
                                   size_t ws_bytes, void* hip_stream) {
   Plan plan;
-  kvs_status st = make_plan(p, &plan);
+  kvs_status st = make_plan(p, &plan, /*per_query=*/true);
   if (st != KVS_OK) return st;
   if ((st = check_per_query(plan)) != KVS_OK) return st;
   if (ws == nullptr || ((uintptr_t)ws % kAlign) != 0) return KVS_ERR_WORKSPACE;
@@ -916,7 +953,7 @@ kvs_status kvs_step_per_query_counts(const kvs_problem* p, const void* Q, const 
                                      int32_t* slot_of_token_out, uint8_t* edge_mask_out, void* ws, size_t ws_bytes,
                                      void* hip_stream) {
   Plan plan;
-  kvs_status st = make_plan(p, &plan);
+  kvs_status st = make_plan(p, &plan, /*per_query=*/true);
   if (st != KVS_OK) return st;
   if ((st = check_per_query(plan)) != KVS_OK) return st;
   if (ws == nullptr || ((uintptr_t)ws % kAlign) != 0) return KVS_ERR_WORKSPACE;

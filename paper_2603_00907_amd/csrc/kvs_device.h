@@ -29,6 +29,7 @@ constexpr int kMinChunkLen = 256;        // tokens
 constexpr int kMaxChunkLen = 2048;       // tokens that chunks aim for at most.  A chunk is up to a quarter longer to save a launch
                                          // a round of workgroups, and longer still where a unit has kMaxChunks of them: nothing
                                          // may be sized by this
+constexpr int kMaxRoundChunkLen = 4096;  // tokens that chunks cut for whole rounds of workgroups are at most
 constexpr int kScoreWorkgroups = 1024;   // score workgroups a launch aims for (4 per CU)
 constexpr int kObarMinChunk = 1024;      // tokens per workgroup of the o_bar pass (at most kMaxChunks per unit)
 #ifndef KVS_MERGE_TOKENS

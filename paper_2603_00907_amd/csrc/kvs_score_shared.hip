@@ -19,11 +19,11 @@
 // terms fills and drains once per stage, and so does the size of its steps: one block of 32 rows at a time leaves registers
 // for a whole tile's operands (64 rows at a time and stages of NW * 16 tokens: sweep 0 of 8 units of 131072 tokens, 512 rows,
 // 178 us, now 167; 64 of 32768, 224 rows, 183 and 164, with V in sweep 1 210 and 212).
-//  Sweep 0 takes S^T = K Q^T (a lane holds one query column
-// and 16 token rows: running statistics are lane-private and no wavefront needs another's).  Sweep 1 takes S = Q K^T
-// (a lane holds one token and 16 query rows: the sum over the wavefront's rows is a sum over registers); the
-// wavefronts' shares meet in LDS, and each of them finishes 16 of the stage's tokens after the next
-// barrier: alpha_bar, and with OBAR the same tokens' rows of V, requested one stage before.
+// Sweep 0 takes S^T = K Q^T (a lane holds one query column and 16 token rows: running statistics are lane-private and no
+// wavefront needs another's).  Sweep 1 takes S = Q K^T (a lane holds one token and 16 query rows: the sum over the
+// wavefront's rows is a sum over registers); the wavefronts' shares meet in LDS, and each of them finishes 32 (with the
+// pass over V 16) of the stage's tokens after the next barrier: alpha_bar, and with OBAR the same tokens' rows of V,
+// requested one stage before.
 //
 // Running statistics without a running maximum: sum 2^(e - m) for a reference m that stays (see kSumLimit in
 // kvs_mfma_tile.h).  The first stage of a chunk takes m from its maxima; a stage whose own sum is not below the limit in
