@@ -17,8 +17,8 @@ constexpr int kNonTemporal = 2;           // cache-policy bit of K tile loads th
 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Sums of 2^(e - m) over a row's logits e against a reference m that stays where it is (sweep 0 of the kernels for more
-// than 64 query rows): m is kHeadroom above the largest logit seen when it was last set, and a group of terms whose own
+// Sums of 2^(e - m) over a row's logits e against a reference m that stays where it is (sweep 0 of the bf16 kernels and of
+// fp32 above 64 query rows): m is kHeadroom above the largest logit seen when it was last set, and a group of terms whose own
 // sum is not below kSumLimit sets it again.  Any m would do for the sum, which is a floating-point number, but not for
 // the exponent's argument, which is rounded in proportion to its size: the largest term's stays between -7.5 and 16,
 // where that rounding is at most that of the finished normaliser.  (A row that puts its weight on one token 2^61 above

@@ -5,7 +5,7 @@
 // maximum and sum of exponentials, base-2 domain), a small kernel reduces them to one normaliser
 // per query row and unit, sweep 1 recomputes the logits, normalises them and writes alpha_bar.
 // (o_bar needs a pass over V: a streaming pass of its own beside the edge selection, see kvs_select.hip, or,
-// in large launches of the kernel for 65..128 query rows, carried along by sweep 1.)
+// in large launches of the wide kernel, carried along by sweep 1.)
 //
 // The logit tile is computed transposed, S^T[token, query] = K_tile * Q^T, with
 // v_mfma_f32_32x32x16_bf16: the A operand is a 32-token tile of K, the B operand a block of
@@ -21,17 +21,20 @@
 //
 // A workgroup's wavefronts split the chunk's tiles.  Three kernels:
 //   score_mfma_kernel       up to 64 query rows per wavefront, all register-stationary, two tile
-//                           buffers per wavefront.  Windows of at most 64 rows (WQ = 1); on request also
-//                           windows above 128 rows, where WQ wavefronts split the rows of a pass, share
-//                           tiles and combine alpha_bar through LDS with a workgroup barrier per tile.
-//   score_mfma_wide_kernel  65..128 rows, in blocks of 64: one block register-stationary and one re-read from an
+//                           buffers per wavefront.  On request only, windows above 128 rows: WQ wavefronts split
+//                           the rows of a pass, share tiles and combine alpha_bar through LDS with a workgroup
+//                           barrier per tile.
+//   score_mfma_wide_kernel  4..128 rows, in blocks of 64: one block register-stationary and one re-read from an
 //                           LDS copy of the Q block for every tile; in small launches also up to 256 rows, with
-//                           every block read from LDS (eight wavefronts).
+//                           every block read from LDS (eight wavefronts).  Up to 64 rows it took the place of
+//                           score_mfma_kernel, whose sweep 1 shuffles and cannot carry V: steps of 48 units of 32768
+//                           tokens with 32 rows 374 -> 363 us (V apart: 369), 100 of 20000 with 64 rows 483 -> 466,
+//                           64 of 32768 with 56 rows and cardinalities 520 -> 492.
 //   score_shared_kernel     (kvs_score_shared.hip) more than 128 rows.
 //   score_mfma_f32_kernel   fp32 inputs, up to 64 rows, v_mfma_f32_32x32x2_f32.
 //   score_split_kernel      (kvs_score_split.hip) fp32 inputs, more than 64 rows.
-// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit; over 64 rows c multiplies
-// the terms (256 caches of 2560 rows, 128 query rows: sweep 0 56 -> 41 us, sweep 1 63 -> 60 with the cardinalities in the
+// Rows of an already merged cache (cardinalities c given) enter with log2(c) added to the logit; in the wide kernel c
+// multiplies the terms (256 caches of 2560 rows, 128 query rows: sweep 0 56 -> 41 us, sweep 1 63 -> 60 with the cardinalities in the
 // tile's loads).
 #include <cstdlib>
 #include <type_traits>
@@ -142,48 +145,16 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     // this wavefront's block of query rows, kept in registers as MFMA B operands
     bf16x8 bq[NT][KS];
     float cq[NT];
-    if (WQ == 1) {
-      // One coalesced, swizzled copy of the block in LDS per workgroup, then operand reads from LDS:
-      // 4x less L2 traffic than per-wavefront row gathers.  Every wavefront fetches a quarter of the
-      // rows into its own second tile buffer, which is idle until the operands are in registers.
-      constexpr int RW = QROWS / kWaves;              // rows staged per wavefront
-      constexpr int QLD = RW / RPI > 0 ? RW / RPI : 1;
-      const uint4* Qg = reinterpret_cast<const uint4*>(Qu);
 #pragma unroll
-      for (int i = 0; i < QLD; ++i) {
-        const int lr = i * RPI + st_row;              // local row in this wavefront's buffer
-        const int qrow = min(qp + wave * RW + min(lr, RW - 1), R - 1);   // rows past R repeat the last row
-        const int piece = st_slot ^ (lr % LPR);
-        __builtin_amdgcn_global_load_lds(KVS_GLOBAL_PTR(Qg + (size_t)qrow * LPR + piece),
-                                         KVS_LDS_PTR(my_k + TILEB + i * 1024), 16, 0, 0);
-      }
-      __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0)
-      __syncthreads();
+    for (int nt = 0; nt < NT; ++nt) {
+      const int qrow = qp + wq * QROWS + nt * 32 + col;
+      const bool ok = qrow < R;
+      cq[nt] = (PHASE == 1 && ok) ? sm_c[qrow] : INFINITY;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int row = nt * 32 + col;
-        const int lr = row % RW;
-        const unsigned char* src = sm_k[row / RW][1] + lr * ROWB;
-        cq[nt] = (PHASE == 1 && qp + row < R) ? sm_c[qp + row] : INFINITY;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          const int slot = (2 * kk + half) ^ (lr % LPR);
-          bq[nt][kk] = *reinterpret_cast<const bf16x8*>(src + slot * 16);
-        }
-      }
-      __syncthreads();                                // the second buffers go back to the K tiles
-    } else {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int qrow = qp + wq * QROWS + nt * 32 + col;
-        const bool ok = qrow < R;
-        cq[nt] = (PHASE == 1 && ok) ? sm_c[qrow] : INFINITY;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          uint4 raw = make_uint4(0, 0, 0, 0);
-          if (ok) raw = *reinterpret_cast<const uint4*>(Qu + (size_t)qrow * D + kk * 16 + 8 * half);
-          bq[nt][kk] = *reinterpret_cast<bf16x8*>(&raw);
-        }
+      for (int kk = 0; kk < KS; ++kk) {
+        uint4 raw = make_uint4(0, 0, 0, 0);
+        if (ok) raw = *reinterpret_cast<const uint4*>(Qu + (size_t)qrow * D + kk * 16 + 8 * half);
+        bq[nt][kk] = *reinterpret_cast<bf16x8*>(&raw);
       }
     }
     int lim[NT];                                      // causal window: last row each query column attends to
@@ -200,7 +171,6 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const int tile_t0 = t0 + j * kTile;
       const int base_t = min(tile_t0, t1 - kTile);  // first token of the (possibly moved back) tile
       const int shift = (tile_t0 >= t1) ? kTile : tile_t0 - base_t;   // leading rows that are not ours
-      if (WQ == 1 && shift == kTile) break;         // this wavefront has run out of tiles
 
       // wait for this tile only (loads return in order: at most the NLD loads of the next tile may
       // still be in flight); first half of the k-steps: operands to registers, MFMAs
@@ -310,27 +280,20 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
         p[0] += __shfl_xor(p[0], 1, kWave);
         const int v = (lane >> 1) & 15;
         const int row = 8 * (v / 4) + 4 * half + (v % 4);
-        float a_tok = p[0];
-        if (WQ > 1) {
-          // the WQ wavefronts that share this tile add their query blocks up through LDS
-          if ((lane & 1) == 0) sm_alpha[wave][row] = a_tok;
-          __syncthreads();
-          if (wq == 0 && lane < kTile) {
-            a_tok = 0.f;
+        // the WQ wavefronts that share this tile add their query blocks up through LDS
+        if ((lane & 1) == 0) sm_alpha[wave][row] = p[0];
+        __syncthreads();
+        if (wq == 0 && lane < kTile) {
+          float a_tok = 0.f;
 #pragma unroll
-            for (int w = 0; w < WQ; ++w) a_tok += sm_alpha[wave + w][lane];
-            if (lane >= shift) {
-              float* dst = alpha_bar + un.in_row + base_t + lane;
-              if (!first_pass) a_tok += *dst;
-              *dst = a_tok;
-            }
+          for (int w = 0; w < WQ; ++w) a_tok += sm_alpha[wave + w][lane];
+          if (lane >= shift) {
+            float* dst = alpha_bar + un.in_row + base_t + lane;
+            if (!first_pass) a_tok += *dst;
+            *dst = a_tok;
           }
-          __syncthreads();
-        } else if ((lane & 1) == 0 && row >= shift) {
-          float* dst = alpha_bar + un.in_row + base_t + row;
-          if (!first_pass) a_tok += *dst;
-          *dst = a_tok;
         }
+        __syncthreads();
       }
     }
 
@@ -368,10 +331,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   }
 }
 
-// 65..256 query rows in ONE pass over K, as QB blocks of 64 rows (QB = 2: up to 128 rows, four wavefronts per
+// 4..256 query rows in ONE pass over K, as QB blocks of 64 rows (QB = 1, 2: up to 64, 128 rows, four wavefronts per
 // workgroup, two workgroups per CU; QB = 3, 4: up to 192 / 256 rows, eight wavefronts per workgroup and one workgroup
 // per CU, because the Q block then takes 48 / 64 KB of LDS).  All rows' operands plus the accumulators do not fit the
-// registers of a wavefront at two wavefronts per SIMD, so only rows 0..63 are register-stationary (QB = 2; none
+// registers of a wavefront at two wavefronts per SIMD, so only rows 0..63 are register-stationary (QB <= 2; none
 // with more blocks); the others stay in the workgroup's swizzled LDS copy of the Q block and are re-read for every
 // tile (16 KB of LDS reads per block and tile, hidden behind the MFMAs already in the pipe).  The K tile is
 // moved to registers whole (all k-steps) at the start of a tile, which frees its single LDS buffer
@@ -383,7 +346,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
 // COUNTS: the launch has cardinalities (sweep 0; both ways in one kernel cost the one without them 0.6 us of 7.7 in a
 // small launch and 1 % in a large one.  Sweep 1 has one multiplication for them and no form of its own).
 template <int D, int PHASE, bool STREAM, bool CAUSAL, bool OBAR, bool COUNTS, int QB, typename Tab>
-__global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mfma_wide_kernel(
+__global__ __launch_bounds__(QB <= 2 ? 256 : 512, QB <= 2 ? 2 : 1) void score_mfma_wide_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row, const uint16_t* __restrict__ V, float* __restrict__ o_part) {
@@ -395,9 +358,9 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   constexpr int ROWB = D * 2;
   constexpr int TILEB = kTile * ROWB;
   constexpr int QROWS = 64 * QB;            // query rows per wavefront (QB blocks of 64)
-  constexpr int NW = QB == 2 ? 4 : 8;       // wavefronts per workgroup
+  constexpr int NW = QB <= 2 ? 4 : 8;       // wavefronts per workgroup
   constexpr int NTHR = NW * kWave;
-  static_assert(QB >= 2 && QB <= 4, "the Q block must fit the LDS beside the tile buffers");
+  static_assert(QB >= 1 && QB <= 4, "the Q block must fit the LDS beside the tile buffers");
   static_assert(KS == 4 || KS == 8, "operand reads come in groups of four");
 
   __shared__ __attribute__((aligned(1024))) unsigned char sm_k[NW][TILEB];
@@ -466,7 +429,7 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
 
   // the Q block, once per workgroup: every wavefront fetches its share of the rows (rows past R repeat the last one)
   {
-    constexpr int RPW = QROWS / NW;           // 32 or 24 rows
+    constexpr int RPW = QROWS / NW;           // 16, 32 or 24 rows
     constexpr int QLD = RPW / RPI;
     static_assert(RPW % RPI == 0, "whole load instructions");
 #pragma unroll
@@ -497,11 +460,11 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  bf16x8 bq[2][KS];                         // rows 0..63, register-stationary (two blocks only: with more, the
+  bf16x8 bq[2][KS];                         // rows 0..63, register-stationary (up to two blocks: with more, the
                                             // statistics of eight column blocks take the registers and every block
                                             // is read from LDS)
 #pragma unroll
-  for (int g = 0; g < (QB == 2 ? KS / 4 : 0); ++g) {
+  for (int g = 0; g < (QB <= 2 ? KS / 4 : 0); ++g) {
     lds_read_4x16<0>(bq[0][4 * g], bq[0][4 * g + 1], bq[0][4 * g + 2], bq[0][4 * g + 3], q_addr + 4 * g);
     lds_read_4x16<32 * ROWB>(bq[1][4 * g], bq[1][4 * g + 1], bq[1][4 * g + 2], bq[1][4 * g + 3], q_addr + 4 * g);
   }
@@ -569,11 +532,12 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
       constexpr int NTB = decltype(ntc)::value;
       f32x16 acc[2];
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (h == 0 && QB == 2) {
+      if (h == 0 && QB <= 2) {
+        if (NTB == 1) acc[1] = zero;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
+          for (int nt = 0; nt < NTB; ++nt) {
             acc[nt] = (PHASE == 0)
                 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], bq[nt][kk], kk == 0 ? zero : acc[nt], 0, 0, 0)
                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[nt][kk], a[kk], kk == 0 ? zero : acc[nt], 0, 0, 0);
@@ -725,8 +689,14 @@ __global__ __launch_bounds__(QB == 2 ? 256 : 512, QB == 2 ? 2 : 1) void score_mf
     };
     typedef std::integral_constant<int, 1> one_t;
     typedef std::integral_constant<int, 2> two_t;
-    block(std::integral_constant<int, 0>{}, two_t{});
-    if constexpr (QB == 2) {
+    if constexpr (QB == 1) {
+      if (R > 32) block(std::integral_constant<int, 0>{}, two_t{});
+      else block(std::integral_constant<int, 0>{}, one_t{});
+    } else {
+      block(std::integral_constant<int, 0>{}, two_t{});
+    }
+    if constexpr (QB == 1) {
+    } else if constexpr (QB == 2) {
       block(std::integral_constant<int, 1>{}, two_t{});
     } else {
       // the last block holds one or two column blocks of 32 rows (uniform)
@@ -812,7 +782,7 @@ hipError_t launch_wide_t(const UnitTable& tab, const Shape& sh_in, const void* Q
                          const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
                          hipStream_t stream) {
   Shape sh = sh_in;
-  dim3 grid(tab.total_chunks), block(QB == 2 ? 256 : 512);
+  dim3 grid(tab.total_chunks), block(QB <= 2 ? 256 : 512);
   auto sweep0 = [&](auto counts_c) {
     launch_with_table(tab, [&](const auto& t) {
       hipLaunchKernelGGL((score_mfma_wide_kernel<D, 0, STREAM, CAUSAL, false, decltype(counts_c)::value, QB, KVS_TABLE_TYPE(t)>), grid,
@@ -876,12 +846,11 @@ template <int D>
 hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const void* K,
                     const int32_t* counts_in, float* alpha_bar, const Workspace& ws, const void* V,
                     hipStream_t stream) {
-  // At most 64 query rows per wavefront: with more, the stationary Q operands, the accumulators and
+  // At most 64 query rows stationary in a wavefront's registers: with more, the Q operands, the accumulators and
   // the tile operands no longer fit the 256 registers that two wavefronts per SIMD leave each, and
   // every spill reload waits for ALL loads in flight, the tile prefetch included.
   const int R = sh.R;
-  if (R <= 32) return launch_t<D, 1, 1>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
-  if (R <= 64) return launch_t<D, 2, 1>(tab, sh, Q, K, counts_in, alpha_bar, ws, stream);
+  if (R <= 64) return launch_wide<D, 1>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);
   // 65..256 rows: rows 64.. from LDS, one pass over K (KVS_DEBUG_SCORE_WIDE: 1 keeps the kernels of the last two lines for
   // more than 128, 2 the one whose wavefronts share the K tiles whatever the launch's size)
   const int forced = debug_switch(KVS_DEBUG_SCORE_WIDE);
@@ -1150,12 +1119,11 @@ bool score_mfma_supported(const UnitTable& tab, const Shape& sh, kvs_dtype dt) {
   return true;
 }
 
-// Sweep 1 of the kernel for more than 64 query rows can carry the pass over V along (o_part then holds one partial
-// per score chunk).
+// Sweep 1 of the bf16 kernels can carry the pass over V along (o_part then holds one partial per score chunk).
 bool score_mfma_takes_values(const Shape& sh, kvs_dtype dt) {
   if (dt != KVS_BF16) return false;
   const bool wide_off = debug_switch(KVS_DEBUG_SCORE_WIDE) == 1;
-  return sh.R > 64 && (sh.R <= 128 || !wide_off);
+  return sh.R <= 128 || !wide_off;
 }
 
 // V: non-null asks for that fused pass (only where score_mfma_takes_values says so).
