@@ -98,7 +98,7 @@ int group_end(const Plan& plan, int first, int cap) {
   return i;
 }
 
-// per_query: the chunks are the pieces of the per-query kernels as well.
+// per_query: for a per-query call (its chunks may be the pieces of the per-query kernels as well).
 kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
   if (p == nullptr) return KVS_ERR_INVALID_ARG;
   if (p->n_units < 1 || p->group < 1 || p->window < 1) return KVS_ERR_INVALID_ARG;
@@ -188,11 +188,26 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     // 159 + 194; 48 of 32768 with 224 rows, 512 at a time: 768 workgroups 132 + 166, 480 126 + 162.  Steps: 48 of 16384, 224
     // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
     // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
-    // better in more rounds (128 ragged units 1029 -> 1081).  fp32 above 64 rows: no difference.
+    // better in more rounds (128 ragged units 1029 -> 1081).  fp32 above 64 rows, of whose workgroups 512 run at once up to 128
+    // rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89.
     const int rows = plan->shape.R;
-    const bool rounds = !per_query && (plan->dtype == KVS_BF16 || rows <= 64) && debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
-    const long long at_once = rows > 256 ? 256 : 512, once = rows > 128 ? 256 : 128;
-    const int grain = rows > 256 ? 256 : 128;        // tokens of a stage of those kernels
+    // Per-query calls: those whose alpha_bar comes from kvs_score's two sweeps have its chunks, and so its bits (fp32, 8 units of
+    // 8192 1158 -> 919 us, 4 of 3000 with 32 rows 301 -> 170; 100 of 9000, one bf16 row 547 -> 436).  The others' chunks are
+    // the pieces of their own kernels, which cut them finer in small launches (48 of 16384, 224 rows 821 -> 664; 64 of 32768,
+    // 128 rows 913 -> 879; 40 of 32768, 64 rows 598 -> 530; 100 of 21000 927 -> 933; above 256 rows 24 ragged ones lost,
+    // 675 -> 703, and equal ones gained nothing).
+    const bool pieces = per_query && plan->dtype == KVS_BF16 && rows >= 4;
+    const bool rounds = debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
+    const bool split = plan->dtype == KVS_F32 && rows > 64;
+    const long long at_once = rows > (split ? 128 : 256) ? 256 : 512, once = rows > 128 ? 256 : 128;
+    const int grain = split ? 64 : rows > 256 ? 256 : 128;        // tokens of a stage of those kernels
+    // Launches that leave compute units without a workgroup when chunks have kMinChunkLen tokens: shorter ones, as long as a
+    // compute unit gets no second workgroup, of a tile for each of the four wavefronts that work on tiles of their own, or
+    // of one or two tiles that all wavefronts share.  Steps: one fp32 unit of 1024 tokens, 8 rows 26.8 -> 24.3 us; 8 units of
+    // 4096, 128 rows 33.2 -> 30.6, fp32 62.9 -> 52.5; 4 of 2000 29.3 -> 26.6, fp32 54.2 -> 37.6; 8 of 4096, 256 rows
+    // 39.2 -> 37.5; 8 of 6000 fp32 65.7 -> 60.7.  (8 of 8192 with chunks of 128, two workgroups per compute unit, 39.4 -> 40.6, with 256
+    // rows 46 -> 51.)
+    const long long tiny_grain = split || (plan->dtype == KVS_BF16 && rows > 256) ? 64 : 128;
     for (int first = 0, end; first < p->n_units; first = end) {
       end = group_end(*plan, first, plan->group_cap);
       auto workgroups = [&](long long w) {
@@ -217,7 +232,14 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
         tokens += plan->units[u].len;
         equal = equal && plan->units[u].len == plan->units[first].len;
       }
-      if (rounds && (equal || rows > 128) && tokens >= at_once * want) {
+      long long tiny = kMinChunkLen;
+      if (rounds && tokens < kTinyWorkgroups * kMinChunkLen) {
+        for (long long w = kMinChunkLen - tiny_grain; w > 0 && workgroups(w) <= kTinyWorkgroups; w -= tiny_grain) tiny = w;
+      }
+      if (tiny < kMinChunkLen) {
+        longer = tiny;
+      } else if (rounds && !(pieces && rows > 256) && (equal || rows > 128) &&
+                 tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * want)) {
         long long best = 0;
         for (long long k = 1; k <= 4; ++k) {
           long long w = (tokens + k * at_once - 1) / (k * at_once);
@@ -228,7 +250,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
           }
           w = (w + grain - 1) / grain * grain;
           while (w <= kMaxRoundChunkLen && workgroups(w) > k * at_once) w += grain;
-          if (w > kMaxRoundChunkLen || w < kMinChunkLen) continue;
+          if (w > kMaxRoundChunkLen || w < (split ? kMinChunkLen / 2 : kMinChunkLen)) continue;
           if (best == 0 || k * (w + once) < best) {
             best = k * (w + once);
             longer = w;

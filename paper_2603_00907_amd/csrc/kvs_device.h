@@ -25,7 +25,8 @@ constexpr int kMaxGroupUnits = 1024;
 #endif
 constexpr long long kGroupTokens = KVS_GROUP_TOKENS;
 constexpr int kMaxChunks = 64;           // token chunks (= score workgroups) per unit
-constexpr int kMinChunkLen = 256;        // tokens
+constexpr int kMinChunkLen = 256;        // tokens, but for launches of fewer workgroups than compute units
+constexpr long long kTinyWorkgroups = 256;
 constexpr int kMaxChunkLen = 2048;       // tokens that chunks aim for at most.  A chunk is up to a quarter longer to save a launch
                                          // a round of workgroups, and longer still where a unit has kMaxChunks of them: nothing
                                          // may be sized by this
@@ -539,6 +540,7 @@ inline int pq_split(long long chunks, long long rows, long long longest, int R, 
     const long long pieces = chunks << (split + 1);
     const bool few = pieces <= (light ? 512 : 256);
     const bool uneven = (longest >> split) * (light ? 320 : 240) > rows && (longest >> split) > 256;
+    if ((longest >> (split + 1)) < 32) break;               // (a tile's rows)
     if (!few && !(uneven && pieces <= kMaxPqPieces)) break;
     ++split;
   }

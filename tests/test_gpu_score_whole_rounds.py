@@ -1,6 +1,6 @@
 """Launches whose score chunks are cut for whole rounds of workgroups: one to four rounds, equal units and (above 128 rows)
 ragged ones, chunks that end inside a stage of the kernel for more than 128 rows, wavefronts with one and with two blocks of
-query rows, one launch per 512 rows."""
+query rows, one launch per 512 rows.  And launches of few workgroups, whose chunks are shorter than a stage."""
 
 import numpy as np
 import pytest
@@ -23,13 +23,32 @@ pytestmark = pytest.mark.gpu
     (40, 4111, 4111, 128, 2, 17, "f32", False, False),        # fp32, 34 rows
 ])
 def test_score_in_whole_rounds(n, shortest, longest, D, G, W, dtype, counts, causal):
-    import torch
-    import paper_2603_00907_amd as kvs
     rng = np.random.default_rng(n * D + G * W)
     lens = [int(x) for x in rng.integers(shortest, longest + 1, n)]
-    R, total = G * W, sum(lens)
-    at_once = 256 if R > 256 else 512
+    at_once, total = (256 if G * W > 256 else 512), sum(lens)
     assert total >= at_once * max(256, total // (512 if total <= 1 << 20 else 1024))      # what the rule is for
+    check(lens, D, G, W, dtype, counts, causal)
+
+
+@pytest.mark.parametrize("lens,D,G,W,dtype,counts,causal", [
+    ([700, 33, 129, 5000, 64, 1025], 128, 4, 32, "bf16", False, False),      # a tile per wavefront, last chunks of 1 to 127
+    ([1000, 513, 4000], 64, 1, 8, "bf16", True, True),
+    ([300, 2000, 1], 128, 1, 1, "bf16", False, False),                       # vector kernel
+    ([1024, 200, 3333], 64, 2, 4, "f32", True, False),
+    ([4000, 65, 129], 128, 5, 32, "bf16", True, False),                      # 160 rows, chunks of 128
+    ([2000, 65, 700], 128, 8, 64, "bf16", False, True),                      # 512 rows, chunks of 64
+    ([2000, 65, 32, 1999], 128, 4, 32, "f32", False, True),                  # fp32, 128 rows, chunks of 64
+    ([6000] * 8, 64, 3, 67, "f32", True, False),                             # fp32, 201 rows, chunks of 192
+    ([6100] * 16, 128, 4, 30, "f32", False, False),                          # fp32, a round of 512
+])
+def test_score_in_short_chunks(lens, D, G, W, dtype, counts, causal):
+    check(lens, D, G, W, dtype, counts, causal)
+
+
+def check(lens, D, G, W, dtype, counts, causal):
+    import torch
+    import paper_2603_00907_amd as kvs
+    n, R = len(lens), G * W
     rows = np.cumsum([0] + [x + 3 for x in lens])
     io = torch.float32 if dtype == "f32" else torch.bfloat16
     p = kvs.Problem(lens=lens, budgets=[2048] * n, group=G, window=W, head_dim=D, dtype=dtype, n_sink=4,
