@@ -43,8 +43,8 @@
 // products still run on the stored rows; c_t multiplies the term in the sums over a row (a logarithm in the exponent would
 // round with its size), the weight of the Value SUM is the term of ONE token, and 1 / c_t scales
 // the product V_t . o and the squared norms afterwards.
-// A workgroup has four wavefronts; wavefront w owns query rows 32w .. 32w+31 of a pass of 128 rows and
-// keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
+// A workgroup has four wavefronts; with more than 32 query rows wavefront w owns query rows 32w .. 32w+31 of a pass of 128
+// rows and keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
 // 16-byte pieces, as in the score kernels).  Results do not depend on timing: no atomics, fixed orders.
 #include <algorithm>
 #include <type_traits>
@@ -362,6 +362,192 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
           *reinterpret_cast<float4*>(dst + 32 * db + 8 * g + 4 * half) = o4;
         }
       }
+    }
+  }
+}
+
+// The same for up to 32 query rows: the kernel above gives every wavefront 32 rows of its own, so three of four would
+// multiply rows that don't exist.  Here the wavefronts take the piece's tiles in turn, each with all query rows and its
+// operands straight from memory (nothing is shared, so nothing goes through LDS and nothing waits for a barrier), and
+// add their sums up at the end, in wavefront order, each brought to the largest of their references.
+// The registers of the K and V operands are refilled for the wavefront's next tile as soon as they have been multiplied.
+// Bound by memory where there are many pieces, else by the wavefronts' chains.  Steps, before -> with both narrow kernels (us):
+// 32 rows, 100 units of 21000 tokens 902 -> 749 (two passes over K and V and the merge of it at 5 TB/s: 680), 8 of 32768
+// 127 -> 108, 8 of 8192 61 -> 50 (see pq_split); head dim 64, 12 of 29384 130 -> 88; 16 rows and cardinalities, 40 of 20000 510 -> 343;
+// 7 rows, 128 ragged ones of 700 to 1500 110 -> 90.  One unit of 1000 tokens: 29.3 -> 27.5.
+constexpr int kNarrowRows = kPqNarrowRows;
+template <int D, bool COUNTS, typename Tab>
+__global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
+    float* __restrict__ o_part, float* __restrict__ p_part, float2* __restrict__ stat_part, const int split) {
+  constexpr int KS = D / 16;
+  constexpr int DB = D / 32;
+  constexpr int ROWB = D * 2;
+  __shared__ __attribute__((aligned(16))) float sm_o[kWaves][kNarrowRows][D + 4];
+  __shared__ float sm_m[kWaves][kNarrowRows], sm_z[kWaves][kNarrowRows], sm_w[kWaves][kNarrowRows];
+
+  const int ui = find_unit(tab, (int)blockIdx.x >> split);
+  const Unit un = tab.unit(ui);
+  int t0, t1;
+  piece_range(un, blockIdx.x, split, t0, t1);
+  const int ntiles = (t1 - t0 + kTile - 1) / kTile;          // (a piece may be empty: it leaves zeros)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int col = lane % 32, half = lane / 32;
+  const int R = sh.R;
+  const float sl2 = sh.scale_log2;
+  const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
+  const unsigned char* Vg = reinterpret_cast<const unsigned char*>(V + (size_t)un.in_row * D);
+  const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
+  const uint32_t lane_at = (uint32_t)col * ROWB + (uint32_t)half * 16;     // this lane's first piece in a tile
+
+  bf16x8 ident[2];                          // identity operand, as above
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k0 = 16 * kk + 8 * half + 2 * i;
+      w[i] = (k0 == col ? 0x3F80u : 0u) | (k0 + 1 == col ? 0x3F800000u : 0u);
+    }
+    ident[kk] = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+  }
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // a tile always holds 32 whole rows, see above (a wavefront without a tile loads the last one and uses nothing of it)
+  auto tile_base = [&](int j) { return min(t0 + min(j, max(ntiles - 1, 0)) * kTile, t1 - kTile); };
+  auto load = [&](const unsigned char* base, int j, uint4* r) {
+    const unsigned char* src = base + (size_t)tile_base(j) * ROWB;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) r[kk] = *reinterpret_cast<const uint4*>(src + (lane_at + 32u * kk));
+    asm volatile("" ::: "memory");          // issue them here: sunk to their use they would be waited for at once
+  };
+
+  const bool ok = col < R;
+  bf16x8 bq[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, col, ok, kk, half);
+  float m_run = !ok ? INFINITY : c_row != nullptr ? c_row[(size_t)un.index * R + col] : -INFINITY;
+  float z = 0.f, z_lost = 0.f, wsum = 0.f;
+  const int lim = last_seen_row(sh.causal, un.len, col);
+  f32x16 accO[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) accO[db] = zero;
+
+  uint4 rk[KS], rv[KS];
+  load(Kg, wave, rk);
+  load(Vg, wave, rv);
+  for (int j = wave; j < ntiles; j += kWaves) {
+    const int base = tile_base(j);
+    const int shift = t0 + j * kTile - base;                 // leading rows that belong to the tile before
+    float cc[16];
+    if (COUNTS) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) cc[v] = (float)cnt[base + 8 * (v / 4) + 4 * half + (v % 4)];
+    }
+    f32x16 acc = zero;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rk[kk]), bq[kk], acc, 0, 0, 0);
+    load(Kg, j + kWaves, rk);
+    float p[16];
+    const bool masked = shift > 0 || (sh.causal > 0 && base + kTile > un.len - sh.causal + 1);
+    auto seen = [&](int v) {
+      const int row = 8 * (v / 4) + 4 * half + (v % 4);
+      return row >= shift && base + row <= lim;
+    };
+    auto terms = [&](float m) {             // the tile's terms against reference m; returns their sum
+#pragma unroll
+      for (int v = 0; v < 16; ++v) p[v] = ex2(fmaf(acc[v], sl2, -m));
+      if (masked) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) p[v] = seen(v) ? p[v] : 0.f;
+      }
+      float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < 16; ++v) s4[v % 4] += p[v];
+      return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    };
+    float ts = terms(m_run);
+    if (!COUNTS && c_row == nullptr && __any(!(ts < kSumLimit))) {         // the reference rises, as above
+      float tm = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) tm = fmaxf(tm, !masked || seen(v) ? acc[v] : -INFINITY);
+      tm = fmaxf(tm, __shfl_xor(tm, 32, kWave));
+      const float m_new = fmaxf(m_run, fmaf(tm, sl2, kHeadroom));
+      const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+      const float down = m_run == m_new ? 1.f : ex2(m_run - m_safe);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) accO[db] *= down;
+      wsum *= down;
+      z *= down;
+      z_lost *= down;
+      m_run = m_new;
+      ts = terms(m_safe);
+    }
+    add_compensated(z, z_lost, ts);
+    bf16x8 ph[2], pl[2];
+    float pw[16];
+    split8w(p, ph[0], pl[0], pw);
+    split8w(p + 8, ph[1], pl[1], pw + 8);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) wsum = COUNTS ? fmaf(pw[v], cc[v], wsum) : wsum + pw[v];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {       // a block of V turned token-major (see above) and multiplied
+      f32x16 y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rv[2 * db]), ident[0], zero, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rv[2 * db + 1]), ident[1], y, 0, 0, 0);
+      float yf[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) yf[v] = y[v];
+      const bf16x8 vt0 = pack8(yf), vt1 = pack8(yf + 8);
+      accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt0, ph[0], accO[db], 0, 0, 0);
+      accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt1, ph[1], accO[db], 0, 0, 0);
+      accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt0, pl[0], accO[db], 0, 0, 0);
+      accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt1, pl[1], accO[db], 0, 0, 0);
+    }
+    load(Vg, j + kWaves, rv);
+  }
+
+  wsum += __shfl_xor(wsum, 32, kWave);      // the other half's token rows
+  z -= z_lost;
+  z += __shfl_xor(z, 32, kWave);
+  if (half == 0) {
+    sm_m[wave][col] = m_run;
+    sm_z[wave][col] = z;
+    sm_w[wave][col] = wsum;
+  }
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(&sm_o[wave][col][32 * db + 8 * g + 4 * half]) =
+          make_float4(accO[db][4 * g], accO[db][4 * g + 1], accO[db][4 * g + 2], accO[db][4 * g + 3]);
+  }
+  __syncthreads();
+  // thread: four dimensions of a query row
+  for (int x = tid; x < R * (D / 4); x += kThreads) {
+    const int q = x / (D / 4), d = x % (D / 4) * 4;
+    float m = sm_m[0][q];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, sm_m[w][q]);
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    float zs = 0.f, ws = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float mw = sm_m[w][q];
+      const float f = mw == m ? 1.f : ex2(mw - m_safe);
+      const float4 ow = *reinterpret_cast<const float4*>(&sm_o[w][q][d]);
+      o.x = fmaf(f, ow.x, o.x);
+      o.y = fmaf(f, ow.y, o.y);
+      o.z = fmaf(f, ow.z, o.z);
+      o.w = fmaf(f, ow.w, o.w);
+      zs = fmaf(f, sm_z[w][q], zs);
+      ws = fmaf(f, sm_w[w][q], ws);
+    }
+    *reinterpret_cast<float4*>(o_part + ((size_t)blockIdx.x * R + q) * D + d) = o;
+    if (d == 0) {
+      p_part[(size_t)blockIdx.x * R + q] = ws;
+      if (c_row == nullptr) stat_part[(size_t)blockIdx.x * R + q] = make_float2(m, zs);
     }
   }
 }
@@ -903,6 +1089,184 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   }
 }
 
+// The same for up to 32 query rows: the wavefronts take the piece's tiles in turn, each with all query rows and its operands
+// straight from memory, as in pq_out_narrow_kernel; a tile's sums are whole in its wavefront.
+template <int D, bool COUNTS, typename Tab>
+__global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
+    const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
+    const uint16_t* __restrict__ o_hi,
+    const uint16_t* __restrict__ o_lo, const float* __restrict__ oo, float* a_tok, float* c_edge, const int split) {
+  constexpr int KS = D / 16;
+  constexpr int ROWB = D * 2;
+  constexpr int STRIDE = kTile - 1;         // output rows per tile: the last row only serves as "next token"
+  __shared__ int sm_marked;
+  __shared__ __attribute__((aligned(16))) float sm_negc[kNarrowRows], sm_oo[kNarrowRows];
+  __shared__ __attribute__((aligned(16))) int sm_lim[kNarrowRows];
+  __shared__ RedoSmem<D> sm_redo;
+
+  const int ui = find_unit(tab, (int)blockIdx.x >> split);
+  const Unit un = tab.unit(ui);
+  int t0, t1;
+  piece_range(un, blockIdx.x, split, t0, t1);
+  if (t0 >= t1) return;                     // nothing left of the chunk for this piece
+  const int ntiles = (t1 - t0 + STRIDE - 1) / STRIDE;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int col = lane % 32, half = lane / 32;
+  const int R = sh.R;
+  const float Rf = (float)R;
+  const float sl2 = sh.scale_log2;
+  const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
+  const unsigned char* Vg = reinterpret_cast<const unsigned char*>(V + (size_t)un.in_row * D);
+  float* At = a_tok + un.in_row;
+  float* Ce = c_edge + un.in_row;
+  float* Al = sh.alpha_out != nullptr ? sh.alpha_out + un.in_row : nullptr;
+  const int32_t* cnt = COUNTS ? counts_in + un.in_row : nullptr;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const uint32_t lane_at = (uint32_t)col * ROWB + (uint32_t)half * 16;
+
+  auto tile_first = [&](int j) { return t0 + j * STRIDE; };
+  auto tile_base = [&](int j) { return min(tile_first(min(j, ntiles - 1)), un.len - kTile); };
+  auto load = [&](const unsigned char* base, int j, uint4* r) {
+    const unsigned char* src = base + (size_t)tile_base(j) * ROWB;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) r[kk] = *reinterpret_cast<const uint4*>(src + (lane_at + 32u * kk));
+    asm volatile("" ::: "memory");
+  };
+  uint4 rk[KS], rv[KS];
+  load(Kg, wave, rk);
+  load(Vg, wave, rv);
+
+  bf16x8 bq[KS], boh[KS], bol[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, col, col < R, kk, half);
+    boh[kk] = row_operand<D>(o_hi + (size_t)un.index * R * D, col, col < R, kk, half);
+    bol[kk] = row_operand<D>(o_lo + (size_t)un.index * R * D, col, col < R, kk, half);
+  }
+  if (tid == 0) sm_marked = 0;
+  if (tid < kNarrowRows) {
+    sm_negc[tid] = (tid < R) ? -c_row[(size_t)un.index * R + tid] : -INFINITY;   // exp2(-inf) = 0: no such row
+    sm_oo[tid] = (tid < R) ? oo[(size_t)un.index * R + tid] : 0.f;
+    sm_lim[tid] = last_seen_row(sh.causal, un.len, tid);
+  }
+  __syncthreads();
+
+  // the value of the next lane (the next token's; the last column's is not used)
+  auto next_f = [](float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xF, 0xF, true));
+  };
+  auto next_u = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, true); };
+  for (int j = wave; j < ntiles; j += kWaves) {
+    const int base = tile_base(j), shift = tile_first(j) - base;
+    float cc = 1.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
+    if (COUNTS) {
+      cc = (float)cnt[base + col];
+      ic = __builtin_amdgcn_rcpf(cc);
+    }
+    f32x16 accS = zero;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      accS = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[kk], as_bf16x8(rk[kk]), accS, 0, 0, 0);
+    load(Kg, j + kWaves, rk);
+    f32x16 accX;                            // ||o||^2 - 2 v.o (COUNTS: -2 V.o, scaled below)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 o4 = *reinterpret_cast<const float4*>(&sm_oo[8 * g + 4 * half]);
+      accX[4 * g] = COUNTS ? 0.f : o4.x;
+      accX[4 * g + 1] = COUNTS ? 0.f : o4.y;
+      accX[4 * g + 2] = COUNTS ? 0.f : o4.z;
+      accX[4 * g + 3] = COUNTS ? 0.f : o4.w;
+    }
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(boh[kk], as_bf16x8(rv[kk]), accX, 0, 0, 0);
+      accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bol[kk], as_bf16x8(rv[kk]), accX, 0, 0, 0);
+    }
+    // squared norm of the row and its product with the next one: this lane's half of the dimensions, then both
+    float vv = 0.f, vd = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      const uint4 a = rv[kk];
+      vv = dot2(a.x, a.x, vv); vd = dot2(a.x, next_u(a.x), vd);
+      vv = dot2(a.y, a.y, vv); vd = dot2(a.y, next_u(a.y), vd);
+      vv = dot2(a.z, a.z, vv); vd = dot2(a.z, next_u(a.z), vd);
+      vv = dot2(a.w, a.w, vv); vd = dot2(a.w, next_u(a.w), vd);
+    }
+    load(Vg, j + kWaves, rv);
+    vv += __shfl_xor(vv, 32, kWave);
+    vd += __shfl_xor(vd, 32, kWave);
+    if (COUNTS) {
+      vv = vv * ic * ic;
+      vd = vd * ic * next_f(ic);
+    }
+    const float vp = fmaf(2.f, vd, vv + next_f(vv));                       // ||v_t + v_{t+1}||^2
+    const int t_abs = base + col;
+    float sumA = 0.f, sumC = 0.f, sumP = 0.f;
+    float leastA = INFINITY, leastC = INFINITY;
+    auto rows = [&](auto tail_tag) {        // the terms of pq_norms_kernel
+      constexpr bool TAIL = decltype(tail_tag)::value;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int q0 = 8 * g + 4 * half;
+        const float4 nc4 = *reinterpret_cast<const float4*>(&sm_negc[q0]);
+        const float nc[4] = {nc4.x, nc4.y, nc4.z, nc4.w};
+        float ov[4] = {0.f, 0.f, 0.f, 0.f};
+        if (COUNTS) {
+          const float4 o4 = *reinterpret_cast<const float4*>(&sm_oo[q0]);
+          ov[0] = o4.x; ov[1] = o4.y; ov[2] = o4.z; ov[3] = o4.w;
+        }
+        int lim[4] = {0, 0, 0, 0};
+        if (TAIL) {
+          const int4 l4 = *reinterpret_cast<const int4*>(&sm_lim[q0]);
+          lim[0] = l4.x; lim[1] = l4.y; lim[2] = l4.z; lim[3] = l4.w;
+        }
+        float d2s[4], p2s[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int v = 4 * g + i;
+          float a = ex2(fmaf(accS[v], sl2, nc[i]));
+          if (TAIL && t_abs > lim[i]) a = 0.f;
+          sumP += a;
+          if (COUNTS) a *= cc;
+          const float x = COUNTS ? fmaf(accX[v], ic, ov[i]) : accX[v];
+          const float a_n = next_f(a), x_n = next_f(x);
+          const float d2 = vv + x;
+          const float p2 = fmaf(2.f, x + x_n, vp);
+          sumA = fmaf(a * fabsf(fmaf(-2.f * Rf, a, 1.f)), __builtin_amdgcn_sqrtf(fabsf(d2)), sumA);
+          sumC = fmaf(a * a_n, __builtin_amdgcn_sqrtf(fabsf(p2)), sumC);
+          d2s[i] = d2;
+          p2s[i] = p2;
+        }
+        leastA = min3(min3(leastA, d2s[0], d2s[1]), d2s[2], d2s[3]);
+        leastC = min3(min3(leastC, p2s[0], p2s[1]), p2s[2], p2s[3]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (sh.causal > 0 && base + kTile > un.len - sh.causal + 1) rows(std::true_type{});
+    else rows(std::false_type{});
+    int redo = (leastA < kCancel * vv || leastC < kCancel * vp) ? 1 : 0;     // see pq_norms_kernel
+    redo |= __shfl_xor(redo, 32, kWave);
+    sumA += __shfl_xor(sumA, 32, kWave);    // the other half's 16 query rows
+    sumC += __shfl_xor(sumC, 32, kWave);
+    sumP += __shfl_xor(sumP, 32, kWave);
+    if (half == 0 && col >= shift && col <= shift + STRIDE - 1 && t_abs < t1) {
+      if (redo) sm_marked = 1;
+      At[t_abs] = redo ? -sumA : sumA;      // (sumA >= 0; -0 counts)
+      Ce[t_abs] = col == kTile - 1 ? 0.f : sumC * Rf;        // (only the unit's last token: it has no next one)
+      if (Al != nullptr) Al[t_abs] = COUNTS ? sumP * cc : sumP;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): this wavefront's A_t and C_t are out
+  __syncthreads();
+  if (sm_marked) {
+    for (int t = t0; t < t1; t += kRedoSpan) {
+      redo_marked<D, COUNTS>(sh, un, t, min(t1, t + kRedoSpan), Q, K, V, counts_in, c_row, o_hi, o_lo, a_tok, c_edge, sm_redo);
+      __syncthreads();
+    }
+  }
+}
+
 template <int D, bool COUNTS>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const void* V,
                     const int32_t* counts_in, const float* c_row, float* o_part, uint16_t* o_hi, uint16_t* o_lo,
@@ -919,10 +1283,16 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   float2* stat_part = reinterpret_cast<float2*>(o_part + (size_t)grid.x * sh.R * D);   // behind the launch's partials
   float* p_part = reinterpret_cast<float*>(stat_part + (size_t)grid.x * sh.R);
   const bool own_rows = sh.c_row_out != nullptr;            // the normalisers come from here
+  const bool narrow = sh.R <= kNarrowRows;                  // (figures at pq_out_narrow_kernel)
   launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                       (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
-                       stat_part, split);
+    if (narrow)
+      hipLaunchKernelGGL((pq_out_narrow_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                         (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
+                         stat_part, split);
+    else
+      hipLaunchKernelGGL((pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                         (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
+                         stat_part, split);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -932,8 +1302,12 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                       (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+    if (narrow)
+      hipLaunchKernelGGL((pq_norms_narrow_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                         (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+    else
+      hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
+                         (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
   });
   return hipGetLastError();
 }
