@@ -189,7 +189,8 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
     // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
     // better in more rounds (128 ragged units 1029 -> 1081).  fp32 above 64 rows, of whose workgroups 512 run at once up to 128
-    // rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89.
+    // rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89; not with chunks below 192 tokens
+    // (8 of 8192: 71.4 with two workgroups of 128 per compute unit, 69.9 with one of 256).
     const int rows = plan->shape.R;
     // Per-query calls: those whose alpha_bar comes from kvs_score's two sweeps have its chunks, and so its bits (fp32, 8 units of
     // 8192 1158 -> 919 us, 4 of 3000 with 32 rows 301 -> 170; 100 of 9000, one bf16 row 547 -> 436).  The others' chunks are
@@ -250,7 +251,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
           }
           w = (w + grain - 1) / grain * grain;
           while (w <= kMaxRoundChunkLen && workgroups(w) > k * at_once) w += grain;
-          if (w > kMaxRoundChunkLen || w < (split ? kMinChunkLen / 2 : kMinChunkLen)) continue;
+          if (w > kMaxRoundChunkLen || w < (split ? kMinChunkLen * 3 / 4 : kMinChunkLen)) continue;
           if (best == 0 || k * (w + once) < best) {
             best = k * (w + once);
             longer = w;
