@@ -36,7 +36,8 @@
 namespace kvs {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;         // threads of a workgroup, and
+constexpr int kMoreThreads = 512;     // of one that has a compute unit to itself (see launch_merge_k)
 #ifndef KVS_MERGE_PREFETCH
 #define KVS_MERGE_PREFETCH 3
 #endif
@@ -48,10 +49,11 @@ __device__ __forceinline__ float group_sum(float x) {
 }
 
 // First token t >= from that starts a slot (t == 0 or mask[t-1] == 0); n if there is none.
-// Called by the whole workgroup; sm is 1 + kThreads / kWave ints of scratch.
+// Called by the whole workgroup of THREADS threads; sm is THREADS / kWave ints of scratch.
+template <int THREADS>
 __device__ __forceinline__ int first_slot_start(const uint8_t* __restrict__ mk, int from, int n, int* sm) {
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  for (int base = from;; base += kThreads) {
+  for (int base = from;; base += THREADS) {
     const int t = base + tid;
     const bool start = (t >= n) || (t == 0) || (mk[t - 1] == 0);
     const uint64_t bal = __ballot(start);
@@ -59,15 +61,15 @@ __device__ __forceinline__ int first_slot_start(const uint8_t* __restrict__ mk, 
     __syncthreads();
     int best = 0x7fffffff;
 #pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) best = min(best, sm[w]);
+    for (int w = 0; w < THREADS / kWave; ++w) best = min(best, sm[w]);
     __syncthreads();
     if (best != 0x7fffffff) return min(best, n);
   }
 }
 
 // NORMS: `alpha_bar` holds A_t and `c_edge` C_t (o_bar and o_part are not used); otherwise c_edge is not used.
-template <typename T, int D, bool STREAM, bool COUNTS, bool NORMS, typename Tab>
-__global__ __launch_bounds__(kThreads) void merge_kernel(
+template <typename T, int D, bool STREAM, bool COUNTS, bool NORMS, int THREADS, typename Tab>
+__global__ __launch_bounds__(THREADS) void merge_kernel(
     const Tab tab, const Shape sh, const T* __restrict__ K, const T* __restrict__ V,
     const int32_t* __restrict__ counts_in, const float* __restrict__ alpha_bar, const float* __restrict__ o_bar, const float* __restrict__ o_part,
     const float* __restrict__ c_edge,
@@ -75,14 +77,15 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     T* __restrict__ V_out, int32_t* __restrict__ counts, const int split) {
   constexpr int EPL = Piece<T>::N;
   constexpr int LPR = D / EPL;
-  constexpr int GROUPS = kThreads / LPR;
+  constexpr int GROUPS = THREADS / LPR;
+  constexpr int WAVES = THREADS / kWave;
   constexpr int FRAG = 2 * D + 4;           // accK[D], accV[D], U, rows, first token, cardinality
 
   __shared__ float sm_frag[GROUPS][2][FRAG];   // [g][0]: head fragment, [g][1]: tail / through fragment
   __shared__ int sm_flag[GROUPS];              // bit 0: head fragment ends here, 1: through, 2: tail starts here
   __shared__ int sm_tail_slot[GROUPS];
-  __shared__ int sm_scan[2 * (kThreads / kWave)];
-  __shared__ float sm_obar[kThreads / D][D];
+  __shared__ int sm_scan[2 * WAVES];
+  __shared__ float sm_obar[THREADS / D][D];
 
   // 2^split workgroups share a range of kMergeTokens tokens
   const int range = (int)blockIdx.x >> split;
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   const int ta = nom_a + tid, tb = nom_b + tid;
   const bool start_a = (ta >= n) || (ta == 0) || (mk[ta - 1] == 0);
   const bool start_b = (tb >= n) || (tb == 0) || (mk[tb - 1] == 0);
-  constexpr int PARTS = kThreads / D;          // threads per channel when adding up the chunk sums
+  constexpr int PARTS = THREADS / D;          // threads per channel when adding up the chunk sums
   constexpr int PER = kMaxChunks / PARTS;
   float part_sum = 0.f;
   if (!NORMS && o_bar == nullptr) {
@@ -132,17 +135,17 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     const uint64_t ba = __ballot(start_a), bb = __ballot(start_b);
     if (lane == 0) {
       sm_scan[wave] = ba ? nom_a + wave * kWave + (__ffsll((long long)ba) - 1) : 0x7fffffff;
-      sm_scan[4 + wave] = bb ? nom_b + wave * kWave + (__ffsll((long long)bb) - 1) : 0x7fffffff;
+      sm_scan[WAVES + wave] = bb ? nom_b + wave * kWave + (__ffsll((long long)bb) - 1) : 0x7fffffff;
     }
   }
   __syncthreads();
   int A = 0x7fffffff, B = 0x7fffffff;
 #pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) { A = min(A, sm_scan[w]); B = min(B, sm_scan[4 + w]); }
+  for (int w = 0; w < THREADS / kWave; ++w) { A = min(A, sm_scan[w]); B = min(B, sm_scan[WAVES + w]); }
   __syncthreads();
   // a slot longer than the probe window: keep looking (rare)
-  A = (A == 0x7fffffff) ? first_slot_start(mk, nom_a + kThreads, n, sm_scan) : min(A, n);
-  B = (B == 0x7fffffff) ? first_slot_start(mk, nom_b + kThreads, n, sm_scan) : min(B, n);
+  A = (A == 0x7fffffff) ? first_slot_start<THREADS>(mk, nom_a + THREADS, n, sm_scan) : min(A, n);
+  B = (B == 0x7fffffff) ? first_slot_start<THREADS>(mk, nom_b + THREADS, n, sm_scan) : min(B, n);
   if (A >= B) return;                          // the whole nominal range lies inside a slot owned earlier
 
   // Unit-wide base pointers (uniform: they live in scalar registers) plus 32-bit byte offsets per lane:
@@ -464,12 +467,29 @@ static hipError_t launch_merge_k(const UnitTable& tab, const Shape& sh, const vo
                                  const int32_t* counts_in, const float* alpha_bar, const float* o_bar,
                                  const float* o_part, const uint8_t* edge_mask, const int32_t* slot, void* K_out,
                                  void* V_out, int32_t* counts, hipStream_t stream, const float* c_edge = nullptr) {
-  const int split = merge_split(tab.total_mblocks);
-  launch_with_table(tab, [&](const auto& t) {
-    hipLaunchKernelGGL((merge_kernel<T, D, STREAM, COUNTS, NORMS, KVS_TABLE_TYPE(t)>), dim3(tab.total_mblocks << split), dim3(kThreads), 0,
-                       stream, t, sh, (const T*)K, (const T*)V, counts_in, alpha_bar, o_bar, o_part, c_edge, edge_mask,
-                       slot, (T*)K_out, (T*)V_out, counts, split);
-  });
+  // 129 to 256 ranges of 128 channels: one workgroup of eight wavefronts per range instead of one or two of four, which hides
+  // more of the rows' latency and forms the range's ends and o_bar once.  Steps, before -> after (us): 8 units of 8192
+  // 37.8 -> 37.3, fp32 69.8 -> 67.5; 8 of 7000 36.2 -> 35.5, fp32 65.0 -> 63.9; one of 65000 65.9 -> 64.8; per query, 8 of
+  // 6000 75.7 -> 74.8.  Not fewer ranges (8 of 4096, cut in two, 29.1, so 30.5) nor more (8 of 12000 47.2, so 48.1), and not
+  // 64 channels, where a lane group walks half as many tokens to begin with (8 of 8000 34.0, so 35.1).
+  const bool more = D == 128 && !STREAM && tab.total_mblocks > 128 && tab.total_mblocks <= 256;
+  const int split = more ? 0 : merge_split(tab.total_mblocks);
+  // (256 ranges are at most 65536 rows of 1 KB for K and V together: never enough for the streaming policy)
+  auto launch = [&](auto threads) {
+    constexpr int THREADS = decltype(threads)::value;
+    launch_with_table(tab, [&](const auto& t) {
+      hipLaunchKernelGGL((merge_kernel<T, D, STREAM, COUNTS, NORMS, THREADS, KVS_TABLE_TYPE(t)>), dim3(tab.total_mblocks << split),
+                         dim3(THREADS), 0, stream, t, sh, (const T*)K, (const T*)V, counts_in, alpha_bar, o_bar, o_part,
+                         c_edge, edge_mask, slot, (T*)K_out, (T*)V_out, counts, split);
+    });
+  };
+  if constexpr (D == 128 && !STREAM) {
+    if (more) {
+      launch(std::integral_constant<int, kMoreThreads>{});
+      return hipGetLastError();
+    }
+  }
+  launch(std::integral_constant<int, kThreads>{});
   return hipGetLastError();
 }
 
