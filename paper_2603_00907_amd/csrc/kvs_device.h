@@ -536,7 +536,7 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
 // 58.5 in two, 65.4 in four) and no pieces below 64 rows (8 of 2048, 128 chunks of 128: 39.3 in two, 41.0 uncut, 47.7 in four).
 constexpr int kMaxPqPieces = 1024;
 constexpr int kMaxPqSplit = 3;
-constexpr int kPqNarrowRows = 32;         // up to here the per-query kernels are the narrow ones (bf16)
+constexpr int kPqNarrowRows = 32;         // up to here a tile takes one wavefront of the per-query kernels (bf16)
 inline int pq_split(long long chunks, long long rows, long long longest, int R, int D) {
   const bool narrow = R <= kPqNarrowRows, light = !narrow && (R <= 64 || D == 64);
   int split = 0;

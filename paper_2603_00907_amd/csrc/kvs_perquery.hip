@@ -43,7 +43,7 @@
 // products still run on the stored rows; c_t multiplies the term in the sums over a row (a logarithm in the exponent would
 // round with its size), the weight of the Value SUM is the term of ONE token, and 1 / c_t scales
 // the product V_t . o and the squared norms afterwards.
-// A workgroup has four wavefronts; with more than 32 query rows wavefront w owns query rows 32w .. 32w+31 of a pass of 128
+// A workgroup has four wavefronts; but for the narrow kernels' few query rows wavefront w owns query rows 32w .. 32w+31 of a pass of 128
 // rows and keeps their operands in registers; all four walk the same K and V tiles, staged through LDS (XOR-swizzled
 // 16-byte pieces, as in the score kernels).  Results do not depend on timing: no atomics, fixed orders.
 #include <algorithm>
@@ -366,17 +366,16 @@ __global__ __launch_bounds__(kThreads, KVS_PQ_OUT_OCC) void pq_out_kernel(
   }
 }
 
-// The same for up to 32 query rows: the kernel above gives every wavefront 32 rows of its own, so three of four would
-// multiply rows that don't exist.  Here the wavefronts take the piece's tiles in turn, each with all query rows and its
-// operands straight from memory (nothing is shared, so nothing goes through LDS and nothing waits for a barrier), and
+// The same for few query rows: the kernel above gives every wavefront 32 rows of its own, so with up to 32 three of four would
+// multiply rows that don't exist.  Here a tile takes RB wavefronts, one per block of 32 rows, and the workgroup's 4 / RB teams
+// take the piece's tiles in turn, every wavefront with its operands straight from memory (nothing is shared, so nothing goes through LDS and nothing waits for a barrier), and
 // add their sums up at the end, in wavefront order, each brought to the largest of their references.
 // The registers of the K and V operands are refilled for the wavefront's next tile as soon as they have been multiplied.
 // Bound by memory where there are many pieces, else by the wavefronts' chains.  Steps, before -> with both narrow kernels (us):
 // 32 rows, 100 units of 21000 tokens 902 -> 749 (two passes over K and V and the merge of it at 5 TB/s: 680), 8 of 32768
 // 127 -> 108, 8 of 8192 61 -> 50 (see pq_split); head dim 64, 12 of 29384 130 -> 88; 16 rows and cardinalities, 40 of 20000 510 -> 343;
 // 7 rows, 128 ragged ones of 700 to 1500 110 -> 90.  One unit of 1000 tokens: 29.3 -> 27.5.
-constexpr int kNarrowRows = kPqNarrowRows;
-template <int D, bool COUNTS, typename Tab>
+template <int D, bool COUNTS, int RB, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
@@ -384,8 +383,9 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
   constexpr int ROWB = D * 2;
-  __shared__ __attribute__((aligned(16))) float sm_o[kWaves][kNarrowRows][D + 4];
-  __shared__ float sm_m[kWaves][kNarrowRows], sm_z[kWaves][kNarrowRows], sm_w[kWaves][kNarrowRows];
+  constexpr int TEAMS = kWaves / RB;
+  __shared__ __attribute__((aligned(16))) float sm_o[kWaves][32][D + 4];
+  __shared__ float sm_m[kWaves][32], sm_z[kWaves][32], sm_w[kWaves][32];
 
   const int ui = find_unit(tab, (int)blockIdx.x >> split);
   const Unit un = tab.unit(ui);
@@ -394,6 +394,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
   const int ntiles = (t1 - t0 + kTile - 1) / kTile;          // (a piece may be empty: it leaves zeros)
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int col = lane % 32, half = lane / 32;
+  const int team = wave / RB, qrow = 32 * (wave % RB) + col;
   const int R = sh.R;
   const float sl2 = sh.scale_log2;
   const unsigned char* Kg = reinterpret_cast<const unsigned char*>(K + (size_t)un.in_row * D);
@@ -423,21 +424,21 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
     asm volatile("" ::: "memory");          // issue them here: sunk to their use they would be waited for at once
   };
 
-  const bool ok = col < R;
+  const bool ok = qrow < R;
   bf16x8 bq[KS];
 #pragma unroll
-  for (int kk = 0; kk < KS; ++kk) bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, col, ok, kk, half);
-  float m_run = !ok ? INFINITY : c_row != nullptr ? c_row[(size_t)un.index * R + col] : -INFINITY;
+  for (int kk = 0; kk < KS; ++kk) bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, qrow, ok, kk, half);
+  float m_run = !ok ? INFINITY : c_row != nullptr ? c_row[(size_t)un.index * R + qrow] : -INFINITY;
   float z = 0.f, z_lost = 0.f, wsum = 0.f;
-  const int lim = last_seen_row(sh.causal, un.len, col);
+  const int lim = last_seen_row(sh.causal, un.len, qrow);
   f32x16 accO[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) accO[db] = zero;
 
   uint4 rk[KS], rv[KS];
-  load(Kg, wave, rk);
-  load(Vg, wave, rv);
-  for (int j = wave; j < ntiles; j += kWaves) {
+  load(Kg, team, rk);
+  load(Vg, team, rv);
+  for (int j = team; j < ntiles; j += TEAMS) {
     const int base = tile_base(j);
     const int shift = t0 + j * kTile - base;                 // leading rows that belong to the tile before
     float cc[16];
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
     f32x16 acc = zero;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(rk[kk]), bq[kk], acc, 0, 0, 0);
-    load(Kg, j + kWaves, rk);
+    load(Kg, j + TEAMS, rk);
     float p[16];
     const bool masked = shift > 0 || (sh.causal > 0 && base + kTile > un.len - sh.causal + 1);
     auto seen = [&](int v) {
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
       accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt0, pl[0], accO[db], 0, 0, 0);
       accO[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt1, pl[1], accO[db], 0, 0, 0);
     }
-    load(Vg, j + kWaves, rv);
+    load(Vg, j + TEAMS, rv);
   }
 
   wsum += __shfl_xor(wsum, 32, kWave);      // the other half's token rows
@@ -526,23 +527,24 @@ __global__ __launch_bounds__(kThreads, 2) void pq_out_narrow_kernel(
   // thread: four dimensions of a query row
   for (int x = tid; x < R * (D / 4); x += kThreads) {
     const int q = x / (D / 4), d = x % (D / 4) * 4;
-    float m = sm_m[0][q];
+    const int first = q / 32, qw = q % 32;  // the first wavefront with this row, and its row there
+    float m = sm_m[first][qw];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, sm_m[w][q]);
+    for (int w = RB; w < kWaves; w += RB) m = fmaxf(m, sm_m[first + w][qw]);
     const float m_safe = m == -INFINITY ? 0.f : m;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     float zs = 0.f, ws = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float mw = sm_m[w][q];
+    for (int w = 0; w < kWaves; w += RB) {
+      const float mw = sm_m[first + w][qw];
       const float f = mw == m ? 1.f : ex2(mw - m_safe);
-      const float4 ow = *reinterpret_cast<const float4*>(&sm_o[w][q][d]);
+      const float4 ow = *reinterpret_cast<const float4*>(&sm_o[first + w][qw][d]);
       o.x = fmaf(f, ow.x, o.x);
       o.y = fmaf(f, ow.y, o.y);
       o.z = fmaf(f, ow.z, o.z);
       o.w = fmaf(f, ow.w, o.w);
-      zs = fmaf(f, sm_z[w][q], zs);
-      ws = fmaf(f, sm_w[w][q], ws);
+      zs = fmaf(f, sm_z[first + w][qw], zs);
+      ws = fmaf(f, sm_w[first + w][qw], ws);
     }
     *reinterpret_cast<float4*>(o_part + ((size_t)blockIdx.x * R + q) * D + d) = o;
     if (d == 0) {
@@ -1089,9 +1091,9 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_kernel(
   }
 }
 
-// The same for up to 32 query rows: the wavefronts take the piece's tiles in turn, each with all query rows and its operands
-// straight from memory, as in pq_out_narrow_kernel; a tile's sums are whole in its wavefront.
-template <int D, bool COUNTS, typename Tab>
+// The same for few query rows: RB wavefronts to a tile, and their operands straight from memory, as in pq_out_narrow_kernel.
+// With one a tile's sums are whole in its wavefront and nothing waits.
+template <int D, bool COUNTS, int RB, typename Tab>
 __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ counts_in, const float* __restrict__ c_row,
@@ -1100,9 +1102,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
   constexpr int KS = D / 16;
   constexpr int ROWB = D * 2;
   constexpr int STRIDE = kTile - 1;         // output rows per tile: the last row only serves as "next token"
+  constexpr int TEAMS = kWaves / RB, ROWS = 32 * RB;
   __shared__ int sm_marked;
-  __shared__ __attribute__((aligned(16))) float sm_negc[kNarrowRows], sm_oo[kNarrowRows];
-  __shared__ __attribute__((aligned(16))) int sm_lim[kNarrowRows];
+  __shared__ __attribute__((aligned(16))) float sm_negc[ROWS], sm_oo[ROWS];
+  __shared__ __attribute__((aligned(16))) int sm_lim[ROWS];
+  __shared__ float sm_out[RB > 1 ? 2 : 1][RB > 1 ? kWaves : 1][3][kTile];    // sums of A, C and alpha / R over a wavefront's rows
   __shared__ RedoSmem<D> sm_redo;
 
   const int ui = find_unit(tab, (int)blockIdx.x >> split);
@@ -1113,6 +1117,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
   const int ntiles = (t1 - t0 + STRIDE - 1) / STRIDE;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int col = lane % 32, half = lane / 32;
+  const int team = wave / RB, rb = wave % RB, qrow = 32 * rb + col;
   const int R = sh.R;
   const float Rf = (float)R;
   const float sl2 = sh.scale_log2;
@@ -1134,18 +1139,18 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
     asm volatile("" ::: "memory");
   };
   uint4 rk[KS], rv[KS];
-  load(Kg, wave, rk);
-  load(Vg, wave, rv);
+  load(Kg, team, rk);
+  load(Vg, team, rv);
 
   bf16x8 bq[KS], boh[KS], bol[KS];
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
-    bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, col, col < R, kk, half);
-    boh[kk] = row_operand<D>(o_hi + (size_t)un.index * R * D, col, col < R, kk, half);
-    bol[kk] = row_operand<D>(o_lo + (size_t)un.index * R * D, col, col < R, kk, half);
+    bq[kk] = row_operand<D>(Q + (size_t)un.index * R * D, qrow, qrow < R, kk, half);
+    boh[kk] = row_operand<D>(o_hi + (size_t)un.index * R * D, qrow, qrow < R, kk, half);
+    bol[kk] = row_operand<D>(o_lo + (size_t)un.index * R * D, qrow, qrow < R, kk, half);
   }
   if (tid == 0) sm_marked = 0;
-  if (tid < kNarrowRows) {
+  if (tid < ROWS) {
     sm_negc[tid] = (tid < R) ? -c_row[(size_t)un.index * R + tid] : -INFINITY;   // exp2(-inf) = 0: no such row
     sm_oo[tid] = (tid < R) ? oo[(size_t)un.index * R + tid] : 0.f;
     sm_lim[tid] = last_seen_row(sh.causal, un.len, tid);
@@ -1157,7 +1162,10 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xF, 0xF, true));
   };
   auto next_u = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, true); };
-  for (int j = wave; j < ntiles; j += kWaves) {
+  // (as many rounds for every wavefront, since those of a team meet in each; one without a tile does the last one again and
+  // leaves it)
+  for (int j = team, round = 0; j - team < ntiles; j += TEAMS, ++round) {
+    if (RB == 1 && j >= ntiles) break;
     const int base = tile_base(j), shift = tile_first(j) - base;
     float cc = 1.f, ic = 1.f;               // COUNTS: this lane's token stands for c tokens, v = V / c
     if (COUNTS) {
@@ -1168,11 +1176,11 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk)
       accS = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[kk], as_bf16x8(rk[kk]), accS, 0, 0, 0);
-    load(Kg, j + kWaves, rk);
+    load(Kg, j + TEAMS, rk);
     f32x16 accX;                            // ||o||^2 - 2 v.o (COUNTS: -2 V.o, scaled below)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 o4 = *reinterpret_cast<const float4*>(&sm_oo[8 * g + 4 * half]);
+      const float4 o4 = *reinterpret_cast<const float4*>(&sm_oo[32 * rb + 8 * g + 4 * half]);
       accX[4 * g] = COUNTS ? 0.f : o4.x;
       accX[4 * g + 1] = COUNTS ? 0.f : o4.y;
       accX[4 * g + 2] = COUNTS ? 0.f : o4.z;
@@ -1193,7 +1201,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
       vv = dot2(a.z, a.z, vv); vd = dot2(a.z, next_u(a.z), vd);
       vv = dot2(a.w, a.w, vv); vd = dot2(a.w, next_u(a.w), vd);
     }
-    load(Vg, j + kWaves, rv);
+    load(Vg, j + TEAMS, rv);
     vv += __shfl_xor(vv, 32, kWave);
     vd += __shfl_xor(vd, 32, kWave);
     if (COUNTS) {
@@ -1208,7 +1216,7 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
       constexpr bool TAIL = decltype(tail_tag)::value;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int q0 = 8 * g + 4 * half;
+        const int q0 = 32 * rb + 8 * g + 4 * half;
         const float4 nc4 = *reinterpret_cast<const float4*>(&sm_negc[q0]);
         const float nc[4] = {nc4.x, nc4.y, nc4.z, nc4.w};
         float ov[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1250,6 +1258,26 @@ __global__ __launch_bounds__(kThreads, 2) void pq_norms_narrow_kernel(
     sumA += __shfl_xor(sumA, 32, kWave);    // the other half's 16 query rows
     sumC += __shfl_xor(sumC, 32, kWave);
     sumP += __shfl_xor(sumP, 32, kWave);
+    if (RB > 1) {                           // the team's other rows (two buffers: one barrier per round)
+      float (&out)[kWaves][3][kTile] = reinterpret_cast<float (&)[2][kWaves][3][kTile]>(sm_out)[round & 1];
+      if (half == 0) {
+        out[wave][0][col] = redo ? -sumA : sumA;
+        out[wave][1][col] = sumC;
+        out[wave][2][col] = sumP;
+      }
+      __syncthreads();
+      sumA = sumC = sumP = 0.f;
+      redo = 0;
+#pragma unroll
+      for (int w = 0; w < RB; ++w) {
+        const float a = out[team * RB + w][0][col];
+        redo |= (int)(__float_as_uint(a) >> 31);
+        sumA += fabsf(a);
+        sumC += out[team * RB + w][1][col];
+        sumP += out[team * RB + w][2][col];
+      }
+      if (rb != 0 || j >= ntiles) continue;
+    }
     if (half == 0 && col >= shift && col <= shift + STRIDE - 1 && t_abs < t1) {
       if (redo) sm_marked = 1;
       At[t_abs] = redo ? -sumA : sumA;      // (sumA >= 0; -0 counts)
@@ -1283,16 +1311,23 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   float2* stat_part = reinterpret_cast<float2*>(o_part + (size_t)grid.x * sh.R * D);   // behind the launch's partials
   float* p_part = reinterpret_cast<float*>(stat_part + (size_t)grid.x * sh.R);
   const bool own_rows = sh.c_row_out != nullptr;            // the normalisers come from here
-  const bool narrow = sh.R <= kNarrowRows;                  // (figures at pq_out_narrow_kernel)
+  // Up to 32 rows both narrow kernels (figures at pq_out_narrow_kernel).  33 to 64 rows, two wavefronts to a tile, with 64
+  // channels (12 units of 29384 135 -> 114 us, one of 1000 35.6 -> 34.8); with 128 channels the outputs' reads of every tile by
+  // two wavefronts cost more than the idle rows (8 of 32768 131 -> 138), and the norms gain from some 256 K tokens on
+  // (8 of 32768 131.3 -> 130.0, 4 of 100000 193 -> 186, 100 of 21000 892 -> 858, 40 of 20000 with cardinalities 446 -> 415;
+  // 4 ragged ones, 150000 tokens, 90.1 -> 92.2, 32 of 3000 85.9 -> 87.8).
+  const bool one = sh.R <= kPqNarrowRows, two = !one && sh.R <= 2 * kPqNarrowRows;
+  const bool narrow_norms = D == 64 || rows >= (1 << 18);
   launch_with_table(tab, [&](const auto& t) {
-    if (narrow)
-      hipLaunchKernelGGL((pq_out_narrow_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                         (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
-                         stat_part, split);
-    else
-      hipLaunchKernelGGL((pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                         (const uint16_t*)K, (const uint16_t*)V, counts_in, own_rows ? nullptr : c_row, o_part, p_part,
-                         stat_part, split);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, 0, stream, t, sh, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, counts_in,
+                         own_rows ? nullptr : c_row, o_part, p_part, stat_part, split);
+    };
+    if constexpr (D == 64) {
+      if (two) return launch(pq_out_narrow_kernel<D, COUNTS, 2, KVS_TABLE_TYPE(t)>);
+    }
+    if (one) return launch(pq_out_narrow_kernel<D, COUNTS, 1, KVS_TABLE_TYPE(t)>);
+    launch(pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>);
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1302,12 +1337,13 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   });
   if ((e = hipGetLastError()) != hipSuccess) return e;
   launch_with_table(tab, [&](const auto& t) {
-    if (narrow)
-      hipLaunchKernelGGL((pq_norms_narrow_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                         (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
-    else
-      hipLaunchKernelGGL((pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh, (const uint16_t*)Q,
-                         (const uint16_t*)K, (const uint16_t*)V, counts_in, c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, 0, stream, t, sh, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, counts_in,
+                         c_row, o_hi, o_lo, oo, a_tok, c_edge, split);
+    };
+    if (one) return launch(pq_norms_narrow_kernel<D, COUNTS, 1, KVS_TABLE_TYPE(t)>);
+    if (two && narrow_norms) return launch(pq_norms_narrow_kernel<D, COUNTS, 2, KVS_TABLE_TYPE(t)>);
+    launch(pq_norms_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>);
   });
   return hipGetLastError();
 }
