@@ -531,6 +531,8 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
 // because a unit has at most 64, cuts them as long as the longest piece is a larger share of the rows than that (3 ragged
 // units, 255000 rows, 128 query rows, 188 chunks: 187 us in two, 250 uncut; 14 units, where all chunks are as long: 191
 // against 175): not below 128 rows, and into at most kMaxPqPieces.
+// No second workgroup for pieces below 64 rows (8 of 2048, 64 query rows: 256 pieces of 64 46.8 us, 512 of 32 50.6; 4 of 4000 44.2
+// and 48.8; head dim 64, 128 rows, 8 of 2048 45.8 and 49.5).
 // Up to 32 rows the four wavefronts take tiles of their own, and a piece costs its combination of their sums: no second
 // workgroup on a CU (8 units of 8192, 256 chunks: 50.4 us uncut, 59.0 in two, with pq_out_kernel 61.2; 2 of 30000, 118 chunks:
 // 58.5 in two, 65.4 in four) and no pieces below 64 rows (8 of 2048, 128 chunks of 128: 39.3 in two, 41.0 uncut, 47.7 in four).
@@ -542,7 +544,7 @@ inline int pq_split(long long chunks, long long rows, long long longest, int R, 
   int split = 0;
   while (split < kMaxPqSplit) {
     const long long pieces = chunks << (split + 1);
-    const bool few = pieces <= (light ? 512 : 256);
+    const bool few = pieces <= (light && (longest >> (split + 1)) >= 64 ? 512 : 256);
     const bool uneven = (longest >> split) * (light || narrow ? 320 : 240) > rows && (longest >> split) > 256;
     if ((longest >> (split + 1)) < (narrow ? 64 : 32)) break;               // (a tile's rows)
     if (!few && !(uneven && pieces <= kMaxPqPieces)) break;
