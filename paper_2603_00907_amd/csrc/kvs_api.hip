@@ -184,7 +184,9 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     // Whole rounds of as few workgroups as run at once: a workgroup of the kernels for more than 128 rows spends 6 to 12 us
     // on what it does once for its chunk (the time of 160 to 310 tokens), a launch whose last round is half full half a
     // round.  Of one to four rounds with the shortest chunks that fit them, the one whose rounds take the least time, counted
-    // in tokens.  Sweeps of 8 units of 131072 tokens, 512 rows, 256 workgroups at a time: two rounds 167 + 200 us, one
+    // in tokens; no longer chunks where that makes no fewer rounds (16 units of 4000 to 40000 tokens, 224 rows, per query 302 us,
+    // with 446 chunks of 768 instead of 485 of 704 308; 16 of 10000, 128 rows, per query 117, with 432 of 384 instead of 512 of
+    // 320 122).  Sweeps of 8 units of 131072 tokens, 512 rows, 256 workgroups at a time: two rounds 167 + 200 us, one
     // 159 + 194; 48 of 32768 with 224 rows, 512 at a time: 768 workgroups 132 + 166, 480 126 + 162.  Steps: 48 of 16384, 224
     // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
     // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
@@ -195,13 +197,15 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     // Per-query calls: those whose alpha_bar comes from kvs_score's two sweeps have its chunks, and so its bits (fp32, 8 units of
     // 8192 1158 -> 919 us, 4 of 3000 with 32 rows 301 -> 170; 100 of 9000, one bf16 row 547 -> 436).  The others' chunks are
     // the pieces of their own kernels, which cut them finer in small launches (48 of 16384, 224 rows 821 -> 664; 64 of 32768,
-    // 128 rows 913 -> 879; 40 of 32768, 64 rows 598 -> 530; 100 of 21000 927 -> 933; above 256 rows 24 ragged ones lost,
-    // 675 -> 703, and equal ones gained nothing).
+    // 128 rows 927 -> 915; 40 of 32768, 64 rows 608 -> 521; 48 of 3000 to 24000, 224 rows 706 -> 547; above 256 rows 24 ragged
+    // ones lost, 675 -> 703, and equal ones gained nothing).
     const bool pieces = per_query && plan->dtype == KVS_BF16 && rows >= 4;
     const bool rounds = debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
     const bool split = plan->dtype == KVS_F32 && rows > 64;
     const long long at_once = rows > (split ? 128 : 256) ? 256 : 512, once = rows > 128 ? 256 : 128;
-    const int grain = split ? 64 : rows > 256 ? 256 : 128;        // tokens of a stage of those kernels
+    // tokens of a stage of those kernels, or of a tile for each of their four wavefronts; above 32 rows the wavefronts of the
+    // per-query kernels share every tile
+    const int grain = split || (pieces && rows > kPqNarrowRows) ? kWave : rows > 256 ? 256 : 128;
     // Launches that leave compute units without a workgroup when chunks have kMinChunkLen tokens: shorter ones, as long as a
     // compute unit gets no second workgroup, of a tile for each of the four wavefronts that work on tiles of their own, or
     // of one or two tiles that all wavefronts share.  Steps: one fp32 unit of 1024 tokens, 8 rows 26.8 -> 24.3 us; 8 units of
@@ -241,18 +245,27 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
         longer = tiny;
       } else if (rounds && !(pieces && rows > 256) && (equal || rows > 128) &&
                  tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * want)) {
-        long long best = 0;
+        long long best = (workgroups(longer) + at_once - 1) / at_once * (longer + once);
         for (long long k = 1; k <= 4; ++k) {
+          const long long per_unit = k * at_once / (end - first);
+          if (per_unit == 0) continue;
+          // the shortest w, in units of grain, whose workgroups fit (their number never grows with w)
           long long w = (tokens + k * at_once - 1) / (k * at_once);
-          if (equal) {
-            const long long per_unit = k * at_once / (end - first);
-            if (per_unit == 0) continue;
-            w = (plan->units[first].len + per_unit - 1) / per_unit;
+          if (equal) w = (plan->units[first].len + per_unit - 1) / per_unit;
+          w = (w + grain - 1) / grain;
+          if (workgroups(w * grain) > k * at_once) {
+            long long fits = kMaxRoundChunkLen / grain;
+            if (w >= fits || workgroups(fits * grain) > k * at_once) continue;
+            while (fits - w > 1) {
+              const long long mid = (w + fits) / 2;
+              if (workgroups(mid * grain) > k * at_once) w = mid;
+              else fits = mid;
+            }
+            w = fits;
           }
-          w = (w + grain - 1) / grain * grain;
-          while (w <= kMaxRoundChunkLen && workgroups(w) > k * at_once) w += grain;
+          w *= grain;
           if (w > kMaxRoundChunkLen || w < (split ? kMinChunkLen * 3 / 4 : kMinChunkLen)) continue;
-          if (best == 0 || k * (w + once) < best) {
+          if (k * (w + once) < best) {
             best = k * (w + once);
             longer = w;
           }

@@ -12,7 +12,7 @@
 #include "kvs.h"
 #include "kvs_debug.h"
 
-namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); extern bool stub_asks_for_fused; }
+namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); int stub_chunks(); extern bool stub_asks_for_fused; }
 
 static int g_failed = 0;
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); ++g_failed; } } while (0)
@@ -155,6 +155,54 @@ static void values_ride(int nu, int len, int budget, bool rode, int parts) {
   }
 }
 
+// How many score chunks a call on the given units (one launch) is cut into.
+static void chunks_of(std::vector<int32_t> len, int group, int window, int D, kvs_dtype dt, bool per_query, int chunks) {
+  std::vector<int32_t> budget(len);
+  for (int32_t& b : budget) b /= 3;
+  Problem pr(len, budget, group, window, D, dt);
+  const size_t elt = dt == KVS_F32 ? 4 : 2;
+  size_t ws_bytes = 0;
+  EXPECT((per_query ? kvs_per_query_workspace_size(&pr.p, &ws_bytes) : kvs_workspace_size(&pr.p, &ws_bytes)) == KVS_OK);
+  Arena a;
+  void* Q = a.take(len.size() * group * window * D * elt);
+  void* K = a.take((size_t)pr.rows_in * D * elt);
+  void* V = a.take((size_t)pr.rows_in * D * elt);
+  void* Ko = a.take((size_t)pr.rows_out * D * elt);
+  void* Vo = a.take((size_t)pr.rows_out * D * elt);
+  int32_t* cnt = (int32_t*)a.take((size_t)pr.rows_out * 4);
+  void* ws = a.take(ws_bytes);
+  EXPECT((per_query ? kvs_step_per_query(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)
+                    : kvs_step(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)) == KVS_OK);
+  if (kvs::stub_chunks() != chunks) {
+    std::printf("%zu units, the first of %d tokens, %d rows, head dim %d%s%s: %d chunks instead of %d\n", len.size(), len[0],
+                group * window, D, dt == KVS_F32 ? ", fp32" : "", per_query ? ", per query" : "", kvs::stub_chunks(), chunks);
+    EXPECT(!"the launch's chunks");
+  }
+}
+
+// Whole rounds of workgroups: fewer rounds than chunks of the ordinary length would take, or as many with shorter chunks, and
+// never longer ones in as many rounds (512 workgroups at a time here, 256 above 256 rows).
+static void whole_rounds() {
+  auto equal = [](int nu, int len) { return std::vector<int32_t>(nu, len); };
+  chunks_of(equal(48, 16384), 7, 32, 128, KVS_BF16, true, 480);     // 528 would be two rounds
+  chunks_of(equal(48, 16384), 7, 32, 128, KVS_BF16, false, 480);
+  chunks_of(equal(64, 32768), 4, 32, 128, KVS_BF16, false, 512);    // 1024
+  chunks_of(equal(8, 131072), 8, 64, 128, KVS_BF16, false, 256);    // 512, 256 at a time
+  chunks_of(equal(16, 10000), 4, 32, 128, KVS_BF16, true, 512);     // one round of 320 tokens each, not of 384
+  chunks_of(equal(16, 10000), 7, 32, 128, KVS_BF16, true, 512);
+  chunks_of(equal(12, 50000), 7, 32, 128, KVS_BF16, true, 504);
+  chunks_of(equal(24, 6500), 4, 16, 128, KVS_BF16, true, 504);
+  chunks_of(equal(64, 3277), 4, 32, 128, KVS_BF16, true, 512);
+  chunks_of(equal(100, 21000), 4, 32, 128, KVS_BF16, true, 1000);   // two rounds either way, of 2112 tokens each
+  chunks_of(equal(40, 32768), 4, 16, 128, KVS_BF16, true, 480);     // pieces of whole tiles of 32 that all wavefronts share
+  chunks_of(equal(8, 16431), 4, 64, 64, KVS_BF16, false, 416);
+  chunks_of(equal(16, 8402), 1, 64, 128, KVS_F32, false, 432);
+  std::vector<int32_t> ragged;
+  for (int i = 0; i < 16; ++i) ragged.push_back(4000 + 2400 * i);
+  chunks_of(ragged, 7, 32, 128, KVS_BF16, false, 507);
+  chunks_of(ragged, 7, 32, 128, KVS_BF16, true, 507);
+}
+
 int main() {
   std::mt19937 rng(12345);
   size_t bytes = 0;
@@ -224,6 +272,7 @@ int main() {
   equal_units(100, 2560, 32);
   kvs::stub_asks_for_fused = false;
   kvs_debug_set(KVS_DEBUG_SCORE_FUSED, 0);
+  whole_rounds();
   EXPECT(kvs_debug_set(99, 1) == -1);
   std::printf(g_failed ? "host layer: %d checks failed\n" : "host layer: all checks passed (%d stub launches)\n",
               g_failed ? g_failed : kvs::stub_launches());

@@ -12,6 +12,8 @@ static int g_most_parts = 0;            // select workgroups of the unit that ha
 bool stub_asks_for_fused = false;       // launch_unit_table sets KVS_DEBUG_SCORE_FUSED, as another thread may at any time
 bool stub_values_rode() { return g_values_rode; }
 int stub_most_parts() { return g_most_parts; }
+static int g_chunks = 0;                // score chunks of the last launch
+int stub_chunks() { return g_chunks; }
 
 static hipError_t ok() { ++g_launches; return hipSuccess; }
 
@@ -20,6 +22,7 @@ static const Unit* g_written = nullptr;   // where the last launch_unit_table pu
 static int g_written_n = 0;
 
 static void check_table(const UnitTable& tab) {
+  g_chunks = tab.total_chunks;
   if (tab.n_units < 1 || tab.n_units > kMaxGroupUnits) __builtin_trap();
   // a group beyond the inline descriptors must have had its descriptors written, to where the kernels will look
   if (tab.n_units > kInlineUnits) {
