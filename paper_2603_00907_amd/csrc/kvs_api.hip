@@ -548,7 +548,9 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     // so does one with a unit of more than 32768 tokens whose selection is not shared out by meeting parts: a launch of
     // many units (128 ragged ones of 4 K to 64 K tokens: 1055 against 1076 us per step), or a unit too long for the parts
     // that it may have (32 of 131072: 1052 against 1122; 24 of 100000: 632 and 698; 8 of 524288: 1306 and 1388).
-    sh.ride = sh.stream;
+    // And so does a window of up to 64 rows of 64 channels, whose sweep 1 runs in four workgroups per compute unit without V and
+    // three with it (100 of 29584 tokens, 16 rows: 418 us, riding 432; 50 ragged ones of 20000 to 32000 186, riding 207).
+    sh.ride = sh.stream && !(sh.D == 64 && sh.R <= 64);
     for (const Unit& un : units) {
       if (un.len <= kSelRegSlices * 4 * kSelThreads) continue;
       const bool meet = few_units && select_exchanges(un, sh) &&

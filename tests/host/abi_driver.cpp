@@ -134,8 +134,8 @@ static void equal_units(int nu, int len, int window) {
 // One step over nu equal units (one launch, more than the caches hold): whether sweep 1 carries the pass over V, and the
 // select workgroups per unit.  A unit of more than 32768 tokens whose selection is not shared out by parts that meet keeps V
 // apart: that selection is then hidden beside the pass.
-static void values_ride(int nu, int len, int budget, bool rode, int parts) {
-  Problem pr(std::vector<int32_t>(nu, len), std::vector<int32_t>(nu, budget), 4, 32, 128, KVS_BF16);
+static void values_ride(int nu, int len, int budget, bool rode, int parts, int window = 32, int D = 128) {
+  Problem pr(std::vector<int32_t>(nu, len), std::vector<int32_t>(nu, budget), 4, window, D, KVS_BF16);
   pr.p.n_sink = 32;
   size_t ws_bytes = 0;
   EXPECT(kvs_workspace_size(&pr.p, &ws_bytes) == KVS_OK);
@@ -267,6 +267,9 @@ int main() {
   values_ride(24, 100000, 8192, false, 1);
   values_ride(8, 300000, 8192, false, 1);
   values_ride(8, 524288, 8192, false, 1);
+  values_ride(64, 32768, 8192, true, 4, 8);     // 32 rows: with 128 channels only
+  values_ride(64, 32768, 8192, false, 1, 8, 64);
+  values_ride(64, 32768, 8192, true, 4, 17, 64);
   values_ride(8, 131072, 131072, false, 1);     // nothing to select: as before the selection was shared out
   kvs::stub_asks_for_fused = true;              // the switch for the one-pass kernel changes inside a call on a large group
   equal_units(100, 2560, 32);

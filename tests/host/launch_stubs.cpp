@@ -93,7 +93,7 @@ bool score_mfma_supported(const UnitTable& tab, const Shape& sh, kvs_dtype) {
   for (int i = 0; i < tab.n_units; ++i) if (tab.unit(i).len < 32) return false;
   return true;
 }
-bool score_mfma_takes_values(const Shape& sh, kvs_dtype dt) { return dt == KVS_BF16 && sh.R > 64; }
+bool score_mfma_takes_values(const Shape& sh, kvs_dtype dt) { return dt == KVS_BF16 && sh.R >= 4; }
 bool score_fused_supported(const UnitTable&, const Shape& sh, kvs_dtype dt) { return dt == KVS_BF16 && sh.R > 64 && sh.R <= 128; }
 hipError_t launch_score_fused(const UnitTable& tab, const Shape&, const void*, const void*, const void*, const int32_t*,
                               float*, const Workspace& ws, hipStream_t) {
