@@ -98,8 +98,9 @@ int group_end(const Plan& plan, int first, int cap) {
   return i;
 }
 
-// per_query: for a per-query call (its chunks may be the pieces of the per-query kernels as well).
-kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
+// per_query: for a per-query call (its chunks may be the pieces of the per-query kernels as well).  counts: for a call with
+// cardinalities (no workspace size depends on it: per-query calls have chunks of their own).
+kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, bool counts = false) {
   if (p == nullptr) return KVS_ERR_INVALID_ARG;
   if (p->n_units < 1 || p->group < 1 || p->window < 1) return KVS_ERR_INVALID_ARG;
   if ((long long)p->group * p->window > KVS_MAX_Q_ROWS) return KVS_ERR_INVALID_ARG;
@@ -190,7 +191,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     // 159 + 194; 48 of 32768 with 224 rows, 512 at a time: 768 workgroups 132 + 166, 480 126 + 162.  Steps: 48 of 16384, 224
     // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
     // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
-    // better in more rounds (128 ragged units 1029 -> 1081).  fp32 above 64 rows, of whose workgroups 512 run at once up to 128
+    // better in more rounds (128 ragged units 1029 -> 1081; but see below).  fp32 above 64 rows, of whose workgroups 512 run at once up to 128
     // rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89; not with chunks below 192 tokens
     // (8 of 8192: 71.4 with two workgroups of 128 per compute unit, 69.9 with one of 256).
     const int rows = plan->shape.R;
@@ -202,7 +203,17 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
     const bool pieces = per_query && plan->dtype == KVS_BF16 && rows >= 4;
     const bool rounds = debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
     const bool split = plan->dtype == KVS_F32 && rows > 64;
-    const long long at_once = rows > (split ? 128 : 256) ? 256 : 512, once = rows > 128 ? 256 : 128;
+    // What runs at once: two workgroups per compute unit, one of eight wavefronts; three of the vector kernel (132 to 138
+    // registers), and of the wide kernel with up to 64 rows of 64 channels three with cardinalities, four without.  Those two
+    // leave a compute unit idle sooner than they gain from fewer workgroups, so that smaller launches take whole rounds as well,
+    // and ragged ones where that was no loss.  Steps, with 512 at a time -> now (us): one row, 150 units of 4000 173 -> 161, 64
+    // ragged ones of 4096 to 65536 646 -> 605; 3 rows, fp32, 100 of 11000 717 -> 663 (673 before there were whole rounds); 64
+    // channels, 16 rows, 100 of 29584 443 -> 418, 64 of 32768 285 -> 278, 40 of 31250 to 125000 455 -> 445; with cardinalities
+    // 150 of 9000 201 -> 198, but 60 ragged ones 63 -> 65, so equal units only.
+    const bool few = rows < 4;
+    const bool light = plan->dtype == KVS_BF16 && p->head_dim == 64 && !few && rows <= 64 && !pieces;
+    const long long at_once = few || (light && counts) ? 768 : light ? 1024 : rows > (split ? 128 : 256) ? 256 : 512;
+    const long long once = rows > 128 ? 256 : 128;
     // tokens of a stage of those kernels, or of a tile for each of their four wavefronts; above 32 rows the wavefronts of the
     // per-query kernels share every tile
     const int grain = split || (pieces && rows > kPqNarrowRows) ? kWave : rows > 256 ? 256 : 128;
@@ -243,8 +254,8 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false) {
       }
       if (tiny < kMinChunkLen) {
         longer = tiny;
-      } else if (rounds && !(pieces && rows > 256) && (equal || rows > 128) &&
-                 tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * want)) {
+      } else if (rounds && !(pieces && rows > 256) && (equal || rows > 128 || few || (light && !counts)) &&
+                 tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * (few || light ? kMinChunkLen : want))) {
         long long best = (workgroups(longer) + at_once - 1) / at_once * (longer + once);
         for (long long k = 1; k <= 4; ++k) {
           const long long per_unit = k * at_once / (end - first);
@@ -669,7 +680,7 @@ kvs_status kvs_score_counts(const kvs_problem* p, const void* Q, const void* K, 
                             const int32_t* counts_in, float* alpha_bar, float* o_bar, void* ws, size_t ws_bytes,
                             void* hip_stream) {
   Plan plan;
-  kvs_status st = make_plan(p, &plan);
+  kvs_status st = make_plan(p, &plan, /*per_query=*/false, counts_in != nullptr);
   if (st != KVS_OK) return st;
   Workspace w;
   if ((st = check_ws(plan, ws, ws_bytes, &w, ws)) != KVS_OK) return st;
@@ -840,7 +851,7 @@ kvs_status kvs_step_counts(const kvs_problem* p, const void* Q, const void* K, c
                            void* K_out, void* V_out, int32_t* counts_out, int32_t* slot_of_token_out,
                            uint8_t* edge_mask_out, void* ws, size_t ws_bytes, void* hip_stream) {
   Plan plan;
-  const kvs_status st = make_plan(p, &plan);
+  const kvs_status st = make_plan(p, &plan, /*per_query=*/false, counts_in != nullptr);
   if (st != KVS_OK) return st;
   return step_with_workspace(plan, Q, K, V, counts_in, K_out, V_out, counts_out, slot_of_token_out, edge_mask_out, ws,
                              ws_bytes, hip_stream);
@@ -881,7 +892,7 @@ kvs_status kvs_step_static(const kvs_problem* p, const void* Q, const void* K, c
                            void* K_out, void* V_out, int32_t* counts_out, int32_t* slot_of_token_out,
                            uint8_t* edge_mask_out, void* hip_stream) {
   Plan plan;
-  kvs_status st = make_plan(p, &plan);
+  kvs_status st = make_plan(p, &plan, /*per_query=*/false, counts_in != nullptr);
   if (st != KVS_OK) return st;
   // the size check needs no device: a problem beyond the array is refused before anything touches the GPU
   if (carve(plan, nullptr).bytes > (size_t)KVS_STATIC_SCRATCH_BYTES) return KVS_ERR_WORKSPACE;

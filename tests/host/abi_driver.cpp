@@ -156,7 +156,8 @@ static void values_ride(int nu, int len, int budget, bool rode, int parts, int w
 }
 
 // How many score chunks a call on the given units (one launch) is cut into.
-static void chunks_of(std::vector<int32_t> len, int group, int window, int D, kvs_dtype dt, bool per_query, int chunks) {
+static void chunks_of(std::vector<int32_t> len, int group, int window, int D, kvs_dtype dt, bool per_query, int chunks,
+                      bool counts = false) {
   std::vector<int32_t> budget(len);
   for (int32_t& b : budget) b /= 3;
   Problem pr(len, budget, group, window, D, dt);
@@ -170,9 +171,10 @@ static void chunks_of(std::vector<int32_t> len, int group, int window, int D, kv
   void* Ko = a.take((size_t)pr.rows_out * D * elt);
   void* Vo = a.take((size_t)pr.rows_out * D * elt);
   int32_t* cnt = (int32_t*)a.take((size_t)pr.rows_out * 4);
+  int32_t* cin = counts ? (int32_t*)a.take((size_t)pr.rows_in * 4) : nullptr;
   void* ws = a.take(ws_bytes);
-  EXPECT((per_query ? kvs_step_per_query(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)
-                    : kvs_step(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)) == KVS_OK);
+  EXPECT((per_query ? kvs_step_per_query_counts(&pr.p, Q, K, V, cin, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)
+                    : kvs_step_counts(&pr.p, Q, K, V, cin, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)) == KVS_OK);
   if (kvs::stub_chunks() != chunks) {
     std::printf("%zu units, the first of %d tokens, %d rows, head dim %d%s%s: %d chunks instead of %d\n", len.size(), len[0],
                 group * window, D, dt == KVS_F32 ? ", fp32" : "", per_query ? ", per query" : "", kvs::stub_chunks(), chunks);
@@ -201,6 +203,15 @@ static void whole_rounds() {
   for (int i = 0; i < 16; ++i) ragged.push_back(4000 + 2400 * i);
   chunks_of(ragged, 7, 32, 128, KVS_BF16, false, 507);
   chunks_of(ragged, 7, 32, 128, KVS_BF16, true, 507);
+  // 768 at a time: one to three rows, and up to 64 rows of 64 channels with cardinalities; 1024 without
+  for (kvs_dtype dt : {KVS_F32, KVS_BF16}) {
+    chunks_of(equal(150, 4000), 1, 1, 128, dt, false, 750);
+    chunks_of(equal(100, 11000), 3, 1, 64, dt, false, 700);
+    chunks_of(ragged, 1, 1, 128, dt, false, 649);
+  }
+  chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 1024);
+  chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 768, true);
+  chunks_of(equal(64, 32768), 4, 4, 64, KVS_F32, false, 512);
 }
 
 int main() {
