@@ -174,13 +174,14 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
       return (int)((per + kWave - 1) / kWave * kWave);
     };
     // Units end in chunks of their own, so that a launch has a few more workgroups than meant: a last round that is nearly
-    // empty (two workgroups of the kernel for 65 to 128 bf16 rows run on a CU at a time).  Slightly longer chunks in that
-    // launch group do without it: 64 ragged units of 4 K to 64 K tokens, 1076 workgroups, sweeps 121 + 136 us; at most 1024,
-    // 109 + 122 (the step of two such groups 1066 -> 1032 us, with per-query norms, whose workgroups are the same chunks,
-    // 1915 -> 1821).  Equal units too: 100 of 21000 tokens, 1100 workgroups 566 us, 1000 539; with per-query norms 997 and
-    // 948, with cardinalities 584 and 554; 100 of 11000 296 and 289.  Per group, since the chunks that suit one
-    // group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of 97 + 105.
-    const bool wide = plan->dtype == KVS_BF16 && plan->shape.R > 64 && plan->shape.R <= 128 &&
+    // empty (two workgroups of the wide kernel run on a CU at a time).  Slightly longer chunks in that launch group do without
+    // it: 64 ragged units of 4 K to 64 K tokens, 128 rows, 1076 workgroups, sweeps 121 + 136 us; at most 1024, 109 + 122 (the
+    // step of two such groups 1066 -> 1032 us, with per-query norms, whose workgroups are the same chunks, 1915 -> 1821).  Up to
+    // 64 rows too (8 rows 583 -> 558; 100 of 8000 to 30000 520 -> 495), but not where the chunks are the pieces of per-query
+    // kernels that have not been measured with it.  Equal units whose number fits no whole rounds (below) likewise.  Per group,
+    // since the chunks that suit one group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of
+    // 97 + 105.
+    const bool wide = plan->dtype == KVS_BF16 && plan->shape.R >= (per_query ? 65 : 4) && plan->shape.R <= 128 &&
                       debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
     // Whole rounds of as few workgroups as run at once: a workgroup of the kernels for more than 128 rows spends 6 to 12 us
     // on what it does once for its chunk (the time of 160 to 310 tokens), a launch whose last round is half full half a
@@ -238,7 +239,10 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
       const long long n = wide ? workgroups(want) : 0, full = n / kRound * kRound;
       long long longer = want;
       if (full >= kScoreWorkgroups && n > full && n - full <= kRound / 4) {
-        for (long long w = want + kWave; w <= want + want / 4; w += kWave) {     // (beyond kMaxChunkLen where that is the aim)
+        // (beyond kMaxChunkLen where that is the aim; a tile for each of the score kernel's four wavefronts, one of the
+        // per-query kernels, which share it: 85 units of 24769 with 56 rows and cardinalities, chunks of 2112 995, of 2176 934)
+        const long long step = pieces ? kWave : 4 * 32;
+        for (long long w = (want / step + 1) * step; w <= want + want / 4; w += step) {
           if (workgroups(w) <= full) { longer = w; break; }
         }
       }

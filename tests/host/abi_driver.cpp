@@ -212,6 +212,11 @@ static void whole_rounds() {
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 1024);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 768, true);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_F32, false, 512);
+  // ragged launches a little above two rounds: chunks as much longer as it takes, of a tile for each of four wavefronts
+  std::vector<int32_t> many;
+  for (int i = 0; i < 100; ++i) many.push_back(8000 + 222 * i);
+  for (int group : {1, 2, 4}) chunks_of(many, group, 32, 128, KVS_BF16, false, 978);
+  chunks_of(many, 4, 32, 128, KVS_BF16, true, 1006);
 }
 
 int main() {

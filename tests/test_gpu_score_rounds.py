@@ -1,4 +1,4 @@
-"""Launches whose score chunks are lengthened so that the last round of workgroups is not nearly empty (65 to 128 bf16 rows):
+"""Launches whose score chunks are lengthened so that the last round of workgroups is not nearly empty (4 to 128 bf16 rows):
 every token is scored once, in one launch group and in two with chunk lengths of their own, ragged units and equal ones, with
 cardinalities and in the per-query kernels."""
 
@@ -19,6 +19,7 @@ def workgroups(lens, want):
 @pytest.mark.parametrize("n,longest,D,G,W,seed", [
     (64, 32768, 64, 3, 22, 2),                                          # 66 rows, 1049 workgroups
     (64, 32768, 128, 4, 32, 24),                                    # 128 rows, 1033 workgroups
+    (64, 32768, 128, 1, 32, 24),                                    # 32 rows
     (80, 65536, 64, 4, 32, 3),                                          # a group of 64 units (1045 workgroups) and one of 16
 ])
 def test_score_with_longer_chunks(n, longest, D, G, W, seed):
