@@ -13,17 +13,17 @@
 // beyond that there is one launch per 512 rows.
 //
 // K streams into a ring of stages by global_load_lds, 16-byte pieces XOR-swizzled by the row number; one barrier per stage.
-// A stage is NW * 32 tokens, the next one on its way, or with the pass over V, whose rows take registers, NW * 16 tokens, two
-// on their way (with the rows of V of NW * 32 tokens in registers, or half of them at a time, the kernel spilled, and sweep 1
-// of 64 units of 32768 tokens took 236 to 310 us instead of 210).  A long stage matters because the pipeline of products and
-// terms fills and drains once per stage, and so does the size of its steps: one block of 32 rows at a time leaves registers
-// for a whole tile's operands (64 rows at a time and stages of NW * 16 tokens: sweep 0 of 8 units of 131072 tokens, 512 rows,
-// 178 us, now 167; 64 of 32768, 224 rows, 183 and 164, with V in sweep 1 210 and 212).
+// A stage is NW * 32 tokens, the next one on its way (LONG), or NW * 16 tokens, two on their way, always so with the pass over
+// V, whose rows take registers (with the rows of V of NW * 32 tokens in registers, or half of them at a time, the kernel
+// spilled, and sweep 1 of 64 units of 32768 tokens took 236 to 310 us instead of 210).  Long stages fill and drain the pipeline
+// of products and terms less often; short ones waste less where a chunk ends inside one, and have more loads on their way
+// (both measured, see launch_t).  The steps are blocks of 32 rows, which leaves registers for a whole tile's operands (64 rows
+// at a time and short stages: sweep 0 of 8 units of 131072 tokens, 512 rows, 178 us, now 167; 64 of 32768, 224 rows, 183 and
+// 164, with V in sweep 1 210 and 212).
 // Sweep 0 takes S^T = K Q^T (a lane holds one query column and 16 token rows: running statistics are lane-private and no
 // wavefront needs another's).  Sweep 1 takes S = Q K^T (a lane holds one token and 16 query rows: the sum over the
-// wavefront's rows is a sum over registers); the wavefronts' shares meet in LDS, and each of them finishes 32 (with the
-// pass over V 16) of the stage's tokens after the next barrier: alpha_bar, and with OBAR the same tokens' rows of V,
-// requested one stage before.
+// wavefront's rows is a sum over registers); the wavefronts' shares meet in LDS, and each of them finishes its 32 or 16 of
+// the stage's tokens after the next barrier: alpha_bar, and with OBAR the same tokens' rows of V, requested one stage before.
 //
 // Running statistics without a running maximum: sum 2^(e - m) for a reference m that stays (see kSumLimit in
 // kvs_mfma_tile.h).  The first stage of a chunk takes m from its maxima; a stage whose own sum is not below the limit in
@@ -48,19 +48,19 @@ __device__ __forceinline__ void wait_loads_and_lds() {
   asm volatile("" ::: "memory");
 }
 
-template <int D, int NW, int PHASE, bool STREAM, bool OBAR, typename Tab>
+template <int D, int NW, int PHASE, bool STREAM, bool OBAR, bool LONG, typename Tab>
 __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     const Tab tab, const Shape sh, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ counts_in, float* __restrict__ alpha_bar, float2* __restrict__ stats_part,
     const float* __restrict__ c_row, const uint16_t* __restrict__ V, float* __restrict__ o_part, const int qp) {
-  static_assert(!OBAR || PHASE == 1, "the Value pass belongs to sweep 1");
+  static_assert(!OBAR || (PHASE == 1 && !LONG), "the Value pass belongs to sweep 1 and to short stages");
   constexpr int KS = D / 16;                // MFMA k-steps
   constexpr int LPR = D / 8;                // 16-byte pieces per row
   constexpr int RPI = kWave / LPR;          // rows per load instruction
   constexpr int ROWB = D * 2;
   constexpr int TILEB = kTile * ROWB;
-  constexpr int RW = OBAR ? 16 : 32;        // rows of a stage that every wavefront fetches
-  constexpr int AHEAD = OBAR ? 2 : 1;       // stages of K on their way while one is read
+  constexpr int RW = LONG ? 32 : 16;        // rows of a stage that every wavefront fetches
+  constexpr int AHEAD = LONG ? 1 : 2;       // stages of K on their way while one is read
   constexpr int kBuf = AHEAD + 1;
   constexpr int STAGE = RW * NW;            // tokens per stage
   constexpr int NT = STAGE / kTile;         // tiles per stage
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
                    const float* __restrict__ rd_c) {
     if (has_counts) {
       sm_c[(s + 1) & 1][tid] = (float)raw_c;
-      fetch_counts(s + 2);                                   // (before stage s + 2 of K, whose loads the next wait leaves out)
+      fetch_counts(s + 2);                                   // (before stage s + 2 of K, which the next wait may leave out)
     }
     if (s + AHEAD < nstages) issue_stage(s + AHEAD, wr);
     if (OBAR) load_values(s);
@@ -423,6 +423,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
       asm volatile("; any stage");
 #pragma unroll 1
       for (int i = 0; i < NT; ++i) {
+        if (s0 + i * kTile >= t1) break;                     // (nobody reads the shares of tokens past the chunk's end)
         f32x16 acc[2];
         products(rd + i * TILEB, acc);
         put_share(acc, s & 1, i, s0 + i * kTile, s0 + i * kTile + kTile > causal_from);
@@ -431,8 +432,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
     }
   };
   for (int s = 0; s < nstages; ++s) {
-    // stage s has landed (of the loads after it, at most those of stage s + 1 may be outstanding) in every wavefront,
-    // and nobody reads the buffer of stage s - 1 any more
+    // stage s has landed in every wavefront (with short stages those loads may be outstanding that are of stage s + 1), and
+    // nobody reads the buffer of stage s - 1 any more
     if (AHEAD == 2 && s + 1 < nstages) wait_loads_and_lds<NLD>();
     else wait_loads_and_lds<0>();
     __builtin_amdgcn_s_barrier();
@@ -482,16 +483,30 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   }
 }
 
+// Long stages in sweep 0 without cardinalities (with 64 channels only where K is read past the caches), but for chunks of no
+// more than two of them in workgroups of four wavefronts; and in a sweep 1 without V of 64 channels.  Steps with long -> short
+// stages in sweep 0 (us): cardinalities, 48 units of 21845 tokens, 512 rows 637 -> 618, 20 of 5000 to 30000, 224 rows 128 -> 126,
+// 64 channels, 160 rows 96 -> 91; none, 64 channels, 100 of 1500 to 4000, 256 rows 96 -> 93; 72 of 383 to 3068, 256 rows, chunks
+// of 256, 75.2 -> 74.6; but 104 of 5471 to 21885, 224 rows 509 -> 523, 48 of 3000 to 24000, 512 rows 313 -> 321, 64 channels
+// past the caches, 152 of 6898, 512 rows 315 -> 325, 92 of 5698 to 22795, 256 rows 241 -> 248.  In sweep 1: 16 of 21000, 224
+// rows 129 -> 125, 160 rows 120 -> 117, 512 rows 176 -> 173; but 64 channels, 16 of 21000, 448 rows 130 -> 133.
 template <int D, int NW, bool STREAM>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const int32_t* counts_in,
                     float* alpha_bar, const Workspace& ws, const void* V, hipStream_t stream) {
   const dim3 grid(tab.total_chunks), block(NW * kWave);
+  const bool long0 = counts_in == nullptr && !(NW == 4 && tab.unit(0).chunk_len <= 2 * 32 * NW);
+  constexpr bool LONG1 = D == 64;
   hipError_t e;
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
     launch_with_table(tab, [&](const auto& t) {
-      hipLaunchKernelGGL((score_shared_kernel<D, NW, 0, STREAM, false, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
-                         (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
-                         (const uint16_t*)nullptr, (float*)nullptr, qp);
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, t, sh, (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar,
+                           ws.stats_part, ws.c_row, (const uint16_t*)nullptr, (float*)nullptr, qp);
+      };
+      if constexpr (D == 128 || STREAM) {
+        if (long0) return launch(score_shared_kernel<D, NW, 0, STREAM, false, true, KVS_TABLE_TYPE(t)>);
+      }
+      launch(score_shared_kernel<D, NW, 0, STREAM, false, false, KVS_TABLE_TYPE(t)>);
     });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -499,13 +514,13 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
     if (V != nullptr && qp + NW * 64 >= sh.R) {              // the last launch alone knows the finished alpha_bar
       launch_with_table(tab, [&](const auto& t) {
-        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, true, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, true, false, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
                            (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
                            (const uint16_t*)V, ws.o_part, qp);
       });
     } else {
       launch_with_table(tab, [&](const auto& t) {
-        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, false, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
+        hipLaunchKernelGGL((score_shared_kernel<D, NW, 1, STREAM, false, LONG1, KVS_TABLE_TYPE(t)>), grid, block, 0, stream, t, sh,
                            (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar, ws.stats_part, ws.c_row,
                            (const uint16_t*)nullptr, (float*)nullptr, qp);
       });
