@@ -381,7 +381,7 @@ PerQueryWs carve_per_query(const Plan& plan, void* base, Workspace* w) {
       longest = std::max<long long>(longest, std::min(un.len, un.chunk_len));
     }
     max_chunks = std::max(max_chunks, c);
-    pieces = std::max(pieces, plan.dtype == KVS_F32 ? c : c << pq_split(c, rows, longest, plan.shape.R, plan.shape.D));
+    pieces = std::max(pieces, plan.dtype == KVS_F32 ? c : c << pq_split(end - first, c, rows, longest, plan.shape.R, plan.shape.D));
   }
   // (where a test asks for smaller groups than these, their chunks may be cut finer)
   if (plan.dtype != KVS_F32 && plan.n_units > kInlineUnits)

@@ -538,9 +538,16 @@ hipError_t launch_merge_norms(const UnitTable& tab, const Shape& sh, kvs_dtype d
 // 58.5 in two, 65.4 in four) and no pieces below 64 rows (8 of 2048, 128 chunks of 128: 39.3 in two, 41.0 uncut, 47.7 in four).
 constexpr int kMaxPqPieces = 1024;
 constexpr int kMaxPqSplit = 3;
+// Small launches of 9 to 32 rows of 128 channels keep pq_out_kernel, whose workgroups have no sums of four wavefronts to add up,
+// and its pieces down to a tile (with pq_out_narrow_kernel and pieces of 64, us: 32 rows, one unit of 800 35.7, so 34.1, 4 of 1000
+// 38.1 and 36.7, 8 of 1000 40.9 and 40.2; 16 rows, one of 800 32.1 and 31.2; one of 6000 40.3 and 40.8, 8 of 1900 40.5 and 40.2
+// with pieces of 64, so neither longer units nor larger launches).
 constexpr int kPqNarrowRows = 32;         // up to here a tile takes one wavefront of the per-query kernels (bf16)
-inline int pq_split(long long chunks, long long rows, long long longest, int R, int D) {
-  const bool narrow = R <= kPqNarrowRows, light = !narrow && (R <= 64 || D == 64);
+inline bool pq_small(long long units, long long rows, int R, int D) {
+  return D == 128 && R > 8 && R <= kPqNarrowRows && rows <= 8192 && rows <= 3500 * units;
+}
+inline int pq_split(long long units, long long chunks, long long rows, long long longest, int R, int D) {
+  const bool narrow = R <= kPqNarrowRows && !pq_small(units, rows, R, D), light = !narrow && (R <= 64 || D == 64);
   int split = 0;
   while (split < kMaxPqSplit) {
     const long long pieces = chunks << (split + 1);

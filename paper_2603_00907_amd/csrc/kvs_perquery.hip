@@ -1306,17 +1306,18 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
     rows += un.len;
     longest_chunk = std::max(longest_chunk, std::min(un.len, un.chunk_len));
   }
-  const int split = pq_split(tab.total_chunks, rows, longest_chunk, sh.R, D);
+  const int split = pq_split(tab.n_units, tab.total_chunks, rows, longest_chunk, sh.R, D);
   const dim3 grid(tab.total_chunks << split), block(kThreads);
   float2* stat_part = reinterpret_cast<float2*>(o_part + (size_t)grid.x * sh.R * D);   // behind the launch's partials
   float* p_part = reinterpret_cast<float*>(stat_part + (size_t)grid.x * sh.R);
   const bool own_rows = sh.c_row_out != nullptr;            // the normalisers come from here
-  // Up to 32 rows both narrow kernels (figures at pq_out_narrow_kernel).  33 to 64 rows, two wavefronts to a tile, with 64
+  // Up to 32 rows both narrow kernels (figures at pq_out_narrow_kernel), in small launches the norms' alone (see pq_small).  33 to 64 rows, two wavefronts to a tile, with 64
   // channels (12 units of 29384 135 -> 114 us, one of 1000 35.6 -> 34.8); with 128 channels the outputs' reads of every tile by
   // two wavefronts cost more than the idle rows (8 of 32768 131 -> 138), and the norms gain from some 256 K tokens on
   // (8 of 32768 131.3 -> 130.0, 4 of 100000 193 -> 186, 100 of 21000 892 -> 858, 40 of 20000 with cardinalities 446 -> 415;
   // 4 ragged ones, 150000 tokens, 90.1 -> 92.2, 32 of 3000 85.9 -> 87.8).
   const bool one = sh.R <= kPqNarrowRows, two = !one && sh.R <= 2 * kPqNarrowRows;
+  const bool small = pq_small(tab.n_units, rows, sh.R, D);
   const bool narrow_norms = D == 64 || rows >= (1 << 18);
   launch_with_table(tab, [&](const auto& t) {
     auto launch = [&](auto kernel) {
@@ -1326,7 +1327,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
     if constexpr (D == 64) {
       if (two) return launch(pq_out_narrow_kernel<D, COUNTS, 2, KVS_TABLE_TYPE(t)>);
     }
-    if (one) return launch(pq_out_narrow_kernel<D, COUNTS, 1, KVS_TABLE_TYPE(t)>);
+    if (one && !small) return launch(pq_out_narrow_kernel<D, COUNTS, 1, KVS_TABLE_TYPE(t)>);
     launch(pq_out_kernel<D, COUNTS, KVS_TABLE_TYPE(t)>);
   });
   hipError_t e = hipGetLastError();

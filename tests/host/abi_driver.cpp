@@ -12,7 +12,7 @@
 #include "kvs.h"
 #include "kvs_debug.h"
 
-namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); int stub_chunks(); extern bool stub_asks_for_fused; }
+namespace kvs { int stub_launches(); bool stub_values_rode(); int stub_most_parts(); int stub_chunks(); int stub_pieces(); extern bool stub_asks_for_fused; }
 
 static int g_failed = 0;
 #define EXPECT(cond) do { if (!(cond)) { std::printf("FAILED %s (line %d)\n", #cond, __LINE__); ++g_failed; } } while (0)
@@ -175,10 +175,19 @@ static void chunks_of(std::vector<int32_t> len, int group, int window, int D, kv
   void* ws = a.take(ws_bytes);
   EXPECT((per_query ? kvs_step_per_query_counts(&pr.p, Q, K, V, cin, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)
                     : kvs_step_counts(&pr.p, Q, K, V, cin, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr)) == KVS_OK);
-  if (kvs::stub_chunks() != chunks) {
+  if (chunks >= 0 && kvs::stub_chunks() != chunks) {
     std::printf("%zu units, the first of %d tokens, %d rows, head dim %d%s%s: %d chunks instead of %d\n", len.size(), len[0],
                 group * window, D, dt == KVS_F32 ? ", fp32" : "", per_query ? ", per query" : "", kvs::stub_chunks(), chunks);
     EXPECT(!"the launch's chunks");
+  }
+}
+
+// The pieces that the bf16 per-query kernels cut the chunks into.
+static void pieces_of(int nu, int len, int rows, int D, int pieces) {
+  chunks_of(std::vector<int32_t>(nu, len), 1, rows, D, KVS_BF16, true, -1);
+  if (kvs::stub_pieces() != pieces) {
+    std::printf("%d units of %d tokens, %d rows, head dim %d: %d pieces instead of %d\n", nu, len, rows, D, kvs::stub_pieces(), pieces);
+    EXPECT(!"the launch's pieces");
   }
 }
 
@@ -292,6 +301,14 @@ int main() {
   kvs::stub_asks_for_fused = false;
   kvs_debug_set(KVS_DEBUG_SCORE_FUSED, 0);
   whole_rounds();
+  // small launches of 9 to 32 rows of 128 channels: pieces down to a tile of 32 tokens, else of 64 at least
+  pieces_of(1, 800, 32, 128, 28);
+  pieces_of(4, 1000, 16, 128, 128);
+  pieces_of(8, 1000, 32, 128, 256);
+  pieces_of(1, 6000, 32, 128, 94);
+  pieces_of(1, 800, 8, 128, 14);
+  pieces_of(1, 800, 32, 64, 14);
+  pieces_of(8, 1900, 32, 128, 240);
   EXPECT(kvs_debug_set(99, 1) == -1);
   std::printf(g_failed ? "host layer: %d checks failed\n" : "host layer: all checks passed (%d stub launches)\n",
               g_failed ? g_failed : kvs::stub_launches());

@@ -14,6 +14,8 @@ bool stub_values_rode() { return g_values_rode; }
 int stub_most_parts() { return g_most_parts; }
 static int g_chunks = 0;                // score chunks of the last launch
 int stub_chunks() { return g_chunks; }
+static int g_pieces = 0;                // pieces of the last launch of the bf16 per-query kernels
+int stub_pieces() { return g_pieces; }
 
 static hipError_t ok() { ++g_launches; return hipSuccess; }
 
@@ -123,8 +125,20 @@ hipError_t launch_merge(const UnitTable& tab, const Shape&, kvs_dtype, const voi
                         const float*, const float*, const uint8_t*, const int32_t*, void*, void*, int32_t*, hipStream_t) { check_table(tab); return ok(); }
 hipError_t launch_merge_norms(const UnitTable& tab, const Shape&, kvs_dtype, const void*, const void*, const int32_t*, const float*,
                               const float*, const uint8_t*, const int32_t*, void*, void*, int32_t*, hipStream_t) { check_table(tab); return ok(); }
-hipError_t launch_per_query_norms(const UnitTable& tab, const Shape&, const void*, const void*, const void*, const int32_t*,
-                                  const float*, float*, uint16_t*, uint16_t*, float*, float*, float*, hipStream_t) { check_table(tab); return ok(); }
+hipError_t launch_per_query_norms(const UnitTable& tab, const Shape& sh, const void*, const void*, const void*, const int32_t*,
+                                  const float*, float* o_part, uint16_t* o_hi, uint16_t*, float*, float*, float*, hipStream_t) {
+  check_table(tab);
+  long long rows = 0, longest = 1;
+  for (int i = 0; i < tab.n_units; ++i) {
+    const Unit u = tab.unit(i);
+    rows += u.len;
+    if (u.len < u.chunk_len ? u.len > longest : u.chunk_len > longest) longest = u.len < u.chunk_len ? u.len : u.chunk_len;
+  }
+  g_pieces = tab.total_chunks << pq_split(tab.n_units, tab.total_chunks, rows, longest, sh.R, sh.D);
+  // the pieces' outputs, references, sums and weights' sums lie before what follows them in the workspace
+  if ((long long)((char*)o_hi - (char*)o_part) < (long long)g_pieces * sh.R * (sh.D + 3) * (long long)sizeof(float)) __builtin_trap();
+  return ok();
+}
 hipError_t launch_per_query_norms_f32(const UnitTable& tab, const Shape&, const void*, const void*, const void*, const int32_t*,
                                       const float*, float*, float*, float*, float*, hipStream_t) { check_table(tab); return ok(); }
 hipError_t launch_decode(const UnitTable& tab, const Shape&, kvs_dtype, const void*, const void*, const void*, const int32_t*,

@@ -30,11 +30,23 @@ def test_norms_of_few_rows(D, G, W, base, causal):
     check_sensitivity(w, units, lens, D, G, W, "bf16", causal)
 
 
+@pytest.mark.parametrize("base", ["llama8b_8k", "stream2560"])
+@pytest.mark.parametrize("D,G,W", [(128, 1, 9), (128, 1, 31), (128, 4, 8)])
+def test_norms_of_few_rows_in_a_larger_launch(D, G, W, base):
+    """Above 8192 tokens windows of 9 to 32 rows of 128 channels have the outputs' kernel whose wavefronts take whole tiles, too."""
+    lens = [33, 127, 257, 1500, 6500]
+    w = variant(base, dtype="bf16", head_dim=D, group=G, window=W, n_seq=len(lens), n_kv_heads=1)
+    if w.mean_count > 0:
+        w = w.scaled(fresh_tail=max(W, 8), n_sink=2)
+    units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate(lens)]
+    check_sensitivity(w, units, lens, D, G, W, "bf16", False)
+
+
+@pytest.mark.parametrize("lens", [[700, 64, 40], [8000, 700, 64]])
 @pytest.mark.parametrize("D,G,W", SHAPES)
-def test_few_rows_of_logits_that_climb(D, G, W):
+def test_few_rows_of_logits_that_climb(D, G, W, lens):
     """The Keys grow from a thousandth of their size, up to logits of 20: a wavefront's references rise, and at the end the
     four wavefronts of a piece hold different ones."""
-    lens = [700, 64, 40]
     w = variant("llama8b_8k", dtype="bf16", head_dim=D, group=G, window=W, n_seq=len(lens), n_kv_heads=1)
     units = [generate_unit(w, 0, s, 0, n=n) for s, n in enumerate(lens)]
     for u in units:
