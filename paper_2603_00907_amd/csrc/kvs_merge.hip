@@ -469,10 +469,13 @@ static hipError_t launch_merge_k(const UnitTable& tab, const Shape& sh, const vo
                                  void* V_out, int32_t* counts, hipStream_t stream, const float* c_edge = nullptr) {
   // 129 to 256 ranges of 128 channels: one workgroup of eight wavefronts per range instead of one or two of four, which hides
   // more of the rows' latency and forms the range's ends and o_bar once.  Steps, before -> after (us): 8 units of 8192
-  // 37.8 -> 37.3, fp32 69.8 -> 67.5; 8 of 7000 36.2 -> 35.5, fp32 65.0 -> 63.9; one of 65000 65.9 -> 64.8; per query, 8 of
-  // 6000 75.7 -> 74.8.  Not fewer ranges (8 of 4096, cut in two, 29.1, so 30.5) nor more (8 of 12000 47.2, so 48.1), and not
-  // 64 channels, where a lane group walks half as many tokens to begin with (8 of 8000 34.0, so 35.1).
-  const bool more = D == 128 && !STREAM && tab.total_mblocks > 128 && tab.total_mblocks <= 256;
+  // 37.9 -> 37.1, fp32 70.1 -> 66.9; 8 of 6000 35.5 -> 35.0, fp32 58.7 -> 58.2; 148 of 256 32.1 -> 29.0; one of 65000
+  // 65.9 -> 64.8; per query, 8 of 6000 75.7 -> 74.8.  Not fewer ranges (8 of 4096, cut in two, 29.1, so 30.5) nor more (8 of 12000
+  // 47.2, so 48.1), and not 64 channels, where a lane group walks half as many tokens to begin with (8 of 8000 34.0, so 35.1);
+  // bf16 units of unequal lengths above 144 ranges only (20 of 965 to 1931, 135 ranges, cut in two 30.8, so 31.7; 47 of 300 to 900
+  // 31.9 and 32.7, but 6 of 3000 to 9000, 153 ranges, 35.1 and 34.1).
+  const int least = tab.even || std::is_same<T, float>::value ? 128 : 144;
+  const bool more = D == 128 && !STREAM && tab.total_mblocks > least && tab.total_mblocks <= 256;
   const int split = more ? 0 : merge_split(tab.total_mblocks);
   // (256 ranges are at most 65536 rows of 1 KB for K and V together: never enough for the streaming policy)
   auto launch = [&](auto threads) {

@@ -1,5 +1,6 @@
-"""Merge launches of 129 to 256 ranges of 256 tokens (128 channels), which take workgroups of eight wavefronts: the ends of that
-range, ranges that end short, cardinalities, a run longer than a workgroup looks ahead at once, norms from memory."""
+"""Merge launches of 129 to 256 ranges of 256 tokens (128 channels; bf16 units of unequal lengths: 145), which take workgroups of
+eight wavefronts: the ends of that range, ranges that end short, cardinalities, a run longer than a workgroup looks ahead at
+once, norms from memory."""
 
 import pytest
 
@@ -10,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("base,dtype,lens,budgets", [
-    ("llama8b_8k", "bf16", [32769, 32], [6000, 32]),              # 130 ranges, one of them of a single token
+    ("llama8b_8k", "bf16", [32769, 32], [6000, 32]),              # 130 ranges, one of a single token: four wavefronts still,
+    ("llama8b_8k", "f32", [32769, 32], [6000, 32]),               # eight
+    ("llama8b_8k", "bf16", [36609, 32], [6000, 32]),              # 145 ranges: eight
     ("llama8b_8k", "bf16", [33000, 32536], None),                 # 256
     ("llama8b_8k", "bf16", [32800], [40]),                        # 129; one run swallows nearly everything
     ("tiny", "f32", [20000, 257, 13000], [15000, 200, 2000]),
