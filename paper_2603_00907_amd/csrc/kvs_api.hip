@@ -210,10 +210,12 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
     // and ragged ones where that was no loss.  Steps, with 512 at a time -> now (us): one row, 150 units of 4000 173 -> 161, 64
     // ragged ones of 4096 to 65536 646 -> 605; 3 rows, fp32, 100 of 11000 717 -> 663 (673 before there were whole rounds); 64
     // channels, 16 rows, 100 of 29584 443 -> 418, 64 of 32768 285 -> 278, 40 of 31250 to 125000 455 -> 445; with cardinalities
-    // 150 of 9000 201 -> 198, but 60 ragged ones 63 -> 65, so equal units only.
+    // 150 of 9000 201 -> 198, but 60 ragged ones 63 -> 65, so equal units only.  And one of the eight wavefronts that 129 to 192
+    // rows take in some launches (48 of 16384, 160 rows 231 -> 226, 64 channels, 32 of 9000 71.2 -> 68.1, 40 of 4000 to 16000
+    // 90 -> 87; 48 of 32768 436 -> 441).
     const bool few = rows < 4;
     const bool light = plan->dtype == KVS_BF16 && p->head_dim == 64 && !few && rows <= 64 && !pieces;
-    const long long at_once = few || (light && counts) ? 768 : light ? 1024 : rows > (split ? 128 : 256) ? 256 : 512;
+    const long long resident = few || (light && counts) ? 768 : light ? 1024 : rows > (split ? 128 : 256) ? 256 : 512;
     const long long once = rows > 128 ? 256 : 128;
     // tokens of a stage of those kernels, or of a tile for each of their four wavefronts; above 32 rows the wavefronts of the
     // per-query kernels share every tile
@@ -252,6 +254,11 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
         tokens += plan->units[u].len;
         equal = equal && plan->units[u].len == plan->units[first].len;
       }
+      const bool stream = 2 * tokens * p->head_dim * (long long)plan->elt > kStreamBytes;
+      const long long at_once = plan->dtype == KVS_BF16 && !pieces &&
+                                        score_rows_in_one_workgroup(rows, p->head_dim, stream, counts)
+                                    ? 256
+                                    : resident;
       long long tiny = kMinChunkLen;
       if (rounds && tokens < kTinyWorkgroups * kMinChunkLen) {
         for (long long w = kMinChunkLen - tiny_grain; w > 0 && workgroups(w) <= kTinyWorkgroups; w -= tiny_grain) tiny = w;

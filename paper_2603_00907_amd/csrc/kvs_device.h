@@ -454,6 +454,12 @@ __device__ __forceinline__ void load_row_consts(const Shape& sh, const Unit& un,
   }
 }
 
+// bf16 launches of 129 to 192 rows whose two score sweeps are the wide kernel's form with eight wavefronts, one workgroup per
+// compute unit, whatever their number (the reasons stand where the kernel is chosen).
+inline bool score_rows_in_one_workgroup(int R, int D, bool stream, bool counts) {
+  return R > 128 && R <= 192 && !counts && (D == 64 || stream);
+}
+
 // Launchers (defined next to their kernels).  All enqueue on `stream` and return the launch status.
 // The descriptors of a group of more than kInlineUnits units (host memory) into the workspace, by kernels that
 // carry them in their arguments; nothing where they are regular (UnitTableT::regular: nobody reads them there).

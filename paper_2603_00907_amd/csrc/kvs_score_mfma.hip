@@ -863,8 +863,8 @@ hipError_t launch_d(const UnitTable& tab, const Shape& sh, const void* Q, const 
   // theirs that have half the others' rows: head dim 64 (8 units of 32768 tokens, 160 rows, both sweeps: 42.3 here, 47.5
   // there), rows read past the caches (48 of 32768: 277 and 293; 48 of 16384: 153 and 175) and chunks of 256 tokens (24 of
   // 4096: 40.5 and 44.4).  (8 of 32768: 66.6 and 64.2; with cardinalities 75.8 and 65.9, 48 of 32768 338 and 312.)
-  const bool few_rows = R <= 192 && counts_in == nullptr &&
-                        (D == 64 || sh.stream || tab.unit(0).chunk_len <= kMinChunkLen);
+  const bool few_rows = score_rows_in_one_workgroup(R, D, sh.stream, counts_in != nullptr) ||
+                        (R <= 192 && counts_in == nullptr && tab.unit(0).chunk_len <= kMinChunkLen);
   if (R <= 256 && (tab.total_chunks <= 256 || few_rows) && forced == 0) {
     return R <= 192 ? launch_wide<D, 3>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream)
                     : launch_wide<D, 4>(tab, sh, Q, K, counts_in, alpha_bar, ws, V, stream);

@@ -221,6 +221,12 @@ static void whole_rounds() {
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 1024);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 768, true);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_F32, false, 512);
+  // 256 at a time: 129 to 192 rows without cardinalities, of 64 channels or read past the caches
+  chunks_of(equal(48, 16384), 5, 32, 128, KVS_BF16, false, 240);
+  chunks_of(equal(48, 16384), 5, 32, 128, KVS_BF16, false, 480, true);
+  chunks_of(equal(48, 16384), 5, 32, 128, KVS_BF16, true, 480);
+  chunks_of(equal(32, 9000), 5, 32, 64, KVS_BF16, false, 256);
+  chunks_of(equal(32, 9000), 7, 32, 64, KVS_BF16, false, 512);
   // ragged launches a little above two rounds: chunks as much longer as it takes, of a tile for each of four wavefronts
   std::vector<int32_t> many;
   for (int i = 0; i < 100; ++i) many.push_back(8000 + 222 * i);

@@ -18,7 +18,13 @@ pytestmark = pytest.mark.gpu
     (8, 16390, 16390, 128, 8, 64, "bf16", False, False),      # 512 rows: one round of 256
     (3, 30011, 60000, 128, 9, 33, "bf16", True, False),       # 297 rows: eight wavefronts, two of them with two blocks
     (8, 16500, 16500, 64, 5, 106, "bf16", False, True),       # 530 rows: two launches per sweep
+    (32, 9000, 9000, 64, 5, 32, "bf16", False, False),        # 160 rows of 64 channels: a round of 256
+    (20, 20000, 24000, 128, 6, 32, "bf16", False, True),      # 192 rows, read past the caches, ragged: two rounds of 256
     (90, 12300, 12300, 128, 4, 20, "bf16", True, False),      # 80 rows: several rounds
+    (100, 11000, 11000, 64, 3, 1, "bf16", True, False),       # 3 rows: a round of 768
+    (64, 4000, 21000, 128, 1, 1, "f32", False, False),        # one row, ragged
+    (90, 12000, 12000, 64, 2, 16, "bf16", True, False),       # 32 rows of 64 channels with cardinalities: rounds of 768
+    (50, 20000, 24000, 64, 4, 16, "bf16", False, False),      # without, ragged: a round of 1024
     (64, 4111, 4111, 64, 1, 9, "bf16", False, False),         # 9 rows
     (40, 4111, 4111, 128, 2, 17, "f32", False, False),        # fp32, 34 rows
 ])
