@@ -205,6 +205,12 @@ static void whole_rounds() {
   chunks_of(equal(24, 6500), 4, 16, 128, KVS_BF16, true, 504);
   chunks_of(equal(64, 3277), 4, 32, 128, KVS_BF16, true, 512);
   chunks_of(equal(100, 21000), 4, 32, 128, KVS_BF16, true, 1000);   // two rounds either way, of 2112 tokens each
+  for (int window : {17, 32}) {
+    chunks_of(equal(100, 11000), 4, window, 128, KVS_BF16, false, 500);
+    chunks_of(equal(100, 11000), 4, window, 128, KVS_BF16, true, 500);
+    chunks_of(equal(100, 21000), 4, window, 128, KVS_BF16, false, 1000);
+    chunks_of(equal(64, 21000), 4, window, 128, KVS_BF16, false, 512);
+  }
   chunks_of(equal(40, 32768), 4, 16, 128, KVS_BF16, true, 480);     // pieces of whole tiles of 32 that all wavefronts share
   chunks_of(equal(8, 16431), 4, 64, 64, KVS_BF16, false, 416);
   chunks_of(equal(16, 8402), 1, 64, 128, KVS_F32, false, 432);

@@ -102,6 +102,34 @@ def test_sensitivity_matches_oracle(base, D, G, W, lens, dtype, causal):
     check_sensitivity(w, units, lens, D, G, W, dtype, causal)
 
 
+def check_unit_norms(u, D, cw, alpha, gA, gC, i):
+    """alpha_bar, A_t and C_t (n - 1 of them) of one unit against the oracle."""
+    n = len(alpha)
+    ra, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=cw)
+    A_ref, C_ref = O.per_query_norms(u.Q, u.K, u.V, causal_window=cw, counts=u.counts)
+    assert np.max(np.abs(alpha - ra) / ra) < TOL_ALPHA
+    assert np.isfinite(gA).all() and np.isfinite(gC).all()
+    rows = O.attention_rows(u.Q, u.K, counts=u.counts, causal_window=cw)
+    V64 = O.slot_values(u.V, u.counts)
+    size = np.zeros(n)                           # mean over the rows of alpha ||v_t - o|| (no |1 - 2 alpha|)
+    for a_q in rows:
+        size += a_q * np.linalg.norm(V64 - a_q @ V64, axis=1)
+    size /= rows.shape[0]
+    onorm = np.linalg.norm(rows @ V64, axis=1)    # ||o^{(q)}|| of every row
+    conc = (rows * onorm[:, None]).mean(axis=0)   # mean over the rows of alpha_t ||o||
+    den = A_ref + (alpha_row_tol(u.Q, u.K, u.counts, D) / TOL_NORMS) * size + (TOL_WEIGHT / TOL_NORMS) * conc
+    concC = 2.0 * (rows[:, :-1] * rows[:, 1:] * onorm[:, None]).mean(axis=0)
+    if n == 1:
+        # a unit's only token has alpha = 1 and o = v: A is exactly zero, and what the kernel finds is the
+        # rounding of o against v
+        assert gA[0] <= 1e-5 * np.linalg.norm(V64[0])
+        den = np.ones(1)
+    eA = np.max(np.abs(gA - A_ref) / den)
+    eC = np.max(np.abs(gC - C_ref) / (C_ref + (TOL_WEIGHT / TOL_NORMS) * concC)) if n > 1 else 0.0
+    assert eA < TOL_NORMS, (i, "A", eA)
+    assert eC < TOL_NORMS, (i, "C", eC)
+
+
 def check_sensitivity(w, units, lens, D, G, W, dtype, causal):
     """kvs_sensitivity(_counts) on `units` against the oracle."""
     batch = DeviceBatch(units, group=G, window=W, head_dim=D, dtype=dtype, n_sink=w.n_sink, gap_rows=3,
@@ -123,30 +151,7 @@ def check_sensitivity(w, units, lens, D, G, W, dtype, causal):
     for i, u in enumerate(units):
         n = lens[i]
         r0 = p.in_rows[i]
-        ra, _ = O.score(u.Q, u.K, u.V, counts=u.counts, causal_window=cw)
-        A_ref, C_ref = O.per_query_norms(u.Q, u.K, u.V, causal_window=cw, counts=u.counts)
-        assert np.max(np.abs(alpha[r0:r0 + n] - ra) / ra) < TOL_ALPHA
-        gA, gC = A[r0:r0 + n], C[r0:r0 + n - 1]
-        assert np.isfinite(gA).all() and np.isfinite(gC).all()
-        rows = O.attention_rows(u.Q, u.K, counts=u.counts, causal_window=cw)
-        V64 = O.slot_values(u.V, u.counts)
-        size = np.zeros(n)                           # mean over the rows of alpha ||v_t - o|| (no |1 - 2 alpha|)
-        for a_q in rows:
-            size += a_q * np.linalg.norm(V64 - a_q @ V64, axis=1)
-        size /= rows.shape[0]
-        onorm = np.linalg.norm(rows @ V64, axis=1)    # ||o^{(q)}|| of every row
-        conc = (rows * onorm[:, None]).mean(axis=0)   # mean over the rows of alpha_t ||o||
-        den = A_ref + (alpha_row_tol(u.Q, u.K, u.counts, D) / TOL_NORMS) * size + (TOL_WEIGHT / TOL_NORMS) * conc
-        concC = 2.0 * (rows[:, :-1] * rows[:, 1:] * onorm[:, None]).mean(axis=0)
-        if n == 1:
-            # a unit's only token has alpha = 1 and o = v: A is exactly zero, and what the kernel finds is the
-            # rounding of o against v
-            assert gA[0] <= 1e-5 * np.linalg.norm(V64[0])
-            den = np.ones(1)
-        eA = np.max(np.abs(gA - A_ref) / den)
-        eC = np.max(np.abs(gC - C_ref) / (C_ref + (TOL_WEIGHT / TOL_NORMS) * concC)) if n > 1 else 0.0
-        assert eA < TOL_NORMS, (i, "A", eA)
-        assert eC < TOL_NORMS, (i, "C", eC)
+        check_unit_norms(u, D, cw, alpha[r0:r0 + n], A[r0:r0 + n], C[r0:r0 + n - 1], i)
         assert C[r0 + n - 1] == 0.0                  # a unit's last row has no edge
     for i in range(len(units) - 1):                  # rows between units are never touched
         gap0 = p.in_rows[i] + lens[i]

@@ -6,8 +6,8 @@ import pytest
 
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate_unit
 
-from test_gpu_parity import TOL_ALPHA, variant
-from test_gpu_per_query import TOL_NORMS, check_sensitivity
+from test_gpu_parity import variant
+from test_gpu_per_query import check_sensitivity, check_unit_norms
 
 pytestmark = pytest.mark.gpu
 
@@ -70,32 +70,36 @@ def test_few_rows_with_marked_tokens(D, G, W):
     check_sensitivity(w, [u], [n], D, G, W, "bf16", False)
 
 
-def test_norms_of_64_rows_over_many_tokens():
+@pytest.mark.parametrize("base,causal,marked", [
+    ("llama8b_8k", False, False), ("llama8b_8k", True, True), ("stream2560", False, True), ("stream2560", True, False)])
+def test_norms_of_64_rows_over_many_tokens(base, causal, marked):
     """128 channels and 33 to 64 rows: only launches of 262144 tokens or more have the norms' kernel for them.  Units that are
-    alike, two of them against the oracle and all of them against each other."""
+    alike, two of them against the oracle and all of them against each other; marked: a row's weight on one token, at the ends
+    of tiles and of the unit, so that its norms cancel there."""
     import torch
     import paper_2603_00907_amd as kvs
     n, copies, D, G, W = 2050, 128, 128, 3, 13
-    w = variant("llama8b_8k", dtype="bf16", head_dim=D, group=G, window=W, n_seq=2, n_kv_heads=1)
+    w = variant(base, dtype="bf16", head_dim=D, group=G, window=W, n_seq=2, n_kv_heads=1)
     u = [generate_unit(w, 0, s, 0, n=n) for s in range(2)]
+    for x in u if marked else []:
+        q, K = x.Q.reshape(-1, D).astype(np.float32), x.K.astype(np.float32) * 0.1
+        for i, t in enumerate([0, 30, 31, 61, 62, 92, 93, 128, 1023, n - 2, n - 1]):
+            r = len(q) - 1 if t >= n - 2 else 7 * i % len(q)            # (the last row sees all tokens)
+            K[t] = q[r] * (20.0 * np.sqrt(D) / np.dot(q[r], q[r]))
+        x.K = _bf16(K)
     Q, K, V = (torch.from_numpy(np.stack([getattr(x, f).astype(np.float32).reshape(-1, D) for x in u])).to("cuda", torch.bfloat16)
                .repeat(copies // 2, 1, 1) for f in "QKV")
-    p = kvs.Problem(lens=[n] * copies, budgets=[n // 2] * copies, group=G, window=W, head_dim=D, dtype="bf16")
+    c = None
+    if u[0].counts is not None:
+        c = torch.from_numpy(np.stack([x.counts for x in u])).to("cuda", torch.int32).repeat(copies // 2, 1)
+    p = kvs.Problem(lens=[n] * copies, budgets=[n // 2] * copies, group=G, window=W, head_dim=D, dtype="bf16", causal=causal)
     assert p.rows_in >= 1 << 18
     alpha, a_tok, c_edge = (torch.full((copies, n), -7.0, device="cuda") for _ in range(3))
     ws = torch.full((kvs.kvs_per_query_workspace_size(p),), 0xFF, dtype=torch.uint8, device="cuda")
-    kvs.kvs_sensitivity(p, Q, K, V, alpha, a_tok, c_edge, ws, stream=torch.cuda.current_stream().cuda_stream)
+    kvs.kvs_sensitivity_counts(p, Q, K, V, c, alpha, a_tok, c_edge, ws, stream=torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     for x in (alpha, a_tok, c_edge):
         assert torch.equal(x.view(copies // 2, 2, n), x[:2].expand(copies // 2, 2, n))
     for i in range(2):
-        q, k, v = (x[i].float().cpu().numpy().astype(np.float64) for x in (Q, K, V))
-        e = q @ k.T / np.sqrt(D)
-        al = np.exp(e - e.max(axis=1, keepdims=True))
-        al /= al.sum(axis=1, keepdims=True)
-        r = v[None] - (al @ v)[:, None]
-        A = (np.abs(al * (1 - 2 * al)) * np.linalg.norm(r, axis=2)).mean(axis=0)
-        C = (al[:, :-1] * al[:, 1:] * np.linalg.norm(r[:, :-1] + r[:, 1:], axis=2)).mean(axis=0)
-        assert np.max(np.abs(alpha[i].cpu().numpy() / al.mean(axis=0) - 1)) < TOL_ALPHA
-        assert np.max(np.abs(a_tok[i].cpu().numpy() / A - 1)) < TOL_NORMS
-        assert np.max(np.abs(c_edge[i, :-1].cpu().numpy() / C - 1)) < TOL_NORMS
+        check_unit_norms(u[i], D, W if causal else 0, *(x[i].cpu().numpy().astype(np.float64) for x in (alpha, a_tok)),
+                         c_edge[i, :-1].cpu().numpy().astype(np.float64), i)

@@ -42,3 +42,35 @@ def test_score_of_few_rows(D, G, W, counts, causal, ride):
         assert np.max(np.abs(got[at] - ref) / ref) < TOL_ALPHA, i
         values = O.slot_values(v, ci)
         assert (np.abs(got_o[i] - ref_o) <= TOL_ALPHA * (ref @ np.abs(values)) + 1e-7).all(), i
+
+
+@pytest.mark.parametrize("G,W,counts,causal", [(1, 16, False, False), (4, 8, True, True), (4, 16, False, True)])
+def test_score_of_few_rows_past_the_caches(G, W, counts, causal):
+    """128 channels, K and V above 192 MB: read past the caches, the pass over V carried along by sweep 1."""
+    import torch
+    import paper_2603_00907_amd as kvs
+    lens, D = [32000 - 777 * i for i in range(18)], 128
+    n, R = len(lens), G * W
+    rows = np.cumsum([0] + lens)
+    assert 4 * int(rows[-1]) * D > 192 << 20
+    p = kvs.Problem(lens=lens, budgets=[2048] * n, group=G, window=W, head_dim=D, dtype="bf16", n_sink=4, causal=causal)
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    K, V = (torch.randn((int(rows[-1]), D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    Q = torch.randn((n, R, D), generator=gen, device="cuda").to(torch.bfloat16)
+    c = torch.randint(1, 50, (int(rows[-1]),), generator=gen, device="cuda", dtype=torch.int32) if counts else None
+    alpha = torch.full((int(rows[-1]),), -7.0, device="cuda")
+    o_bar = torch.full((n, D), -7.0, device="cuda")
+    ws = torch.full((kvs.kvs_workspace_size(p),), 0xFF, dtype=torch.uint8, device="cuda")
+    kvs.kvs_score_counts(p, Q, K, V, c, alpha, o_bar, ws, stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got, got_o = alpha.cpu().numpy(), o_bar.cpu().numpy()
+    for i in range(n):
+        assert abs(got[rows[i]:rows[i + 1]].astype(np.float64).sum() - 1) < TOL_ALPHA, i      # TOL_ALPHA of every term
+    for i in (0, 9, n - 1):
+        at = slice(rows[i], rows[i + 1])
+        k, v = (x[at].float().cpu().numpy() for x in (K, V))
+        ci = c[at].cpu().numpy() if counts else None
+        ref, ref_o = O.score(Q[i].float().cpu().numpy().reshape(G, W, D), k, v, counts=ci, causal_window=W if causal else 0)
+        assert np.max(np.abs(got[at] - ref) / ref) < TOL_ALPHA, i
+        values = O.slot_values(v, ci)
+        assert (np.abs(got_o[i] - ref_o) <= TOL_ALPHA * (ref @ np.abs(values)) + 1e-7).all(), i
