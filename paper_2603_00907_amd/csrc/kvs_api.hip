@@ -86,6 +86,7 @@ struct Plan {
   Unit* dev_table = nullptr;     // where a group of more than kInlineUnits units keeps its descriptors (workspace), or
                                  // null: the call has no such memory and its groups stay within kInlineUnits
   hipStream_t stream = nullptr;  // the call's stream (the descriptors are written on it)
+  bool counts = false;           // the call has cardinalities
 };
 
 // One past the last unit of the launch group that starts at unit `first`.
@@ -119,6 +120,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
   }
 
   plan->n_units = p->n_units;
+  plan->counts = counts;
   plan->dtype = p->io_dtype;
   plan->elt = (p->io_dtype == KVS_F32) ? 4 : 2;
   plan->shape.R = p->group * p->window;
@@ -571,8 +573,11 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     // many units (128 ragged ones of 4 K to 64 K tokens: 1055 against 1076 us per step), or a unit too long for the parts
     // that it may have (32 of 131072: 1052 against 1122; 24 of 100000: 632 and 698; 8 of 524288: 1306 and 1388).
     // And so does a window of up to 64 rows of 64 channels, whose sweep 1 runs in four workgroups per compute unit without V and
-    // three with it (100 of 29584 tokens, 16 rows: 418 us, riding 432; 50 ragged ones of 20000 to 32000 186, riding 207).
-    sh.ride = sh.stream && !(sh.D == 64 && sh.R <= 64);
+    // three with it (100 of 29584 tokens, 16 rows: 418 us, riding 432; 50 ragged ones of 20000 to 32000 186, riding 207), where
+    // it has more than two workgroups per compute unit (8 of 131072 174, riding 166) and, with cardinalities, of which sweep 0
+    // has three in any case, where units are unequal (50 of 20000 to 32000 202, riding 216; 150 of 9000 199, riding 195).
+    const bool light = sh.D == 64 && sh.R <= 64;
+    sh.ride = sh.stream && (!light || (plan.counts ? tab.even != 0 : chunks <= kScoreWorkgroups / 2));
     for (const Unit& un : units) {
       if (un.len <= kSelRegSlices * 4 * kSelThreads) continue;
       const bool meet = few_units && select_exchanges(un, sh) &&

@@ -134,8 +134,11 @@ static void equal_units(int nu, int len, int window) {
 // One step over nu equal units (one launch, more than the caches hold): whether sweep 1 carries the pass over V, and the
 // select workgroups per unit.  A unit of more than 32768 tokens whose selection is not shared out by parts that meet keeps V
 // apart: that selection is then hidden beside the pass.
-static void values_ride(int nu, int len, int budget, bool rode, int parts, int window = 32, int D = 128) {
-  Problem pr(std::vector<int32_t>(nu, len), std::vector<int32_t>(nu, budget), 4, window, D, KVS_BF16);
+static void values_ride(int nu, int len, int budget, bool rode, int parts, int window = 32, int D = 128, bool counts = false,
+                        int more = 0) {
+  std::vector<int32_t> lens(nu, len);
+  lens[0] += more;                              // units of unequal lengths
+  Problem pr(lens, std::vector<int32_t>(nu, budget), 4, window, D, KVS_BF16);
   pr.p.n_sink = 32;
   size_t ws_bytes = 0;
   EXPECT(kvs_workspace_size(&pr.p, &ws_bytes) == KVS_OK);
@@ -147,7 +150,8 @@ static void values_ride(int nu, int len, int budget, bool rode, int parts, int w
   void* Vo = a.take((size_t)pr.rows_out * 128 * 2);
   int32_t* cnt = (int32_t*)a.take((size_t)pr.rows_out * 4);
   void* ws = a.take(ws_bytes);
-  EXPECT(kvs_step(&pr.p, Q, K, V, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr) == KVS_OK);
+  int32_t* cin = counts ? (int32_t*)a.take((size_t)pr.rows_in * 4) : nullptr;
+  EXPECT(kvs_step_counts(&pr.p, Q, K, V, cin, Ko, Vo, cnt, nullptr, nullptr, ws, ws_bytes, nullptr) == KVS_OK);
   if (kvs::stub_values_rode() != rode || kvs::stub_most_parts() != parts) {
     std::printf("%d x %d: V %s, %d select workgroups per unit\n", nu, len, kvs::stub_values_rode() ? "rode" : "apart",
                 kvs::stub_most_parts());
@@ -304,8 +308,12 @@ int main() {
   values_ride(24, 100000, 8192, false, 1);
   values_ride(8, 300000, 8192, false, 1);
   values_ride(8, 524288, 8192, false, 1);
-  values_ride(64, 32768, 8192, true, 4, 8);     // 32 rows: with 128 channels only
-  values_ride(64, 32768, 8192, false, 1, 8, 64);
+  values_ride(64, 32768, 8192, true, 4, 8);     // 32 rows: with 64 channels where two workgroups run on a compute unit, or
+  values_ride(64, 32768, 8192, false, 1, 8, 64);                  // three of equal units with cardinalities
+  values_ride(8, 131072, 8192, true, 32, 8, 64);
+  values_ride(64, 32768, 8192, true, 4, 8, 64, true);
+  values_ride(64, 32700, 8192, false, 1, 8, 64, true, 60);
+  values_ride(64, 32700, 8192, true, 4, 8, 128, true, 60);
   values_ride(64, 32768, 8192, true, 4, 17, 64);
   values_ride(8, 131072, 131072, false, 1);     // nothing to select: as before the selection was shared out
   kvs::stub_asks_for_fused = true;              // the switch for the one-pass kernel changes inside a call on a large group
