@@ -179,10 +179,11 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
     // empty (two workgroups of the wide kernel run on a CU at a time).  Slightly longer chunks in that launch group do without
     // it: 64 ragged units of 4 K to 64 K tokens, 128 rows, 1076 workgroups, sweeps 121 + 136 us; at most 1024, 109 + 122 (the
     // step of two such groups 1066 -> 1032 us, with per-query norms, whose workgroups are the same chunks, 1915 -> 1821).  Up to
-    // 64 rows too (8 rows 583 -> 558; 100 of 8000 to 30000 520 -> 495), but not where the chunks are the pieces of per-query
-    // kernels that have not been measured with it.  Equal units whose number fits no whole rounds (below) likewise.  Per group,
-    // since the chunks that suit one group cost the next: chosen for both together, its sweeps took 102 + 113 us instead of
-    // 97 + 105.
+    // 64 rows too (8 rows 583 -> 558; 100 of 8000 to 30000 520 -> 495), but not where the chunks are the pieces of their per-query
+    // kernels, which were not measured with it, and from one round on (56 of 1757 to 14060, 516 workgroups, 4 rows 145 -> 131,
+    // 128 rows 162 -> 144; 20 of 20000 to 32000, per query 345 -> 286).  Equal units whose number fits no whole rounds (below)
+    // likewise.  Per group, since the chunks that suit one group cost the next: chosen for both together, its sweeps took
+    // 102 + 113 us instead of 97 + 105.
     const bool wide = plan->dtype == KVS_BF16 && plan->shape.R >= (per_query ? 65 : 4) && plan->shape.R <= 128 &&
                       debug_switch(KVS_DEBUG_SCORE_CHUNK) == 0;
     // Whole rounds of as few workgroups as run at once: a workgroup of the kernels for more than 128 rows spends 6 to 12 us
@@ -194,9 +195,10 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
     // 159 + 194; 48 of 32768 with 224 rows, 512 at a time: 768 workgroups 132 + 166, 480 126 + 162.  Steps: 48 of 16384, 224
     // rows 299 -> 253 (with the kernel's other changes), 160 rows 256 -> 231; 64 of 32768, 128 rows 516 -> 509, one row
     // 590 -> 563; 48 of 30000, fp32, 32 rows 773 -> 739.  Up to 128 rows equal units only: pieces of unequal lengths balance
-    // better in more rounds (128 ragged units 1029 -> 1081; but see below).  fp32 above 64 rows, of whose workgroups 512 run at once up to 128
-    // rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89; not with chunks below 192 tokens
-    // (8 of 8192: 71.4 with two workgroups of 128 per compute unit, 69.9 with one of 256).
+    // better in more rounds (128 ragged units 1029 -> 1081; but see below), above that ragged ones too (48 of 3000 to 24000, 160
+    // rows 233 -> 201, 224 rows 261 -> 214, 512 rows 391 -> 312, 16 of 4000 to 40000 182 -> 169).  fp32 above 64 rows, of whose
+    // workgroups 512 run at once up to 128 rows and 256 above: 8 of 12000, 256 rows 138 -> 115, 16 of 6000, 128 rows 94 -> 89;
+    // not with chunks below 192 tokens (8 of 8192: 71.4 with two workgroups of 128 per compute unit, 69.9 with one of 256).
     const int rows = plan->shape.R;
     // Per-query calls: those whose alpha_bar comes from kvs_score's two sweeps have its chunks, and so its bits (fp32, 8 units of
     // 8192 1158 -> 919 us, 4 of 3000 with 32 rows 301 -> 170; 100 of 9000, one bf16 row 547 -> 436).  The others' chunks are
@@ -242,7 +244,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
       constexpr long long kRound = kScoreWorkgroups / 2;
       const long long n = wide ? workgroups(want) : 0, full = n / kRound * kRound;
       long long longer = want;
-      if (full >= kScoreWorkgroups && n > full && n - full <= kRound / 4) {
+      if (full >= kRound && n > full && n - full <= kRound / 4) {
         // (beyond kMaxChunkLen where that is the aim; a tile for each of the score kernel's four wavefronts, one of the
         // per-query kernels, which share it: 85 units of 24769 with 56 rows and cardinalities, chunks of 2112 995, of 2176 934)
         const long long step = pieces ? kWave : 4 * 32;

@@ -237,7 +237,11 @@ static void whole_rounds() {
   chunks_of(equal(48, 16384), 5, 32, 128, KVS_BF16, true, 480);
   chunks_of(equal(32, 9000), 5, 32, 64, KVS_BF16, false, 256);
   chunks_of(equal(32, 9000), 7, 32, 64, KVS_BF16, false, 512);
-  // ragged launches a little above two rounds: chunks as much longer as it takes, of a tile for each of four wavefronts
+  // ragged launches a little above one round, or two: chunks as much longer as it takes, of a tile for each of four wavefronts
+  std::vector<int32_t> some;
+  for (int i = 0; i < 20; ++i) some.push_back(20000 + 640 * i);
+  for (int group : {1, 2, 4}) chunks_of(some, group, 32, 128, KVS_BF16, false, 463);
+  chunks_of(some, 4, 32, 128, KVS_BF16, true, 489);
   std::vector<int32_t> many;
   for (int i = 0; i < 100; ++i) many.push_back(8000 + 222 * i);
   for (int group : {1, 2, 4}) chunks_of(many, group, 32, 128, KVS_BF16, false, 978);

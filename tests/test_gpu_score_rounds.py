@@ -8,6 +8,7 @@ import pytest
 from oracle import kvs_oracle as O
 
 from test_gpu_parity import TOL_ALPHA, switches
+from test_gpu_score_whole_rounds import check
 
 pytestmark = pytest.mark.gpu
 
@@ -51,6 +52,12 @@ def test_score_with_longer_chunks(n, longest, D, G, W, seed):
         ref, ref_o = O.score(Q[i].float().cpu().numpy().reshape(G, W, D), k, v)
         assert np.max(np.abs(got[rows[i]:rows[i] + lens[i]] - ref) / ref) < TOL_ALPHA, i
         assert (np.abs(got_o[i] - ref_o) <= TOL_ALPHA * (ref @ np.abs(v)) + 1e-7).all(), i
+
+
+@pytest.mark.parametrize("G,W,counts,causal", [(1, 4, False, True), (4, 32, True, False)])
+def test_score_with_longer_chunks_in_one_round(G, W, counts, causal):
+    """520 chunks of 1024 tokens become 463 of 1152; V is carried along by sweep 1."""
+    check([20000 + 640 * i for i in range(20)], 128, G, W, "bf16", counts, causal)
 
 
 @pytest.mark.parametrize("counts", [False, True])
