@@ -217,6 +217,7 @@ static void whole_rounds() {
   }
   chunks_of(equal(40, 32768), 4, 16, 128, KVS_BF16, true, 480);     // pieces of whole tiles of 32 that all wavefronts share
   chunks_of(equal(8, 16431), 4, 64, 64, KVS_BF16, false, 416);
+  chunks_of(equal(24, 10721), 8, 64, 64, KVS_BF16, false, 216);     // two rounds of 512 and one of 1280, and what a workgroup does once
   chunks_of(equal(16, 8402), 1, 64, 128, KVS_F32, false, 432);
   std::vector<int32_t> ragged;
   for (int i = 0; i < 16; ++i) ragged.push_back(4000 + 2400 * i);
