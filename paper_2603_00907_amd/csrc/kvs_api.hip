@@ -580,10 +580,17 @@ kvs_status for_each_group(const Plan& plan, F&& f, Select select = Select::kOneW
     // three with it (100 of 29584 tokens, 16 rows: 418 us, riding 432; 50 ragged ones of 20000 to 32000 186, riding 207), where
     // it has more than two workgroups per compute unit (8 of 131072 174, riding 166) and, with cardinalities, of which sweep 0
     // has three in any case, where units are unequal (50 of 20000 to 32000 202, riding 216; 150 of 9000 199, riding 195).
-    const bool light = sh.D == 64 && sh.R <= 64;
-    sh.ride = sh.stream && (!light || (plan.counts ? tab.even != 0 : chunks <= kScoreWorkgroups / 2));
+    // With 128 channels and up to 64 rows it is the larger of those launches that gain, those with cardinalities, and those
+    // with such long units (32 rows: 30 ragged ones of 9000 to 30000 156 us, riding 160; 56 of 1757 to 14060 124 and 130; 60 of
+    // 3000 to 20000 173 and 177, with cardinalities 182 and 179; 100 of 2000 to 12000 189 and 191; 12 of 30000 to 100000 242
+    // and 234, of 49804 177 and 171).
+    const bool larger = 2 * rows * sh.D * (long long)plan.elt > 2 * kStreamBytes;
+    const auto is_long = [](const Unit& un) { return un.len > kSelRegSlices * 4 * kSelThreads; };
+    sh.ride = sh.stream;
+    if (sh.R <= 64 && sh.D == 64) sh.ride = sh.stream && (plan.counts ? tab.even != 0 : chunks <= kScoreWorkgroups / 2);
+    else if (sh.R <= 64 && !plan.counts && !larger) sh.ride = sh.stream && std::any_of(units.begin(), units.end(), is_long);
     for (const Unit& un : units) {
-      if (un.len <= kSelRegSlices * 4 * kSelThreads) continue;
+      if (!is_long(un)) continue;
       const bool meet = few_units && select_exchanges(un, sh) &&
                         select_parts(un, sh, tab.n_units, n_cus, split_mode, /*beside_values=*/false) > 1;
       if (!meet) sh.ride = 0;

@@ -319,6 +319,10 @@ int main() {
   values_ride(64, 32768, 8192, true, 4, 8, 64, true);
   values_ride(64, 32700, 8192, false, 1, 8, 64, true, 60);
   values_ride(64, 32700, 8192, true, 4, 8, 128, true, 60);
+  values_ride(60, 9000, 2000, false, 1, 8);                       // with 128 channels in the larger launches, or cardinalities
+  values_ride(60, 9000, 2000, true, 3, 8, 128, true);
+  values_ride(60, 9000, 2000, true, 3);
+  values_ride(8, 60000, 9000, true, 30, 8);                       // and with long units whose selection is shared out
   values_ride(64, 32768, 8192, true, 4, 17, 64);
   values_ride(8, 131072, 131072, false, 1);     // nothing to select: as before the selection was shared out
   kvs::stub_asks_for_fused = true;              // the switch for the one-pass kernel changes inside a call on a large group
