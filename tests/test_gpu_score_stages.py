@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     ([2900 + 431 * i for i in range(30)], 128, 9, 32, True, True),
     ([33000 + 97 * i for i in range(24)], 64, 9, 32, False, True),       # read past the caches: long in sweep 0, V in sweep 1
     ([20000 + 97 * i for i in range(40)], 64, 7, 32, False, False),
+    ([20000 + 97 * i for i in range(40)], 64, 8, 32, True, True),        # with cardinalities
+    ([20000 + 97 * i for i in range(40)], 64, 9, 32, True, False),
 ])
 def test_score_in_stages(lens, D, G, W, counts, causal):
     check(lens, D, G, W, "bf16", counts, causal)
