@@ -1314,7 +1314,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
   // Up to 32 rows both narrow kernels (figures at pq_out_narrow_kernel), in small launches the norms' alone (see pq_small).  33 to 64 rows, two wavefronts to a tile, with 64
   // channels (12 units of 29384 135 -> 114 us, one of 1000 35.6 -> 34.8); with 128 channels the outputs' reads of every tile by
   // two wavefronts cost more than the idle rows (8 of 32768 131 -> 138), and the norms gain from some 256 K tokens on
-  // (8 of 32768 131.3 -> 130.0, 4 of 100000 193 -> 186, 100 of 21000 892 -> 858, 40 of 20000 with cardinalities 446 -> 415;
+  // (8 of 32768 131.3 -> 130.0, 4 of 100000 193 -> 186, 100 of 21000 892 -> 865, 40 of 20000 with cardinalities 446 -> 418;
   // 4 ragged ones, 150000 tokens, 90.1 -> 92.2, 32 of 3000 85.9 -> 87.8).
   const bool one = sh.R <= kPqNarrowRows, two = !one && sh.R <= 2 * kPqNarrowRows;
   const bool small = pq_small(tab.n_units, rows, sh.R, D);
