@@ -214,9 +214,10 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
     // and ragged ones where that was no loss.  Steps, with 512 at a time -> now (us): one row, 150 units of 4000 173 -> 161, 64
     // ragged ones of 4096 to 65536 646 -> 605; 3 rows, fp32, 100 of 11000 717 -> 663 (673 before there were whole rounds); 64
     // channels, 16 rows, 100 of 29584 443 -> 418, 64 of 32768 285 -> 278, 40 of 31250 to 125000 455 -> 445; with cardinalities
-    // 150 of 9000 201 -> 198, but 60 ragged ones 63 -> 65, so equal units only.  Below 512 tokens for each of the 1024 equal units
-    // lose (64 channels, 64 rows, 30 of 10000 59.3, so 61.2; 8 rows, 16 of 25759 83.9 and 84.6; 32 rows, 100 of 4500 78.3 and 78.5),
-    // ragged ones gain as much as they lose (60 of 3000 to 9000 72.6, so 71.4; 20 of 8000 to 30000 70.0 and 70.9).  And one of the eight wavefronts that 129 to 192
+    // 150 of 9000 201 -> 198, but 60 ragged ones 63 -> 65, so equal units only.  Equal units of fewer than 512 tokens for
+    // each of the 1024 take rounds of 512 (64 channels, 64 rows, 30 of 10000 59.0, of 1024 61.2; 8 rows, 16 of 25759 83.8 and 84.6;
+    // 64 rows, 149 of 2777, which miss both with the ordinary chunks, 79.5 and 81.1); ragged ones gain as much as they lose by that
+    // (60 of 3000 to 9000 72.6, of 1024 71.4; 20 of 8000 to 30000 70.0 and 70.9).  And one of the eight wavefronts that 129 to 192
     // rows take in some launches (48 of 16384, 160 rows 231 -> 226, 64 channels, 32 of 9000 71.2 -> 68.1, 40 of 4000 to 16000
     // 90 -> 87; 48 of 32768 436 -> 441).
     const bool few = rows < 4;
@@ -264,6 +265,8 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
       const long long at_once = plan->dtype == KVS_BF16 && !pieces &&
                                         score_rows_in_one_workgroup(rows, p->head_dim, stream, counts)
                                     ? 256
+                                : light && !counts && equal && tokens < 2 * resident * kMinChunkLen
+                                    ? resident / 2
                                     : resident;
       long long tiny = kMinChunkLen;
       if (rounds && tokens < kTinyWorkgroups * kMinChunkLen) {
@@ -272,7 +275,7 @@ kvs_status make_plan(const kvs_problem* p, Plan* plan, bool per_query = false, b
       if (tiny < kMinChunkLen) {
         longer = tiny;
       } else if (rounds && !(pieces && rows > 256) && (equal || rows > 128 || few || (light && !counts)) &&
-                 tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * (light && !counts && equal ? 2 * kMinChunkLen : few || light ? kMinChunkLen : want))) {
+                 tokens >= (split ? kTinyWorkgroups * kMinChunkLen : at_once * (at_once > 512 ? kMinChunkLen : want))) {
         // (fewer rounds also where they take as long: 24 of 10721, 64 channels, 512 rows with cardinalities 111 -> 107)
         const long long plain = (longer + kWave - 1) / kWave * kWave;
         long long best = (workgroups(plain) + at_once - 1) / at_once * (plain + once) + 1;

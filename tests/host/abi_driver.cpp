@@ -232,8 +232,9 @@ static void whole_rounds() {
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 1024);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 768, true);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_F32, false, 512);
-  chunks_of(equal(16, 25759), 4, 2, 64, KVS_BF16, false, 496);      // not with fewer than 512 tokens for each of the 1024
+  chunks_of(equal(16, 25759), 4, 2, 64, KVS_BF16, false, 496);      // 512 at a time with fewer tokens than 512 for each of the 1024
   chunks_of(equal(30, 10000), 4, 16, 64, KVS_BF16, false, 480);
+  chunks_of(equal(149, 2777), 1, 64, 64, KVS_BF16, false, 447);
   chunks_of(equal(100, 5300), 4, 8, 64, KVS_BF16, false, 900);
   // 256 at a time: 129 to 192 rows without cardinalities, of 64 channels or read past the caches
   chunks_of(equal(48, 16384), 5, 32, 128, KVS_BF16, false, 240);
