@@ -217,6 +217,8 @@ static void whole_rounds() {
   }
   chunks_of(equal(40, 32768), 4, 16, 128, KVS_BF16, true, 480);     // pieces of whole tiles of 32 that all wavefronts share
   chunks_of(equal(8, 16431), 4, 64, 64, KVS_BF16, false, 416);
+  chunks_of(equal(34, 4481), 4, 32, 128, KVS_BF16, false, 408);     // a tile for each of four wavefronts: 384 tokens take no longer than 320
+  chunks_of(equal(16, 10000), 4, 32, 128, KVS_BF16, false, 432);
   chunks_of(equal(24, 10721), 8, 64, 64, KVS_BF16, false, 216);     // two rounds of 512 and one of 1280, and what a workgroup does once
   chunks_of(equal(16, 8402), 1, 64, 128, KVS_F32, false, 432);
   std::vector<int32_t> ragged;
@@ -232,7 +234,7 @@ static void whole_rounds() {
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 1024);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_BF16, false, 768, true);
   chunks_of(equal(64, 32768), 4, 4, 64, KVS_F32, false, 512);
-  chunks_of(equal(16, 25759), 4, 2, 64, KVS_BF16, false, 496);      // 512 at a time with fewer tokens than 512 for each of the 1024
+  chunks_of(equal(16, 25759), 4, 2, 64, KVS_BF16, false, 464);      // 512 at a time with fewer tokens than 512 for each of the 1024
   chunks_of(equal(30, 10000), 4, 16, 64, KVS_BF16, false, 480);
   chunks_of(equal(149, 2777), 1, 64, 64, KVS_BF16, false, 447);
   chunks_of(equal(100, 5300), 4, 8, 64, KVS_BF16, false, 900);
