@@ -483,19 +483,20 @@ __global__ __launch_bounds__(NW * kWave, 2) void score_shared_kernel(
   }
 }
 
-// Long stages in sweep 0 without cardinalities (with 64 channels with and without, but only where K is read past the caches),
-// except for chunks of no more than two of them in workgroups of four wavefronts; and in a sweep 1 without V of 64 channels.  Steps with long -> short
-// stages in sweep 0 (us): cardinalities, 48 units of 21845 tokens, 512 rows 637 -> 618, 20 of 5000 to 30000, 224 rows 128 -> 126,
-// 64 channels, 160 rows 96 -> 91; none, 64 channels, 100 of 1500 to 4000, 256 rows 96 -> 93; 72 of 383 to 3068, 256 rows, chunks
-// of 256, 75.2 -> 74.6; but 104 of 5471 to 21885, 224 rows 509 -> 523, 48 of 3000 to 24000, 512 rows 313 -> 321, 64 channels
-// past the caches, 152 of 6898, 512 rows 315 -> 325, 92 of 5698 to 22795, 256 rows 241 -> 248.  In sweep 1: 16 of 21000, 224
-// rows 129 -> 125, 160 rows 120 -> 117, 512 rows 176 -> 173; but 64 channels, 16 of 21000, 448 rows 130 -> 133.
-// (Cardinalities past the caches, 64 channels: 200 of 5000, 512 rows 361 -> 367, 64 of 32768, 256 rows 396 -> 401.)
+// Long stages in sweep 0 without cardinalities, but for 64 channels in workgroups of eight wavefronts, and with 64 channels where K
+// is read past the caches, whatever the rest; never for chunks of no more than two of them in workgroups of four wavefronts.  And in
+// a sweep 1 without V of 64 channels.  Steps with long -> short stages in sweep 0 (us): cardinalities, 48 units of 21845 tokens, 512
+// rows 637 -> 618, 20 of 5000 to 30000, 224 rows 128 -> 126, 64 channels, 160 rows 96 -> 91; none, 64 channels, 512 rows, 24 of 10721
+// 115 -> 112, 8 of 65536 190 -> 187; 72 of 383 to 3068, 256 rows, chunks of 256, 75.2 -> 74.6; but 104 of 5471 to 21885, 224 rows
+// 509 -> 523, 48 of 3000 to 24000, 512 rows 313 -> 321, 64 channels, 256 rows, 32 of 10101 to 20203 135.5 -> 137.7, 16 of 40000 158 ->
+// 160, 40 of 9000 98.4 either way, past the caches 152 of 6898, 512 rows 315 -> 325, 92 of 5698 to 22795, 256 rows 241 -> 248, with
+// cardinalities 200 of 5000, 512 rows 361 -> 367, 64 of 32768, 256 rows 396 -> 401.  In sweep 1: 16 of 21000, 224 rows 129 -> 125,
+// 160 rows 120 -> 117, 512 rows 176 -> 173; but 64 channels, 16 of 21000, 448 rows 130 -> 133.
 template <int D, int NW, bool STREAM>
 hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const void* K, const int32_t* counts_in,
                     float* alpha_bar, const Workspace& ws, const void* V, hipStream_t stream) {
   const dim3 grid(tab.total_chunks), block(NW * kWave);
-  const bool long0 = (counts_in == nullptr || D == 64) && !(NW == 4 && tab.unit(0).chunk_len <= 2 * 32 * NW);
+  const bool long0 = (counts_in == nullptr || (D == 64 && STREAM)) && !(NW == 4 && tab.unit(0).chunk_len <= 2 * 32 * NW);
   constexpr bool LONG1 = D == 64;
   hipError_t e;
   for (int qp = 0; qp < sh.R; qp += NW * 64) {
@@ -504,7 +505,7 @@ hipError_t launch_t(const UnitTable& tab, const Shape& sh, const void* Q, const 
         hipLaunchKernelGGL(kernel, grid, block, 0, stream, t, sh, (const uint16_t*)Q, (const uint16_t*)K, counts_in, alpha_bar,
                            ws.stats_part, ws.c_row, (const uint16_t*)nullptr, (float*)nullptr, qp);
       };
-      if constexpr (D == 128 || STREAM) {
+      if constexpr (D == 128 || STREAM || NW == 4) {
         if (long0) return launch(score_shared_kernel<D, NW, 0, STREAM, false, true, KVS_TABLE_TYPE(t)>);
       }
       launch(score_shared_kernel<D, NW, 0, STREAM, false, false, KVS_TABLE_TYPE(t)>);

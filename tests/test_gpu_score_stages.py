@@ -12,7 +12,10 @@ pytestmark = pytest.mark.gpu
     ([4000 + 431 * i for i in range(24)], 128, 7, 32, False, False),     # long in sweep 0, short in sweep 1
     ([4000 + 431 * i for i in range(24)], 128, 7, 32, True, True),       # short in both
     ([300 + 37 * i for i in range(72)], 128, 8, 32, False, True),        # chunks of two long stages: short ones
-    ([4000 + 431 * i for i in range(24)], 64, 8, 32, False, True),       # short in sweep 0, long in sweep 1
+    ([4000 + 431 * i for i in range(24)], 64, 8, 32, False, True),       # long in both
+    ([4000 + 431 * i for i in range(24)], 64, 9, 32, False, True),       # short in sweep 0, long in sweep 1
+    ([300 + 37 * i for i in range(72)], 64, 7, 32, False, False),        # the same with chunks of two long stages
+    ([4000 + 431 * i for i in range(24)], 64, 7, 32, True, False),
     ([2900 + 431 * i for i in range(30)], 64, 9, 32, True, False),       # the same with eight wavefronts
     ([2900 + 431 * i for i in range(30)], 128, 8, 64, False, False),
     ([2900 + 431 * i for i in range(30)], 128, 9, 32, True, True),
